@@ -31,7 +31,8 @@ sys.path.insert(0, ROOT)
 
 PEAK_INT8_TOPS = 5000.0       # MI355X dense int8 MFMA peak, TOP/s (published 5.0 POP/s)
 PEAK_HBM_GBS = 8000.0
-INT8_OPS_PER_RING_MAC = 72    # 36 digit pairs x (multiply + add)
+INT8_OPS_PER_RING_MAC = 72    # digit kernels: 36 digit pairs x (multiply + add)
+RESIDUE_OPS_PER_RING_MAC = 36   # residue GEMM: 18 moduli x (multiply + add)
 
 
 def parse():
@@ -309,14 +310,17 @@ def bench_matmul_other_ring(args, bits):
     spin.profile_enable(False)
     macs = 2.0 * n * M * M * M
     key = "gemm_limb" if path == spin.LIMB_MFMA else "gemm_valu"
+    if spin.profile_read("gemm_residue")[1] > 0:
+        key, pairs = "gemm_residue", 36                       # residues modulo 36 numbers instead of 136 digit pairs
     tot, cnt = spin.profile_read(key)
     pk, pc = spin.profile_read("pack")
     spin.profile_reset()
     gemm_ms = tot / cnt
     roof = None
     if path == spin.LIMB_MFMA:
-        ach = macs * 2 * pairs / (cnt / args.steps) / (gemm_ms * 1e-3) / 1e12      # digit pairs x (multiply + add)
-        roof = {"bound": "mfma", "kernel": "limb128_gemm_kernel" if bits == 128 else "limb_gemm_kernel<unsigned int>",
+        ach = macs * 2 * pairs / (cnt / args.steps) / (gemm_ms * 1e-3) / 1e12      # int8 products x (multiply + add)
+        roof = {"bound": "mfma", "kernel": "residue_gemm_kernel" if key == "gemm_residue" else "limb128_gemm_kernel" if bits == 128
+                else "limb_gemm_kernel<unsigned int>",
                 "achieved": ach, "peak": PEAK_INT8_TOPS, "unit": "TOP/s", "frac": ach / PEAK_INT8_TOPS,
                 "traffic": None, "avg_launch_ms": gemm_ms}
     ring = "u%d" % bits
@@ -588,18 +592,23 @@ def run_config(args, cfg):
     kernels = {k: spin.profile_read(k) for k in spin.KERNELS}
     spin.profile_reset()
     gemm_key = "gemm_limb" if path == spin.LIMB_MFMA else "gemm_valu"
+    # products above a size run on the residue GEMM; a step's products all take the one or all the other kernel
+    residue = path == spin.LIMB_MFMA and kernels["gemm_residue"][1] > 0
+    if residue:
+        gemm_key = "gemm_residue"
+    ops_per_mac = RESIDUE_OPS_PER_RING_MAC if residue else INT8_OPS_PER_RING_MAC
     gemm_ms, gemm_launches = kernels[gemm_key]
-    pack_ms = kernels["pack"][0] if path == spin.LIMB_MFMA else kernels["open"][0]
+    pack_ms = kernels["pack"][0] + kernels["combine"][0] if path == spin.LIMB_MFMA else kernels["open"][0]
     launches_per_step = gemm_launches / args.steps
     gemm_avg_ms = gemm_ms / gemm_launches
     gemm_ms_per_step = gemm_ms / args.steps
     if path == spin.LIMB_MFMA:
         # all GEMM launches of a step together: algorithmic int8 operations / their summed kernel time
-        achieved = ring_macs * INT8_OPS_PER_RING_MAC / (gemm_ms_per_step * 1e-3) / 1e12
-        with_pack = ring_macs * INT8_OPS_PER_RING_MAC / ((gemm_ms + pack_ms) / args.steps * 1e-3) / 1e12
+        achieved = ring_macs * ops_per_mac / (gemm_ms_per_step * 1e-3) / 1e12
+        with_pack = ring_macs * ops_per_mac / ((gemm_ms + pack_ms) / args.steps * 1e-3) / 1e12
         # which GEMM kernel the library picks: the row-streaming one for products of few column tiles, at most
         # three parties and an even inner dimension (it builds the left fragments itself), else the tile kernel
-        kernel_name = "limb_gemm_rows_kernel" if all_rows else "limb_gemm_kernel"
+        kernel_name = "residue_gemm_kernel" if residue else "limb_gemm_rows_kernel" if all_rows else "limb_gemm_kernel"
         traffic = measured_traffic(kernel_name, cfg)
         roofline = {"bound": "mfma", "kernel": kernel_name, "achieved": achieved, "peak": PEAK_INT8_TOPS,
                     "unit": "TOP/s", "frac": achieved / PEAK_INT8_TOPS, "traffic": traffic,
@@ -608,8 +617,9 @@ def run_config(args, cfg):
                     "avg_launch_ms": gemm_avg_ms, "launches_per_step": launches_per_step,
                     "ring_mac_per_s": ring_macs / (gemm_ms_per_step * 1e-3),
                     "frac_with_pack": with_pack / PEAK_INT8_TOPS,
-                    "note": "frac = int8 operations of all limb-GEMM launches of a step / their kernel time; frac_with_pack "
-                            "also counts the pack kernels that open E, F and split the operands into digits"}
+                    "note": "frac = int8 operations of all GEMM launches of a step / their kernel time (%d per ring "
+                            "multiply-add); frac_with_pack also counts the kernels that open E, F and convert the "
+                            "operands, and those that turn residues back into words" % ops_per_mac}
     else:
         # 64-bit multiply-add on the vector ALU: 256 CUs x 4 SIMDs x 16 lanes per clock at 2.4 GHz; the compiled
         # inner loop spends four VALU instructions per ring MAC (v_mad_u64_u32, 2 x v_mul_lo_u32, v_add3_u32),
@@ -640,7 +650,7 @@ def run_config(args, cfg):
                    "ring_macs_per_step": ring_macs},
         "roofline": roofline, "stream_kernels": streams,
         "step_ms_median": step_ms[len(step_ms) // 2] if step_ms else None, "step_ms_min": step_ms[0] if step_ms else None,
-        "limb_roofline_ring_mac_per_s": PEAK_INT8_TOPS * 1e12 / INT8_OPS_PER_RING_MAC,
+        "limb_roofline_ring_mac_per_s": PEAK_INT8_TOPS * 1e12 / (ops_per_mac if path == spin.LIMB_MFMA else INT8_OPS_PER_RING_MAC),
         # the protocol's view: one secure product of the plaintext shapes per step, whatever n
         "secure_matmul_mac_per_s": ring_macs / (2 * n) / (ms_per_step * 1e-3),
     }

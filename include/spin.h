@@ -135,6 +135,12 @@ size_t spin_beaver_matmul_grouped_workspace_bytes(int n, int groups, const spin_
 /* Bytes of workspace spin_beaver_matmul needs; 0 if the arguments are invalid. */
 size_t spin_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int K, int path);
 
+/* Bytes of workspace with which spin_beaver_matmul (and _nt) is fastest; never less than it needs, 0 if the
+ * arguments are invalid.  Large products run on residues modulo 18 small primes (powers), whose operand copies take
+ * 18 bytes an element; with less than this workspace such a product is computed in more blocks, or by the
+ * digit kernels.  The result is the same words either way.                                                    */
+size_t spin_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path);
+
 /* spin_beaver_matmul for callers that cannot allocate device memory, and so cannot bring a workspace:
  * code running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * operands, result and checks as spin_beaver_matmul; the workspace is an array of
@@ -252,6 +258,7 @@ spin_status spin128_beaver_matmul(int n, int batch, int M, int N, int K,
                                   uint64_t *Z, int path,
                                   void *workspace, size_t workspace_bytes, spin_stream stream);
 size_t spin128_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int K, int path);
+size_t spin128_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path);
 spin_status spin128_beaver_mul(int n, size_t count,
                                const uint64_t *x, const uint64_t *y,
                                const uint64_t *a, const uint64_t *b, const uint64_t *c,

@@ -39,7 +39,9 @@ typedef enum {
     SPIN_KERNEL_CAST = 10,      /* spin_cast_64_to_32 */
     SPIN_KERNEL_PROBE = 11,     /* spin_probe_mfma */
     SPIN_KERNEL_MUL_TRUNC = 12, /* spin_beaver_mul_trunc */
-    SPIN_KERNEL_COUNT = 13
+    SPIN_KERNEL_GEMM_RESIDUE = 13,   /* residue GEMM; its packs count as SPIN_KERNEL_PACK */
+    SPIN_KERNEL_COMBINE = 14,        /* residues back to ring words */
+    SPIN_KERNEL_COUNT = 15
 } spin_kernel;
 void spin_profile_enable(int on);
 spin_status spin_profile_read(int kernel, double *total_ms, unsigned *launches);

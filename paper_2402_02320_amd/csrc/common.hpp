@@ -108,6 +108,7 @@ template <class T> struct MatmulArgsT {
     const T *X, *Y, *A, *B, *C;
     T *Z;
     void *workspace;
+    size_t workspace_bytes;
     bool y_transposed;     // Y and B are stored [n][batch][N][K] instead of [n][batch][K][N]
 };
 typedef MatmulArgsT<u64> MatmulArgs;
@@ -121,6 +122,19 @@ spin_status launch_matmul_limb(const MatmulArgs &a, hipStream_t s);
 // groups of different shapes in shared launches (a[g].workspace is ignored: every group gets its own part of `workspace`)
 size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a);
 spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s);
+// Ring multiply-adds below which the residue GEMM is not even estimated: it measured no faster than the digit kernels at
+// 2 x 512^3 (64-bit, 49.6 against 50.9 us) and 2 x 128^3 (128-bit, 52 against 48 us), and the estimate costs host time.
+constexpr double kResidueMinMacs64 = 4e8, kResidueMinMacs128 = 1e7;
+inline double ring_macs(int n, int batch, int M, int N, int K) { return 2.0 * n * batch * M * N * K; }
+// The residue GEMM (gemm_residue.hip) where it is estimated to take less than `digit_cost_us`; `taken` says whether it
+// ran.  Works within a.workspace_bytes.  T = u64 or u128.
+template <class T>
+spin_status launch_matmul_residue(const MatmulArgsT<T> &a, double digit_cost_us, hipStream_t s, const char *where, bool &taken);
+// Workspace with which the residue GEMM works in few blocks; 0 where it is not the faster one.
+template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N, int K, double digit_cost_us);
+// The larger of the digit path's need and of that.
+size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K);
+size_t limb128_preferred_workspace_bytes(int n, int batch, int M, int N, int K);
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K);
 spin_status launch_matmul_limb32(const MatmulArgs32 &a, hipStream_t s);
 spin_status launch_mfma_probe(const u64 *operands, int blocks, int iters, u64 *sink, hipStream_t s);

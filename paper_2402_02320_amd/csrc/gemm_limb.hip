@@ -827,19 +827,38 @@ inline int choose_splits(long tiles, int steps)
 // one CU (about a microsecond), the unit of choose_splits: the row kernel walks 2 KT steps per block of 32
 // rows and column tile; the other path adds the left pack, an HBM stream of (3n + 1) operand-sized matrices
 // at about 5 MB per step-time, and one more launch.
+template <class T> inline double rows_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
+{
+    const int cus = compute_units();
+    return (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8);
+}
+template <class T> inline double tile_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
+{
+    const int cus = compute_units();
+    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
+    const int sp = choose_splits(tiles, 2 * p.KT);
+    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * (double)a.M * a.K;
+    return (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.0e6 + 5;
+}
 template <class T> inline bool rows_kernel_applies(const MatmulArgsT<T> &a, const Plan &p)
 {
     if (!std::is_same<T, u64>::value) return false;
     if (a.n > 3 || a.K % 2 != 0 || p.KT > Ring<u64>::max_chunk_tiles) return false;
+    if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return false;
+    return rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p);
+}
+
+// Estimated time of the digit kernels in microseconds, for the choice between them and the residue GEMM: 1.5 us a k-step
+// (72 MFMAs of 32 cycles on random operands) and the packs as streams.  Within 15 % of the measured times of 40 shapes
+// between 256^3 and 4096^3.
+inline double digit_cost_us(const MatmulArgs &a, const Plan &p)
+{
+    if (rows_kernel_applies<u64>(a, p)) return 1.5 * rows_kernel_cost<u64>(a, p) + 10;
     const int cus = compute_units();
-    const long rblocks = rows_grid(a.batch, a.M, p.tilesN);
-    if (rblocks > 0x7fffffffL) return false;
-    const double cost_rows = (double)((rblocks + cus - 1) / cus) * (2 * p.KT + 8);
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = choose_splits(tiles, 2 * p.KT);
-    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * (double)a.M * a.K;
-    const double cost_tiles = (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.0e6 + 5;
-    return cost_rows <= cost_tiles;
+    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
+    return 1.5 * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
 }
 
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
@@ -879,6 +898,11 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     char *packB = packA + p.packA_bytes;
 
     if constexpr (std::is_same<T, u64>::value) {
+        if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
+            bool taken = false;
+            const spin_status st = launch_matmul_residue<T>(a, digit_cost_us(a, p), s, "spin_beaver_matmul(residue gemm)", taken);
+            if (taken) return st;
+        }
         if (rows_kernel_applies<T>(a, p)) return launch_rows(a, p, packB, s, where_pack, where_gemm);
     }
 
@@ -1047,6 +1071,15 @@ size_t limb_workspace_bytes(int n, int batch, int M, int N, int K)
 {
     Plan p = make_plan<u64>(n, batch, M, N, K);
     return p.packA_bytes + p.packB_bytes;
+}
+
+size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
+{
+    const Plan p = make_plan<u64>(n, batch, M, N, K);
+    if (ring_macs(n, batch, M, N, K) < kResidueMinMacs64) return p.packA_bytes + p.packB_bytes;
+    MatmulArgs a{};
+    a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
+    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_us(a, p)));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)

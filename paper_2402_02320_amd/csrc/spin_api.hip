@@ -154,6 +154,13 @@ size_t spin_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int K,
     return 0;
 }
 
+size_t spin_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path)
+{
+    if (check_matmul_dims(n, batch, M, N, K) == SPIN_OK && path == SPIN_GEMM_LIMB_MFMA)
+        return limb_preferred_workspace_bytes(n, batch, M, N, K);
+    return spin_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
+}
+
 // Everything spin_beaver_matmul checks except the workspace; touches no HIP call.
 static spin_status check_matmul64(int n, int batch, int M, int N, int K, const uint64_t *X, const uint64_t *Y,
                                   const uint64_t *A, const uint64_t *B, const uint64_t *C, uint64_t *Z,
@@ -174,7 +181,7 @@ static spin_status beaver_matmul64(int n, int batch, int M, int N, int K, const 
     const size_t need = spin_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
     if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need)
         return SPIN_EWORKSPACE;
-    MatmulArgs a{n, batch, M, N, K, X, Y, A, B, C, Z, workspace, y_transposed};
+    MatmulArgs a{n, batch, M, N, K, X, Y, A, B, C, Z, workspace, workspace_bytes, y_transposed};
     return path == SPIN_GEMM_LIMB_MFMA ? launch_matmul_limb(a, (hipStream_t)stream)
                                        : launch_matmul_valu(a, (hipStream_t)stream);
 }
@@ -225,7 +232,7 @@ spin_status spin_beaver_matmul_grouped(int n, int groups, const spin_matmul_grou
         MatmulArgs args[SPIN_MAX_GROUPS];
         for (int g = 0; g < groups; ++g) {
             const spin_matmul_group &d = desc[g];
-            args[g] = MatmulArgs{n, d.batch, d.M, d.N, d.K, d.X, d.Y, d.A, d.B, d.C, d.Z, nullptr, d.y_transposed != 0};
+            args[g] = MatmulArgs{n, d.batch, d.M, d.N, d.K, d.X, d.Y, d.A, d.B, d.C, d.Z, nullptr, 0, d.y_transposed != 0};
         }
         const spin_status st = launch_matmul_limb_grouped(n, groups, args, workspace, (hipStream_t)stream);
         if (st != SPIN_ERANGE) return st;                // SPIN_ERANGE: a group does not fit a shared launch, nothing was launched
@@ -289,7 +296,7 @@ spin_status spin_beaver_matmul_static(int n, int batch, int M, int N, int K, con
     NoTimingScope no_events;                             // event timing would create event objects
     // Nothing in the workspace has to start at zero: the pack kernels (limb path) and the opening of E and F
     // (baseline path) overwrite every byte a later kernel reads, padding included, on every call.
-    MatmulArgs a{n, batch, M, N, K, X, Y, A, B, C, Z, ws, false};
+    MatmulArgs a{n, batch, M, N, K, X, Y, A, B, C, Z, ws, SPIN_STATIC_WORKSPACE_BYTES, false};
     return path == SPIN_GEMM_LIMB_MFMA ? launch_matmul_limb(a, (hipStream_t)stream)
                                        : launch_matmul_valu(a, (hipStream_t)stream);
 }
@@ -444,6 +451,13 @@ size_t spin128_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int
     return 0;
 }
 
+size_t spin128_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path)
+{
+    if (check_matmul_dims(n, batch, M, N, K) == SPIN_OK && path == SPIN_GEMM_LIMB_MFMA)
+        return limb128_preferred_workspace_bytes(n, batch, M, N, K);
+    return spin128_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
+}
+
 spin_status spin128_beaver_matmul(int n, int batch, int M, int N, int K, const uint64_t *X, const uint64_t *Y,
                                   const uint64_t *A, const uint64_t *B, const uint64_t *C, uint64_t *Z,
                                   int path, void *workspace, size_t workspace_bytes, spin_stream stream)
@@ -455,7 +469,7 @@ spin_status spin128_beaver_matmul(int n, int batch, int M, int N, int K, const u
     const size_t need = spin128_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
     if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need)
         return SPIN_EWORKSPACE;
-    MatmulArgs128 a{n, batch, M, N, K, r128(X), r128(Y), r128(A), r128(B), r128(C), r128(Z), workspace, false};
+    MatmulArgs128 a{n, batch, M, N, K, r128(X), r128(Y), r128(A), r128(B), r128(C), r128(Z), workspace, workspace_bytes, false};
     return path == SPIN_GEMM_LIMB_MFMA ? launch_matmul_limb128(a, (hipStream_t)stream)
                                        : launch_matmul_valu<u128>(a, (hipStream_t)stream);
 }
@@ -518,7 +532,7 @@ spin_status spin32_beaver_matmul(int n, int batch, int M, int N, int K, const ui
     const size_t need = spin32_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
     if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need)
         return SPIN_EWORKSPACE;
-    MatmulArgs32 a{n, batch, M, N, K, X, Y, A, B, C, Z, workspace, false};
+    MatmulArgs32 a{n, batch, M, N, K, X, Y, A, B, C, Z, workspace, workspace_bytes, false};
     return path == SPIN_GEMM_LIMB_MFMA ? launch_matmul_limb32(a, (hipStream_t)stream)
                                        : launch_matmul_valu<u32>(a, (hipStream_t)stream);
 }

@@ -45,6 +45,10 @@ def lib():
         L.spin_beaver_matmul_grouped_workspace_bytes.restype = sz
         L.spin_beaver_matmul_workspace_bytes.argtypes = [i32] * 5 + [i32]
         L.spin_beaver_matmul_workspace_bytes.restype = sz
+        L.spin_beaver_matmul_preferred_workspace_bytes.argtypes = [i32] * 5 + [i32]
+        L.spin_beaver_matmul_preferred_workspace_bytes.restype = sz
+        L.spin128_beaver_matmul_preferred_workspace_bytes.argtypes = [i32] * 5 + [i32]
+        L.spin128_beaver_matmul_preferred_workspace_bytes.restype = sz
         L.spin_beaver_mul.argtypes = [i32, sz] + [p] * 6 + [p]
         L.spin_beaver_mul_trunc.argtypes = [i32, sz, i32] + [p] * 9 + [p]
         L.spin_beaver_mul_trunc.restype = i32
@@ -141,6 +145,17 @@ def beaver_matmul_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
     return int(lib().spin_beaver_matmul_workspace_bytes(n, batch, M, N, K, path))
 
 
+def _matmul_workspace(dims, path, need_of, preferred_of, device):
+    """A workspace of the preferred size, or, where that much memory is not free, of the size needed."""
+    preferred = int(preferred_of(*dims, path))
+    if preferred == 0:
+        raise SpinError("invalid matmul dimensions")
+    try:
+        return torch.empty(preferred, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return torch.empty(int(need_of(*dims, path)), dtype=torch.uint8, device=device)
+
+
 def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_transposed=False):
     """X, A: [n,batch,M,K]; Y, B: [n,batch,K,N] (or [n,batch,N,K] with y_transposed, for X . Y^T);
     C: [n,batch,M,N] -> Z [n,batch,M,N]."""
@@ -151,11 +166,11 @@ def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_tra
         raise SpinError("inconsistent operand shapes")
     if out is None:
         out = torch.empty_like(C)
-    need = beaver_matmul_workspace_bytes(n, batch, M, N, K, path)
-    if need == 0:
-        raise SpinError("invalid matmul dimensions")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+        workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin_beaver_matmul_workspace_bytes,
+                                      lib().spin_beaver_matmul_preferred_workspace_bytes, X.device)
+    elif beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
+        raise SpinError("invalid matmul dimensions")
     if not (workspace.is_cuda and workspace.is_contiguous()):
         raise SpinError("workspace must be a contiguous CUDA tensor")
     call = lib().spin_beaver_matmul_nt if y_transposed else lib().spin_beaver_matmul
@@ -361,11 +376,11 @@ class ring128:
             raise SpinError("inconsistent operand shapes")
         if out is None:
             out = torch.empty_like(C)
-        need = ring128.beaver_matmul_workspace_bytes(n, batch, M, N, K, path)
-        if need == 0:
-            raise SpinError("invalid matmul dimensions")
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+            workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin128_beaver_matmul_workspace_bytes,
+                                          lib().spin128_beaver_matmul_preferred_workspace_bytes, X.device)
+        elif ring128.beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
+            raise SpinError("invalid matmul dimensions")
         _check(lib().spin128_beaver_matmul(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"),
                                            _dev(C, "C"), _dev(out, "Z"), path, workspace.data_ptr(),
                                            workspace.numel() * workspace.element_size(), _stream()))
@@ -470,7 +485,8 @@ class ring32:
 
 
 KERNELS = {"random": 0, "share": 1, "open": 2, "beaver_mul": 3, "trunc": 4, "pack": 5, "gemm_limb": 6,
-           "gemm_valu": 7, "lincomb": 8, "binary": 9, "cast": 10, "probe": 11, "beaver_mul_trunc": 12}
+           "gemm_valu": 7, "lincomb": 8, "binary": 9, "cast": 10, "probe": 11, "beaver_mul_trunc": 12,
+           "gemm_residue": 13, "combine": 14}
 
 
 def probe_mfma(operands, blocks, iters, sink=None):
