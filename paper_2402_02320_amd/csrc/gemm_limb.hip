@@ -864,19 +864,15 @@ inline double digit_cost_us(const MatmulArgs &a, const Plan &p)
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
                                const char *where_gemm)
 {
-    {
-        KernelTimer timer(SPIN_KERNEL_PACK, s);
-        launch_pack_right<u64>(a, packB, p.nblkB, p.KT, s);
-        spin_status st = check_launch(where_pack);
-        if (st != SPIN_OK) return st;
-    }
+    launch_pack<u64>(a, nullptr, packB, 0, p.nblkB, p.KT, false, s);
+    spin_status st = check_launch(where_pack);
+    if (st != SPIN_OK) return st;
     RowGemmArgs g{a.X, a.A, packB, a.C, a.Z, a.batch, a.M, a.N, a.K, p.KT, p.tilesN};
     // One workgroup fits a CU, so more workgroups than CUs only queue: launch one per CU (a multiple of 8, so that
     // an item keeps its XCD) and let each walk its items, the producer running ahead across item boundaries.
     const unsigned items = (unsigned)rows_grid(a.batch, a.M, p.tilesN);
     const unsigned resident = (unsigned)std::max(8, compute_units() / 8 * 8);
     const unsigned grid = items > resident && ((long)items / resident + 1) * p.KT < (1L << 30) ? resident : items;
-    spin_status st = SPIN_OK;
     for_party_count(a.n, [&](auto np) {
         constexpr int NP = decltype(np)::value <= 3 ? decltype(np)::value : 3;   // n <= 3 is checked by the caller
         static OncePerDevice lds_allowed;
@@ -906,7 +902,12 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
         if (rows_kernel_applies<T>(a, p)) return launch_rows(a, p, packB, s, where_pack, where_gemm);
     }
 
-    launch_pack<T>(a, packA, packB, p.nblkA, p.nblkB, p.KT, s);
+    const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
+    constexpr int chunk = Ring<T>::max_chunk_tiles;
+    const int first_ktn = p.KT < chunk ? p.KT : chunk;
+    const int splits = choose_splits(total, 2 * first_ktn);
+    // with several workgroups to a tile their parts are added onto Z, which starts out as C
+    launch_pack<T>(a, packA, packB, p.nblkA, p.nblkB, p.KT, splits > 1 && a.C != a.Z, s);
     spin_status st = check_launch(where_pack);
     if (st != SPIN_OK) return st;
 
@@ -916,14 +917,6 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     if (st != SPIN_OK) return st;
     GemmArgs<T> g{packA, packB, a.C, a.Z, a.n, a.batch, a.M, a.N, p.nblkA, p.nblkB, p.KT, 0, 0, p.tilesM, p.tilesN,
                   1, 0};
-    const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    constexpr int chunk = Ring<T>::max_chunk_tiles;
-    const int first_ktn = p.KT < chunk ? p.KT : chunk;
-    const int splits = choose_splits(total, 2 * first_ktn);
-    if (splits > 1 && a.C != a.Z) {                      // the parts are added onto Z, which starts out as C
-        st = launch_open<T>(a.C, nullptr, (size_t)a.n * a.batch * a.M * a.N, 1, a.Z, s);
-        if (st != SPIN_OK) return st;
-    }
     for (int kt0 = 0; kt0 < p.KT; kt0 += chunk) {
         g.kt0 = kt0;
         g.ktn = p.KT - kt0 < chunk ? p.KT - kt0 : chunk;
@@ -943,9 +936,9 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
 
 // ---- grouped call: products of different shapes, a handful of launches for all of them ----------------
 // Every group gets its own fragment stores inside the workspace (the packs of all groups run before their
-// GEMMs), chooses the row-streaming or the tile kernel as a single product would, and the groups of one kind
-// share a launch: right packs (plain / stored transposed), left packs (tile-kernel groups only), row GEMMs,
-// tile GEMMs -- at most five launches per kGroupsPerLaunch groups.  Tiles are not shared between workgroups
+// GEMMs), chooses the row-streaming or the tile kernel as a single product would, and the groups share launches: all
+// packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, the row GEMMs, the
+// tile GEMMs.  Tiles are not shared between workgroups
 // here (the groups together fill the chip), so Z needs no pre-copy.
 template <class Args, class Launch> inline spin_status launch_in_tables(const std::vector<Args> &args,
                                                                         const std::vector<unsigned> &blocks, Launch &&launch)
@@ -980,38 +973,37 @@ size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a)
 spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s)
 {
     constexpr int WAVES = 4;
-    std::vector<PackArgs<u64>> left, right_plain, right_t;
-    std::vector<unsigned> left_blocks, right_plain_blocks, right_t_blocks, row_blocks, tile_blocks;
+    std::vector<GroupedPackSide> sides;
+    std::vector<unsigned> side_blocks, row_blocks, tile_blocks;
     std::vector<RowGemmArgs> rows;
     std::vector<GemmArgs<u64>> tiles;
-    bool vec = true;
     char *ws = (char *)workspace;
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
         const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K);
         if (p.KT > Ring<u64>::max_chunk_tiles) return SPIN_ERANGE;
-        vec = vec && m.K % 2 == 0;
+        const int odd = m.K % 2;                         // rows not 16-byte aligned
         char *packA = ws, *packB = ws + p.packA_bytes;
         ws += p.packA_bytes + p.packB_bytes;
         if (m.y_transposed) {
-            right_t.push_back(PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.N, m.K, p.nblkB, p.KT});
-            right_t_blocks.push_back(pack_left_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
+            sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.N, m.K, p.nblkB, p.KT}, 2 + odd});
+            side_blocks.push_back(pack_left_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
         } else {
-            right_plain.push_back(PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT});
-            right_plain_blocks.push_back(pack_right_blocks(p.nblkB, p.KT) * m.batch);
+            sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT}, 4});
+            side_blocks.push_back(pack_right_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
         }
         if (rows_kernel_applies<u64>(m, p)) {
             rows.push_back(RowGemmArgs{m.X, m.A, packB, m.C, m.Z, m.batch, m.M, m.N, m.K, p.KT, p.tilesN});
             row_blocks.push_back((unsigned)rows_grid(m.batch, m.M, p.tilesN));
         } else {
-            left.push_back(PackArgs<u64>{m.X, m.A, packA, n, m.batch, m.M, m.K, p.nblkA, p.KT});
-            left_blocks.push_back(pack_left_blocks<WAVES>(p.nblkA, p.KT) * m.batch);
+            sides.push_back({PackArgs<u64>{m.X, m.A, packA, n, m.batch, m.M, m.K, p.nblkA, p.KT}, odd});
+            side_blocks.push_back(pack_left_blocks<WAVES>(p.nblkA, p.KT) * m.batch);
             tiles.push_back(GemmArgs<u64>{packA, packB, m.C, m.Z, n, m.batch, m.M, m.N, p.nblkA, p.nblkB, p.KT, 0, p.KT,
                                           p.tilesM, p.tilesN, 1, 2 * p.KT});
             tile_blocks.push_back((unsigned)((long)p.tilesM * p.tilesN * n * m.batch));
         }
     }
-    for (const std::vector<unsigned> *v : {&left_blocks, &right_plain_blocks, &right_t_blocks, &row_blocks, &tile_blocks}) {
+    for (const std::vector<unsigned> *v : {&side_blocks, &row_blocks, &tile_blocks}) {
         unsigned long sum = 0;                           // a launch of up to kGroupsPerLaunch groups must fit a grid
         for (unsigned b : *v) sum += b;
         if (sum > 0x7fffffffUL) return SPIN_ERANGE;
@@ -1021,18 +1013,9 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
         constexpr int NP = decltype(np)::value;
         {
             KernelTimer timer(SPIN_KERNEL_PACK, s);
-            launch_in_tables(right_plain, right_plain_blocks, [&](const GroupTable<PackArgs<u64>> &t, unsigned total) {
-                pack_right_grouped_kernel<NP, u64, false><<<total, 256, 0, s>>>(t);
+            launch_in_tables(sides, side_blocks, [&](const GroupTable<GroupedPackSide> &t, unsigned total) {
+                pack_grouped_kernel<NP><<<total, 256, 0, s>>>(t);
             });
-            auto pack_rows = [&](const std::vector<PackArgs<u64>> &v, const std::vector<unsigned> &blocks, auto right_c) {
-                constexpr bool RIGHT = decltype(right_c)::value;
-                launch_in_tables(v, blocks, [&](const GroupTable<PackArgs<u64>> &t, unsigned total) {
-                    if (vec) pack_left_grouped_kernel<NP, u64, true, WAVES, RIGHT, false><<<total, 64 * WAVES, 0, s>>>(t);
-                    else pack_left_grouped_kernel<NP, u64, false, WAVES, RIGHT, false><<<total, 64 * WAVES, 0, s>>>(t);
-                });
-            };
-            pack_rows(right_t, right_t_blocks, std::true_type());
-            pack_rows(left, left_blocks, std::false_type());
             st = check_launch("spin_beaver_matmul_grouped(pack)");
             if (st != SPIN_OK) return;
         }

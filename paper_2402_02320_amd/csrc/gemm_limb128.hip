@@ -217,7 +217,7 @@ spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
     }
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
-    launch_pack<u128>(a, packA, packB, p.nblkA, p.nblkB, p.KT, s);
+    launch_pack<u128>(a, packA, packB, p.nblkA, p.nblkB, p.KT, false, s);
     st = check_launch("spin128_beaver_matmul(pack)");
     if (st != SPIN_OK) return st;
 

@@ -94,14 +94,14 @@ template <class T> struct PackArgs {
 // 64-element row segment, every store two contiguous half-fragment chunks; consecutive waves continue
 // along the row.
 // `block` is the workgroup's index within its batch entry b.
-template <int NP, class T, bool NT>
+template <int NP, class T, int WAVES, bool NT>
 __device__ __forceinline__ void pack_right_body(const PackArgs<T> &a, long block, int b)
 {
     constexpr int ND = sizeof(T);
     constexpr bool KEEP = sizeof(T) <= 8;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int nblk2 = (a.nblk + 1) / 2;                    // pairs of column blocks
-    const long tile = block * 4 + wave;                    // (kt, half, block pair), block pair fastest
+    const long tile = block * WAVES + wave;                // (kt, half, block pair), block pair fastest
     if (tile >= (long)nblk2 * a.KT * 2) return;
     const int blk2 = (int)(tile % nblk2);
     const int half = (int)(tile / nblk2 % 2), kt = (int)(tile / nblk2 / 2);
@@ -169,12 +169,9 @@ __device__ __forceinline__ void pack_right_body(const PackArgs<T> &a, long block
     }
     if (owns) store_digit_rows<T, NT>(w, frag(1));
 }
-__host__ __device__ inline unsigned pack_right_blocks(int nblk, int KT) { return (unsigned)(((long)((nblk + 1) / 2) * KT * 2 + 3) / 4); }
-
-template <int NP, class T, bool NT>
-__global__ __launch_bounds__(256) void pack_right_kernel(PackArgs<T> a)
+template <int WAVES> __host__ __device__ inline unsigned pack_right_blocks(int nblk, int KT)
 {
-    pack_right_body<NP, T, NT>(a, blockIdx.x, blockIdx.z);
+    return (unsigned)(((long)((nblk + 1) / 2) * KT * 2 + WAVES - 1) / WAVES);
 }
 
 // Several products of different shapes in one launch (the grouped call): the descriptors travel as a kernel
@@ -192,26 +189,19 @@ template <class Args> __device__ inline int group_of(const GroupTable<Args> &t, 
     return g;
 }
 
-template <int NP, class T, bool NT>
-__global__ __launch_bounds__(256) void pack_right_grouped_kernel(GroupTable<PackArgs<T>> t)
-{
-    const int gi = group_of(t, blockIdx.x);
-    const PackArgs<T> a = t.e[gi];
-    const unsigned local = blockIdx.x - t.first[gi], per_batch = pack_right_blocks(a.nblk, a.KT);
-    pack_right_body<NP, T, NT>(a, local % per_batch, (int)(local / per_batch));
-}
-
 // Left side: source M x K row-major, a fragment row is a matrix row.  Reading 16 consecutive k per
 // lane directly would make every wave-wide load touch 64 different rows; instead a wave reads its
 // 32 x 32 tile (blk, kt) as whole-row segments (16 bytes per lane, 32 k of one row contiguous), sums the parties'
 // shares in that layout, and turns each 32 x 32 tile through LDS (rows padded by 16 bytes,
 // conflict-free for 16-byte accesses both ways) so that each lane ends up with the 16 consecutive k
 // of one row that a fragment chunk needs.  WAVES = waves per block (LDS: WAVES x 32 padded rows).
-// RIGHT = true packs a right operand that is stored transposed ([N][K] row-major, the layout of K in
+// `right` packs a right operand that is stored transposed ([N][K] row-major, the layout of K in
 // Q.K^T): the access pattern is the left side's, the slot rule the right side's (party 0's slot holds
 // B_0 + F).
-template <int NP, class T, bool VEC, int WAVES, bool RIGHT, bool NT>
-__device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block, int b)
+template <class T> constexpr int turn_row_bytes = 32 * sizeof(T) + 16;       // one row of the LDS turn
+
+template <int NP, class T, bool VEC, int WAVES, bool NT>
+__device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block, int b, char *lds, bool right)
 {
     constexpr int ND = sizeof(T);
     constexpr bool KEEP = sizeof(T) <= 8;
@@ -219,9 +209,8 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
     constexpr int LPR = 32 / EPL;                // lanes that cover the 32 k of one row: 8, 16 or 32
     constexpr int RPL = 64 / LPR;                // rows per wave-wide load: 8, 4 or 2
     constexpr int NL = 32 / RPL;                 // loads per lane: 4, 8 or 16
-    constexpr int kRowBytes = 32 * ND + 16;
+    constexpr int kRowBytes = turn_row_bytes<T>;
     struct alignas(16) Pair { T e[EPL]; };
-    __shared__ __attribute__((aligned(16))) char turn[WAVES][32 * kRowBytes];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     long tile = block * WAVES + wave;                       // (blk, kt) pair
     const bool active = tile < (long)a.nblk * a.KT;
@@ -263,7 +252,7 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
     };
     // lane -> LDS: written as (row RPL j + lane / LPR, k position lane % LPR), read back as
     // (row lane % 32, k 16 (lane / 32) ..)
-    char *mine = turn[wave];
+    char *mine = lds + wave * (32 * kRowBytes);
     auto turn_and_store = [&](const Pair (&v)[NL], char *dst) {
         __syncthreads();                                    // the previous round's reads are done
 #pragma unroll
@@ -316,7 +305,7 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
     }
     turn_and_store(opened, frag(0));
     if constexpr (KEEP) {
-        if (RIGHT) {
+        if (right) {
 #pragma unroll
             for (int j = 0; j < NL; ++j)
 #pragma unroll
@@ -329,7 +318,7 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
             tv[j] = load(t, blk * 32 + RPL * j + lane / LPR);
-            if (RIGHT) {
+            if (right) {
 #pragma unroll
                 for (int q = 0; q < EPL; ++q) tv[j].e[q] += opened[j].e[q];
             }
@@ -339,19 +328,61 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
 }
 template <int WAVES> __host__ __device__ inline unsigned pack_left_blocks(int nblk, int KT) { return (unsigned)(((long)nblk * KT + WAVES - 1) / WAVES); }
 
-template <int NP, class T, bool VEC, int WAVES, bool RIGHT, bool NT>
-__global__ __launch_bounds__(64 * WAVES) void pack_left_kernel(PackArgs<T> a)
+// Everything that precedes the GEMM of one product in one launch: workgroups 0 .. left_blocks - 1 of a batch entry
+// pack left operands, the next right_blocks right ones, the last copy_blocks set Z = C where several workgroups will add
+// onto a tile of Z.  The parts are independent and each of them alone leaves most of the chip idle at the sizes where a
+// launch counts: a layer of 4 parties, 250 x 301 x 785, where they were three launches of 12.8 + 9.8 + 3.3 us, went from
+// 60.5 to 49.6 us, one of 2 parties, 1024^3, from 162.7 to 158.5 us.
+template <class T> struct PackLaunch {
+    PackArgs<T> left, right;
+    const T *copy_from;
+    T *copy_to;
+    size_t copy_count;                                   // elements, all parties and batch entries
+    unsigned left_blocks, right_blocks, copy_blocks;     // per batch entry
+};
+template <class T> constexpr int pack_waves = sizeof(T) <= 8 ? 4 : 2;
+constexpr int kCopyPerThread = 8;
+
+template <int NP, class T, bool VEC, bool TRANSPOSED, bool NT>
+__global__ __launch_bounds__(64 * pack_waves<T>) void pack_kernel(PackLaunch<T> a)
 {
-    pack_left_body<NP, T, VEC, WAVES, RIGHT, NT>(a, blockIdx.x, blockIdx.z);
+    constexpr int WAVES = pack_waves<T>;
+    __shared__ __attribute__((aligned(16))) char lds[WAVES * 32 * turn_row_bytes<T>];
+    unsigned block = blockIdx.x;
+    if (block < a.left_blocks) {
+        pack_left_body<NP, T, VEC, WAVES, NT>(a.left, block, blockIdx.z, lds, false);
+    } else if ((block -= a.left_blocks) < a.right_blocks) {
+        if constexpr (TRANSPOSED) pack_left_body<NP, T, VEC, WAVES, NT>(a.right, block, blockIdx.z, lds, true);
+        else pack_right_body<NP, T, WAVES, NT>(a.right, block, blockIdx.z);
+    } else {
+        block -= a.right_blocks;
+        size_t i = ((size_t)blockIdx.z * a.copy_blocks + block) * (64 * WAVES * kCopyPerThread) + threadIdx.x;
+#pragma unroll
+        for (int u = 0; u < kCopyPerThread; ++u, i += 64 * WAVES)
+            if (i < a.copy_count) a.copy_to[i] = a.copy_from[i];
+    }
 }
 
-template <int NP, class T, bool VEC, int WAVES, bool RIGHT, bool NT>
-__global__ __launch_bounds__(64 * WAVES) void pack_left_grouped_kernel(GroupTable<PackArgs<T>> t)
+// The same for several products of different shapes: every entry of the table is one side of one product.  Six attention
+// products of 3 parties, with three pack launches of 10.3 + 10.3 + 9.4 us before: 69.1 -> 52.4 us a call.
+struct GroupedPackSide {
+    PackArgs<u64> a;
+    int kind;                                            // 0, 1: left (16-byte rows or not); 2, 3: transposed right; 4: right
+};
+template <int NP>
+__global__ __launch_bounds__(256) void pack_grouped_kernel(GroupTable<GroupedPackSide> t)
 {
+    __shared__ __attribute__((aligned(16))) char lds[4 * 32 * turn_row_bytes<u64>];
     const int gi = group_of(t, blockIdx.x);
-    const PackArgs<T> a = t.e[gi];
-    const unsigned local = blockIdx.x - t.first[gi], per_batch = pack_left_blocks<WAVES>(a.nblk, a.KT);
-    pack_left_body<NP, T, VEC, WAVES, RIGHT, NT>(a, local % per_batch, (int)(local / per_batch));
+    const PackArgs<u64> a = t.e[gi].a;
+    const int kind = t.e[gi].kind;
+    const unsigned local = blockIdx.x - t.first[gi];
+    const unsigned per_batch = kind == 4 ? pack_right_blocks<4>(a.nblk, a.KT) : pack_left_blocks<4>(a.nblk, a.KT);
+    const unsigned block = local % per_batch;
+    const int b = (int)(local / per_batch);
+    if (kind == 0 || kind == 2) pack_left_body<NP, u64, true, 4, false>(a, block, b, lds, kind == 2);
+    else if (kind == 1 || kind == 3) pack_left_body<NP, u64, false, 4, false>(a, block, b, lds, kind == 3);
+    else pack_right_body<NP, u64, 4, false>(a, block, b);
 }
 
 // One direct-to-LDS load: 64 lanes x 16 bytes from src + lane*16 to the LDS address lds_dst + lane*16.
@@ -403,62 +434,70 @@ __device__ inline TileId map_tile(long id, int tilesM, int tilesN, long total)
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Launches the pack kernels of one Beaver matmul: left operands from X, A; right operands from Y, B.
-// Calls fn(std::true_type) when one side's share streams exceed the caches, fn(std::false_type) otherwise.
-template <class T, class F> inline void for_pack_streaming(int n, int batch, int rows, int cols, F &&fn)
+// Operand sets beyond the caches (kPackStreamingBytes per side) use non-temporal accesses.
+template <class T> inline bool pack_streams(int n, int batch, int rows, int cols)
 {
-    if ((size_t)n * batch * rows * cols * sizeof(T) >= kPackStreamingBytes) fn(std::true_type());
-    else fn(std::false_type());
+    return (size_t)n * batch * rows * cols * sizeof(T) >= kPackStreamingBytes;
 }
 
-template <class T>
-inline void launch_pack_left(const MatmulArgsT<T> &a, char *packA, int nblkA, int KT, hipStream_t s)
+template <class T> inline void launch_pack_part(const MatmulArgsT<T> &a, const PackLaunch<T> &p, bool nt, hipStream_t s)
 {
-    PackArgs<T> pa{a.X, a.A, packA, a.n, a.batch, a.M, a.K, nblkA, KT};
-    constexpr int WAVES = sizeof(T) <= 8 ? 4 : 2;
-    constexpr int EPL = 16 / sizeof(T);
-    const bool vec = a.K % EPL == 0;                     // rows 16-byte aligned
+    constexpr int threads = 64 * pack_waves<T>;
+    const bool vec = a.K % (16 / (int)sizeof(T)) == 0;   // rows 16-byte aligned
+    const dim3 grid(p.left_blocks + p.right_blocks + p.copy_blocks, 1, a.batch);
     for_party_count(a.n, [&](auto np) {
         constexpr int NP = decltype(np)::value;
-        for_pack_streaming<T>(a.n, a.batch, a.M, a.K, [&](auto nt) {
-            constexpr bool NT = decltype(nt)::value;
-            dim3 ga(pack_left_blocks<WAVES>(nblkA, KT), 1, a.batch);
-            if (vec) pack_left_kernel<NP, T, true, WAVES, false, NT><<<ga, 64 * WAVES, 0, s>>>(pa);
-            else pack_left_kernel<NP, T, false, WAVES, false, NT><<<ga, 64 * WAVES, 0, s>>>(pa);
-        });
-    });
-}
-
-template <class T>
-inline void launch_pack_right(const MatmulArgsT<T> &a, char *packB, int nblkB, int KT, hipStream_t s)
-{
-    constexpr int WAVES = sizeof(T) <= 8 ? 4 : 2;
-    constexpr int EPL = 16 / sizeof(T);
-    const bool vec = a.K % EPL == 0;
-    for_party_count(a.n, [&](auto np) {
-        constexpr int NP = decltype(np)::value;
-        for_pack_streaming<T>(a.n, a.batch, a.K, a.N, [&](auto nt) {
-            constexpr bool NT = decltype(nt)::value;
-            if (a.y_transposed) {                        // Y, B stored [N][K]: rows of the source are fragment rows
-                PackArgs<T> pb{a.Y, a.B, packB, a.n, a.batch, a.N, a.K, nblkB, KT};
-                dim3 gb(pack_left_blocks<WAVES>(nblkB, KT), 1, a.batch);
-                if (vec) pack_left_kernel<NP, T, true, WAVES, true, NT><<<gb, 64 * WAVES, 0, s>>>(pb);
-                else pack_left_kernel<NP, T, false, WAVES, true, NT><<<gb, 64 * WAVES, 0, s>>>(pb);
-            } else {
-                PackArgs<T> pb{a.Y, a.B, packB, a.n, a.batch, a.K, a.N, nblkB, KT};
-                dim3 gb(pack_right_blocks(nblkB, KT), 1, a.batch);
-                pack_right_kernel<NP, T, NT><<<gb, 256, 0, s>>>(pb);
+        auto go = [&](auto vec_c, auto transposed_c, auto nt_c) {
+            pack_kernel<NP, T, decltype(vec_c)::value, decltype(transposed_c)::value, decltype(nt_c)::value><<<grid, threads, 0, s>>>(p);
+        };
+        auto with_nt = [&](auto vec_c, auto transposed_c) {
+            if (nt) go(vec_c, transposed_c, std::true_type());
+            else go(vec_c, transposed_c, std::false_type());
+        };
+        if constexpr (sizeof(T) == 8) {                  // only the 64-bit calls take a transposed right operand
+            if (a.y_transposed) {
+                if (vec) with_nt(std::true_type(), std::true_type());
+                else with_nt(std::false_type(), std::true_type());
+                return;
             }
-        });
+        }
+        if constexpr (sizeof(T) == 16) {
+            with_nt(std::true_type(), std::false_type());
+        } else {
+            if (vec) with_nt(std::true_type(), std::false_type());
+            else with_nt(std::false_type(), std::false_type());
+        }
     });
 }
 
+// Packs the left operands (X, A; unless packA is null) and the right ones (Y, B) of one Beaver matmul, and copies C to Z
+// when copy_c is set: one launch, or one per side where only one of them streams past the caches.
 template <class T>
-inline void launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int nblkA, int nblkB, int KT, hipStream_t s)
+inline void launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int nblkA, int nblkB, int KT, bool copy_c, hipStream_t s)
 {
     KernelTimer timer(SPIN_KERNEL_PACK, s);
-    launch_pack_left<T>(a, packA, nblkA, KT, s);
-    launch_pack_right<T>(a, packB, nblkB, KT, s);
+    constexpr int WAVES = pack_waves<T>;
+    PackLaunch<T> p{};
+    p.left = PackArgs<T>{a.X, a.A, packA, a.n, a.batch, a.M, a.K, nblkA, KT};
+    if (a.y_transposed) p.right = PackArgs<T>{a.Y, a.B, packB, a.n, a.batch, a.N, a.K, nblkB, KT};
+    else p.right = PackArgs<T>{a.Y, a.B, packB, a.n, a.batch, a.K, a.N, nblkB, KT};
+    p.left_blocks = packA ? pack_left_blocks<WAVES>(nblkA, KT) : 0;
+    p.right_blocks = a.y_transposed ? pack_left_blocks<WAVES>(nblkB, KT) : pack_right_blocks<WAVES>(nblkB, KT);
+    if (copy_c) {
+        p.copy_from = a.C;
+        p.copy_to = a.Z;
+        p.copy_count = (size_t)a.n * a.batch * a.M * a.N;
+        const size_t per_block = 64 * WAVES * kCopyPerThread, blocks = (p.copy_count + per_block - 1) / per_block;
+        p.copy_blocks = (unsigned)((blocks + a.batch - 1) / a.batch);
+    }
+    const bool nt_left = pack_streams<T>(a.n, a.batch, a.M, a.K), nt_right = pack_streams<T>(a.n, a.batch, a.K, a.N);
+    if (p.left_blocks > 0 && nt_left != nt_right) {
+        PackLaunch<T> one = p;
+        one.right_blocks = one.copy_blocks = 0;
+        launch_pack_part<T>(a, one, nt_left, s);
+        p.left_blocks = 0;
+    }
+    launch_pack_part<T>(a, p, nt_right, s);
 }
 
 }  // namespace
