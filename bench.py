@@ -594,15 +594,16 @@ def run_config(args, cfg):
     gemm_key = "gemm_limb" if path == spin.LIMB_MFMA else "gemm_valu"
     # products above a size run on the residue GEMM; a step's products all take the one or all the other kernel
     residue = path == spin.LIMB_MFMA and kernels["gemm_residue"][1] > 0
-    if residue:
-        gemm_key = "gemm_residue"
+    direct = path == spin.LIMB_MFMA and kernels["gemm_direct"][1] > 0      # small products: one launch on the vector ALU
+    if residue or direct:
+        gemm_key = "gemm_residue" if residue else "gemm_direct"
     ops_per_mac = RESIDUE_OPS_PER_RING_MAC if residue else INT8_OPS_PER_RING_MAC
     gemm_ms, gemm_launches = kernels[gemm_key]
     pack_ms = kernels["pack"][0] + kernels["combine"][0] if path == spin.LIMB_MFMA else kernels["open"][0]
     launches_per_step = gemm_launches / args.steps
     gemm_avg_ms = gemm_ms / gemm_launches
     gemm_ms_per_step = gemm_ms / args.steps
-    if path == spin.LIMB_MFMA:
+    if path == spin.LIMB_MFMA and not direct:
         # all GEMM launches of a step together: algorithmic int8 operations / their summed kernel time
         achieved = ring_macs * ops_per_mac / (gemm_ms_per_step * 1e-3) / 1e12
         with_pack = ring_macs * ops_per_mac / ((gemm_ms + pack_ms) / args.steps * 1e-3) / 1e12
@@ -626,7 +627,7 @@ def run_config(args, cfg):
         # each taken at full rate
         peak = 256 * 4 * 16 * 2.4e9 / 4 / 1e12
         achieved = ring_macs / (gemm_ms_per_step * 1e-3) / 1e12
-        roofline = {"bound": "alu", "kernel": "valu_gemm_kernel", "achieved": achieved, "peak": peak,
+        roofline = {"bound": "alu", "kernel": "direct_matmul_kernel" if direct else "valu_gemm_kernel", "achieved": achieved, "peak": peak,
                     "unit": "T ring MAC/s", "frac": achieved / peak, "traffic": None, "traffic_source": None,
                     "avg_launch_ms": gemm_avg_ms, "launches_per_step": launches_per_step}
     # HBM-bound side kernels: algorithmic bytes of all their launches in a step / their summed event time
@@ -654,7 +655,7 @@ def run_config(args, cfg):
         # the protocol's view: one secure product of the plaintext shapes per step, whatever n
         "secure_matmul_mac_per_s": ring_macs / (2 * n) / (ms_per_step * 1e-3),
     }
-    if path == spin.LIMB_MFMA and args.mfma_ceiling:
+    if path == spin.LIMB_MFMA and not direct and args.mfma_ceiling:
         out["mfma_ceiling"] = mfma_ceiling(roofline["achieved"])
     if not args.no_cpu_baseline:
         Z0 = gemm_z[0]

@@ -41,7 +41,8 @@ typedef enum {
     SPIN_KERNEL_MUL_TRUNC = 12, /* spin_beaver_mul_trunc */
     SPIN_KERNEL_GEMM_RESIDUE = 13,   /* residue GEMM; its packs count as SPIN_KERNEL_PACK */
     SPIN_KERNEL_COMBINE = 14,        /* residues back to ring words */
-    SPIN_KERNEL_COUNT = 15
+    SPIN_KERNEL_GEMM_DIRECT = 15,    /* small matmuls in one launch */
+    SPIN_KERNEL_COUNT = 16
 } spin_kernel;
 void spin_profile_enable(int on);
 spin_status spin_profile_read(int kernel, double *total_ms, unsigned *launches);

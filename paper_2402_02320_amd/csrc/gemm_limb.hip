@@ -848,17 +848,18 @@ template <class T> inline bool rows_kernel_applies(const MatmulArgsT<T> &a, cons
     return rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p);
 }
 
-// Estimated time of the digit kernels in microseconds, for the choice between them and the residue GEMM: 1.5 us a k-step
-// (72 MFMAs of 32 cycles on random operands) and the packs as streams.  Within 15 % of the measured times of 40 shapes
+// Estimated time of the digit kernels in microseconds, for the choice between them, the residue GEMM and the direct kernel:
+// 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.  Within 15 % of the measured times of 40 shapes
 // between 256^3 and 4096^3.
-inline double digit_cost_us(const MatmulArgs &a, const Plan &p)
+template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p)
 {
-    if (rows_kernel_applies<u64>(a, p)) return 1.5 * rows_kernel_cost<u64>(a, p) + 10;
+    if (rows_kernel_applies<T>(a, p)) return 1.5 * rows_kernel_cost<T>(a, p) + 10;
     const int cus = compute_units();
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = choose_splits(tiles, 2 * p.KT);
-    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
-    return 1.5 * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
+    const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
+    const double step = sizeof(T) == 8 ? 1.5 : 0.85;
+    return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
 }
 
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
@@ -893,10 +894,12 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
 
+    const double digits_us = digit_cost_us<T>(a, p);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digits_us)) return launch_matmul_direct<T>(a, s, where_gemm);
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;
-            const spin_status st = launch_matmul_residue<T>(a, digit_cost_us(a, p), s, "spin_beaver_matmul(residue gemm)", taken);
+            const spin_status st = launch_matmul_residue<T>(a, digits_us, s, "spin_beaver_matmul(residue gemm)", taken);
             if (taken) return st;
         }
         if (rows_kernel_applies<T>(a, p)) return launch_rows(a, p, packB, s, where_pack, where_gemm);
@@ -1062,7 +1065,7 @@ size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
     if (ring_macs(n, batch, M, N, K) < kResidueMinMacs64) return p.packA_bytes + p.packB_bytes;
     MatmulArgs a{};
     a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
-    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_us(a, p)));
+    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_us<u64>(a, p)));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)

@@ -209,10 +209,12 @@ size_t limb128_workspace_bytes(int n, int batch, int M, int N, int K)
 spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
 {
     const Plan128 p = make_plan128(a.n, a.batch, a.M, a.N, a.K);
+    const double digits_us = digit128_cost_us(a.n, a.batch, p);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, 16, digits_us)) return launch_matmul_direct<u128>(a, s, "spin128_beaver_matmul(direct)");
     spin_status st = SPIN_OK;
     if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs128) {
         bool taken = false;
-        st = launch_matmul_residue<u128>(a, digit128_cost_us(a.n, a.batch, p), s, "spin128_beaver_matmul(residue gemm)", taken);
+        st = launch_matmul_residue<u128>(a, digits_us, s, "spin128_beaver_matmul(residue gemm)", taken);
         if (taken) return st;
     }
     char *packA = (char *)a.workspace;

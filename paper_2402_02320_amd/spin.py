@@ -486,7 +486,7 @@ class ring32:
 
 KERNELS = {"random": 0, "share": 1, "open": 2, "beaver_mul": 3, "trunc": 4, "pack": 5, "gemm_limb": 6,
            "gemm_valu": 7, "lincomb": 8, "binary": 9, "cast": 10, "probe": 11, "beaver_mul_trunc": 12,
-           "gemm_residue": 13, "combine": 14}
+           "gemm_residue": 13, "combine": 14, "gemm_direct": 15}
 
 
 def probe_mfma(operands, blocks, iters, sink=None):
