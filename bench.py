@@ -211,9 +211,8 @@ def bench_poly(args):
     ms = (t_end - t_begin) * 1e3 / args.steps
     err = float((spin.decode(spin.open(y), p) * (0.01353417 / 2.0 ** -6) - torch.exp2(z)).abs().max())
     el = 8.0 * count
-    # per step: lincomb (x+t3): 2n; mul: 6n (u read twice counts once: 5n+... u,u,a,b,c in, out) ; trunc 5n;
-    # lincomb (+t2) 2n; mul 6n; lincomb+trunc (2 terms + tuple): 6n  -- element-sized transfers per party
-    alg = {"lincomb": (2 * n + 2 * n + 6 * n) * el / 3, "beaver_mul": 5 * n * el, "trunc": 5 * n * el}
+    # one pass per step: x, two triples and two truncation tuples in, the result out
+    alg = {"lincomb": 14 * n * el}
     kernels = {}
     for k, b in alg.items():
         tot, cnt = spin.profile_read(k)

@@ -222,6 +222,17 @@ spin_status spin_lincomb_trunc(int n, size_t count, int terms, const uint64_t *c
                                const uint64_t *r, const uint64_t *r_top, const uint64_t *r_msb,
                                uint64_t *out, spin_stream stream);
 
+/* The completed-square quartic of Section 7.2, Eq. (4), in one pass, word for word what these calls give:
+ *     u   = x + [i=0] t3                                   (spin_lincomb_trunc, f = 0)
+ *     v   = Truncate(u * u, f[0]) + [i=0] t2               (spin_beaver_mul_trunc; spin_lincomb_trunc, f = 0)
+ *     out = Truncate(v * v + lin x + [i=0] t0, f[1])       (spin_beaver_mul; spin_lincomb_trunc)
+ * triples, tuples: HOST arrays of six DEVICE pointers, a, b, c of the first square, then of the second; r, r_top, r_msb
+ * of the first truncation, then of the second; f: HOST array of two.  All tensors [n][count]; out may alias any input.
+ * 1 <= f[k] <= 61.                                                                                                  */
+spin_status spin_completed_square_trunc(int n, size_t count, const uint64_t *x, uint64_t t3, uint64_t t2, uint64_t lin,
+                                        uint64_t t0, const uint64_t *const *triples, const uint64_t *const *tuples,
+                                        const int *f, uint64_t *out, spin_stream stream);
+
 /* Binary sharing (Section 4.1): 64 independent bit positions per word,
  * x = XOR_i x_i.  XOR of sharings is local (Section 4.3 Addition); AND consumes
  * a bit triple (a, b, c = a AND b) and is the GF(2) form of the Beaver update.

@@ -34,7 +34,7 @@ typedef enum {
     SPIN_KERNEL_PACK = 5,       /* open + digit split + fragment layout for the limb GEMM */
     SPIN_KERNEL_GEMM_LIMB = 6,
     SPIN_KERNEL_GEMM_VALU = 7,
-    SPIN_KERNEL_LINCOMB = 8,
+    SPIN_KERNEL_LINCOMB = 8,    /* lincomb_trunc, completed_square_trunc */
     SPIN_KERNEL_BINARY = 9,     /* bshare, bopen, beaver_and */
     SPIN_KERNEL_CAST = 10,      /* spin_cast_64_to_32 */
     SPIN_KERNEL_PROBE = 11,     /* spin_probe_mfma */

@@ -103,6 +103,13 @@ struct LincombTerms { const u64 *in[SPIN_MAX_TERMS]; u64 coef[SPIN_MAX_TERMS]; i
 spin_status launch_lincomb_trunc(int n, size_t count, const LincombTerms &t, u64 constant, int f, const u64 *r,
                                  const u64 *r_top, const u64 *r_msb, u64 *out, hipStream_t s);
 
+struct CompletedSquare {               // operands of spin_completed_square_trunc: two triples, two truncation tuples
+    const u64 *x, *a[2], *b[2], *c[2], *r[2], *r_top[2], *r_msb[2];
+    u64 t3, t2, lin, t0;
+    int f[2];
+};
+spin_status launch_completed_square(int n, size_t count, const CompletedSquare &q, u64 *out, hipStream_t s);
+
 template <class T> struct MatmulArgsT {
     int n, batch, M, N, K;
     const T *X, *Y, *A, *B, *C;

@@ -205,8 +205,7 @@ __global__ __launch_bounds__(kBlock) void beaver_mul_bcast_kernel(const u64 *__r
 // registers; steps as listed at spin_trunc in include/spin.h.  Every tuple word is read before the first
 // store, and no pointer is declared restrict, so `out` may be any of the inputs.
 template <int NP, class T, bool NT>
-__device__ inline void truncate_and_store(const T (&y)[NP], const T *r, const T *r_top, const T *r_msb, size_t count,
-                                          size_t v, int f, T *out)
+__device__ inline void truncate(T (&y)[NP], const T *r, const T *r_top, const T *r_msb, size_t count, size_t v, int f)
 {
     constexpr int L = Lanes<T>::bits;              // ring width l
     T rt[NP], rm[NP];
@@ -225,8 +224,16 @@ __device__ inline void truncate_and_store(const T (&y)[NP], const T *r, const T 
         T b = rm[i] - 2 * c_msb * rm[i];
         T o = (b << (L - 1 - f)) - rt[i];
         if (i == 0) o += (c_msb << (L - 1 - f)) + c_top - ((T)1 << (L - 2 - f));
-        st<NT>(out + (size_t)i * count + v, o);
+        y[i] = o;
     }
+}
+template <int NP, class T, bool NT>
+__device__ inline void truncate_and_store(T (&y)[NP], const T *r, const T *r_top, const T *r_msb, size_t count, size_t v,
+                                          int f, T *out)
+{
+    truncate<NP, T, NT>(y, r, r_top, r_msb, count, v, f);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) st<NT>(out + (size_t)i * count + v, y[i]);
 }
 
 template <int NP, class T, bool NT>
@@ -297,6 +304,39 @@ __global__ __launch_bounds__(kBlock) void lincomb_trunc_kernel(LincombTerms t, u
 #pragma unroll
         for (int i = 0; i < NP; ++i) st<NT>(out + (size_t)i * count + v, y[i]);
     }
+}
+
+// ((x + t3)^2 + t2)^2 + lin x + t0 with the two truncations in between and after (Section 7.2, Eq. (4)), in one pass:
+// 14n words an element where the five passes of lincomb, mul_trunc, lincomb, mul and lincomb_trunc move 25n.  HBM-bound;
+// u, v and both products stay in registers.  Every input is read before the store, so `out` may be any of them.
+template <int NP, bool NT>
+__global__ __launch_bounds__(kBlock) void completed_square_kernel(CompletedSquare q, size_t count, u64 *out)
+{
+    size_t v = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (v >= count) return;
+    u64 x[NP], y[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) y[i] = x[i] = ld<NT>(q.x + (size_t)i * count + v);
+    // y <- y * y + (party 0's) constant added beforehand
+    auto square = [&](const u64 *a, const u64 *b, const u64 *c, u64 add) {
+        u64 av[NP], bv[NP], cv[NP], e = add, f = add;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const size_t o = (size_t)i * count + v;
+            av[i] = ld<NT>(a + o); bv[i] = ld<NT>(b + o); cv[i] = ld<NT>(c + o);
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) { e += y[i] - av[i]; f += y[i] - bv[i]; }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) y[i] = cv[i] + e * (i == 0 ? bv[i] + f : bv[i]) + av[i] * f;
+    };
+    square(q.a[0], q.b[0], q.c[0], q.t3);
+    truncate<NP, u64, NT>(y, q.r[0], q.r_top[0], q.r_msb[0], count, v, q.f[0]);
+    square(q.a[1], q.b[1], q.c[1], q.t2);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) y[i] += q.lin * x[i];
+    y[0] += q.t0;
+    truncate_and_store<NP, u64, NT>(y, q.r[1], q.r_top[1], q.r_msb[1], count, v, q.f[1], out);
 }
 
 // Fixed64 -> Fixed32 (Section 7.1): every party keeps the low 32 bits of its own share; the sum of the
@@ -625,6 +665,18 @@ spin_status launch_lincomb_trunc(int n, size_t count, const LincombTerms &t, u64
         });
     });
     return check_launch("spin_lincomb_trunc");
+}
+
+spin_status launch_completed_square(int n, size_t count, const CompletedSquare &q, u64 *out, hipStream_t s)
+{
+    KernelTimer timer(SPIN_KERNEL_LINCOMB, s);
+    for_party_count(n, [&](auto np) {
+        // 14 tensors where the multiplication, for which the limit was measured, moves six
+        for_streaming((size_t)n * count * sizeof(u64) / 6 * 14, [&](auto nt) {
+            completed_square_kernel<decltype(np)::value, decltype(nt)::value><<<grid_for(count), kBlock, 0, s>>>(q, count, out);
+        });
+    });
+    return check_launch("spin_completed_square_trunc");
 }
 
 }  // namespace spin

@@ -420,6 +420,27 @@ spin_status spin_lincomb_trunc(int n, size_t count, int terms, const uint64_t *c
     return launch_lincomb_trunc(n, count, t, constant, f, r, r_top, r_msb, out, (hipStream_t)stream);
 }
 
+spin_status spin_completed_square_trunc(int n, size_t count, const uint64_t *x, uint64_t t3, uint64_t t2, uint64_t lin,
+                                        uint64_t t0, const uint64_t *const *triples, const uint64_t *const *tuples,
+                                        const int *f, uint64_t *out, spin_stream stream)
+{
+    if (bad_ptr(x) || bad_ptr(out) || triples == nullptr || tuples == nullptr || f == nullptr || bad_n(n) || count == 0)
+        return SPIN_EINVAL;
+    CompletedSquare q;
+    q.x = x;
+    q.t3 = t3; q.t2 = t2; q.lin = lin; q.t0 = t0;
+    for (int k = 0; k < 2; ++k) {
+        for (int j = 0; j < 3; ++j)
+            if (bad_ptr(triples[3 * k + j]) || bad_ptr(tuples[3 * k + j])) return SPIN_EINVAL;
+        if (f[k] < 1 || f[k] > 61) return SPIN_EINVAL;
+        q.a[k] = triples[3 * k]; q.b[k] = triples[3 * k + 1]; q.c[k] = triples[3 * k + 2];
+        q.r[k] = tuples[3 * k]; q.r_top[k] = tuples[3 * k + 1]; q.r_msb[k] = tuples[3 * k + 2];
+        q.f[k] = f[k];
+    }
+    if (count > kMaxCount) return SPIN_ERANGE;
+    return launch_completed_square(n, count, q, out, (hipStream_t)stream);
+}
+
 // ---- Z_2^128 --------------------------------------------------------------------------------------
 static inline const u128 *r128(const uint64_t *p) { return (const u128 *)p; }
 static inline u128 *r128(uint64_t *p) { return (u128 *)p; }

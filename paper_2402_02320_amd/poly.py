@@ -35,9 +35,5 @@ def evaluate_completed_square(x, k4p_log2, t3, t2, t1, t0, p, triples, tuples):
     p - k4p_log2)."""
     shift = -k4p_log2
     k4p = 2.0 ** k4p_log2
-    u = spin.lincomb_trunc([x], [1], encode_public(t3, p))
-    u2 = spin.beaver_mul_trunc(u, u, *triples[0], *tuples[0], p)
-    v = spin.lincomb_trunc([u2], [1], encode_public(t2, p), out=u2)
-    v2 = spin.beaver_mul(v, v, *triples[1])
-    return spin.lincomb_trunc([v2, x], [1, encode_public(k4p * t1, p) << shift],
-                              encode_public(k4p * t0, 2 * p) << shift, p + shift, tuples[1], out=v2)
+    return spin.completed_square_trunc(x, encode_public(t3, p), encode_public(t2, p), encode_public(k4p * t1, p) << shift,
+                                       encode_public(k4p * t0, 2 * p) << shift, triples, tuples, (p, p + shift))

@@ -57,6 +57,8 @@ def lib():
         L.spin_trunc.argtypes = [i32, sz, i32] + [p] * 5 + [p]
         L.spin_lincomb_trunc.argtypes = [i32, sz, i32, p, p, u64, i32, p, p, p, p, p]
         L.spin_lincomb_trunc.restype = i32
+        L.spin_completed_square_trunc.argtypes = [i32, sz, p, u64, u64, u64, u64, p, p, p, p, p]
+        L.spin_completed_square_trunc.restype = i32
         L.spin_bshare.argtypes = [p, sz, i32, u64, u64, p, p]
         L.spin_bopen.argtypes = [p, p, sz, i32, p, p]
         L.spin_beaver_and.argtypes = [i32, sz] + [p] * 6 + [p]
@@ -334,6 +336,28 @@ def lincomb_trunc(terms, coefs, constant=0, f=0, tuple_=None, out=None):
                 raise SpinError("truncation tuple must have the shape of the terms")
     _check(lib().spin_lincomb_trunc(n, terms[0][0].numel(), len(terms), ptrs, cf, int(constant) % (1 << 64), f,
                                     r, rt, rm, _dev(out, "out"), _stream()))
+    return out
+
+
+def completed_square_trunc(x, t3, t2, lin, t0, triples, tuples, f, out=None):
+    """((x + t3)^2 truncated by f[0], + t2)^2 + lin x + t0, truncated by f[1], in one pass.  t3, t2, lin, t0: public ring
+    elements; triples, tuples: two (a, b, c) and two (r, r_top, r_msb) of x's shape."""
+    for t in tuple(triples[0]) + tuple(tuples[0]) + tuple(triples[1]):
+        if t.shape != x.shape:
+            raise SpinError("inconsistent operand shapes")
+    for t in tuples[1]:
+        if t.numel() != x.numel():
+            raise SpinError("truncation tuple must have the shape of the terms")
+    if out is None:
+        out = torch.empty_like(x)
+    six = ctypes.c_void_p * 6
+    (a0, b0, c0), (a1, b1, c1) = triples
+    (r0, rt0, rm0), (r1, rt1, rm1) = tuples
+    t_ptr = six(*[_dev(t, "triple") for t in (a0, b0, c0, a1, b1, c1)])
+    u_ptr = six(*[_dev(t, "tuple") for t in (r0, rt0, rm0, r1, rt1, rm1)])
+    const = [int(v) % (1 << 64) for v in (t3, t2, lin, t0)]
+    _check(lib().spin_completed_square_trunc(x.shape[0], x[0].numel(), _dev(x, "x"), *const, t_ptr, u_ptr,
+                                             (ctypes.c_int * 2)(*f), _dev(out, "out"), _stream()))
     return out
 
 
