@@ -115,8 +115,14 @@ def _dev(t, name):
     return t.data_ptr()
 
 
-def _stream():
-    return torch.cuda.current_stream().cuda_stream
+# The handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object around it, 2.6 us of the 6 to 9
+# a call takes on the host; the raw query takes 0.3 us.  Every call asks anew: streams are the caller's to change.
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream():
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def random(count, seed, stream_id, party, first_idx=0, device="cuda"):
