@@ -280,6 +280,9 @@ struct ResidueGemmArgs {
     char *y;                         // [party][modulus][tile][wave][chunk][1024]
     int parties, L, tilesM, tilesN, KT;
     unsigned first_item, items;      // modulus x party x tile: this launch takes [first_item, first_item + items)
+    unsigned whole;                  // of them, those in whole rounds of the grid; the rest are shared, `parts` workgroups each
+    int parts;
+    char *y_parts;                   // residues of the later parts: [item - whole][part - 1][tile]
 };
 
 // Persistent: one workgroup per CU, items dealt in rounds so that the 32 workgroups of an XCD work on neighbouring
@@ -318,29 +321,38 @@ __global__ __launch_bounds__(256) void residue_gemm_kernel(ResidueGemmArgs g)
     // thread, and kept in LDS behind the stages: half a dozen integer divisions per item would otherwise sit between
     // the matrix instructions (about 300 scalar instructions).
     const unsigned first = gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
-    if (first >= g.items) return;                        // whole workgroup
-    const int rounds = (int)((g.items - 1 - first) / gridDim.x) + 1;     // at most kMaxRounds: the host splits the launch
+    // The items beyond the last whole round would leave most of the grid idle: each is shared by `parts` workgroups, which
+    // take an even-length run of its k-steps each (the same run of neighbouring tiles on neighbouring workgroups).
+    const unsigned rest = g.items - g.whole;
+    const int part = rest > 0 ? (int)(first / rest) : g.parts;           // >= parts: nothing of the rest
+    const bool shares = part < g.parts;
+    const int rounds = (int)(g.whole / gridDim.x) + (shares ? 1 : 0);    // at most kMaxRounds: the host splits the launch
+    if (rounds == 0) return;                             // whole workgroup
+    const int part_s0 = shares ? 2 * (part * g.KT / g.parts) : 0, part_s1 = shares ? 2 * ((part + 1) * g.KT / g.parts) : 0;
     v4i *table = (v4i *)(lds + S::NSTAGE * S::stage_bytes);
     for (int r = threadIdx.x; r < rounds; r += 256) {
-        const unsigned id = g.first_item + first + (unsigned)r * gridDim.x, pm = id / tiles, tile = id % tiles;
+        const bool shared_item = shares && r == rounds - 1;
+        const unsigned local = shared_item ? g.whole + first % rest : first + (unsigned)r * gridDim.x;
+        const unsigned id = g.first_item + local, pm = id / tiles, tile = id % tiles;
         const unsigned party = pm % (unsigned)g.parties, mod = pm / (unsigned)g.parties;
         const TileId t = tile_of(tile, g.tilesM, g.tilesN);
         constexpr int per_panel = kPanel / S::BN;        // output tiles to a panel of columns
         v4i e;
         e.x = (int)((mod * g.a_mod + (size_t)t.tm * g.KT * kPanelStep) >> 10);
         e.y = (int)((mod * g.b_mod + (size_t)(t.tn / per_panel) * g.KT * kPanelStep + (t.tn % per_panel) * S::b_bytes) >> 10);
-        e.z = (int)((party * g.L + mod) * tiles + tile);
+        // later parts lie behind all first ones (negative: counted from y_parts)
+        e.z = shared_item && part > 0 ? ~(int)((local - g.whole) * (g.parts - 1) + part - 1) : (int)((party * g.L + mod) * tiles + tile);
         e.w = (int)(mod | party << 16);
         table[r] = e;
     }
     __syncthreads();
-    struct Item { u32 a_kb, b_kb, y_tile; int mod, party; };             // fragment offsets in KiB
+    struct Item { u32 a_kb, b_kb; int y_tile, mod, party; };             // fragment offsets in KiB
     auto item_of = [&](int r) {
         const v4i e = table[r];
         Item i;
         i.a_kb = (u32)__builtin_amdgcn_readfirstlane(e.x);
         i.b_kb = (u32)__builtin_amdgcn_readfirstlane(e.y);
-        i.y_tile = (u32)__builtin_amdgcn_readfirstlane(e.z);
+        i.y_tile = __builtin_amdgcn_readfirstlane(e.z);
         const int w = __builtin_amdgcn_readfirstlane(e.w);
         i.mod = w & 0xffff;
         i.party = w >> 16;
@@ -351,11 +363,33 @@ __global__ __launch_bounds__(256) void residue_gemm_kernel(ResidueGemmArgs g)
     const u32 lds0 = (u32)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const size_t wave_a = wave * (S::a_loads * 1024), wave_b = wave * (S::b_loads * 1024);
     int ld_round = 0;
-    Item ld = item_of(0);
+    Item ld;
+    const char *ld_a, *ld_b;
+    int ld_left, ld_second;                              // steps left in this operand pair, and then in the second one
     auto at_kb = [](const char *base, u32 kb) { return base + ((size_t)kb << 10); };
-    const char *ld_a = at_kb(g.E, ld.a_kb) + wave_a, *ld_b = at_kb(g.B, ld.b_kb) + ld.party * g.b_slot + wave_b;
-    int ld_left = g.KT;
-    bool ld_second = false;
+    auto first_pair = [&](int kt) {                      // (E, B_i') from k-step kt on
+        ld_a = at_kb(g.E, ld.a_kb) + wave_a + (size_t)kt * kPanelStep;
+        ld_b = at_kb(g.B, ld.b_kb) + ld.party * g.b_slot + wave_b + (size_t)kt * kPanelStep;
+    };
+    auto second_pair = [&](int kt) {                     // (A_i, F)
+        ld_a = at_kb(g.A, ld.a_kb) + ld.party * g.a_slot + wave_a + (size_t)kt * kPanelStep;
+        ld_b = at_kb(g.F, ld.b_kb) + wave_b + (size_t)kt * kPanelStep;
+    };
+    auto set_item = [&]() {
+        ld = item_of(ld_round);
+        const bool shared_item = shares && ld_round == rounds - 1;
+        const int s0 = shared_item ? part_s0 : 0, s1 = shared_item ? part_s1 : 2 * g.KT;
+        if (s0 < g.KT) {
+            first_pair(s0);
+            ld_left = min(s1, g.KT) - s0;
+            ld_second = max(s1 - g.KT, 0);
+        } else {
+            second_pair(s0 - g.KT);
+            ld_left = s1 - s0;
+            ld_second = 0;
+        }
+    };
+    set_item();
     size_t ld_inc = kPanelStep;
     u32 ld_stage = 0;
     auto issue_load = [&](int q) {                       // q is a constant after unrolling
@@ -368,17 +402,13 @@ __global__ __launch_bounds__(256) void residue_gemm_kernel(ResidueGemmArgs g)
         if (--ld_left != 0) {
             ld_a += ld_inc;
             ld_b += ld_inc;
-        } else if (!ld_second) {                         // (E, B_i') -> (A_i, F)
-            ld_second = true;
-            ld_left = g.KT;
-            ld_a = at_kb(g.A, ld.a_kb) + ld.party * g.a_slot + wave_a;
-            ld_b = at_kb(g.F, ld.b_kb) + wave_b;
+        } else if (ld_second > 0) {
+            ld_left = ld_second;
+            ld_second = 0;
+            second_pair(0);
         } else if (ld_round + 1 < rounds) {
-            ld = item_of(++ld_round);
-            ld_second = false;
-            ld_left = g.KT;
-            ld_a = at_kb(g.E, ld.a_kb) + wave_a;
-            ld_b = at_kb(g.B, ld.b_kb) + ld.party * g.b_slot + wave_b;
+            ++ld_round;
+            set_item();
         } else {
             ld_inc = 0;                                  // nothing is left: stand still
             ld_left = 0x7fffffff;
@@ -449,16 +479,18 @@ __global__ __launch_bounds__(256) void residue_gemm_kernel(ResidueGemmArgs g)
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
     for (int round = 0; round < rounds; ++round) {
+        const int steps = shares && round == rounds - 1 ? part_s1 - part_s0 : 2 * g.KT;      // even
         iteration(B0(), Y());
         iteration(B1(), N());
-        for (int s = 1; s < g.KT; ++s) {                 // 2 KT steps in all
+        for (int s = 2; s < steps; s += 2) {
             iteration(B0(), N());
             iteration(B1(), N());
         }
         // acc mod p, one byte each: q = floor(acc / p) exactly up to a wrap of the remainder to p itself
         const Item it = item_of(round);
         const int p = kModuli[it.mod], recip = kResidue<T>.acc_recip[it.mod], shift = kResidue<T>.acc_shift[it.mod];
-        char *dst = g.y + (size_t)it.y_tile * S::tile_bytes + wave * (S::stores * 1024) + lane16;
+        char *dst = (it.y_tile >= 0 ? g.y + (size_t)it.y_tile * S::tile_bytes : g.y_parts + (size_t)~it.y_tile * S::tile_bytes) +
+                    wave * (S::stores * 1024) + lane16;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -490,14 +522,35 @@ template <class T> struct ResidueCombineArgs {
     T *Z;
     size_t party_stride;             // elements between two parties' matrices
     int M, N, row0, col0;            // whole output; first row and column of this block of tiles
-    int tilesM, tilesN;
+    int tilesM, tilesN, parties;
     unsigned waves;                  // parties x tiles x 4 x chunks
+    const char *y_parts;             // residues of the items from `whole` on that came in `parts` parts, the later ones
+    unsigned whole;
+    int parts;
 };
+
+// (a + b) mod p of four bytes each, up to a multiple of p that leaves it a byte: both are at most p, and a sum of p or more
+// loses p.
+__device__ inline u32 add_residues(u32 a, u32 b, u32 p)
+{
+    const u32 pp = p | p << 16;
+    u32 r[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u32 sum = ((a >> (8 * h)) & 0x00ff00ffu) + ((b >> (8 * h)) & 0x00ff00ffu);     // below 2^10 each
+        // the lesser of sum and sum - p as unsigned halves (sum - p wraps to a large one when sum < p)
+        const u32 less = sum + (0x02000200u - pp);       // bit 9 of a half: sum >= p
+        const u32 mask = ((less >> 9) & 0x00010001u) * 0xffffu;
+        r[h] = sum - (pp & mask);
+    }
+    return r[0] | r[1] << 8;
+}
+
 
 // One lane: the 16 bytes per modulus that one lane of the GEMM stored = 4 rows x 4 columns (16 apart).  S of an
 // element is a sum of byte products: with y_l and the bytes of P/p_l as operands of 4-byte dot products, byte column j
 // of the result costs a fourth of L instructions; Q joins as one more factor with the bytes of -P.
-template <class T, int NJ>
+template <class T, int NJ, bool PARTS>
 __global__ __launch_bounds__(256) void residue_combine_kernel(ResidueCombineArgs<T> a)
 {
     using S = ResidueShape<NJ>;
@@ -512,6 +565,35 @@ __global__ __launch_bounds__(256) void residue_combine_kernel(ResidueCombineArgs
     v4i y[R::L];
 #pragma unroll
     for (int l = 0; l < R::L; ++l) y[l] = *(const v4i *)(src + l * mod_stride);
+    // Later parts are fetched six moduli at a time, so that their loads fly together; a modulus whose item is whole
+    // fetches its own residues again and adds zero.
+    if constexpr (PARTS) {
+        const size_t in_tile = (wave * S::stores + chunk) * 1024 + lane * 16;
+        auto item = [&](int l) { return (l * (unsigned)a.parties + party) * tiles + tile; };     // the GEMM's numbering
+        constexpr int kTogether = 6;
+        static_assert(R::L % kTogether == 0, "whole groups of moduli");
+#pragma unroll
+        for (int l0 = 0; l0 < R::L; l0 += kTogether) {
+            if (item(l0 + kTogether - 1) < a.whole) continue;            // items of later moduli have higher numbers
+            for (int part = 1; part < a.parts; ++part) {
+                v4i more[kTogether];
+#pragma unroll
+                for (int k = 0; k < kTogether; ++k) {
+                    const unsigned id = item(l0 + k);
+                    const char *from = id < a.whole ? src + (l0 + k) * mod_stride
+                                                    : a.y_parts + (size_t)((id - a.whole) * (a.parts - 1) + part - 1) * S::tile_bytes + in_tile;
+                    more[k] = *(const v4i *)from;
+                }
+#pragma unroll
+                for (int k = 0; k < kTogether; ++k) {
+                    const u32 mask = item(l0 + k) < a.whole ? 0u : ~0u;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        y[l0 + k][j] = (int)add_residues((u32)y[l0 + k][j], (u32)more[k][j] & mask, kModuli[l0 + k]);
+                }
+            }
+        }
+    }
 
     const TileId t = tile_of(tile, a.tilesM, a.tilesN);
     const int row = a.row0 + t.tm * kPanel + (int)(wave / 2) * 128 + (int)(chunk / (NJ / 4)) * 16 + 4 * (lane / 16);
@@ -576,10 +658,24 @@ __global__ __launch_bounds__(256) void residue_combine_kernel(ResidueCombineArgs
 // parties at a time (all, or one), panelsM x panelsN panels of the output at a time, the inner dimension in chunks of
 // at most kc.
 struct ResiduePlan {
-    int group, panelsM, panelsN, totalM, totalN, kc, KT;
+    int group, panelsM, panelsN, totalM, totalN, cols, kc, KT;           // cols: N
     bool narrow;                     // output tiles of 256 x 128 instead of 256 x 256
+    bool share;                      // the items beyond the last whole round of workgroups are shared (needs room for parts)
     size_t a_mod, b_mod, a_slot, b_slot, y_bytes;
 };
+
+// Products of a few rounds spend much of their time in the last, partly filled one: 2 parties 1000 x 1000 x 5700 (2.25 rounds)
+// took 713 us with whole items, 620 with the rest of the items shared; 2 parties 2048^3 over Z_2^128 in the workspace it needs,
+// block by block, 2051 and 1795 us.  The parts are reduced modulo p one by one and added when they are combined.
+// How many workgroups share an item beyond the last whole round of `grid`: as many as the grid holds, runs of at least
+// sixteen k-steps.
+inline int parts_of(unsigned items, unsigned grid, int KT)
+{
+    const unsigned rest = items % grid;
+    return rest == 0 ? 1 : (int)std::max(1u, std::min(grid / rest, (unsigned)KT / 8));
+}
+inline unsigned resident_workgroups(int cus) { return (unsigned)std::max(8, cus / 8 * 8); }
+inline size_t tile_bytes_of(bool narrow) { return narrow ? ResidueShape<4>::tile_bytes : ResidueShape<8>::tile_bytes; }
 
 // The most a caller is told to bring for a plan of few blocks (1.8 % of the card's memory).
 constexpr size_t kAmpleWorkspace = (size_t)5 << 30;
@@ -588,7 +684,16 @@ template <class T> inline size_t plan_bytes(const ResiduePlan &p)
 {
     return (size_t)(1 + p.group) * (p.a_slot + p.b_slot) + p.y_bytes;
 }
-template <class T> inline void plan_sizes(ResiduePlan &p)
+// Output tiles across panels c .. c + pn - 1 (narrow ones only where there are columns).
+inline int tiles_across(const ResiduePlan &p, int c, int pn)
+{
+    return p.narrow ? ceil_div(std::min(p.cols - c * kPanel, pn * kPanel), ResidueShape<4>::BN) : pn;
+}
+template <class T> inline unsigned plan_items(const ResiduePlan &p)
+{
+    return (unsigned)(p.group * ResidueTables<T>::L * p.panelsM * tiles_across(p, 0, p.panelsN));
+}
+template <class T> inline void plan_sizes(ResiduePlan &p, int cus)
 {
     constexpr int L = ResidueTables<T>::L;
     p.a_mod = (size_t)p.panelsM * p.KT * kPanelStep;
@@ -596,27 +701,34 @@ template <class T> inline void plan_sizes(ResiduePlan &p)
     p.a_slot = p.a_mod * L;
     p.b_slot = p.b_mod * L;
     p.y_bytes = (size_t)p.group * L * p.panelsM * p.panelsN * kPanel * kPanel;
+    const unsigned items = plan_items<T>(p), grid = resident_workgroups(cus);
+    if (p.share) p.y_bytes += (size_t)(items % grid) * (parts_of(items, grid, p.KT) - 1) * tile_bytes_of(p.narrow);
 }
 
 // Estimated time in microseconds of a plan.  A k-step of a 256 x 256 tile is 256 MFMAs of 16 cycles on four SIMDs;
-// packing and combining stream their bytes; every block of the plan costs three launches.  Fitted to 60 measurements
+// packing and combining stream their bytes; every block of the plan costs three launches and their ramps.  Fitted to 60 measurements
 // between 128^3 and 3500^3 (both rings, small and ample workspaces): within 15 % of all that take over 100 us.
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int M, int N, int K, int cus)
 {
     constexpr int L = ResidueTables<T>::L;
-    constexpr double kStreamBytesPerUs = 4.7e6, kBlockUs = 40.0, kStepUs = 0.64, kItemUs = 4.2;
+    constexpr double kStreamBytesPerUs = 4.7e6, kFirstBlockUs = 18.0, kBlockUs = 40.0, kStepUs = 0.64, kItemUs = 4.2;
     const int blocksM = ceil_div(p.totalM, p.panelsM), blocksN = ceil_div(p.totalN, p.panelsN), chunks = ceil_div(K, p.kc);
     const int groups = ceil_div(n, p.group);
-    const long tiles = (long)p.panelsM * p.panelsN * (p.narrow ? 2 : 1) * L * p.group;
-    const double step = p.narrow ? kStepUs * 0.55 : kStepUs, item = p.narrow ? kItemUs * 0.6 : kItemUs;
-    const double gemm = (double)chunks * blocksM * blocksN * groups * ((tiles + cus - 1) / cus) * (2 * p.KT * step + item);
+    const unsigned items = plan_items<T>(p), grid = resident_workgroups(cus), rest = items % grid;
+    const int parts = p.share ? parts_of(items, grid, p.KT) : 1;
+    const double step = p.narrow ? kStepUs * 0.66 : kStepUs, item = p.narrow ? kItemUs * 0.6 : kItemUs;
+    const double whole = 2 * p.KT * step + item;
+    double round_us = items / grid * whole;
+    if (rest > 0) round_us += 2 * p.KT * step / parts + item;
+    if (parts > 1) round_us += 2.0 * rest * (parts - 1) * tile_bytes_of(p.narrow) / kStreamBytesPerUs + (sizeof(T) == 8 ? 6 : 12);
+    const double gemm = (double)chunks * blocksM * blocksN * groups * round_us;
     const bool left_kept = p.group == n;                 // the left triples stay converted across the blocks of a row
     const double lw = (double)M * K, rw = (double)N * K, w = sizeof(T);
     const int left_reps = left_kept ? 1 : blocksN, right_reps = left_kept && blocksN == 1 ? 1 : blocksM;
     const double left = lw * (w * n + L + left_reps * n * (w + L));
     const double right = right_reps * rw * (w * n + L + n * (w + L));
     const double out = (double)n * M * N * (2 * L + 2 * w) * chunks;
-    return gemm + (left + right + out) / kStreamBytesPerUs + kBlockUs * chunks * blocksM * blocksN * groups;
+    return gemm + (left + right + out) / kStreamBytesPerUs + kFirstBlockUs + kBlockUs * (chunks * blocksM * blocksN * groups - 1);
 }
 
 // The cheapest plan that fits `bytes`; false when none does.  For every number of row blocks only the smallest number
@@ -626,26 +738,28 @@ template <class T> inline bool best_plan(int n, int M, int N, int K, size_t byte
     ResiduePlan p;
     p.totalM = ceil_div(M, kPanel);
     p.totalN = ceil_div(N, kPanel);
+    p.cols = N;
     const int chunks = ceil_div(K, ResidueRing<T>::max_k), cus = compute_units();
     p.kc = ceil_div(ceil_div(K, chunks), kStepK) * kStepK;
     p.KT = p.kc / kStepK;
     bool found = false;
     for (int group = n; group >= 1; group = group > 1 ? 1 : 0)
-        for (int bm = 1; bm <= std::min(p.totalM, 16); ++bm)
-            for (int bn = 1; bn <= std::min(p.totalN, 16); ++bn) {
-                p.group = group;
-                p.panelsM = ceil_div(p.totalM, bm);
-                p.panelsN = ceil_div(p.totalN, bn);
-                plan_sizes<T>(p);
-                if (plan_bytes<T>(p) > bytes) continue;
-                for (int narrow = 0; narrow < 2; ++narrow) {
-                    p.narrow = narrow != 0;
+        for (int kind = 0; kind < 4; ++kind) {           // narrow or wide tiles, with or without room for shared items
+            p.group = group;
+            p.narrow = kind % 2 != 0;
+            p.share = kind < 2;
+            for (int bm = 1; bm <= std::min(p.totalM, 16); ++bm)
+                for (int bn = 1; bn <= std::min(p.totalN, 16); ++bn) {
+                    p.panelsM = ceil_div(p.totalM, bm);
+                    p.panelsN = ceil_div(p.totalN, bn);
+                    plan_sizes<T>(p, cus);
+                    if (plan_bytes<T>(p) > bytes) continue;
                     const double c = plan_cost<T>(p, n, M, N, K, cus);
                     if (!found || c < best_cost) { best = p; best_cost = c; found = true; }
+                    if (bn == 1) bm = 16;                // whole rows of panels fit: no need for more row blocks
+                    break;
                 }
-                if (bn == 1) bm = 16;                    // whole rows of panels fit: no need for more row blocks
-                break;
-            }
+        }
     return found;
 }
 
@@ -657,12 +771,14 @@ spin_status launch_residue_gemm(const ResidueGemmArgs &g, hipStream_t s, const c
     spin_status st = allow_dynamic_lds((const void *)kernel, ResidueShape<NJ>::lds_bytes, lds_allowed);
     if (st != SPIN_OK) return st;
     KernelTimer timer(SPIN_KERNEL_GEMM_RESIDUE, s);
-    const unsigned resident = (unsigned)std::max(8, compute_units() / 8 * 8);
-    for (unsigned i = 0; i < g.items; i += resident * kMaxRounds) {
+    const unsigned resident = resident_workgroups(compute_units()), most = resident * (kMaxRounds - 1);
+    for (unsigned i = 0; i < g.items; i += most) {       // only the last launch has items beyond its whole rounds
         ResidueGemmArgs part = g;
         part.first_item = i;
-        part.items = std::min(g.items - i, resident * kMaxRounds);
-        kernel<<<std::min(part.items, resident), 256, ResidueShape<NJ>::lds_bytes, s>>>(part);
+        part.items = std::min(g.items - i, most);
+        part.whole = part.items / resident * resident;
+        const unsigned grid = part.whole > 0 ? resident : part.items * (unsigned)part.parts;
+        kernel<<<grid, 256, ResidueShape<NJ>::lds_bytes, s>>>(part);
         st = check_launch(where);
         if (st != SPIN_OK) return st;
     }
@@ -714,18 +830,28 @@ template <class T> spin_status run_residue(const MatmulArgsT<T> &a, const Residu
                         }
                         ResidueGemmArgs g{E, A, F, B, (size_t)L * pm * KT * kPanelStep, (size_t)L * pn * KT * kPanelStep,
                                           (size_t)pm * KT * kPanelStep, (size_t)pn * KT * kPanelStep, y, last - p0, L, pm,
-                                          pn * (p.narrow ? 2 : 1), KT, 0, 0};
-                        const unsigned tiles = (unsigned)(g.tilesM * g.tilesN);
+                                          tiles_across(p, c, pn), KT, 0, 0, 0, 1, nullptr};
+                        const unsigned tiles = (unsigned)(g.tilesM * g.tilesN), resident = resident_workgroups(compute_units());
                         g.items = tiles * L * (unsigned)g.parties;
+                        g.y_parts = y + (size_t)g.items * tile_bytes_of(p.narrow);
+                        // as many parts as the workspace has room for (blocks at the edge differ from the plan's)
+                        const unsigned rest = g.items % resident;
+                        const size_t room = ((size_t)((char *)a.workspace + a.workspace_bytes - g.y_parts)) / tile_bytes_of(p.narrow);
+                        if (rest > 0 && p.share) g.parts = std::min(parts_of(g.items, resident, KT), 1 + (int)std::min(room / rest, (size_t)1 << 20));
                         spin_status st = p.narrow ? launch_residue_gemm<T, 4>(g, s, where) : launch_residue_gemm<T, 8>(g, s, where);
                         if (st != SPIN_OK) return st;
                         ResidueCombineArgs<T> cb{y, (k0 == 0 ? a.C : a.Z) + ((size_t)p0 * a.batch + b) * zmat,
                                                  a.Z + ((size_t)p0 * a.batch + b) * zmat, a.batch * zmat, a.M, a.N, r * kPanel,
-                                                 c * kPanel, g.tilesM, g.tilesN, 0};
+                                                 c * kPanel, g.tilesM, g.tilesN, g.parties, 0, g.y_parts, g.items / resident * resident, g.parts};
                         cb.waves = (unsigned)g.parties * tiles * 4 * (p.narrow ? ResidueShape<4>::stores : ResidueShape<8>::stores);
                         KernelTimer timer(SPIN_KERNEL_COMBINE, s);
-                        if (p.narrow) residue_combine_kernel<T, 4><<<cb.waves / 4, 256, 0, s>>>(cb);
-                        else residue_combine_kernel<T, 8><<<cb.waves / 4, 256, 0, s>>>(cb);
+                        auto combine = [&](auto nj_c) {
+                            constexpr int NJ = decltype(nj_c)::value;
+                            if (cb.parts > 1) residue_combine_kernel<T, NJ, true><<<cb.waves / 4, 256, 0, s>>>(cb);
+                            else residue_combine_kernel<T, NJ, false><<<cb.waves / 4, 256, 0, s>>>(cb);
+                        };
+                        if (p.narrow) combine(std::integral_constant<int, 4>());
+                        else combine(std::integral_constant<int, 8>());
                         st = check_launch(where);
                         if (st != SPIN_OK) return st;
                     }
