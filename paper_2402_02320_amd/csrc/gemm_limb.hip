@@ -781,6 +781,37 @@ __global__ __launch_bounds__(64 * (NP + 1)) void limb_gemm_rows_grouped_kernel(G
     limb_gemm_rows_body<NP>(t.e[gi], blockIdx.x - t.first[gi], 0x7fffffffu);
 }
 
+// Row and tile products of one grouped call together: both kinds take a whole CU per workgroup and seldom fill the chip alone.
+// Six attention products of 3 parties: a launch of 27 us (rows) and one of 12.5 us (tiles) became one.  Fewer groups a
+// launch, so that both tables fit the 4 KB of kernel arguments.  The waves beyond a row workgroup's NP + 1 leave at once
+// (ended waves do not count at barriers).
+constexpr int kGroupsTogether = 16;
+template <class Args> struct SmallGroupTable {
+    int count;
+    unsigned first[kGroupsTogether + 1];
+    Args e[kGroupsTogether];
+};
+template <class Args> __device__ inline int group_of(const SmallGroupTable<Args> &t, unsigned id)
+{
+    int g = 0;
+    for (int i = 1; i < t.count; ++i) g += id >= t.first[i] ? 1 : 0;
+    return g;
+}
+template <int NP>
+__global__ __launch_bounds__(256) void limb_gemm_mixed_grouped_kernel(SmallGroupTable<RowGemmArgs> rows, SmallGroupTable<GemmArgs<u64>> tiles,
+                                                                      unsigned row_blocks)
+{
+    if (blockIdx.x < row_blocks) {
+        if (threadIdx.x >= 64 * (NP + 1)) return;
+        const int gi = group_of(rows, blockIdx.x);
+        limb_gemm_rows_body<NP>(rows.e[gi], blockIdx.x - rows.first[gi], 0x7fffffffu);
+    } else {
+        const unsigned id = blockIdx.x - row_blocks;
+        const int gi = group_of(tiles, id);
+        limb_gemm_body<u64>(tiles.e[gi], id - tiles.first[gi]);
+    }
+}
+
 // ------------------------------------------------------------------ host ---
 struct Plan {
     int KT, nblkA, nblkB, tilesM, tilesN;
@@ -940,8 +971,8 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
 // ---- grouped call: products of different shapes, a handful of launches for all of them ----------------
 // Every group gets its own fragment stores inside the workspace (the packs of all groups run before their
 // GEMMs), chooses the row-streaming or the tile kernel as a single product would, and the groups share launches: all
-// packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, the row GEMMs, the
-// tile GEMMs.  Tiles are not shared between workgroups
+// packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, then the row and the
+// tile GEMMs, together in one launch when neither has more than kGroupsTogether groups.  Tiles are not shared between workgroups
 // here (the groups together fill the chip), so Z needs no pre-copy.
 template <class Args, class Launch> inline spin_status launch_in_tables(const std::vector<Args> &args,
                                                                         const std::vector<unsigned> &blocks, Launch &&launch)
@@ -1007,9 +1038,9 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
         }
     }
     for (const std::vector<unsigned> *v : {&side_blocks, &row_blocks, &tile_blocks}) {
-        unsigned long sum = 0;                           // a launch of up to kGroupsPerLaunch groups must fit a grid
+        unsigned long sum = 0;                           // a launch must fit a grid, the rows and the tiles together too
         for (unsigned b : *v) sum += b;
-        if (sum > 0x7fffffffUL) return SPIN_ERANGE;
+        if (sum > (v == &side_blocks ? 0x7fffffffUL : 0x3fffffffUL)) return SPIN_ERANGE;
     }
     spin_status st = SPIN_OK;
     for_party_count(n, [&](auto np) {
@@ -1022,8 +1053,33 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             st = check_launch("spin_beaver_matmul_grouped(pack)");
             if (st != SPIN_OK) return;
         }
+        constexpr int RP = NP <= 3 ? NP : 3;                 // groups reach the row kernel only when n <= 3
+        if (!rows.empty() && !tiles.empty() && rows.size() <= kGroupsTogether && tiles.size() <= kGroupsTogether) {
+            static OncePerDevice lds_allowed;
+            auto kernel = limb_gemm_mixed_grouped_kernel<RP>;
+            constexpr int lds = std::max(kRowLds, GemmShape<u64>::lds_bytes);
+            st = allow_dynamic_lds((const void *)kernel, lds, lds_allowed);
+            if (st != SPIN_OK) return;
+            SmallGroupTable<RowGemmArgs> rt;
+            SmallGroupTable<GemmArgs<u64>> tt;
+            auto fill = [](auto &t, const auto &args, const std::vector<unsigned> &blocks) {
+                unsigned total = 0;
+                t.count = (int)args.size();
+                for (int i = 0; i < t.count; ++i) {
+                    t.first[i] = total;
+                    t.e[i] = args[i];
+                    total += blocks[i];
+                }
+                for (int i = t.count; i <= kGroupsTogether; ++i) t.first[i] = total;
+                return total;
+            };
+            const unsigned row_total = fill(rt, rows, row_blocks), tile_total = fill(tt, tiles, tile_blocks);
+            KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
+            kernel<<<row_total + tile_total, 256, lds, s>>>(rt, tt, row_total);
+            st = check_launch("spin_beaver_matmul_grouped(gemm)");
+            return;
+        }
         if (!rows.empty()) {
-            constexpr int RP = NP <= 3 ? NP : 3;             // groups reach the row kernel only when n <= 3
             static OncePerDevice lds_allowed;
             auto kernel = limb_gemm_rows_grouped_kernel<RP>;
             st = allow_dynamic_lds((const void *)kernel, kRowLds, lds_allowed);

@@ -1,0 +1,32 @@
+"""A grouped Beaver matmul whose products go to both limb GEMM kernels (an odd inner dimension excludes the row kernel), for
+the party counts the row kernel takes: the two kinds share one launch.  Compared with the VALU path, and with more groups than
+one shared launch holds."""
+import pytest
+import torch
+
+from paper_2402_02320_amd import spin
+
+pytestmark = pytest.mark.gpu
+
+
+def uniform(g, *shape):
+    return torch.empty(shape, dtype=torch.int64, device="cuda").random_(-2 ** 63, 2 ** 63 - 1, generator=g)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("count", [2, 6, 36])
+def test_rows_and_tiles_together(n, count):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 100 + count)
+    shapes = [(2, 196, 96, 64, True), (3, 49, 32, 49, False), (1, 33, 64, 130, False), (2, 70, 65, 33, True), (1, 1, 1, 2, False),
+              (1, 5, 7, 1, True)]
+    groups = []
+    for i in range(count):
+        batch, M, N, K, tr = shapes[i % len(shapes)]
+        y = (N, K) if tr else (K, N)
+        groups.append(dict(X=uniform(g, n, batch, M, K), Y=uniform(g, n, batch, *y), A=uniform(g, n, batch, M, K),
+                           B=uniform(g, n, batch, *y), C=uniform(g, n, batch, M, N), y_transposed=tr))
+    want = spin.beaver_matmul_grouped(groups, path=spin.VALU)
+    for _ in range(2):
+        got = spin.beaver_matmul_grouped(groups)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
