@@ -708,10 +708,10 @@ template <class T> inline void plan_sizes(ResiduePlan &p, int cus)
 // Estimated time in microseconds of a plan.  A k-step of a 256 x 256 tile is 256 MFMAs of 16 cycles on four SIMDs;
 // packing and combining stream their bytes; every block of the plan costs three launches and their ramps.  Fitted to 60 measurements
 // between 128^3 and 3500^3 (both rings, small and ample workspaces): within 15 % of all that take over 100 us.
-template <class T> inline double plan_cost(const ResiduePlan &p, int n, int M, int N, int K, int cus)
+template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {
     constexpr int L = ResidueTables<T>::L;
-    constexpr double kStreamBytesPerUs = 4.7e6, kFirstBlockUs = 18.0, kBlockUs = 40.0, kStepUs = 0.64, kItemUs = 4.2;
+    constexpr double kStreamBytesPerUs = 4.7e6, kFirstBlockUs = 26.0, kBlockUs = 40.0, kStepUs = 0.64, kItemUs = 4.2;
     const int blocksM = ceil_div(p.totalM, p.panelsM), blocksN = ceil_div(p.totalN, p.panelsN), chunks = ceil_div(K, p.kc);
     const int groups = ceil_div(n, p.group);
     const unsigned items = plan_items<T>(p), grid = resident_workgroups(cus), rest = items % grid;
@@ -728,12 +728,17 @@ template <class T> inline double plan_cost(const ResiduePlan &p, int n, int M, i
     const double left = lw * (w * n + L + left_reps * n * (w + L));
     const double right = right_reps * rw * (w * n + L + n * (w + L));
     const double out = (double)n * M * N * (2 * L + 2 * w) * chunks;
-    return gemm + (left + right + out) / kStreamBytesPerUs + kFirstBlockUs + kBlockUs * (chunks * blocksM * blocksN * groups - 1);
+    // The constants are those of a call of 320 us.  Shorter ones run at a higher clock (0.85 of the time up to 120 us),
+    // longer ones at a lower: 2x1024^3, which digits take 139 us for, measured 133 where a constant clock says 151, and
+    // 4x4096x200x2048, 562 us by digits, measured 580 where it says 557.
+    const double us = batch * (gemm + (left + right + out) / kStreamBytesPerUs);
+    const double clock = std::min(1.06, std::max(0.85, 0.85 + (us - 120) * (0.15 / 200)));
+    return us * clock + kFirstBlockUs + kBlockUs * ((double)chunks * blocksM * blocksN * groups * batch - 1);
 }
 
 // The cheapest plan that fits `bytes`; false when none does.  For every number of row blocks only the smallest number
 // of column blocks that fits is of interest: more blocks only convert more often.
-template <class T> inline bool best_plan(int n, int M, int N, int K, size_t bytes, ResiduePlan &best, double &best_cost)
+template <class T> inline bool best_plan(int n, int batch, int M, int N, int K, size_t bytes, ResiduePlan &best, double &best_cost)
 {
     ResiduePlan p;
     p.totalM = ceil_div(M, kPanel);
@@ -754,7 +759,7 @@ template <class T> inline bool best_plan(int n, int M, int N, int K, size_t byte
                     p.panelsN = ceil_div(p.totalN, bn);
                     plan_sizes<T>(p, cus);
                     if (plan_bytes<T>(p) > bytes) continue;
-                    const double c = plan_cost<T>(p, n, M, N, K, cus);
+                    const double c = plan_cost<T>(p, n, batch, M, N, K, cus);
                     if (!found || c < best_cost) { best = p; best_cost = c; found = true; }
                     if (bn == 1) bm = 16;                // whole rows of panels fit: no need for more row blocks
                     break;
@@ -858,6 +863,13 @@ template <class T> spin_status run_residue(const MatmulArgsT<T> &a, const Residu
     return SPIN_OK;
 }
 
+// The estimate for narrow tiles is the less certain one near the line: 5x512^3 is put at 80 us against 83 by digits and
+// takes 78 against 65; 2x768^3, 88 against 95, takes 81 against 85.
+inline bool beats_digits(const ResiduePlan &p, double cost, double digit_cost_us)
+{
+    return cost < digit_cost_us * (p.narrow ? 0.95 : 1.0);
+}
+
 }  // namespace
 
 template <class T>
@@ -865,7 +877,7 @@ spin_status launch_matmul_residue(const MatmulArgsT<T> &a, double digit_cost_us,
 {
     ResiduePlan p;
     double cost = 0;
-    taken = best_plan<T>(a.n, a.M, a.N, a.K, a.workspace_bytes, p, cost) && cost * a.batch < digit_cost_us;
+    taken = best_plan<T>(a.n, a.batch, a.M, a.N, a.K, a.workspace_bytes, p, cost) && beats_digits(p, cost, digit_cost_us);
     return taken ? run_residue<T>(a, p, s, where) : SPIN_OK;
 }
 template spin_status launch_matmul_residue<u64>(const MatmulArgsT<u64> &, double, hipStream_t, const char *, bool &);
@@ -875,7 +887,7 @@ template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N
 {
     ResiduePlan p;
     double cost = 0;
-    return best_plan<T>(n, M, N, K, kAmpleWorkspace, p, cost) && cost * batch < digit_cost_us ? plan_bytes<T>(p) : 0;
+    return best_plan<T>(n, batch, M, N, K, kAmpleWorkspace, p, cost) && beats_digits(p, cost, digit_cost_us) ? plan_bytes<T>(p) : 0;
 }
 template size_t residue_workspace_bytes<u64>(int, int, int, int, int, double);
 template size_t residue_workspace_bytes<u128>(int, int, int, int, int, double);
