@@ -18,8 +18,8 @@
 // and the inner dimension is never split.
 //
 // Kernels:
-//  pack_left/right_kernel (limb_common.hpp)  open E (or F), convert E/A_i (or F/B_i') to
-//                digits and store them as 1 KiB MFMA fragments.
+//  pack_kernel (limb_common.hpp)  opens E and F, converts E, A_i and F, B_i' to digits and stores them as 1 KiB MFMA
+//                fragments: both sides in one launch.
 //  limb_gemm_kernel  per party: Z_i = C_i + [E | A_i] . [B_i' ; F], fragments
 //                streamed global -> LDS with direct-to-LDS loads, 36 MFMAs per
 //                32x32x32 step into 8 diagonal accumulators, recombined once.
@@ -27,7 +27,10 @@
 //                parties: no left pack at all -- a producer wave streams the raw X_j, A_j tiles into LDS
 //                and opens E, one consumer wave per party converts its A_p in registers and runs the MFMAs.
 //  *_grouped_kernel  the same bodies for several products of different shapes in one launch
-//                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments.
+//                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments; row and tile
+//                products share a launch in limb_gemm_mixed_grouped_kernel.
+// Larger products go to the residue GEMM (gemm_residue.hip) and the smallest to one launch of vector arithmetic
+// (gemm_direct.hip); digit_cost_us is this file's side of that choice.
 #include <algorithm>
 #include <vector>
 
@@ -880,8 +883,9 @@ template <class T> inline bool rows_kernel_applies(const MatmulArgsT<T> &a, cons
 }
 
 // Estimated time of the digit kernels in microseconds, for the choice between them, the residue GEMM and the direct kernel:
-// 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.  Within 15 % of the measured times of 40 shapes
-// between 256^3 and 4096^3.
+// 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.
+// Within 15 % of the measured times of 40 shapes between 256^3 and 4096^3, short calls on the high side (5x512^3 is put at
+// 83 us and takes 66).
 template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p)
 {
     if (rows_kernel_applies<T>(a, p)) return 1.5 * rows_kernel_cost<T>(a, p) + 10;

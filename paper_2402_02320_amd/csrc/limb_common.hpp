@@ -364,7 +364,8 @@ __global__ __launch_bounds__(64 * pack_waves<T>) void pack_kernel(PackLaunch<T> 
 }
 
 // The same for several products of different shapes: every entry of the table is one side of one product.  Six attention
-// products of 3 parties, with three pack launches of 10.3 + 10.3 + 9.4 us before: 69.1 -> 52.4 us a call.
+// products of 3 parties, with three pack launches of 10.3 + 10.3 + 9.4 us before: 69.1 -> 52.4 us a
+// call (39.7 with their GEMMs in one launch too).
 struct GroupedPackSide {
     PackArgs<u64> a;
     int kind;                                            // 0, 1: left (16-byte rows or not); 2, 3: transposed right; 4: right

@@ -88,3 +88,15 @@ def test_word_from_residues(bits):
     cases += [[(rng.randrange(M), rng.randrange(M)) for _ in range(rng.randint(1, 40))] for _ in range(40)]
     for terms in cases:
         assert word_by_residues(terms, bits) == sum(a * b for a, b in terms) % M
+
+
+# The choice by estimate shows in the preferred workspace: above the required one only where the residue GEMM is taken.
+# Batched, long and narrow-tiled products near the line, whose estimates once fell on the wrong side, and clear ones.
+@pytest.mark.parametrize("dims,residue", [((3, 2, 700, 700, 700), False), ((4, 1, 4096, 200, 2048), False),
+                                          ((5, 1, 512, 512, 512), False), ((2, 1, 64, 64, 64), False),
+                                          ((2, 1, 2048, 2048, 2048), True), ((5, 1, 4096, 4096, 4096), True)])
+def test_choice_near_the_line(dims, residue):
+    from paper_2402_02320_amd import spin
+    L = spin.lib()
+    need = L.spin_beaver_matmul_workspace_bytes(*dims, spin.LIMB_MFMA)
+    assert (L.spin_beaver_matmul_preferred_workspace_bytes(*dims, spin.LIMB_MFMA) > need) is residue
