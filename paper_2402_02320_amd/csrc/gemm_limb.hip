@@ -882,10 +882,9 @@ template <class T> inline bool rows_kernel_applies(const MatmulArgsT<T> &a, cons
     return rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p);
 }
 
-// Estimated time of the digit kernels in microseconds, for the choice between them, the residue GEMM and the direct kernel:
+// Estimated time of the digit kernels in microseconds, for the choice between them and the direct kernel:
 // 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.
-// Within 15 % of the measured times of 40 shapes between 256^3 and 4096^3, short calls on the high side (5x512^3 is put at
-// 83 us and takes 66).
+// Small products are what it is for; large ones come out up to 40 % too high (the packs overlap their launch).
 template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p)
 {
     if (rows_kernel_applies<T>(a, p)) return 1.5 * rows_kernel_cost<T>(a, p) + 10;
@@ -895,6 +894,18 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
     const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
     const double step = sizeof(T) == 8 ? 1.5 : 0.85;
     return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
+}
+
+// The same for the choice between them and the residue GEMM, fitted to 90 products of 45 us to 1.4 ms (2 to 5 parties, sides 64 to
+// 4096; rms error 5.5 %); parts of shared tiles that are added onto Z cost 0.44 us a megabyte of its words read and written.
+inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p)
+{
+    if (rows_kernel_applies<u64>(a, p)) return 1.25 * rows_kernel_cost<u64>(a, p) + 10;
+    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch, cus = compute_units();
+    const int sp = choose_splits(tiles, 2 * p.KT);
+    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
+    const double added = sp > 1 ? 16.0 * a.n * a.batch * a.M * a.N * 0.44e-6 : 0;
+    return (double)((tiles * sp + cus - 1) / cus) * (1.42 * 2 * ceil_div(p.KT, sp) + 6.7) + pack_bytes / 5.2e6 + added;
 }
 
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
@@ -934,7 +945,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;
-            const spin_status st = launch_matmul_residue<T>(a, digits_us, s, "spin_beaver_matmul(residue gemm)", taken);
+            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p), s, "spin_beaver_matmul(residue gemm)", taken);
             if (taken) return st;
         }
         if (rows_kernel_applies<T>(a, p)) return launch_rows(a, p, packB, s, where_pack, where_gemm);
@@ -1125,7 +1136,7 @@ size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
     if (ring_macs(n, batch, M, N, K) < kResidueMinMacs64) return p.packA_bytes + p.packB_bytes;
     MatmulArgs a{};
     a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
-    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_us<u64>(a, p)));
+    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_large_us(a, p)));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)

@@ -705,35 +705,43 @@ template <class T> inline void plan_sizes(ResiduePlan &p, int cus)
     if (p.share) p.y_bytes += (size_t)(items % grid) * (parts_of(items, grid, p.KT) - 1) * tile_bytes_of(p.narrow);
 }
 
-// Estimated time in microseconds of a plan.  A k-step of a 256 x 256 tile is 256 MFMAs of 16 cycles on four SIMDs;
-// packing and combining stream their bytes; every block of the plan costs three launches and their ramps.  Fitted to 60 measurements
-// between 128^3 and 3500^3 (both rings, small and ample workspaces): within 15 % of all that take over 100 us.
+// Estimated time in microseconds of a plan: k-steps of a tile (256 MFMAs of 16 cycles on four SIMDs), a fixed part per item, the
+// bytes of pack and combine as streams, and three launches with their ramps per block of the plan.  The 64-bit constants are a
+// fit to 90 measured products (2 to 5 parties, sides 64 to 4096, 45 us to 1.4 ms; rms error 4.8 %, digit_cost_large_us 5.5 %):
+// choosing by the two costs 0.3 % over always taking the faster, where one clock and one rate for all streams cost 3.5 % and
+// lost up to 37 % on 5x3269x93x264 (79 us by digits, 109 by residues).  Those of Z_2^128 are within 15 % from 100 us on.
+template <class T> struct ResidueCost;
+template <> struct ResidueCost<u64> {
+    static constexpr double step = 0.585, item = 6.0, narrow_step = 0.617, narrow_item = 0.426;      // of a wide tile's
+    static constexpr double pack_bytes_per_us = 3.8e6, combine_bytes_per_us = 10e6;                  // (its reads come from cache)
+    static constexpr double first_block = 10, shared = 5.5, block = 40;
+};
+template <> struct ResidueCost<u128> {
+    static constexpr double step = 0.64, item = 4.2, narrow_step = 0.66, narrow_item = 0.6;
+    static constexpr double pack_bytes_per_us = 4.7e6, combine_bytes_per_us = 4.7e6, first_block = 18, shared = 12, block = 40;
+};
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {
+    using C = ResidueCost<T>;
     constexpr int L = ResidueTables<T>::L;
-    constexpr double kStreamBytesPerUs = 4.7e6, kFirstBlockUs = 26.0, kBlockUs = 40.0, kStepUs = 0.64, kItemUs = 4.2;
     const int blocksM = ceil_div(p.totalM, p.panelsM), blocksN = ceil_div(p.totalN, p.panelsN), chunks = ceil_div(K, p.kc);
     const int groups = ceil_div(n, p.group);
     const unsigned items = plan_items<T>(p), grid = resident_workgroups(cus), rest = items % grid;
     const int parts = p.share ? parts_of(items, grid, p.KT) : 1;
-    const double step = p.narrow ? kStepUs * 0.66 : kStepUs, item = p.narrow ? kItemUs * 0.6 : kItemUs;
-    const double whole = 2 * p.KT * step + item;
-    double round_us = items / grid * whole;
-    if (rest > 0) round_us += 2 * p.KT * step / parts + item;
-    if (parts > 1) round_us += 2.0 * rest * (parts - 1) * tile_bytes_of(p.narrow) / kStreamBytesPerUs + (sizeof(T) == 8 ? 6 : 12);
-    const double gemm = (double)chunks * blocksM * blocksN * groups * round_us;
+    const double step = p.narrow ? C::step * C::narrow_step : C::step, item = p.narrow ? C::item * C::narrow_item : C::item;
+    const double y_bytes = (double)items * tile_bytes_of(p.narrow), part_bytes = (double)rest * (parts - 1) * tile_bytes_of(p.narrow);
+    double block_us = items / grid * (2 * p.KT * step + item) + 2 * (y_bytes + part_bytes) / C::combine_bytes_per_us;
+    if (rest > 0) block_us += 2 * p.KT * step / parts + item;
+    if (parts > 1) block_us += C::shared;
+    const double blocks = (double)chunks * blocksM * blocksN * groups;
     const bool left_kept = p.group == n;                 // the left triples stay converted across the blocks of a row
-    const double lw = (double)M * K, rw = (double)N * K, w = sizeof(T);
+    const double w = sizeof(T), padM = (double)p.totalM * kPanel, padN = (double)p.totalN * kPanel;
     const int left_reps = left_kept ? 1 : blocksN, right_reps = left_kept && blocksN == 1 ? 1 : blocksM;
-    const double left = lw * (w * n + L + left_reps * n * (w + L));
-    const double right = right_reps * rw * (w * n + L + n * (w + L));
-    const double out = (double)n * M * N * (2 * L + 2 * w) * chunks;
-    // The constants are those of a call of 320 us.  Shorter ones run at a higher clock (0.85 of the time up to 120 us),
-    // longer ones at a lower: 2x1024^3, which digits take 139 us for, measured 133 where a constant clock says 151, and
-    // 4x4096x200x2048, 562 us by digits, measured 580 where it says 557.
-    const double us = batch * (gemm + (left + right + out) / kStreamBytesPerUs);
-    const double clock = std::min(1.06, std::max(0.85, 0.85 + (us - 120) * (0.15 / 200)));
-    return us * clock + kFirstBlockUs + kBlockUs * ((double)chunks * blocksM * blocksN * groups * batch - 1);
+    const double left = (double)K * (M * w * n * (1 + left_reps) + padM * L * (1 + (double)n * left_reps));
+    const double right = (double)right_reps * K * (N * w * 2 * n + padN * L * (n + 1));
+    const double out = (double)n * M * N * 2 * w * chunks;
+    return batch * (blocks * block_us + (left + right) / C::pack_bytes_per_us + out / C::combine_bytes_per_us) + C::first_block +
+           C::block * (blocks * batch - 1);
 }
 
 // The cheapest plan that fits `bytes`; false when none does.  For every number of row blocks only the smallest number
@@ -863,13 +871,6 @@ template <class T> spin_status run_residue(const MatmulArgsT<T> &a, const Residu
     return SPIN_OK;
 }
 
-// The estimate for narrow tiles is the less certain one near the line: 5x512^3 is put at 80 us against 83 by digits and
-// takes 78 against 65; 2x768^3, 88 against 95, takes 81 against 85.
-inline bool beats_digits(const ResiduePlan &p, double cost, double digit_cost_us)
-{
-    return cost < digit_cost_us * (p.narrow ? 0.95 : 1.0);
-}
-
 }  // namespace
 
 template <class T>
@@ -877,7 +878,7 @@ spin_status launch_matmul_residue(const MatmulArgsT<T> &a, double digit_cost_us,
 {
     ResiduePlan p;
     double cost = 0;
-    taken = best_plan<T>(a.n, a.batch, a.M, a.N, a.K, a.workspace_bytes, p, cost) && beats_digits(p, cost, digit_cost_us);
+    taken = best_plan<T>(a.n, a.batch, a.M, a.N, a.K, a.workspace_bytes, p, cost) && cost < digit_cost_us;
     return taken ? run_residue<T>(a, p, s, where) : SPIN_OK;
 }
 template spin_status launch_matmul_residue<u64>(const MatmulArgsT<u64> &, double, hipStream_t, const char *, bool &);
@@ -887,7 +888,7 @@ template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N
 {
     ResiduePlan p;
     double cost = 0;
-    return best_plan<T>(n, batch, M, N, K, kAmpleWorkspace, p, cost) && beats_digits(p, cost, digit_cost_us) ? plan_bytes<T>(p) : 0;
+    return best_plan<T>(n, batch, M, N, K, kAmpleWorkspace, p, cost) && cost < digit_cost_us ? plan_bytes<T>(p) : 0;
 }
 template size_t residue_workspace_bytes<u64>(int, int, int, int, int, double);
 template size_t residue_workspace_bytes<u128>(int, int, int, int, int, double);

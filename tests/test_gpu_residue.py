@@ -37,12 +37,12 @@ def preferred(L, bits, *dims):
 
 
 # n, batch, M, N, K, transposed; all of them are products the residue GEMM takes with ample workspace
-SHAPES64 = [(5, 1, 1025, 1000, 1001, False),      # odd K (no 16-byte rows), one row beyond four panels
+SHAPES64 = [(5, 1, 1025, 1200, 1001, False),      # odd K (no 16-byte rows), one row beyond four panels
             (8, 1, 769, 1023, 1100, True),        # right operand stored transposed, eight parties
             (2, 1, 1300, 1300, 5633, False),      # one k beyond a launch: two chunks, the second onto Z
             (2, 2, 1500, 1030, 1600, False),      # two batch entries
             (3, 1, 2048, 1024, 1537, True),       # odd K, transposed
-           (4, 1, 1024, 1024, 1024, False),      # 4.5 rounds of workgroups: the last items come in two parts
+            (4, 1, 1024, 1024, 1088, False),      # 4.5 rounds of workgroups: the last items come in two parts
            (2, 1, 1500, 1500, 1400, False)]      # 5.06 rounds: a few items in several parts
 
 
