@@ -956,9 +956,14 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     const int first_ktn = p.KT < chunk ? p.KT : chunk;
     const int splits = choose_splits(total, 2 * first_ktn);
     // with several workgroups to a tile their parts are added onto Z, which starts out as C
-    launch_pack<T>(a, packA, packB, p.nblkA, p.nblkB, p.KT, splits > 1 && a.C != a.Z, s);
+    const bool copy_c = splits > 1 && a.C != a.Z;
+    const bool copied = launch_pack<T>(a, packA, packB, p.nblkA, p.nblkB, p.KT, copy_c, s);
     spin_status st = check_launch(where_pack);
     if (st != SPIN_OK) return st;
+    if (copy_c && !copied) {
+        st = launch_open<T>(a.C, nullptr, (size_t)a.n * a.batch * a.M * a.N, 1, a.Z, s);
+        if (st != SPIN_OK) return st;
+    }
 
     static OncePerDevice lds_allowed;                    // one per ring type
     auto kernel = limb_gemm_kernel<T>;

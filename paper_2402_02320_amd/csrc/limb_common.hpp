@@ -1,5 +1,5 @@
 // What the limb-decomposed GEMMs over Z_2^32, Z_2^64 and Z_2^128 share: the balanced-digit conversion, the
-// fragment layout and the two pack kernels that open E (F) and lay all left (right) operands out as
+// fragment layout and the packs that open E (F) and lay all left (right) operands out as
 // int8 MFMA fragments, the direct-to-LDS load, and the mapping of workgroup ids to output tiles.
 //
 // A ring element of ND bytes (ND = 4, 8 or 16) is rewritten as ND balanced digits s_i in [-128,127] with
@@ -328,11 +328,15 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, long block,
 }
 template <int WAVES> __host__ __device__ inline unsigned pack_left_blocks(int nblk, int KT) { return (unsigned)(((long)nblk * KT + WAVES - 1) / WAVES); }
 
-// Everything that precedes the GEMM of one product in one launch: workgroups 0 .. left_blocks - 1 of a batch entry
-// pack left operands, the next right_blocks right ones, the last copy_blocks set Z = C where several workgroups will add
-// onto a tile of Z.  The parts are independent and each of them alone leaves most of the chip idle at the sizes where a
-// launch counts: a layer of 4 parties, 250 x 301 x 785, where they were three launches of 12.8 + 9.8 + 3.3 us, went from
-// 60.5 to 49.6 us, one of 2 parties, 1024^3, from 162.7 to 158.5 us.
+// The packs of one product: left operands, right ones, and the copy Z = C where several workgroups will add onto a tile
+// of Z.  Small ones go out as one launch (kBoth): workgroups 0 .. left_blocks - 1 of a batch entry pack left operands, the
+// next right_blocks right ones, the last copy_blocks copy.  The parts are independent and each of them alone leaves most of
+// the chip idle at the sizes where a launch counts: a layer of 4 parties, 250 x 301 x 785, where they were three launches of
+// 12.8 + 9.8 + 3.3 us, went from 60.5 to 49.6 us, one of 2 parties, 1024^3, from 162.7 to 158.5 us.
+// Streaming ones (kPackStreamingBytes) have a launch a part, because a kernel of all parts runs each at the occupancy of the
+// hungriest: for two parties over Z_2^128 the right pack's 298 registers halve the waves of the left one (447 -> 659 us at
+// 8192 x 64 x 2048).  packs_together draws the line between.
+enum PackSide { kBoth, kLeft, kRight };
 template <class T> struct PackLaunch {
     PackArgs<T> left, right;
     const T *copy_from;
@@ -343,15 +347,15 @@ template <class T> struct PackLaunch {
 template <class T> constexpr int pack_waves = sizeof(T) <= 8 ? 4 : 2;
 constexpr int kCopyPerThread = 8;
 
-template <int NP, class T, bool VEC, bool TRANSPOSED, bool NT>
+template <int NP, class T, bool VEC, bool TRANSPOSED, bool NT, PackSide SIDE>
 __global__ __launch_bounds__(64 * pack_waves<T>) void pack_kernel(PackLaunch<T> a)
 {
     constexpr int WAVES = pack_waves<T>;
-    __shared__ __attribute__((aligned(16))) char lds[WAVES * 32 * turn_row_bytes<T>];
+    __shared__ __attribute__((aligned(16))) char lds[SIDE == kRight && !TRANSPOSED ? 16 : WAVES * 32 * turn_row_bytes<T>];
     unsigned block = blockIdx.x;
-    if (block < a.left_blocks) {
+    if (SIDE == kLeft || (SIDE == kBoth && block < a.left_blocks)) {
         pack_left_body<NP, T, VEC, WAVES, NT>(a.left, block, blockIdx.z, lds, false);
-    } else if ((block -= a.left_blocks) < a.right_blocks) {
+    } else if (SIDE == kRight || (block -= a.left_blocks) < a.right_blocks) {
         if constexpr (TRANSPOSED) pack_left_body<NP, T, VEC, WAVES, NT>(a.right, block, blockIdx.z, lds, true);
         else pack_right_body<NP, T, WAVES, NT>(a.right, block, blockIdx.z);
     } else {
@@ -441,40 +445,57 @@ template <class T> inline bool pack_streams(int n, int batch, int rows, int cols
     return (size_t)n * batch * rows * cols * sizeof(T) >= kPackStreamingBytes;
 }
 
-template <class T> inline void launch_pack_part(const MatmulArgsT<T> &a, const PackLaunch<T> &p, bool nt, hipStream_t s)
+template <class T, PackSide SIDE> inline void launch_pack_part(const MatmulArgsT<T> &a, const PackLaunch<T> &p, bool nt, hipStream_t s)
 {
     constexpr int threads = 64 * pack_waves<T>;
     const bool vec = a.K % (16 / (int)sizeof(T)) == 0;   // rows 16-byte aligned
-    const dim3 grid(p.left_blocks + p.right_blocks + p.copy_blocks, 1, a.batch);
+    const unsigned blocks = SIDE == kLeft ? p.left_blocks : SIDE == kRight ? p.right_blocks : p.left_blocks + p.right_blocks + p.copy_blocks;
+    const dim3 grid(blocks, 1, a.batch);
     for_party_count(a.n, [&](auto np) {
         constexpr int NP = decltype(np)::value;
-        auto go = [&](auto vec_c, auto transposed_c, auto nt_c) {
-            pack_kernel<NP, T, decltype(vec_c)::value, decltype(transposed_c)::value, decltype(nt_c)::value><<<grid, threads, 0, s>>>(p);
+        auto go = [&](auto vec_c, auto transposed_c) {
+            constexpr bool VEC = decltype(vec_c)::value, TRANSPOSED = decltype(transposed_c)::value;
+            if constexpr (SIDE != kBoth) {               // products that stream past the caches have a launch a side
+                if (nt) {
+                    pack_kernel<NP, T, VEC, TRANSPOSED, true, SIDE><<<grid, threads, 0, s>>>(p);
+                    return;
+                }
+            }
+            pack_kernel<NP, T, VEC, TRANSPOSED, false, SIDE><<<grid, threads, 0, s>>>(p);
         };
-        auto with_nt = [&](auto vec_c, auto transposed_c) {
-            if (nt) go(vec_c, transposed_c, std::true_type());
-            else go(vec_c, transposed_c, std::false_type());
-        };
-        if constexpr (sizeof(T) == 8) {                  // only the 64-bit calls take a transposed right operand
+        if constexpr (sizeof(T) == 8 && SIDE != kLeft) { // only the 64-bit calls take a transposed right operand
             if (a.y_transposed) {
-                if (vec) with_nt(std::true_type(), std::true_type());
-                else with_nt(std::false_type(), std::true_type());
+                if (vec) go(std::true_type(), std::true_type());
+                else go(std::false_type(), std::true_type());
                 return;
             }
         }
-        if constexpr (sizeof(T) == 16) {
-            with_nt(std::true_type(), std::false_type());
+        if constexpr (sizeof(T) == 16 || SIDE == kRight) {                   // alignment of rows is all the same
+            go(std::true_type(), std::false_type());
         } else {
-            if (vec) with_nt(std::true_type(), std::false_type());
-            else with_nt(std::false_type(), std::false_type());
+            if (vec) go(std::true_type(), std::false_type());
+            else go(std::false_type(), std::false_type());
         }
     });
 }
 
-// Packs the left operands (X, A; unless packA is null) and the right ones (Y, B) of one Beaver matmul, and copies C to Z
-// when copy_c is set: one launch, or one per side where only one of them streams past the caches.
+// Whether the packs of both sides go out as one launch.  Measured over 600 products of 1 to 8 parties, one launch takes 4 to
+// 25 us less than two up to 1000 workgroups and no more beyond, except where its registers cost one side half of its waves: the
+// left pack of two parties over Z_2^128 once it has more workgroups than the chip holds at one wave per SIMD (1500 x 300 x 700,
+// 528 of them: 191 us a call against 180; 1024 x 64 x 512, 256 of them: 110 against 117).
+template <class T> inline bool packs_together(int n, unsigned long left_blocks)
+{
+    return sizeof(T) != 16 || n != 2 || left_blocks <= 2ul * compute_units();
+}
+// The copy rides along up to this size of C: at the occupancy of the packs it is slower than a launch of its own (5 parties 1024^3,
+// 42 MB: 388 us a call with it in the pack, 364 without; 3 parties over Z_2^32, 16384 x 128 x 576, 25 MB: 169 and 164; 8 parties 700 x
+// 500 x 300, 22 MB: 115 and 122).
+constexpr size_t kCopyWithPackBytes = (size_t)23 << 20;
+
+// Packs the left operands (X, A; unless packA is null) and the right ones (Y, B) of one Beaver matmul.  Where copy_c is set and
+// one of its launches can take the copy of C to Z along, that is done too; returns whether it was.
 template <class T>
-inline void launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int nblkA, int nblkB, int KT, bool copy_c, hipStream_t s)
+inline bool launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int nblkA, int nblkB, int KT, bool copy_c, hipStream_t s)
 {
     KernelTimer timer(SPIN_KERNEL_PACK, s);
     constexpr int WAVES = pack_waves<T>;
@@ -484,21 +505,36 @@ inline void launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int n
     else p.right = PackArgs<T>{a.Y, a.B, packB, a.n, a.batch, a.K, a.N, nblkB, KT};
     p.left_blocks = packA ? pack_left_blocks<WAVES>(nblkA, KT) : 0;
     p.right_blocks = a.y_transposed ? pack_left_blocks<WAVES>(nblkB, KT) : pack_right_blocks<WAVES>(nblkB, KT);
+    const bool nt_left = pack_streams<T>(a.n, a.batch, a.M, a.K), nt_right = pack_streams<T>(a.n, a.batch, a.K, a.N);
+    const bool both = p.left_blocks > 0 && !nt_left && !nt_right && packs_together<T>(a.n, (unsigned long)p.left_blocks * a.batch);
+    const size_t count = (size_t)a.n * a.batch * a.M * a.N, per_block = 64 * WAVES * kCopyPerThread;
+    copy_c = copy_c && count * sizeof(T) <= kCopyWithPackBytes && !(nt_left && nt_right);
     if (copy_c) {
         p.copy_from = a.C;
         p.copy_to = a.Z;
-        p.copy_count = (size_t)a.n * a.batch * a.M * a.N;
-        const size_t per_block = 64 * WAVES * kCopyPerThread, blocks = (p.copy_count + per_block - 1) / per_block;
-        p.copy_blocks = (unsigned)((blocks + a.batch - 1) / a.batch);
+        p.copy_count = count;
+        p.copy_blocks = (unsigned)(((count + per_block - 1) / per_block + a.batch - 1) / a.batch);
     }
-    const bool nt_left = pack_streams<T>(a.n, a.batch, a.M, a.K), nt_right = pack_streams<T>(a.n, a.batch, a.K, a.N);
-    if (p.left_blocks > 0 && nt_left != nt_right) {
-        PackLaunch<T> one = p;
-        one.right_blocks = one.copy_blocks = 0;
-        launch_pack_part<T>(a, one, nt_left, s);
+    if (both) {
+        launch_pack_part<T, kBoth>(a, p, false, s);
+        return copy_c;
+    }
+    // the copy goes with a side that does not stream, in the kernel of both with no workgroups for the other side
+    const bool copy_left = copy_c && !nt_left && p.left_blocks > 0, copy_right = copy_c && !copy_left;
+    PackLaunch<T> one = p;
+    if (copy_left) {
+        one.right_blocks = 0;
+        launch_pack_part<T, kBoth>(a, one, false, s);
+    } else if (p.left_blocks > 0) {
+        launch_pack_part<T, kLeft>(a, p, nt_left, s);
+    }
+    if (copy_right) {
         p.left_blocks = 0;
+        launch_pack_part<T, kBoth>(a, p, false, s);
+    } else {
+        launch_pack_part<T, kRight>(a, p, nt_right, s);
     }
-    launch_pack_part<T>(a, p, nt_right, s);
+    return copy_c;
 }
 
 }  // namespace
