@@ -491,6 +491,9 @@ template <class T> inline bool packs_together(int n, unsigned long left_blocks)
 // 42 MB: 388 us a call with it in the pack, 364 without; 3 parties over Z_2^32, 16384 x 128 x 576, 25 MB: 169 and 164; 8 parties 700 x
 // 500 x 300, 22 MB: 115 and 122).
 constexpr size_t kCopyWithPackBytes = (size_t)23 << 20;
+// Where only one of the sides streams, the copy goes with the other, which is then short: 7 parties over Z_2^32, 2880 x 128 x 1440, 10
+// MB: 177 us a call with it, 170 without; 5 parties 2000 x 100 x 1000, 8 MB: 147 and 150.
+constexpr size_t kCopyWithSideBytes = (size_t)8 << 20;
 
 // Packs the left operands (X, A; unless packA is null) and the right ones (Y, B) of one Beaver matmul.  Where copy_c is set and
 // one of its launches can take the copy of C to Z along, that is done too; returns whether it was.
@@ -508,7 +511,7 @@ inline bool launch_pack(const MatmulArgsT<T> &a, char *packA, char *packB, int n
     const bool nt_left = pack_streams<T>(a.n, a.batch, a.M, a.K), nt_right = pack_streams<T>(a.n, a.batch, a.K, a.N);
     const bool both = p.left_blocks > 0 && !nt_left && !nt_right && packs_together<T>(a.n, (unsigned long)p.left_blocks * a.batch);
     const size_t count = (size_t)a.n * a.batch * a.M * a.N, per_block = 64 * WAVES * kCopyPerThread;
-    copy_c = copy_c && count * sizeof(T) <= kCopyWithPackBytes && !(nt_left && nt_right);
+    copy_c = copy_c && count * sizeof(T) <= (both ? kCopyWithPackBytes : kCopyWithSideBytes) && !(nt_left && nt_right);
     if (copy_c) {
         p.copy_from = a.C;
         p.copy_to = a.Z;
