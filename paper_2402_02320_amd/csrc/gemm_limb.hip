@@ -32,6 +32,7 @@
 // Larger products go to the residue GEMM (gemm_residue.hip) and the smallest to one launch of vector arithmetic
 // (gemm_direct.hip); digit_cost_us is this file's side of that choice.
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "limb_common.hpp"
@@ -896,16 +897,22 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
     return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
 }
 
-// The same for the choice between them and the residue GEMM, fitted to 90 products of 45 us to 1.4 ms (2 to 5 parties, sides 64 to
-// 4096; rms error 5.5 %); parts of shared tiles that are added onto Z cost 0.44 us a megabyte of its words read and written.
+// The same for the choice between them and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
+// parties, sides 32 to 8192), within 6 % (rms).  The clock is higher where the tiles leave part of the chip idle; parts of shared
+// tiles that are added onto Z cost 0.3 us a megabyte of its words read and written.
 inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p)
 {
-    if (rows_kernel_applies<u64>(a, p)) return 1.25 * rows_kernel_cost<u64>(a, p) + 10;
-    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch, cus = compute_units();
+    const int cus = compute_units();
+    const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
+    if (rows_kernel_applies<u64>(a, p)) {
+        const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
+        return rounds * 1.214 * 2 * p.KT + words * a.N * a.K / 3.85e6 + 3.15 * a.n + 0.331 * out_mb;
+    }
+    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = choose_splits(tiles, 2 * p.KT);
-    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
-    const double added = sp > 1 ? 16.0 * a.n * a.batch * a.M * a.N * 0.44e-6 : 0;
-    return (double)((tiles * sp + cus - 1) / cus) * (1.42 * 2 * ceil_div(p.KT, sp) + 6.7) + pack_bytes / 5.2e6 + added;
+    const double filled = (double)tiles * sp / cus, rounds = std::ceil(filled);
+    return rounds * (1.52 * 2 * ceil_div(p.KT, sp) * (1 - 0.592 * (1 - filled / rounds)) + 6.6) +
+           words * ((double)a.M + a.N) * a.K / 5.4e6 + 1.1 + 1.52 * a.n + (sp > 1 ? 0.305 * out_mb : 0);
 }
 
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
@@ -940,8 +947,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
 
-    const double digits_us = digit_cost_us<T>(a, p);
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digits_us)) return launch_matmul_direct<T>(a, s, where_gemm);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p))) return launch_matmul_direct<T>(a, s, where_gemm);
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;

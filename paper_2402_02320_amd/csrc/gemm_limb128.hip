@@ -13,6 +13,7 @@
 // buffered.  So: workgroup tile 64x64 (4 waves as 2x2), two LDS stages of 64 KB, loads of step s+1
 // issued between the MFMAs of step s, fragments of a step read at its start.
 #include <algorithm>
+#include <cmath>
 
 #include "limb_common.hpp"
 
@@ -183,9 +184,17 @@ inline Plan128 make_plan128(int n, int batch, int M, int N, int K)
     return p;
 }
 
-// Estimated time in microseconds, for the choice between this kernel and the residue GEMM: 3.2 us a k-step (136 MFMAs of 32
-// cycles), within 25 % of the measured times of 12 shapes between 128^3 and 2048^3.
-inline double digit128_cost_us(int n, int batch, const Plan128 &p)
+// Estimated time in microseconds of the pack and this kernel: k-steps (136 MFMAs of 32 cycles; faster, at a higher clock, where
+// the tiles leave part of the chip idle), the packs as streams, and a pack's wave that converts the parties' shares one after
+// another.  A fit to 250 products of 30 us to 1.7 ms, within 7 % (rms).
+inline double digit128_cost_us(int n, int batch, int M, int N, int K, const Plan128 &p)
+{
+    const double filled = (double)p.tilesM * p.tilesN * n * batch / compute_units(), rounds = std::ceil(filled);
+    const double pack_bytes = 16.0 * (3 * n + 1) * batch * ((double)M + N) * K;
+    return rounds * (2.85 * 2 * p.KT * (1 - 0.235 * (1 - filled / rounds)) + 6.9) + pack_bytes / 5.94e6 + 8.4 + 2.07 * n;
+}
+// The k-steps alone, 3.2 us each: the other side of the direct kernel's own rough estimate.
+inline double digit128_rough_us(int n, int batch, const Plan128 &p)
 {
     const long tiles = (long)p.tilesM * p.tilesN * n * batch, cus = compute_units();
     return 3.2 * (double)((tiles + cus - 1) / cus) * (2 * p.KT + 4);
@@ -197,7 +206,7 @@ size_t limb128_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
 {
     const Plan128 p = make_plan128(n, batch, M, N, K);
     if (ring_macs(n, batch, M, N, K) < kResidueMinMacs128) return p.packA_bytes + p.packB_bytes;
-    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u128>(n, batch, M, N, K, digit128_cost_us(n, batch, p)));
+    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u128>(n, batch, M, N, K, digit128_cost_us(n, batch, M, N, K, p)));
 }
 
 size_t limb128_workspace_bytes(int n, int batch, int M, int N, int K)
@@ -209,8 +218,8 @@ size_t limb128_workspace_bytes(int n, int batch, int M, int N, int K)
 spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
 {
     const Plan128 p = make_plan128(a.n, a.batch, a.M, a.N, a.K);
-    const double digits_us = digit128_cost_us(a.n, a.batch, p);
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, 16, digits_us)) return launch_matmul_direct<u128>(a, s, "spin128_beaver_matmul(direct)");
+    const double digits_us = digit128_cost_us(a.n, a.batch, a.M, a.N, a.K, p);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, 16, digit128_rough_us(a.n, a.batch, p))) return launch_matmul_direct<u128>(a, s, "spin128_beaver_matmul(direct)");
     spin_status st = SPIN_OK;
     if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs128) {
         bool taken = false;

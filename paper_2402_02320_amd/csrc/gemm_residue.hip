@@ -706,20 +706,26 @@ template <class T> inline void plan_sizes(ResiduePlan &p, int cus)
 }
 
 // Estimated time in microseconds of a plan: k-steps of a tile (256 MFMAs of 16 cycles on four SIMDs), a fixed part per item, the
-// bytes of pack and combine as streams, and three launches with their ramps per block of the plan.  The 64-bit constants are a
-// fit to 90 measured products (2 to 5 parties, sides 64 to 4096, 45 us to 1.4 ms; rms error 4.8 %, digit_cost_large_us 5.5 %):
-// choosing by the two costs 0.3 % over always taking the faster, where one clock and one rate for all streams cost 3.5 % and
-// lost up to 37 % on 5x3269x93x264 (79 us by digits, 109 by residues).  Those of Z_2^128 are within 15 % from 100 us on.
+// bytes of pack and combine as streams, and the three launches with their ramps.  A wave of the pack converts the parties' shares
+// one after another, so that a short call over Z_2^128 waits 5 us a party for it (63 us in all at 3 parties 320 x 128 x 96).  Both
+// sets are fits to about 2000 products (1 to 8 parties, sides 32 to 8192, wide and narrow tiles, plans of one and of several
+// blocks): rms error 5 % over Z_2^64, 8 % over Z_2^128 where the digit kernels are near.
 template <class T> struct ResidueCost;
 template <> struct ResidueCost<u64> {
-    static constexpr double step = 0.585, item = 6.0, narrow_step = 0.617, narrow_item = 0.426;      // of a wide tile's
-    static constexpr double pack_bytes_per_us = 3.8e6, combine_bytes_per_us = 10e6;                  // (its reads come from cache)
-    static constexpr double first_block = 10, shared = 5.5, block = 40;
+    static constexpr double step = 0.665, item = 0.46, narrow_step = 0.611;                          // of a wide tile's
+    static constexpr double pack_bytes_per_us = 4.46e6, combine_bytes_per_us = 4.87e6;
+    static constexpr double first_block = 11.6, first_block_party = 1.75, shared = 2.5, block = 12.6, block_party = 2.1;
 };
 template <> struct ResidueCost<u128> {
-    static constexpr double step = 0.64, item = 4.2, narrow_step = 0.66, narrow_item = 0.6;
-    static constexpr double pack_bytes_per_us = 4.7e6, combine_bytes_per_us = 4.7e6, first_block = 18, shared = 12, block = 40;
+    static constexpr double step = 0.646, item = 0, narrow_step = 0.615;
+    static constexpr double pack_bytes_per_us = 4.17e6, combine_bytes_per_us = 4.44e6;
+    static constexpr double first_block = 24.8, first_block_party = 4.82, shared = 19, block = 16, block_party = 5.56;
 };
+// Taken where its estimate is this much below the digit kernels'.  On those products, time against always the digit kernels: 0.883
+// over Z_2^128 and 0.985 over Z_2^64 with margin and without; slower than by digits were 4 and 1 products of 2000 by more than 2 % (7 %
+// at most), without the margin 19 and 10 (16 % at most).  With the constants fitted to fewer products and no margin it was 90 of
+// 1900 over Z_2^128 (76 %: 3 parties 320 x 128 x 96 34 -> 63 us) and 11 of 2100 over Z_2^64.
+constexpr double kResidueMargin = 0.95;
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {
     using C = ResidueCost<T>;
@@ -728,7 +734,7 @@ template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batc
     const int groups = ceil_div(n, p.group);
     const unsigned items = plan_items<T>(p), grid = resident_workgroups(cus), rest = items % grid;
     const int parts = p.share ? parts_of(items, grid, p.KT) : 1;
-    const double step = p.narrow ? C::step * C::narrow_step : C::step, item = p.narrow ? C::item * C::narrow_item : C::item;
+    const double step = p.narrow ? C::step * C::narrow_step : C::step, item = p.narrow ? 0 : C::item;
     const double y_bytes = (double)items * tile_bytes_of(p.narrow), part_bytes = (double)rest * (parts - 1) * tile_bytes_of(p.narrow);
     double block_us = items / grid * (2 * p.KT * step + item) + 2 * (y_bytes + part_bytes) / C::combine_bytes_per_us;
     if (rest > 0) block_us += 2 * p.KT * step / parts + item;
@@ -741,7 +747,7 @@ template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batc
     const double right = (double)right_reps * K * (N * w * 2 * n + padN * L * (n + 1));
     const double out = (double)n * M * N * 2 * w * chunks;
     return batch * (blocks * block_us + (left + right) / C::pack_bytes_per_us + out / C::combine_bytes_per_us) + C::first_block +
-           C::block * (blocks * batch - 1);
+           C::first_block_party * n + (C::block + C::block_party * p.group) * (blocks * batch - 1);
 }
 
 // The cheapest plan that fits `bytes`; false when none does.  For every number of row blocks only the smallest number
@@ -878,7 +884,7 @@ spin_status launch_matmul_residue(const MatmulArgsT<T> &a, double digit_cost_us,
 {
     ResiduePlan p;
     double cost = 0;
-    taken = best_plan<T>(a.n, a.batch, a.M, a.N, a.K, a.workspace_bytes, p, cost) && cost < digit_cost_us;
+    taken = best_plan<T>(a.n, a.batch, a.M, a.N, a.K, a.workspace_bytes, p, cost) && cost < kResidueMargin * digit_cost_us;
     return taken ? run_residue<T>(a, p, s, where) : SPIN_OK;
 }
 template spin_status launch_matmul_residue<u64>(const MatmulArgsT<u64> &, double, hipStream_t, const char *, bool &);
@@ -888,7 +894,7 @@ template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N
 {
     ResiduePlan p;
     double cost = 0;
-    return best_plan<T>(n, batch, M, N, K, kAmpleWorkspace, p, cost) && cost < digit_cost_us ? plan_bytes<T>(p) : 0;
+    return best_plan<T>(n, batch, M, N, K, kAmpleWorkspace, p, cost) && cost < kResidueMargin * digit_cost_us ? plan_bytes<T>(p) : 0;
 }
 template size_t residue_workspace_bytes<u64>(int, int, int, int, int, double);
 template size_t residue_workspace_bytes<u128>(int, int, int, int, int, double);
