@@ -712,19 +712,21 @@ template <class T> inline void plan_sizes(ResiduePlan &p, int cus)
 // blocks): rms error 5 % over Z_2^64, 8 % over Z_2^128 where the digit kernels are near.
 template <class T> struct ResidueCost;
 template <> struct ResidueCost<u64> {
-    static constexpr double step = 0.665, item = 0.46, narrow_step = 0.611;                          // of a wide tile's
-    static constexpr double pack_bytes_per_us = 4.46e6, combine_bytes_per_us = 4.87e6;
-    static constexpr double first_block = 11.6, first_block_party = 1.75, shared = 2.5, block = 12.6, block_party = 2.1;
+    static constexpr double step = 0.661, item = 0.34, narrow_step = 0.608;                          // of a wide tile's
+    static constexpr double pack_bytes_per_us = 4.46e6, combine_bytes_per_us = 4.8e6;
+    static constexpr double first_block = 11.4, first_block_party = 2.0, block = 13.3, block_party = 2.0;
+    static constexpr double shared = 0, shared_part = 2.0;                                           // the combine fetches part by part
 };
 template <> struct ResidueCost<u128> {
-    static constexpr double step = 0.646, item = 0, narrow_step = 0.615;
-    static constexpr double pack_bytes_per_us = 4.17e6, combine_bytes_per_us = 4.44e6;
-    static constexpr double first_block = 24.8, first_block_party = 4.82, shared = 19, block = 16, block_party = 5.56;
+    static constexpr double step = 0.636, item = 0, narrow_step = 0.613;
+    static constexpr double pack_bytes_per_us = 4.2e6, combine_bytes_per_us = 4.39e6;
+    static constexpr double first_block = 25.2, first_block_party = 4.97, block = 18.2, block_party = 5.43;
+    static constexpr double shared = 4.2, shared_part = 7.1;
 };
-// Taken where its estimate is this much below the digit kernels'.  On those products, time against always the digit kernels: 0.883
-// over Z_2^128 and 0.985 over Z_2^64 with margin and without; slower than by digits were 4 and 1 products of 2000 by more than 2 % (7 %
-// at most), without the margin 19 and 10 (16 % at most).  With the constants fitted to fewer products and no margin it was 90 of
-// 1900 over Z_2^128 (76 %: 3 parties 320 x 128 x 96 34 -> 63 us) and 11 of 2100 over Z_2^64.
+// Taken where its estimate is this much below the digit kernels'.  On those products, time against always the digit kernels: 0.884
+// over Z_2^128 and 0.986 over Z_2^64; slower than by digits were 3 and 1 products of 2000 by more than 2 % (8 % at most), without the
+// margin 17 and 9 (16 %).  With the constants fitted to fewer products and no margin it was 90 of 1900 over Z_2^128 (76 %: 3
+// parties 320 x 128 x 96 34 -> 63 us) and 11 of 2100 over Z_2^64.
 constexpr double kResidueMargin = 0.95;
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {
@@ -738,7 +740,7 @@ template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batc
     const double y_bytes = (double)items * tile_bytes_of(p.narrow), part_bytes = (double)rest * (parts - 1) * tile_bytes_of(p.narrow);
     double block_us = items / grid * (2 * p.KT * step + item) + 2 * (y_bytes + part_bytes) / C::combine_bytes_per_us;
     if (rest > 0) block_us += 2 * p.KT * step / parts + item;
-    if (parts > 1) block_us += C::shared;
+    if (parts > 1) block_us += C::shared + C::shared_part * (parts - 1);
     const double blocks = (double)chunks * blocksM * blocksN * groups;
     const bool left_kept = p.group == n;                 // the left triples stay converted across the blocks of a row
     const double w = sizeof(T), padM = (double)p.totalM * kPanel, padN = (double)p.totalN * kPanel;
