@@ -143,9 +143,9 @@ template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N
 size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K);
 size_t limb128_preferred_workspace_bytes(int n, int batch, int M, int N, int K);
 // Small products in one launch on the vector ALU (gemm_direct.hip), and whether that is estimated to be faster than
-// digit kernels of `digit_cost_us`.  T = u32, u64 or u128
+// digit kernels of `rough_us` and, by the finer estimate, `digits_us`.  T = u32, u64 or u128
 template <class T> spin_status launch_matmul_direct(const MatmulArgsT<T> &a, hipStream_t s, const char *where);
-bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, double digit_cost_us);
+bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, double rough_us, double digits_us);
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K);
 spin_status launch_matmul_limb32(const MatmulArgs32 &a, hipStream_t s);
 spin_status launch_mfma_probe(const u64 *operands, int blocks, int iters, u64 *sink, hipStream_t s);

@@ -12,7 +12,7 @@ namespace spin {
 namespace {
 
 constexpr int kTile = 16;
-// inner dimension per round: four operand tiles of 8.4 KB (8.5 KB for 16-byte elements) in LDS, four workgroups to a CU
+// inner dimension per round: four operand tiles of 8448 bytes in LDS (4352 of 4-byte elements), up to four workgroups to a CU
 template <class T> constexpr int kDepth = sizeof(T) == 16 ? 32 : 64;
 
 template <class T> struct DirectArgs {
@@ -112,20 +112,45 @@ __global__ __launch_bounds__(256) void direct_matmul_kernel(DirectArgs<T> g)
 
 }  // namespace
 
-// Estimated time against that of the digit kernels.  A workgroup's round (load, open, multiply) takes 1.45, 2.8 or 4.2 us
-// over 4-, 8- or 16-byte elements however few tiles there are; beyond that a tile costs the chip 2 or 8 ns for three
-// parties.  Both fitted to 33 shapes between 16^3 and 512 x 512 x 32 (within 20 %).  The digit estimate is about a third
-// high for the smallest products, hence the factors.  Measured, this against the limb path: 3 parties 64^3 5.7 : 18.8 us,
-// 128^3 9.7 : 23.8, 256 x 256 x 64 10.4 : 19.6; left to the limb path: 256^3 30.9 : 25.4, 2 parties 64 x 64 x 512 24.8 : 21.9,
-// 3 parties 512 x 512 x 32 29.2 : 17.7.  Over Z_2^128 long inner dimensions are the residue GEMM's.
-bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, double digit_cost_us)
+// Estimated time against that of the digit kernels, twice; both have to speak for this kernel.
+//
+// Roughly: a workgroup's round (load, open, multiply) takes 1.45, 2.8 or 4.2 us over 4-, 8- or 16-byte elements however few tiles
+// there are; beyond that a tile costs the chip 2 or 8 ns for three parties.  The rough digit estimate is about a third high for
+// the smallest products, hence the factors.
+//
+// In detail: a round's latency grows with the parties, tiles share the chip, and a k-slab of operands that outgrows an XCD's L2 (4
+// MB) has to be read anew by every tile that wants it.  Fits to 12 500 products that the rough estimate takes, within 10 % (rms), and
+// 7 to 10 % on the digit side.  Out of 22 000 products near the line the rough estimate alone takes these by more than 2 % wrongly:
+// 352 over Z_2^32 (up to 2.8 times: 5 parties, batch 61, 6 x 943 x 228, 1014 us against 362), 77 over Z_2^64 (1.8 times: 7 parties,
+// batch 19, 13 x 476 x 43, 135 against 74), 10 over Z_2^128; wide and batched products above all.  With both it is 76, 45 and 2.
+//
+// Measured, this against the limb path: 3 parties 64^3 5.7 : 18.8 us, 128^3 9.7 : 23.8, 256 x 256 x 64 10.4 : 19.6; left to the limb
+// path: 256^3 30.9 : 25.4, 2 parties 64 x 64 x 512 24.8 : 21.9, 3 parties 512 x 512 x 32 29.2 : 17.7.  Over Z_2^128 long inner
+// dimensions are the residue GEMM's.
+bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, double rough_us, double digits_us)
 {
-    const double tiles = (double)ceil_div(M, kTile) * ceil_div(N, kTile) * n * batch;
+    const int tilesM = ceil_div(M, kTile), tilesN = ceil_div(N, kTile);
+    const double tiles = (double)tilesM * tilesN * n * batch;
     const int rounds = ceil_div(K, elem_bytes == 16 ? kDepth<u128> : kDepth<u64>);
     const double each = (elem_bytes == 4 ? 0.002 : 0.008) * (n + 1) / 4;
     const double base = elem_bytes == 4 ? 1.45 : elem_bytes == 8 ? 2.8 : 4.2;
     if (elem_bytes == 16 && rounds > 8) return false;
-    return 2.5 + rounds * (base + each * tiles) < (elem_bytes == 16 ? 0.75 : 0.62) * digit_cost_us;
+    if (2.5 + rounds * (base + each * tiles) >= (elem_bytes == 16 ? 0.75 : 0.62) * rough_us) return false;
+
+    struct Cost { double launch, round, round_party, share, share_party, slab_mb, mb_per_us, alone; };
+    // alone: how much more of the chip a tile takes where the registers leave a CU one workgroup (7 and 8 parties over Z_2^64, 4 to 8
+    // over Z_2^128)
+    const Cost c = elem_bytes == 4   ? Cost{2.24, 1.00, 0.106, 0.458, 0.148, 1.85, 27.4, 0}
+                   : elem_bytes == 8 ? Cost{2.13, 1.81, 0.371, 0.984, 0.313, 2.04, 29.2, n >= 7 ? 0.366 : 0}
+                                     : Cost{2.42, 3.55, 0.160, 1.855, 0.153, 1.98, 20.0, n >= 4 ? 0.844 : 0};
+    const double w = elem_bytes, slab_mb = 2.0 * n * batch * ((double)M + N) * K * w / rounds / 1e6;
+    // bytes of one row of a right operand's tile, in whole lines where its neighbours have the rest of them
+    const double row = tilesN == 1 ? N * w : kTile * w + (N * elem_bytes % 128 == 0 ? 0 : 64);
+    const double read_mb = 2.0 * n * K * (tiles * row + (double)tilesN * n * batch * M * w) / 1e6;
+    const double missed = slab_mb > c.slab_mb ? 1 - c.slab_mb / slab_mb : 0;
+    const double us = c.launch + rounds * (c.round + c.round_party * n + (c.share + c.share_party * n) * (1 + c.alone) * tiles / 256) +
+                      missed * read_mb / c.mb_per_us;
+    return us < 0.97 * digits_us;
 }
 
 template <class T> spin_status launch_matmul_direct(const MatmulArgsT<T> &a, hipStream_t s, const char *where)

@@ -897,6 +897,23 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
     return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
 }
 
+// The same in detail, for small products: the waves of a pack convert the parties' shares one after another, and the
+// output counts.  A fit to 19 500 products of 5 us to 2 ms near the line between the two kernels, within 8 (9 over Z_2^32) % (rms).
+template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p)
+{
+    const int cus = compute_units();
+    const double words = (double)sizeof(T) * (3 * a.n + 1) * a.batch, out_mb = 2e-6 * sizeof(T) * a.n * a.batch * (double)a.M * a.N;
+    if (rows_kernel_applies<T>(a, p)) {
+        const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
+        return rounds * (1.228 * 2 * p.KT + 3.96) + words * a.N * a.K / 4.35e6 + 3.8 + 2.03 * a.n + 0.236 * out_mb;
+    }
+    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
+    const int sp = choose_splits(tiles, 2 * p.KT);
+    const double rounds = (double)((tiles * sp + cus - 1) / cus), packed = words * ((double)a.M + a.N) * a.K;
+    return sizeof(T) == 8 ? rounds * (1.107 * 2 * ceil_div(p.KT, sp) + 4.78) + packed / 4.49e6 + 4.1 + 1.76 * a.n + 0.181 * out_mb
+                          : rounds * (0.716 * 2 * ceil_div(p.KT, sp) + 5.56) + packed / 5.0e6 + 3.7 + 1.36 * a.n + 0.161 * out_mb;
+}
+
 // The same for the choice between them and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
 // parties, sides 32 to 8192), within 6 % (rms).  The clock is higher where the tiles leave part of the chip idle; parts of shared
 // tiles that are added onto Z cost 0.3 us a megabyte of its words read and written.
@@ -947,7 +964,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
 
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p))) return launch_matmul_direct<T>(a, s, where_gemm);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p), digit_cost_small_us<T>(a, p))) return launch_matmul_direct<T>(a, s, where_gemm);
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;

@@ -219,7 +219,7 @@ spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
 {
     const Plan128 p = make_plan128(a.n, a.batch, a.M, a.N, a.K);
     const double digits_us = digit128_cost_us(a.n, a.batch, a.M, a.N, a.K, p);
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, 16, digit128_rough_us(a.n, a.batch, p))) return launch_matmul_direct<u128>(a, s, "spin128_beaver_matmul(direct)");
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, 16, digit128_rough_us(a.n, a.batch, p), digits_us)) return launch_matmul_direct<u128>(a, s, "spin128_beaver_matmul(direct)");
     spin_status st = SPIN_OK;
     if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs128) {
         bool taken = false;
