@@ -153,15 +153,45 @@ def beaver_matmul_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
     return int(lib().spin_beaver_matmul_workspace_bytes(n, batch, M, N, K, path))
 
 
+def beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
+    """The size with which beaver_matmul is fastest; never below beaver_matmul_workspace_bytes."""
+    return int(lib().spin_beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path))
+
+
+# Workspace beyond what a call needs that is taken without a look at the device's memory (0.02 % of it): the look takes 5 to 50 us on
+# the host, as much as a call takes whose workspaces differ by less.
+_UNASKED_BYTES = 64 << 20
+
+
+def _has_room(size, device):
+    """Whether `size` bytes are at most a quarter of the memory this process can still get on the device.  Asking torch for more
+    than there is makes it synchronise and give its whole cache back before it fails, on every call."""
+    free, total = torch.cuda.mem_get_info(device)
+    share = torch.cuda.get_per_process_memory_fraction(device)
+    if share == 1.0 and 4 * size <= free:
+        return True
+    if torch.cuda.is_current_stream_capturing():
+        return False                                     # a graph's own pool has no use for what torch has cached
+    stats = torch.cuda.memory_stats(device)
+    reserved = stats.get("reserved_bytes.all.current", 0)
+    cached = reserved - stats.get("allocated_bytes.all.current", 0) - stats.get("inactive_split_bytes.all.current", 0)
+    return 4 * size <= min(free, int(share * total) - reserved) + cached
+
+
 def _matmul_workspace(dims, path, need_of, preferred_of, device):
-    """A workspace of the preferred size, or, where that much memory is not free, of the size needed."""
-    preferred = int(preferred_of(*dims, path))
-    if preferred == 0:
+    """A workspace of the preferred size, or, where memory is short, of the size needed."""
+    size = int(preferred_of(*dims, path))
+    if size == 0:
         raise SpinError("invalid matmul dimensions")
+    need = int(need_of(*dims, path))
+    if size > need + _UNASKED_BYTES and device.type == "cuda" and not _has_room(size, device):
+        size = need
     try:
-        return torch.empty(preferred, dtype=torch.uint8, device=device)
+        return torch.empty(size, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
-        return torch.empty(int(need_of(*dims, path)), dtype=torch.uint8, device=device)
+        if size == need:
+            raise
+        return torch.empty(need, dtype=torch.uint8, device=device)
 
 
 def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_transposed=False):
@@ -396,6 +426,10 @@ class ring128:
     @staticmethod
     def beaver_matmul_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
         return int(lib().spin128_beaver_matmul_workspace_bytes(n, batch, M, N, K, path))
+
+    @staticmethod
+    def beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
+        return int(lib().spin128_beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path))
 
     @staticmethod
     def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None):
