@@ -137,8 +137,8 @@ inline double ring_macs(int n, int batch, int M, int N, int K) { return 2.0 * n 
 // ran.  Works within a.workspace_bytes.  T = u64 or u128.
 template <class T>
 spin_status launch_matmul_residue(const MatmulArgsT<T> &a, double digit_cost_us, hipStream_t s, const char *where, bool &taken);
-// Workspace with which the residue GEMM works in few blocks; 0 where it is not the faster one.
-template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N, int K, double digit_cost_us);
+// Workspace with which the residue GEMM works in few blocks; 0 where it is not the faster one.  need: the digit path's.
+template <class T> size_t residue_workspace_bytes(int n, int batch, int M, int N, int K, size_t need, double digit_cost_us);
 // The larger of the digit path's need and of that.
 size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K);
 size_t limb128_preferred_workspace_bytes(int n, int batch, int M, int N, int K);

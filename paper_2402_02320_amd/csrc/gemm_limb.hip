@@ -1164,7 +1164,8 @@ size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
     if (ring_macs(n, batch, M, N, K) < kResidueMinMacs64) return p.packA_bytes + p.packB_bytes;
     MatmulArgs a{};
     a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
-    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u64>(n, batch, M, N, K, digit_cost_large_us(a, p)));
+    const size_t need = p.packA_bytes + p.packB_bytes;
+    return std::max(need, residue_workspace_bytes<u64>(n, batch, M, N, K, need, digit_cost_large_us(a, p)));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)

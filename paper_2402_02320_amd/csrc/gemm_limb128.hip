@@ -206,7 +206,8 @@ size_t limb128_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
 {
     const Plan128 p = make_plan128(n, batch, M, N, K);
     if (ring_macs(n, batch, M, N, K) < kResidueMinMacs128) return p.packA_bytes + p.packB_bytes;
-    return std::max(p.packA_bytes + p.packB_bytes, residue_workspace_bytes<u128>(n, batch, M, N, K, digit128_cost_us(n, batch, M, N, K, p)));
+    const size_t need = p.packA_bytes + p.packB_bytes;
+    return std::max(need, residue_workspace_bytes<u128>(n, batch, M, N, K, need, digit128_cost_us(n, batch, M, N, K, p)));
 }
 
 size_t limb128_workspace_bytes(int n, int batch, int M, int N, int K)

@@ -25,3 +25,11 @@ def test_residue_or_digits(bits, n, batch, M, N, K, residue):
     need, preferred = (getattr(spin.lib(), pre + "_beaver_matmul_" + q) for q in ("workspace_bytes", "preferred_workspace_bytes"))
     args = (n, batch, M, N, K, spin.LIMB_MFMA)
     assert (preferred(*args) > need(*args)) is residue
+
+
+def test_no_workspace_of_gigabytes_for_a_hundredth():
+    # 3.5 GB in two blocks are estimated (and measured) no slower than 5.1 GB in one
+    q = spin.beaver_matmul_preferred_workspace_bytes
+    assert spin.beaver_matmul_workspace_bytes(5, 1, 4096, 4096, 4096) < q(5, 1, 4096, 4096, 4096) < 4e9
+    assert spin.beaver_matmul_workspace_bytes(3, 1, 4096, 4096, 2048) < q(3, 1, 4096, 4096, 2048) < 1e9
+    assert spin.ring128.beaver_matmul_preferred_workspace_bytes(2, 1, 2048, 2048, 2048) > 1e9     # 4 % faster than in 0.75 GB
