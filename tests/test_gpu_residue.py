@@ -1,7 +1,7 @@
 """The residue GEMM (large products over Z_2^64 and Z_2^128) against the CPU oracle and the VALU path: partial panels and
-k-steps, a second inner-dimension chunk, transposed right operands, C updated in place, every plan of blocks (ample
-workspace: all parties and the whole output at once; the workspace the call needs: party by party, panel by panel), and
-operands whose digits are all extreme.  Results are ring words, so equality is exact."""
+k-steps, a second inner-dimension chunk, transposed right operands, some plans of several blocks (the others are in
+test_gpu_residue_plans.py), and operands whose digits are all extreme; the same products in place on C in the workspace that
+the call needs, where they mostly go to the digit kernels.  Results are ring words, so equality is exact."""
 import ctypes
 
 import numpy as np
@@ -43,7 +43,7 @@ SHAPES64 = [(5, 1, 1025, 1200, 1001, False),      # odd K (no 16-byte rows), one
             (2, 2, 1500, 1030, 1600, False),      # two batch entries
             (3, 1, 2048, 1024, 1537, True),       # odd K, transposed
             (4, 1, 1024, 1024, 1088, False),      # 4.5 rounds of workgroups: the last items come in two parts
-           (2, 1, 1500, 1500, 1400, False)]      # 5.06 rounds: a few items in several parts
+            (2, 1, 1500, 1500, 1400, False)]     # 5.06 rounds: a few items in several parts
 
 
 @pytest.mark.parametrize("n,batch,M,N,K,transposed", SHAPES64)
