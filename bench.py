@@ -326,7 +326,8 @@ def bench_matmul_other_ring(args, bits):
     print(json.dumps({"metric": "Z_2^%d ring MACs/s for Beaver matmul (side workload)" % bits,
                       "value": macs / (ms * 1e-3), "unit": "ring MAC/s", "n_gpus": 1, "steps": args.steps,
                       "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "vs_baseline": None,
-                      "dtype": ring + " (int8 digits, int32 accumulate)" if path == spin.LIMB_MFMA else ring,
+                      "dtype": "%s (int8 %s, int32 accumulate)" % (ring, "residues" if key == "gemm_residue" else "digits")
+                      if path == spin.LIMB_MFMA else ring,
                       "data": "synthetic",
                       "config": {"workload": "%d parties, M=N=K=%d over Z_2^%d" % (n, M, bits), "gemm_path": args.path},
                       "roofline": roof, "gemm_avg_ms": gemm_ms, "pack_avg_ms": pk / pc if pc else None}))
@@ -642,7 +643,8 @@ def run_config(args, cfg):
         "metric": "Z_2^64 ring MACs/s for Beaver matmul (1 GPU)", "value": ring_macs / (ms_per_step * 1e-3),
         "unit": "ring MAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "u64 (int8 digits, int32 accumulate)" if path == spin.LIMB_MFMA else "u64",
+        "dtype": "u64 (int8 %s, int32 accumulate)" % ("residues" if residue else "digits")
+        if path == spin.LIMB_MFMA and not direct else "u64",
         "data": "synthetic",
         "config": {"workload": "config %d: %d parties, f=%d, %s; step = %s" % (cfg, n, f, c.dist, "; then ".join(legs)),
                    "gemm_path": args.path, "parties": n, "launch": "hip graph replay" if args.graph else "eager",

@@ -136,9 +136,9 @@ size_t spin_beaver_matmul_grouped_workspace_bytes(int n, int groups, const spin_
 size_t spin_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int K, int path);
 
 /* Bytes of workspace with which spin_beaver_matmul (and _nt) is fastest; never less than it needs, 0 if the
- * arguments are invalid.  Large products run on residues modulo 18 small primes (powers), whose operand copies take
- * 18 bytes an element; with less than this workspace such a product is computed in more blocks, or by the
- * digit kernels.  The result is the same words either way.                                                    */
+ * arguments are invalid.  Large products run on residues modulo 18 pairwise coprime numbers of at most eight bits (36 for
+ * spin128_beaver_matmul), whose operand copies take 18 (36) bytes an element; with less than this workspace such a product
+ * is computed in more blocks, or by the digit kernels.  The result is the same words either way.                  */
 size_t spin_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path);
 
 /* spin_beaver_matmul for callers that cannot allocate device memory, and so cannot bring a workspace:

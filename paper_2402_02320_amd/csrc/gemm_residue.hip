@@ -538,14 +538,12 @@ __device__ inline u32 add_residues(u32 a, u32 b, u32 p)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const u32 sum = ((a >> (8 * h)) & 0x00ff00ffu) + ((b >> (8 * h)) & 0x00ff00ffu);     // below 2^10 each
-        // the lesser of sum and sum - p as unsigned halves (sum - p wraps to a large one when sum < p)
-        const u32 less = sum + (0x02000200u - pp);       // bit 9 of a half: sum >= p
-        const u32 mask = ((less >> 9) & 0x00010001u) * 0xffffu;
+        const u32 test = sum + (0x02000200u - pp);       // bit 9 of a half: sum >= p
+        const u32 mask = ((test >> 9) & 0x00010001u) * 0xffffu;
         r[h] = sum - (pp & mask);
     }
     return r[0] | r[1] << 8;
 }
-
 
 // One lane: the 16 bytes per modulus that one lane of the GEMM stored = 4 rows x 4 columns (16 apart).  S of an
 // element is a sum of byte products: with y_l and the bytes of P/p_l as operands of 4-byte dot products, byte column j
