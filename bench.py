@@ -295,7 +295,8 @@ def bench_matmul_other_ring(args, bits):
         return torch.empty(shape, dtype=torch.int32, device="cuda").random_(-2 ** 31, 2 ** 31)
     X, Y, A, B, C = (rnd((n, 1, M, M)) for _ in range(5))
     Z = torch.empty_like(C)
-    ws = torch.empty(R.beaver_matmul_workspace_bytes(n, 1, M, M, M, path), dtype=torch.uint8, device="cuda")
+    size = R.beaver_matmul_preferred_workspace_bytes if bits == 128 else R.beaver_matmul_workspace_bytes
+    ws = torch.empty(size(n, 1, M, M, M, path), dtype=torch.uint8, device="cuda")
     for _ in range(args.warmup):
         R.beaver_matmul(X, Y, A, B, C, path=path, out=Z, workspace=ws)
     torch.cuda.synchronize()

@@ -861,7 +861,8 @@ inline int choose_splits(long tiles, int steps)
 // estimated cost than the tile kernel plus its pre-pass over the left operands.  Costs are in k-steps of
 // one CU (about a microsecond), the unit of choose_splits: the row kernel walks 2 KT steps per block of 32
 // rows and column tile; the other path adds the left pack, an HBM stream of (3n + 1) operand-sized matrices
-// at about 5 MB per step-time, and one more launch.
+// at about 5 MB per step-time.  The 5 steps were its launch, when it had one of its own; below kPackStreamingBytes it rides
+// with the right pack now.  They were left as measured then: the row kernel keeps the products it had.
 template <class T> inline double rows_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
 {
     const int cus = compute_units();

@@ -13,11 +13,12 @@
 //  residue_gemm_kernel     Y_l = [E | A_i] . [B_i' ; F] mod p_l, one byte per element and modulus.
 //  residue_combine_kernel  S from the L bytes of an element, Z_i = C_i + S.
 //
-// Measured, whole call, digit kernels against this: 5 parties 4096^3 17.6 -> 10.9 ms (GEMM 8.9, pack 1.5, combine 0.6 ms),
-// 2 x 2048^3 over Z_2^128 3.4 -> 1.4 ms.  The GEMM runs at 0.53 of the nominal int8 peak, 0.77 of what a register-only
+// Measured, whole call, digit kernels against this: 5 parties 4096^3 17.6 -> 10.9 ms (GEMM 8.8, pack 1.5, combine 0.6 ms),
+// 2 x 2048^3 over Z_2^128 3.4 -> 1.33 ms.  The GEMM runs at 0.55 to 0.57 of the nominal int8 peak, 0.80 of what a register-only
 // loop sustains on random bytes; without its loads it would be 14 % faster (10 % of that are L2 misses), without its
-// epilogue 2 %.  It is bound by the power of matrix units and operand traffic together: a fifth LDS stage, another order
-// of the two operand pairs on half of the XCDs, or loads bunched in the first half of a step change it by 1 %.
+// epilogue 2 %.  The matrix pipes are busy 0.71 of the cycles at 1.9 GHz, the L2 0.95 of them (11.4 TB/s, hit rate 0.80): it is
+// bound by the power of matrix units and operand traffic together; a fifth LDS stage, another order of the two operand
+// pairs on half of the XCDs, or loads bunched in the first half of a step change it by 1 %.
 //
 // Fragment: 16 rows (columns) x 64 k = 1 KiB; lane l's 16 bytes at 16 l are row l % 16, k = 16 (l / 16) + 0..15.
 // Store of one operand: [modulus][panel of 256 rows][kt64][16 fragments][1024], so that a workgroup's share of one
