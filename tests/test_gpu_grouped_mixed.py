@@ -30,3 +30,18 @@ def test_rows_and_tiles_together(n, count):
     for _ in range(2):
         got = spin.beaver_matmul_grouped(groups)
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+# eight parties: beyond two right-hand pack workgroups a CU those packs have a launch of their own; with and without packs by rows
+@pytest.mark.parametrize("shapes", [[(1, 64, 2048, 512, False), (2, 33, 65, 64, True)], [(1, 64, 2112, 512, False), (2, 33, 65, 64, True)],
+                                    [(3, 20, 4100, 301, False)] * 3 + [(1, 70, 50, 33, True)], [(1, 64, 4096, 1000, False)]])
+def test_eight_parties_many_right_operands(shapes):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(shapes))
+    groups = []
+    for batch, M, N, K, tr in shapes:
+        y = (N, K) if tr else (K, N)
+        groups.append(dict(X=uniform(g, 8, batch, M, K), Y=uniform(g, 8, batch, *y), A=uniform(g, 8, batch, M, K),
+                           B=uniform(g, 8, batch, *y), C=uniform(g, 8, batch, M, N), y_transposed=tr))
+    want = spin.beaver_matmul_grouped(groups, path=spin.VALU)
+    assert all(torch.equal(a, b) for a, b in zip(spin.beaver_matmul_grouped(groups), want))

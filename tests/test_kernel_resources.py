@@ -12,7 +12,7 @@ EM_AMDGPU, PT_NOTE, NT_AMDGPU_METADATA = 224, 4, 32
 
 
 def kernels():
-    """mangled name -> registers per lane, of every kernel in the library."""
+    """mangled name -> registers per lane and bytes of spilled ones, of every kernel in the library."""
     blob, out = open(LIB, "rb").read(), {}
     for at in (m.start() for m in re.finditer(b"\x7fELF\x02\x01", blob)):
         if struct.unpack_from("<H", blob, at + 18)[0] != EM_AMDGPU:
@@ -27,7 +27,7 @@ def kernels():
                 pos += 12 + (name + 3) // 4 * 4
                 if note == NT_AMDGPU_METADATA:
                     for k in msgpack.unpackb(blob[pos:pos + desc])["amdhsa.kernels"]:
-                        out[k[".name"]] = k[".vgpr_count"]          # AGPRs of the unified file included
+                        out[k[".name"]] = k[".vgpr_count"], k[".private_segment_fixed_size"]   # AGPRs of the unified file included
                 pos += (desc + 3) // 4 * 4
     return out
 
@@ -39,6 +39,16 @@ def kernels():
                                                (7, "j", "right", 256)])    # two; one
 def test_one_sided_packs_keep_their_waves(np, ring, side, most):
     which = {"both": 0, "left": 1, "right": 2}[side]
-    found = {n: v for n, v in kernels().items()
+    found = {n: v for n, (v, _) in kernels().items()
              if re.search(r"pack_kernelILi%dE%sLb[01]ELb0ELb[01]ELNS\w*PackSideE%dE" % (np, ring, which), n)}
     assert len(found) >= 2 and max(found.values()) <= most, found
+
+
+def test_packs_of_three_parties_keep_two_waves():
+    found = {n: v for n, (v, _) in kernels().items() if re.search(r"pack_(grouped_)?kernelILi3E(m|LNS)", n)}
+    assert len(found) >= 5 and max(found.values()) <= 256, found
+
+
+def test_grouped_packs_of_right_operands_for_eight_parties():
+    spilled = [s for n, (_, s) in kernels().items() if re.search(r"pack_grouped_kernelILi8ELNS\w*PackSideE2E", n)]
+    assert len(spilled) == 1 and spilled[0] <= 64            # 388 bytes in one kernel with the packs by rows
