@@ -868,31 +868,34 @@ template <class T> inline double rows_kernel_cost(const MatmulArgsT<T> &a, const
     const int cus = compute_units();
     return (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8);
 }
-template <class T> inline double tile_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
+template <class T> inline double tile_kernel_cost(const MatmulArgsT<T> &a, const Plan &p, int sp)
 {
     const int cus = compute_units();
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = choose_splits(tiles, 2 * p.KT);
     const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * (double)a.M * a.K;
     return (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.0e6 + 5;
 }
-template <class T> inline bool rows_kernel_applies(const MatmulArgsT<T> &a, const Plan &p)
+// What all estimates of a product need: which kernel it takes and how many workgroups would share a tile.
+struct DigitRoute { bool rows; int splits; };
+template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {
-    if (!std::is_same<T, u64>::value) return false;
-    if (a.n > 3 || a.K % 2 != 0 || p.KT > Ring<u64>::max_chunk_tiles) return false;
-    if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return false;
-    return rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p);
+    DigitRoute r{false, choose_splits((long)p.tilesM * p.tilesN * a.n * a.batch, 2 * p.KT)};
+    if (!std::is_same<T, u64>::value) return r;
+    if (a.n > 3 || a.K % 2 != 0 || p.KT > Ring<u64>::max_chunk_tiles) return r;
+    if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return r;
+    r.rows = rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p, r.splits);
+    return r;
 }
 
 // Estimated time of the digit kernels in microseconds, for the choice between them and the direct kernel:
 // 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.
 // Small products are what it is for; large ones come out up to 40 % too high (the packs overlap their launch).
-template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p)
+template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
 {
-    if (rows_kernel_applies<T>(a, p)) return 1.5 * rows_kernel_cost<T>(a, p) + 10;
+    if (r.rows) return 1.5 * rows_kernel_cost<T>(a, p) + 10;
     const int cus = compute_units();
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = choose_splits(tiles, 2 * p.KT);
+    const int sp = r.splits;
     const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
     const double step = sizeof(T) == 8 ? 1.5 : 0.85;
     return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
@@ -900,16 +903,16 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
 
 // The same in detail, for small products: the waves of a pack convert the parties' shares one after another, and the
 // output counts.  A fit to 19 500 products of 5 us to 2 ms near the line between the two kernels, within 8 (9 over Z_2^32) % (rms).
-template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p)
+template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
 {
     const int cus = compute_units();
     const double words = (double)sizeof(T) * (3 * a.n + 1) * a.batch, out_mb = 2e-6 * sizeof(T) * a.n * a.batch * (double)a.M * a.N;
-    if (rows_kernel_applies<T>(a, p)) {
+    if (r.rows) {
         const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
         return rounds * (1.228 * 2 * p.KT + 3.96) + words * a.N * a.K / 4.35e6 + 3.8 + 2.03 * a.n + 0.236 * out_mb;
     }
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = choose_splits(tiles, 2 * p.KT);
+    const int sp = r.splits;
     const double rounds = (double)((tiles * sp + cus - 1) / cus), packed = words * ((double)a.M + a.N) * a.K;
     return sizeof(T) == 8 ? rounds * (1.107 * 2 * ceil_div(p.KT, sp) + 4.78) + packed / 4.49e6 + 4.1 + 1.76 * a.n + 0.181 * out_mb
                           : rounds * (0.716 * 2 * ceil_div(p.KT, sp) + 5.56) + packed / 5.0e6 + 3.7 + 1.36 * a.n + 0.161 * out_mb;
@@ -918,16 +921,16 @@ template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, co
 // The same for the choice between them and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
 // parties, sides 32 to 8192), within 6 % (rms).  The clock is higher where the tiles leave part of the chip idle; parts of shared
 // tiles that are added onto Z cost 0.3 us a megabyte of its words read and written.
-inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p)
+inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p, const DigitRoute &r)
 {
     const int cus = compute_units();
     const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
-    if (rows_kernel_applies<u64>(a, p)) {
+    if (r.rows) {
         const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
         return rounds * 1.214 * 2 * p.KT + words * a.N * a.K / 3.85e6 + 3.15 * a.n + 0.331 * out_mb;
     }
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = choose_splits(tiles, 2 * p.KT);
+    const int sp = r.splits;
     const double filled = (double)tiles * sp / cus, rounds = std::ceil(filled);
     return rounds * (1.52 * 2 * ceil_div(p.KT, sp) * (1 - 0.592 * (1 - filled / rounds)) + 6.6) +
            words * ((double)a.M + a.N) * a.K / 5.4e6 + 1.1 + 1.52 * a.n + (sp > 1 ? 0.305 * out_mb : 0);
@@ -965,14 +968,16 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
 
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p), digit_cost_small_us<T>(a, p))) return launch_matmul_direct<T>(a, s, where_gemm);
+    const DigitRoute route = digit_route<T>(a, p);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p, route), digit_cost_small_us<T>(a, p, route)))
+        return launch_matmul_direct<T>(a, s, where_gemm);
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;
-            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p), s, "spin_beaver_matmul(residue gemm)", taken);
+            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p, route), s, "spin_beaver_matmul(residue gemm)", taken);
             if (taken) return st;
         }
-        if (rows_kernel_applies<T>(a, p)) return launch_rows(a, p, packB, s, where_pack, where_gemm);
+        if (route.rows) return launch_rows(a, p, packB, s, where_pack, where_gemm);
     }
 
     const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
@@ -1070,7 +1075,7 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT}, 4});
             side_blocks.push_back(pack_right_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
         }
-        if (rows_kernel_applies<u64>(m, p)) {
+        if (digit_route<u64>(m, p).rows) {
             rows.push_back(RowGemmArgs{m.X, m.A, packB, m.C, m.Z, m.batch, m.M, m.N, m.K, p.KT, p.tilesN});
             row_blocks.push_back((unsigned)rows_grid(m.batch, m.M, p.tilesN));
         } else {
@@ -1190,7 +1195,7 @@ size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
     MatmulArgs a{};
     a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
     const size_t need = p.packA_bytes + p.packB_bytes;
-    return std::max(need, residue_workspace_bytes<u64>(n, batch, M, N, K, need, digit_cost_large_us(a, p)));
+    return std::max(need, residue_workspace_bytes<u64>(n, batch, M, N, K, need, digit_cost_large_us(a, p, digit_route<u64>(a, p))));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)
