@@ -1096,8 +1096,8 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
         constexpr int NP = decltype(np)::value;
         {
             KernelTimer timer(SPIN_KERNEL_PACK, s);
-            // The kernel of all kinds spills 97 registers at eight parties, that of right operands alone 13: many of those
-            // have their own launch there (three products 64 x 4096 x 1000, 3072 workgroups: 1120 us a call together, 1091 apart).
+            // At eight parties the kernel of all kinds leaves a SIMD one wave, that of right operands alone two: many of those
+            // have their own launch there (three products 64 x 4096 x 1000, 3072 workgroups: 1030 us a call, 1013 to 1050 together).
             bool apart = false;
             if constexpr (NP == 8) {
                 std::vector<GroupedPackSide> some[2];

@@ -29,6 +29,13 @@ def test_ring64(n, batch, M, N, K):
         run(spin.beaver_matmul, n, batch, M, N, K, (), torch.int64, transposed)
 
 
+# whole and ragged tiles, left (right) operands past the caches, rows of 16 and of 8 bytes, for the party counts whose shares take the most registers
+@pytest.mark.parametrize("n,batch,M,N,K", [(8, 1, 1208, 320, 1056), (8, 1, 1205, 70, 1067), (7, 1, 70, 1210, 1057), (6, 2, 133, 165, 297), (8, 2, 131, 163, 295)])
+def test_many_parties(n, batch, M, N, K):
+    for transposed in (False, True):
+        run(spin.beaver_matmul, n, batch, M, N, K, (), torch.int64, transposed)
+
+
 @pytest.mark.parametrize("n,batch,M,N,K", [(5, 1, 16384, 128, 576), (7, 1, 32, 2048, 2048), (4, 1, 300, 500, 3001), (3, 2, 2000, 1000, 96)])
 def test_ring32(n, batch, M, N, K):
     run(spin.ring32.beaver_matmul, n, batch, M, N, K, (), torch.int32)
