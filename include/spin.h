@@ -300,6 +300,8 @@ spin_status spin32_beaver_matmul(int n, int batch, int M, int N, int K,
                                  uint32_t *Z, int path,
                                  void *workspace, size_t workspace_bytes, spin_stream stream);
 size_t spin32_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int K, int path);
+/* With it large products run by Strassen's recursion, in fewer multiplications; the same words with less.           */
+size_t spin32_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path);
 spin_status spin32_beaver_mul(int n, size_t count,
                               const uint32_t *x, const uint32_t *y,
                               const uint32_t *a, const uint32_t *b, const uint32_t *c,

@@ -29,7 +29,7 @@
 //  *_grouped_kernel  the same bodies for several products of different shapes in one launch
 //                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments; row and tile
 //                products share a launch in limb_gemm_mixed_grouped_kernel.
-// Larger products go to the residue GEMM (gemm_residue.hip) and the smallest to one launch of vector arithmetic
+// Larger products go to the residue GEMM (gemm_residue.hip; over Z_2^32 to gemm_strassen.hip) and the smallest to one launch of vector arithmetic
 // (gemm_direct.hip); digit_cost_us is this file's side of that choice.
 #include <algorithm>
 #include <cmath>
@@ -60,7 +60,7 @@ template <> struct Ring<u32> {
 template <class T> struct GemmArgs {
     const char *packA;   // [n+1][batch][nblkA][KT][ND][1024]: slot 0 = E, slot 1+i = A_i
     const char *packB;   // [n+1][batch][nblkB][KT][ND][1024]: slot 0 = F, slot 1+i = B_i'
-    const T *C;          // [n][batch][M][N]  (or Z itself for the later k-chunks)
+    const T *C;          // [n][batch][M][N]  (or Z itself for the later k-chunks); null: nothing to add
     T *Z;
     int n, batch, M, N;
     int nblkA, nblkB, KT;
@@ -299,7 +299,7 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
     const T *Cm = g.C + (size_t)pb * mat;
     T *Zm = g.Z + (size_t)pb * mat;
     const bool interior = (tm + 1) * S::BM <= g.M && (tn + 1) * S::BN <= g.N;     // uniform over the workgroup
-    const bool atomic = g.splits > 1;
+    const bool atomic = g.splits > 1, no_c = atomic || g.C == nullptr;
     T cv[WM][WN][16];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -309,7 +309,7 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
             const int row0 = tm * S::BM + (wm * WM + i) * 32 + 4 * (lane / 32);
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                cv[i][j][r] = atomic ? (T)0 : Cm[(size_t)min(row0 + 8 * (r / 4) + r % 4, g.M - 1) * g.N + col];
+                cv[i][j][r] = no_c ? (T)0 : Cm[(size_t)min(row0 + 8 * (r / 4) + r % 4, g.M - 1) * g.N + col];
         }
     __builtin_amdgcn_sched_barrier(0);
     iteration(B1(), F(), F(), F());                       // step steps-1
@@ -817,6 +817,7 @@ __global__ __launch_bounds__(256) void limb_gemm_mixed_grouped_kernel(SmallGroup
 }
 
 // ------------------------------------------------------------------ host ---
+constexpr size_t kPreferredMost = (size_t)16 << 30;       // of a preferred workspace over Z_2^32
 struct Plan {
     int KT, nblkA, nblkB, tilesM, tilesN;
     size_t packA_bytes, packB_bytes;
@@ -978,6 +979,11 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
             if (taken) return st;
         }
         if (route.rows) return launch_rows(a, p, packB, s, where_pack, where_gemm);
+    }
+    if constexpr (std::is_same<T, u32>::value) {
+        bool taken = false;
+        const spin_status st = launch_matmul_strassen32(a, s, taken);
+        if (taken) return st;
     }
 
     const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
@@ -1202,6 +1208,25 @@ size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)
 {
     Plan p = make_plan<u32>(n, batch, M, N, K);
     return p.packA_bytes + p.packB_bytes;
+}
+
+size_t limb32_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
+{
+    return std::max(limb32_workspace_bytes(n, batch, M, N, K), strassen32_workspace_bytes(n, batch, M, N, K, kPreferredMost));
+}
+
+spin_status launch_limb32_products(const char *packA, const char *packB, int n, int batch, int M, int N, int K, u32 *Z, hipStream_t s)
+{
+    using S = GemmShape<u32>;
+    static OncePerDevice lds_allowed;
+    auto kernel = limb_gemm_kernel<u32>;
+    spin_status st = allow_dynamic_lds((const void *)kernel, S::lds_bytes, lds_allowed);
+    if (st != SPIN_OK) return st;
+    const int KT = K / 32;
+    const GemmArgs<u32> g{packA, packB, nullptr, Z, n, batch, M, N, M / 32, N / 32, KT, 0, KT, M / S::BM, N / S::BN, 1, 2 * KT};
+    KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
+    kernel<<<(unsigned)((long)g.tilesM * g.tilesN * n * batch), 256, S::lds_bytes, s>>>(g);
+    return check_launch("spin32_beaver_matmul(limb gemm)");
 }
 
 spin_status launch_matmul_limb(const MatmulArgs &a, hipStream_t s)

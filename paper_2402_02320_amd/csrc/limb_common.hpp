@@ -33,7 +33,7 @@ template <class T> __device__ inline T to_digits(T a) { return (a + digit_bias<T
 // stores, and the shares of all parties stay in registers until then (64 registers a party).
 template <class T> __device__ inline void computed_here(T &v)
 {
-    if constexpr (sizeof(T) == 16) {
+    if constexpr (std::is_same<T, u128>::value) {
         u64 low = (u64)v, high = (u64)(v >> 64);
         asm volatile("" : "+v"(low), "+v"(high));
         v = (T)high << 64 | low;

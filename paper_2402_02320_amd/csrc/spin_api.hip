@@ -542,6 +542,13 @@ size_t spin32_beaver_matmul_workspace_bytes(int n, int batch, int M, int N, int 
     return 0;
 }
 
+size_t spin32_beaver_matmul_preferred_workspace_bytes(int n, int batch, int M, int N, int K, int path)
+{
+    if (path == SPIN_GEMM_LIMB_MFMA && check_matmul_dims(n, batch, M, N, K) == SPIN_OK)
+        return limb32_preferred_workspace_bytes(n, batch, M, N, K);
+    return spin32_beaver_matmul_workspace_bytes(n, batch, M, N, K, path);
+}
+
 spin_status spin32_beaver_matmul(int n, int batch, int M, int N, int K, const uint32_t *X, const uint32_t *Y,
                                  const uint32_t *A, const uint32_t *B, const uint32_t *C, uint32_t *Z,
                                  int path, void *workspace, size_t workspace_bytes, spin_stream stream)

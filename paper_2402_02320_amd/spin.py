@@ -85,6 +85,8 @@ def lib():
         L.spin32_beaver_matmul.argtypes = L.spin_beaver_matmul.argtypes
         L.spin32_beaver_matmul_workspace_bytes.argtypes = L.spin_beaver_matmul_workspace_bytes.argtypes
         L.spin32_beaver_matmul_workspace_bytes.restype = sz
+        L.spin32_beaver_matmul_preferred_workspace_bytes.argtypes = L.spin_beaver_matmul_workspace_bytes.argtypes
+        L.spin32_beaver_matmul_preferred_workspace_bytes.restype = sz
         L.spin32_beaver_mul.argtypes = L.spin_beaver_mul.argtypes
         L.spin32_trunc.argtypes = L.spin_trunc.argtypes
         L.spin_cast_64_to_32.argtypes = [p, sz, p, p]
@@ -510,6 +512,10 @@ class ring32:
         return int(lib().spin32_beaver_matmul_workspace_bytes(n, batch, M, N, K, path))
 
     @staticmethod
+    def beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path=LIMB_MFMA):
+        return int(lib().spin32_beaver_matmul_preferred_workspace_bytes(n, batch, M, N, K, path))
+
+    @staticmethod
     def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None):
         n, batch, M, K = X.shape
         N = Y.shape[3]
@@ -518,11 +524,11 @@ class ring32:
             raise SpinError("inconsistent operand shapes")
         if out is None:
             out = torch.empty_like(C)
-        need = ring32.beaver_matmul_workspace_bytes(n, batch, M, N, K, path)
-        if need == 0:
-            raise SpinError("invalid matmul dimensions")
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+            workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin32_beaver_matmul_workspace_bytes,
+                                          lib().spin32_beaver_matmul_preferred_workspace_bytes, X.device)
+        elif ring32.beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
+            raise SpinError("invalid matmul dimensions")
         _check(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
                                           _dev32(B, "B"), _dev32(C, "C"), _dev32(out, "Z"), path,
                                           workspace.data_ptr(), workspace.numel() * workspace.element_size(),
