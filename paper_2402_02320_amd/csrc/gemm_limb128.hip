@@ -32,7 +32,8 @@ struct Gemm128Args {
     int nblkA, nblkB, KT;
     int kt0, ktn;        // this launch covers k-tiles [kt0, kt0+ktn) of both operand pairs
     int tilesM, tilesN;
-};
+    int splits, split_steps;     // workgroups per output tile: each takes split_steps of the 2 ktn k-steps and, when splits > 1, adds
+};                               // its part onto Z atomically (Z then starts out as C)
 
 struct Shape128 {
     static constexpr int ND = kDigits128;
@@ -53,7 +54,11 @@ __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
     const int lane = threadIdx.x % 64;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int wm = wave / 2, wn = wave % 2;
-    const TileId tile = map_tile(blockIdx.x, g.tilesM, g.tilesN, (long)g.tilesM * g.tilesN * g.n * g.batch);
+    // work item = (split, tile), tiles fastest: neighbours on an XCD work on neighbouring tiles of one k-range
+    const long tiles_total = (long)g.tilesM * g.tilesN * g.n * g.batch;
+    const long item = xcd_contiguous_id(blockIdx.x, tiles_total * g.splits);
+    const int split = (int)(item / tiles_total);
+    const TileId tile = tile_of(item % tiles_total, g.tilesM, g.tilesN);
     const int pb = tile.pb, tm = tile.tm, tn = tile.tn;
     const int party = pb / g.batch, b = pb % g.batch;
 
@@ -66,18 +71,21 @@ __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
     const char *b_second = g.packB + (size_t)b * g.nblkB * blk_stride;     // F
     const char *b_first = b_second + (size_t)(1 + party) * slotB;          // B_i'
 
-    const int steps = 2 * g.ktn;
+    const int s0 = split * g.split_steps;                // this workgroup's k-steps [s0, s0 + steps)
+    const int steps = min(g.split_steps, 2 * g.ktn - s0);
+    const bool starts_in_second = s0 >= g.ktn;
     const u32 lds0 = (u32)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const u32 lane16 = lane * 16;
 
     // Load cursor (scalar unit): this wave loads fragments f = 4q + wave, q < 16: block f / 16 = q / 4
     // of the tile and digit f % 16 = 4 (q % 4) + wave.
     const size_t kt0_off = (size_t)g.kt0 * (ND * kFrag) + wave * kFrag;
-    const char *ld_a = a_first + (size_t)tm * (S::BM / 32) * blk_stride + kt0_off;
-    const char *ld_b = b_first + (size_t)tn * (S::BN / 32) * blk_stride + kt0_off;
+    const size_t start_off = (size_t)(starts_in_second ? s0 - g.ktn : s0) * (ND * kFrag) + kt0_off;
+    const char *ld_a = (starts_in_second ? a_second : a_first) + (size_t)tm * (S::BM / 32) * blk_stride + start_off;
+    const char *ld_b = (starts_in_second ? b_second : b_first) + (size_t)tn * (S::BN / 32) * blk_stride + start_off;
     const char *second_a = a_second + (size_t)tm * (S::BM / 32) * blk_stride + kt0_off;
     const char *second_b = b_second + (size_t)tn * (S::BN / 32) * blk_stride + kt0_off;
-    int ld_left = g.ktn;
+    int ld_left = starts_in_second ? 0x7fffffff : g.ktn - s0;            // steps until the cursor switches operand pair
     const u32 ld_lds0 = lds0 + wave * kFrag;
     u32 ld_lds = ld_lds0;
     auto issue_load = [&](int q) {
@@ -146,6 +154,34 @@ __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
     u128 *Zm = g.Z + (size_t)pb * mat;
     const int col = tn * S::BN + wn * 32 + lane % 32;
     const int row0 = tm * S::BM + wm * 32 + 4 * (lane / 32);
+    auto sum_of = [&](int r) {
+        u128 v = 0;
+#pragma unroll
+        for (int d = 0; d < ND; ++d) v += (u128)(__int128)acc[d][r] << (8 * d);
+        return v;
+    };
+    // Parts of a tile: the low words are added first, and the addition that wraps a low word (its return value tells) carries into
+    // the high one.  Every wrap is seen by exactly one of the additions, so the sum is right whatever their order.
+    if (g.splits > 1) {
+        u64 low[16], before[16], high[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r / 4) + r % 4;
+            const u128 v = sum_of(r);
+            low[r] = (u64)v;
+            high[r] = (u64)(v >> 64);
+            before[r] = 0;
+            if (row < g.M && col < g.N)
+                before[r] = atomicAdd((unsigned long long *)(Zm + (size_t)row * g.N + col), (unsigned long long)low[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r / 4) + r % 4;
+            if (row < g.M && col < g.N)
+                atomicAdd((unsigned long long *)(Zm + (size_t)row * g.N + col) + 1, (unsigned long long)(high[r] + (before[r] + low[r] < low[r] ? 1 : 0)));
+        }
+        return;
+    }
     auto epilogue = [&](auto interior_c) {
         constexpr bool INTERIOR = decltype(interior_c)::value;
         u128 cv[16];
@@ -157,9 +193,7 @@ __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int row = row0 + 8 * (r / 4) + r % 4;
-            u128 v = cv[r];
-#pragma unroll
-            for (int d = 0; d < ND; ++d) v += (u128)(__int128)acc[d][r] << (8 * d);
+            const u128 v = cv[r] + sum_of(r);
             if (INTERIOR || (row < g.M && col < g.N)) Zm[(size_t)row * g.N + col] = v;
         }
     };
@@ -184,14 +218,39 @@ inline Plan128 make_plan128(int n, int batch, int M, int N, int K)
     return p;
 }
 
-// Estimated time in microseconds of the pack and this kernel: k-steps (136 MFMAs of 32 cycles; faster, at a higher clock, where
-// the tiles leave part of the chip idle), the packs as streams, and a pack's wave that converts the parties' shares one after
-// another.  A fit to 250 products of 30 us to 1.7 ms, within 7 % (rms).
+// How many workgroups share one output tile (one fits a CU), and the estimated time of the GEMM in microseconds: k-steps (136 MFMAs of
+// 32 cycles; faster, at a higher clock, where the tiles leave part of the chip idle), 6.9 us to start and end, and, where parts
+// are added onto Z, the copy of C and two atomic additions an element and part.  Within 8 % (rms) over
+// 49 split products.  Whole calls, 440 small products: 20 % less time than with one workgroup a tile; 4 parties 32 x 32 x 768 135.6 ->
+// 34.0 us, 3 parties 305 x 17 x 875 81.5 -> 38.1.
+struct Split128 { int splits, steps; double us, whole_us; };      // whole_us: with one workgroup a tile
+inline Split128 choose_splits128(int n, int batch, int M, int N, const Plan128 &p)
+{
+    const double cus = compute_units(), tiles = (double)p.tilesM * p.tilesN * n * batch, out_mb = 16e-6 * n * batch * (double)M * N;
+    const int steps = 2 * std::min(p.KT, kMaxChunkTiles128);
+    const double chunks = ceil_div(p.KT, kMaxChunkTiles128);
+    Split128 best{1, steps, 0, 0};
+    for (int want = 1; want <= 16; ++want) {
+        const int part = ceil_div(steps, want), used = ceil_div(steps, part);
+        if (want > 1 && (part < 2 || used != want)) continue;
+        const double filled = tiles * used / cus, rounds = std::ceil(filled);
+        const double us = chunks * (rounds * (2.85 * part * (1 - 0.235 * (1 - filled / rounds)) + 6.9) + (used > 1 ? 3 + 0.5 * used * out_mb : 0));
+        if (want == 1 || us < 0.97 * best.us) best = Split128{used, part, us, want == 1 ? us : best.whole_us};
+    }
+    return best;
+}
+
+// Estimated time in microseconds of the pack and this kernel, for the choice against the residue and the direct kernel: the packs as
+// streams, and a pack's wave that converts the parties' shares one after another.  Without splits a fit to 250 products of 30 us
+// to 1.7 ms, within 7 % (rms).  Splits count where the residue kernels' tiles (256 rows, 128 columns) are mostly padding or their
+// k-steps few: sides up to 48 (5 parties 32 x 32 x 1248 106.9 us by residues, 42.1 split), an inner dimension below 700 (3 parties 416 x 32 x
+// 480 63.0 and 38.5).  Beyond, the line stays where both kernels were fitted without splits; it leaves up to a half on the
+// table for a few thin products (5 parties 163 x 161 x 1460 138.6 and 94.0) and nothing where tiles are full.
 inline double digit128_cost_us(int n, int batch, int M, int N, int K, const Plan128 &p)
 {
-    const double filled = (double)p.tilesM * p.tilesN * n * batch / compute_units(), rounds = std::ceil(filled);
     const double pack_bytes = 16.0 * (3 * n + 1) * batch * ((double)M + N) * K;
-    return rounds * (2.85 * 2 * p.KT * (1 - 0.235 * (1 - filled / rounds)) + 6.9) + pack_bytes / 5.94e6 + 8.4 + 2.07 * n;
+    const Split128 s = choose_splits128(n, batch, M, N, p);
+    return (std::min(M, N) <= 48 || K < 700 ? s.us : s.whole_us) + pack_bytes / 5.94e6 + 8.4 + 2.07 * n;
 }
 // The k-steps alone, 3.2 us each: the other side of the direct kernel's own rough estimate.
 inline double digit128_rough_us(int n, int batch, const Plan128 &p)
@@ -229,21 +288,30 @@ spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
     }
     char *packA = (char *)a.workspace;
     char *packB = packA + p.packA_bytes;
-    launch_pack<u128>(a, packA, packB, p.nblkA, p.nblkB, p.KT, false, s);
+    const Split128 split = choose_splits128(a.n, a.batch, a.M, a.N, p);
+    // with several workgroups to a tile their parts are added onto Z, which starts out as C
+    const bool copy_c = split.splits > 1 && a.C != a.Z;
+    const bool copied = launch_pack<u128>(a, packA, packB, p.nblkA, p.nblkB, p.KT, copy_c, s);
     st = check_launch("spin128_beaver_matmul(pack)");
     if (st != SPIN_OK) return st;
+    if (copy_c && !copied) {
+        st = launch_open<u128>(a.C, nullptr, (size_t)a.n * a.batch * a.M * a.N, 1, a.Z, s);
+        if (st != SPIN_OK) return st;
+    }
 
     static OncePerDevice lds_allowed;
     st = allow_dynamic_lds((const void *)limb128_gemm_kernel, Shape128::lds_bytes, lds_allowed);
     if (st != SPIN_OK) return st;
-    Gemm128Args g{packA, packB, a.C, a.Z, a.n, a.batch, a.M, a.N, p.nblkA, p.nblkB, p.KT, 0, 0, p.tilesM, p.tilesN};
+    Gemm128Args g{packA, packB, a.C, a.Z, a.n, a.batch, a.M, a.N, p.nblkA, p.nblkB, p.KT, 0, 0, p.tilesM, p.tilesN,
+                  1, split.steps};
     const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
     for (int kt0 = 0; kt0 < p.KT; kt0 += kMaxChunkTiles128) {
         g.kt0 = kt0;
         g.ktn = p.KT - kt0 < kMaxChunkTiles128 ? p.KT - kt0 : kMaxChunkTiles128;
-        g.C = kt0 == 0 ? a.C : a.Z;                      // later chunks accumulate onto Z
+        g.C = kt0 == 0 && split.splits == 1 ? a.C : a.Z; // later chunks, and parts, accumulate onto Z
+        g.splits = ceil_div(2 * g.ktn, split.steps);     // parts that have steps (a short last chunk may need one, as a plain addition)
         KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-        limb128_gemm_kernel<<<(unsigned)total, 256, Shape128::lds_bytes, s>>>(g);
+        limb128_gemm_kernel<<<(unsigned)(total * g.splits), 256, Shape128::lds_bytes, s>>>(g);
         st = check_launch("spin128_beaver_matmul(limb gemm)");
         if (st != SPIN_OK) return st;
     }
