@@ -111,6 +111,14 @@ def _check(status):
         raise SpinError(msg)
 
 
+def _check_matmul(status, workspace_bytes_of, *dims):
+    """_check, with the dimensions' own message.  Asked for after the call, not before: the query takes a microsecond."""
+    if status != 0:
+        if workspace_bytes_of(*dims) == 0:
+            raise SpinError("invalid matmul dimensions")
+        _check(status)
+
+
 def _dev(t, name):
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.int64 and t.is_contiguous()):
         raise SpinError("%s must be a contiguous torch.int64 CUDA tensor" % name)
@@ -185,12 +193,14 @@ def _matmul_workspace(dims, path, need_of, preferred_of, device):
     size = int(preferred_of(*dims, path))
     if size == 0:
         raise SpinError("invalid matmul dimensions")
-    need = int(need_of(*dims, path))
-    if size > need + _UNASKED_BYTES and device.type == "cuda" and not _has_room(size, device):
-        size = need
+    if size > _UNASKED_BYTES and device.type == "cuda":      # smaller ones are not worth the second query
+        need = int(need_of(*dims, path))
+        if size > need + _UNASKED_BYTES and not _has_room(size, device):
+            size = need
     try:
         return torch.empty(size, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
+        need = int(need_of(*dims, path))
         if size == need:
             raise
         return torch.empty(need, dtype=torch.uint8, device=device)
@@ -209,13 +219,12 @@ def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_tra
     if workspace is None:
         workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin_beaver_matmul_workspace_bytes,
                                       lib().spin_beaver_matmul_preferred_workspace_bytes, X.device)
-    elif beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
-        raise SpinError("invalid matmul dimensions")
     if not (workspace.is_cuda and workspace.is_contiguous()):
         raise SpinError("workspace must be a contiguous CUDA tensor")
     call = lib().spin_beaver_matmul_nt if y_transposed else lib().spin_beaver_matmul
-    _check(call(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"), _dev(C, "C"),
-                _dev(out, "Z"), path, workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream()))
+    _check_matmul(call(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"), _dev(C, "C"),
+                       _dev(out, "Z"), path, workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream()),
+                  beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
     return out
 
 
@@ -276,12 +285,13 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
 
 def beaver_mul(x, y, a, b, c, out=None):
     n = x.shape[0]
+    shape = x.shape
     for t in (y, a, b, c):
-        if t.shape != x.shape:
+        if t.shape != shape:
             raise SpinError("inconsistent operand shapes")
     if out is None:
         out = torch.empty_like(x)
-    _check(lib().spin_beaver_mul(n, x[0].numel(), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
+    _check(lib().spin_beaver_mul(n, x.numel() // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
                                  _dev(c, "c"), _dev(out, "z"), _stream()))
     return out
 
@@ -289,12 +299,13 @@ def beaver_mul(x, y, a, b, c, out=None):
 def beaver_mul_trunc(x, y, a, b, c, r, r_top, r_msb, f, out=None):
     """Mul then Truncate by f bits in one pass; all operands [n, count]."""
     n = x.shape[0]
+    shape = x.shape
     for t in (y, a, b, c, r, r_top, r_msb):
-        if t.shape != x.shape:
+        if t.shape != shape:
             raise SpinError("inconsistent operand shapes")
     if out is None:
         out = torch.empty_like(x)
-    _check(lib().spin_beaver_mul_trunc(n, x[0].numel(), f, _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
+    _check(lib().spin_beaver_mul_trunc(n, x.numel() // (n or 1), f, _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
                                        _dev(c, "c"), _dev(r, "r"), _dev(r_top, "r_top"), _dev(r_msb, "r_msb"),
                                        _dev(out, "out"), _stream()))
     return out
@@ -316,12 +327,13 @@ def beaver_mul_bcast(x, y, a, b, c, over_inner, out=None):
 
 def trunc(x, r, r_top, r_msb, f, out=None):
     n = x.shape[0]
+    shape = x.shape
     for t in (r, r_top, r_msb):
-        if t.shape != x.shape:
+        if t.shape != shape:
             raise SpinError("inconsistent operand shapes")
     if out is None:
         out = torch.empty_like(x)
-    _check(lib().spin_trunc(n, x[0].numel(), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
+    _check(lib().spin_trunc(n, x.numel() // (n or 1), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
                             _dev(r_msb, "r_msb"), _dev(out, "out"), _stream()))
     return out
 
@@ -346,12 +358,13 @@ def bopen(shares, mask=None, out=None):
 
 def beaver_and(x, y, a, b, c, out=None):
     n = x.shape[0]
+    shape = x.shape
     for t in (y, a, b, c):
-        if t.shape != x.shape:
+        if t.shape != shape:
             raise SpinError("inconsistent operand shapes")
     if out is None:
         out = torch.empty_like(x)
-    _check(lib().spin_beaver_and(n, x[0].numel(), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
+    _check(lib().spin_beaver_and(n, x.numel() // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
                                  _dev(c, "c"), _dev(out, "z"), _stream()))
     return out
 
@@ -372,7 +385,7 @@ def lincomb_trunc(terms, coefs, constant=0, f=0, tuple_=None, out=None):
         for t in tuple_:
             if t.numel() != terms[0].numel():
                 raise SpinError("truncation tuple must have the shape of the terms")
-    _check(lib().spin_lincomb_trunc(n, terms[0][0].numel(), len(terms), ptrs, cf, int(constant) % (1 << 64), f,
+    _check(lib().spin_lincomb_trunc(n, terms[0].numel() // (n or 1), len(terms), ptrs, cf, int(constant) % (1 << 64), f,
                                     r, rt, rm, _dev(out, "out"), _stream()))
     return out
 
@@ -394,7 +407,7 @@ def completed_square_trunc(x, t3, t2, lin, t0, triples, tuples, f, out=None):
     t_ptr = six(*[_dev(t, "triple") for t in (a0, b0, c0, a1, b1, c1)])
     u_ptr = six(*[_dev(t, "tuple") for t in (r0, rt0, rm0, r1, rt1, rm1)])
     const = [int(v) % (1 << 64) for v in (t3, t2, lin, t0)]
-    _check(lib().spin_completed_square_trunc(x.shape[0], x[0].numel(), _dev(x, "x"), *const, t_ptr, u_ptr,
+    _check(lib().spin_completed_square_trunc(x.shape[0], x.numel() // (x.shape[0] or 1), _dev(x, "x"), *const, t_ptr, u_ptr,
                                              (ctypes.c_int * 2)(*f), _dev(out, "out"), _stream()))
     return out
 
@@ -445,11 +458,10 @@ class ring128:
         if workspace is None:
             workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin128_beaver_matmul_workspace_bytes,
                                           lib().spin128_beaver_matmul_preferred_workspace_bytes, X.device)
-        elif ring128.beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
-            raise SpinError("invalid matmul dimensions")
-        _check(lib().spin128_beaver_matmul(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"),
-                                           _dev(C, "C"), _dev(out, "Z"), path, workspace.data_ptr(),
-                                           workspace.numel() * workspace.element_size(), _stream()))
+        _check_matmul(lib().spin128_beaver_matmul(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"),
+                                                  _dev(C, "C"), _dev(out, "Z"), path, workspace.data_ptr(),
+                                                  workspace.numel() * workspace.element_size(), _stream()),
+                      ring128.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
         return out
 
     @staticmethod
@@ -457,7 +469,7 @@ class ring128:
         n = x.shape[0]
         if out is None:
             out = torch.empty_like(x)
-        _check(lib().spin128_beaver_mul(n, ring128._elems(x[0]), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"),
+        _check(lib().spin128_beaver_mul(n, ring128._elems(x) // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"),
                                         _dev(b, "b"), _dev(c, "c"), _dev(out, "z"), _stream()))
         return out
 
@@ -466,7 +478,7 @@ class ring128:
         n = x.shape[0]
         if out is None:
             out = torch.empty_like(x)
-        _check(lib().spin128_trunc(n, ring128._elems(x[0]), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
+        _check(lib().spin128_trunc(n, ring128._elems(x) // (n or 1), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
                                    _dev(r_msb, "r_msb"), _dev(out, "out"), _stream()))
         return out
 
@@ -527,12 +539,11 @@ class ring32:
         if workspace is None:
             workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin32_beaver_matmul_workspace_bytes,
                                           lib().spin32_beaver_matmul_preferred_workspace_bytes, X.device)
-        elif ring32.beaver_matmul_workspace_bytes(n, batch, M, N, K, path) == 0:
-            raise SpinError("invalid matmul dimensions")
-        _check(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
-                                          _dev32(B, "B"), _dev32(C, "C"), _dev32(out, "Z"), path,
-                                          workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                                          _stream()))
+        _check_matmul(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
+                                                 _dev32(B, "B"), _dev32(C, "C"), _dev32(out, "Z"), path,
+                                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                                                 _stream()),
+                      ring32.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
         return out
 
     @staticmethod
@@ -540,7 +551,7 @@ class ring32:
         n = x.shape[0]
         if out is None:
             out = torch.empty_like(x)
-        _check(lib().spin32_beaver_mul(n, x[0].numel(), _dev32(x, "x"), _dev32(y, "y"), _dev32(a, "a"),
+        _check(lib().spin32_beaver_mul(n, x.numel() // (n or 1), _dev32(x, "x"), _dev32(y, "y"), _dev32(a, "a"),
                                        _dev32(b, "b"), _dev32(c, "c"), _dev32(out, "z"), _stream()))
         return out
 
@@ -549,7 +560,7 @@ class ring32:
         n = x.shape[0]
         if out is None:
             out = torch.empty_like(x)
-        _check(lib().spin32_trunc(n, x[0].numel(), f, _dev32(x, "x"), _dev32(r, "r"), _dev32(r_top, "r_top"),
+        _check(lib().spin32_trunc(n, x.numel() // (n or 1), f, _dev32(x, "x"), _dev32(r, "r"), _dev32(r_top, "r_top"),
                                   _dev32(r_msb, "r_msb"), _dev32(out, "out"), _stream()))
         return out
 
