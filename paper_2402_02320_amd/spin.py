@@ -537,8 +537,9 @@ class ring32:
         if out is None:
             out = torch.empty_like(C)
         if workspace is None:
-            workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin32_beaver_matmul_workspace_bytes,
-                                          lib().spin32_beaver_matmul_preferred_workspace_bytes, X.device)
+            L = lib()
+            workspace = _matmul_workspace((n, batch, M, N, K), path, L.spin32_beaver_matmul_workspace_bytes,
+                                          L.spin32_beaver_matmul_preferred_workspace_bytes, X.device)
         _check_matmul(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
                                                  _dev32(B, "B"), _dev32(C, "C"), _dev32(out, "Z"), path,
                                                  workspace.data_ptr(), workspace.numel() * workspace.element_size(),
