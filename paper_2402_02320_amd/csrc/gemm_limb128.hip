@@ -45,6 +45,8 @@ struct Shape128 {
     static constexpr int loads_per_wave = (FA + FB) / 4;         // 16
 };
 
+// SPLIT: several workgroups to a tile (with both endings in one kernel it has a register too few).
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
 {
     using S = Shape128;
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(256) void limb128_gemm_kernel(Gemm128Args g)
     };
     // Parts of a tile: the low words are added first, and the addition that wraps a low word (its return value tells) carries into
     // the high one.  Every wrap is seen by exactly one of the additions, so the sum is right whatever their order.
-    if (g.splits > 1) {
+    if constexpr (SPLIT) {
         u64 low[16], before[16], high[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -299,9 +301,14 @@ spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
         if (st != SPIN_OK) return st;
     }
 
-    static OncePerDevice lds_allowed;
-    st = allow_dynamic_lds((const void *)limb128_gemm_kernel, Shape128::lds_bytes, lds_allowed);
-    if (st != SPIN_OK) return st;
+    static OncePerDevice lds_allowed[2];
+    auto launch = [&](auto kernel, OncePerDevice &allowed, const Gemm128Args &g, long workgroups) {
+        st = allow_dynamic_lds((const void *)kernel, Shape128::lds_bytes, allowed);
+        if (st != SPIN_OK) return;
+        KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
+        kernel<<<(unsigned)workgroups, 256, Shape128::lds_bytes, s>>>(g);
+        st = check_launch("spin128_beaver_matmul(limb gemm)");
+    };
     Gemm128Args g{packA, packB, a.C, a.Z, a.n, a.batch, a.M, a.N, p.nblkA, p.nblkB, p.KT, 0, 0, p.tilesM, p.tilesN,
                   1, split.steps};
     const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
@@ -310,9 +317,8 @@ spin_status launch_matmul_limb128(const MatmulArgs128 &a, hipStream_t s)
         g.ktn = p.KT - kt0 < kMaxChunkTiles128 ? p.KT - kt0 : kMaxChunkTiles128;
         g.C = kt0 == 0 && split.splits == 1 ? a.C : a.Z; // later chunks, and parts, accumulate onto Z
         g.splits = ceil_div(2 * g.ktn, split.steps);     // parts that have steps (a short last chunk may need one, as a plain addition)
-        KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-        limb128_gemm_kernel<<<(unsigned)(total * g.splits), 256, Shape128::lds_bytes, s>>>(g);
-        st = check_launch("spin128_beaver_matmul(limb gemm)");
+        if (g.splits > 1) launch(limb128_gemm_kernel<true>, lds_allowed[1], g, total * g.splits);
+        else launch(limb128_gemm_kernel<false>, lds_allowed[0], g, total);
         if (st != SPIN_OK) return st;
     }
     return SPIN_OK;

@@ -417,14 +417,18 @@ __global__ __launch_bounds__(256) void residue_gemm_kernel(ResidueGemmArgs g)
     };
 
     // ---- read cursor
-    u32 rd_stage = 0;
-    const char *rd_a = lds + wm * 8192 + lane16, *rd_b = lds + S::a_bytes + wn * (NJ * 1024) + lane16;
+    // Scalars with the stage in them, the lane's place added at the load: as lane addresses beside a stage they took two registers
+    // more than there are, spilled around every item.
+    const u32 rd_a0 = wm * 8192, rd_b0 = S::a_bytes + wn * (NJ * 1024);
+    u32 rd_a = rd_a0, rd_b = rd_b0;
     v4i fr[2][S::frags];                                 // [NJ right fragments, 8 left fragments]
     auto read_fragment = [&](int q) -> v4i {
-        return *(const v4i *)(q < NJ ? rd_b + rd_stage + q * 1024 : rd_a + rd_stage + (q - NJ) * 1024);
+        return *(const v4i *)(lds + (q < NJ ? rd_b : rd_a) + lane16 + (q < NJ ? q : q - NJ) * 1024);
     };
     auto advance_read_cursor = [&]() {
-        rd_stage = rd_stage == (S::NSTAGE - 1) * S::stage_bytes ? 0 : rd_stage + S::stage_bytes;
+        const bool last = rd_a == rd_a0 + (S::NSTAGE - 1) * S::stage_bytes;
+        rd_a = last ? rd_a0 : rd_a + S::stage_bytes;
+        rd_b = last ? rd_b0 : rd_b + S::stage_bytes;
     };
 
     v4i acc[8][NJ];

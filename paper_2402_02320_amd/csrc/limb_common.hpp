@@ -251,25 +251,33 @@ __device__ __forceinline__ void pack_left_body(const PackArgs<T> &a, unsigned bl
     const int row0 = blk * 32 + lane / LPR;                 // and the first of them
     const bool inside = blk * 32 + 32 <= M && kt * 32 + 32 <= K;                 // uniform
     // Elements outside the matrix read one inside, so that no load sits behind a branch and has to be awaited before the next is
-    // issued; they become zero before they are stored.  Offsets are 64 bits: 32 rows may be longer than 4 GiB.
-    size_t off[NL];
+    // issued; they become zero before they are stored.  Offsets are 64 bits: 32 rows may be longer than 4 GiB.  One and two parties
+    // over 16-byte rings compute them anew for every matrix, from a number of columns that the compiler cannot tell to be the same:
+    // kept, they take 32 registers, and two parties spill four at two waves a SIMD.  (More parties have one wave and room for them;
+    // computed anew they cost eight parties 8 x 64^3 2 % of the call.)
+    constexpr bool OFFSETS_ANEW = sizeof(T) == 16 && NP <= 2;
+    auto offset = [&](int j, int cols) -> size_t { return (size_t)min(row0 + RPL * j, M - 1) * cols + min(kk, VEC ? K - EPL : K - 1); };
+    size_t off[OFFSETS_ANEW ? 1 : NL];
 #pragma unroll
-    for (int j = 0; j < NL; ++j) off[j] = (size_t)min(row0 + RPL * j, M - 1) * K + min(kk, VEC ? K - EPL : K - 1);
+    for (int j = 0; j < (OFFSETS_ANEW ? 0 : NL); ++j) off[j] = offset(j, K);
     auto load = [&](const T *matrices, int i, Pair (&v)[NL]) {
         const T *base = matrices + ((size_t)i * party_stride + (size_t)b * mat);
+        int cols = K;
+        if (OFFSETS_ANEW) asm volatile("" : "+s"(cols));
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
+            const size_t at = OFFSETS_ANEW ? offset(j, cols) : off[j];
             if constexpr (VEC) {
                 if constexpr (NT && sizeof(T) == 8) {
-                    const u64x2 two = load_share_pair<true>((const u64 *)(base + off[j]));
+                    const u64x2 two = load_share_pair<true>((const u64 *)(base + at));
                     v[j].e[0] = two.x;
                     v[j].e[1] = two.y;
                 } else {
-                    v[j] = *(const Pair *)(base + off[j]);
+                    v[j] = *(const Pair *)(base + at);
                 }
             } else {
 #pragma unroll
-                for (int q = 0; q < EPL; ++q) v[j].e[q] = load_share<NT>(base + off[j] + (kk + q < K ? q : 0));
+                for (int q = 0; q < EPL; ++q) v[j].e[q] = load_share<NT>(base + at + (kk + q < K ? q : 0));
             }
         }
     };
@@ -382,7 +390,10 @@ template <class T> struct PackLaunch {
 };
 template <class T> constexpr int pack_waves = sizeof(T) <= 8 ? 4 : 2;
 constexpr int kCopyPerThread = 8;
-// Two waves on a SIMD wherever that costs no spilled registers (24 to 48 of them, 3 to 7 % of a call, at the others).
+// Two waves on a SIMD wherever that costs no spilled registers (24 to 48 of them, 3 to 7 % of a call, at the others).  No kernel here
+// may spill: where a spilled group of four registers lies partly in spare registers and partly in memory, the compiler (clang 22 of
+// ROCm 7.2) can lose one of the parts.  Eight parties' left pack with the shares of all parties in flight spilled 56; the
+// reload of rows 24 .. 27 of party 0's shares set one register of two, and E was wrong in those rows.
 template <int NP, class T> constexpr int pack_waves_per_simd = (sizeof(T) == 16 ? NP > 2 : NP > 6) ? 1 : 2;
 
 template <int NP, class T, bool VEC, bool TRANSPOSED, bool NT, PackSide SIDE>

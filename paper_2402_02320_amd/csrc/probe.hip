@@ -15,7 +15,7 @@ namespace {
 __global__ __launch_bounds__(256) void mfma_probe_kernel(const v4i *__restrict__ operands, int iters,
                                                         u64 *__restrict__ sink)
 {
-    const int lane = threadIdx.x % 64;
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     v4i fa[2][8], fb[8];                                 // 16 left fragments (two tiles), 8 right fragments
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
@@ -46,7 +46,9 @@ __global__ __launch_bounds__(256) void mfma_probe_kernel(const v4i *__restrict__
         for (int d = 0; d < 8; ++d)
 #pragma unroll
             for (int r = 0; r < 16; ++r) sum += acc[t][d][r];
-    sink[(size_t)blockIdx.x * 256 + threadIdx.x] = (u64)(int64_t)sum;
+    // the thread's number from the wave's and the lane's: kept over the loop it has no register left
+    const unsigned thread = 64 * wave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+    sink[(size_t)blockIdx.x * 256 + thread] = (u64)(int64_t)sum;
 }
 
 }  // namespace

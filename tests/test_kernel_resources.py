@@ -52,3 +52,9 @@ def test_packs_of_three_parties_keep_two_waves():
 def test_grouped_packs_of_right_operands_for_eight_parties():
     spilled = [s for n, (_, s) in kernels().items() if re.search(r"pack_grouped_kernelILi8ELNS\w*PackSideE2E", n)]
     assert len(spilled) == 1 and spilled[0] <= 64            # 388 bytes in one kernel with the packs by rows
+
+
+def test_no_kernel_spills_vector_registers():
+    """The compiler can lose a part of a spilled group of registers (wrong words, no error), so no kernel may depend on it."""
+    spilled = {n: s for n, (_, s) in kernels().items() if s}
+    assert len(kernels()) > 500 and not spilled, spilled
