@@ -221,38 +221,42 @@ inline Plan128 make_plan128(int n, int batch, int M, int N, int K)
 }
 
 // How many workgroups share one output tile (one fits a CU), and the estimated time of the GEMM in microseconds: k-steps (136 MFMAs of
-// 32 cycles; faster, at a higher clock, where the tiles leave part of the chip idle), 6.9 us to start and end, and, where parts
-// are added onto Z, the copy of C and two atomic additions an element and part.  Within 8 % (rms) over
-// 49 split products.  Whole calls, 440 small products: 20 % less time than with one workgroup a tile; 4 parties 32 x 32 x 768 135.6 ->
-// 34.0 us, 3 parties 305 x 17 x 875 81.5 -> 38.1.
-struct Split128 { int splits, steps; double us, whole_us; };      // whole_us: with one workgroup a tile
+// 32 cycles; faster, at a higher clock, where the tiles leave part of the chip idle), 7.5 us to start and end, and, where parts
+// are added onto Z, the copy of C and two atomic additions an element and part; summed over the launches that a long inner
+// dimension takes, of which the last is short.  With the pack below a fit to 8700 products of 12 us to 2 ms (1 to 8 parties, 1 to 64
+// batch entries, sides 16 to 6500), 5900 of them split, within 7 % (rms) of them and of either kind.  Whole calls, 440 small
+// products: 20 % less time than with one workgroup a tile; 4 parties 32 x 32 x 768 135.6 -> 34.0 us, 3 parties 305 x 17 x 875 81.5 -> 38.1.
+struct Split128 { int splits, steps; double us; };
 inline Split128 choose_splits128(int n, int batch, int M, int N, const Plan128 &p)
 {
     const double cus = compute_units(), tiles = (double)p.tilesM * p.tilesN * n * batch, out_mb = 16e-6 * n * batch * (double)M * N;
-    const int steps = 2 * std::min(p.KT, kMaxChunkTiles128);
-    const double chunks = ceil_div(p.KT, kMaxChunkTiles128);
-    Split128 best{1, steps, 0, 0};
+    const int steps = 2 * std::min(p.KT, kMaxChunkTiles128), full = p.KT / kMaxChunkTiles128, rest = 2 * (p.KT % kMaxChunkTiles128);
+    auto launch_us = [&](int chunk_steps, int part) {
+        const int used = ceil_div(chunk_steps, part);
+        const double filled = tiles * used / cus, rounds = std::ceil(filled);
+        return rounds * (3.0 * std::min(part, chunk_steps) * (1 - 0.32 * (1 - filled / rounds)) + 7.5) + (used > 1 ? 0.565 * used * out_mb : 0);
+    };
+    Split128 best{1, steps, 0};
     for (int want = 1; want <= 16; ++want) {
         const int part = ceil_div(steps, want), used = ceil_div(steps, part);
         if (want > 1 && (part < 2 || used != want)) continue;
-        const double filled = tiles * used / cus, rounds = std::ceil(filled);
-        const double us = chunks * (rounds * (2.85 * part * (1 - 0.235 * (1 - filled / rounds)) + 6.9) + (used > 1 ? 3 + 0.5 * used * out_mb : 0));
-        if (want == 1 || us < 0.97 * best.us) best = Split128{used, part, us, want == 1 ? us : best.whole_us};
+        double us = used > 1 ? 1.5 : 0;
+        if (full > 0) us += full * launch_us(2 * kMaxChunkTiles128, part);
+        if (rest > 0) us += launch_us(rest, part);
+        if (want == 1 || us < 0.97 * best.us) best = Split128{used, part, us};
     }
     return best;
 }
 
 // Estimated time in microseconds of the pack and this kernel, for the choice against the residue and the direct kernel: the packs as
-// streams, and a pack's wave that converts the parties' shares one after another.  Without splits a fit to 250 products of 30 us
-// to 1.7 ms, within 7 % (rms).  Splits count where the residue kernels' tiles (256 rows, 128 columns) are mostly padding or their
-// k-steps few: sides up to 48 (5 parties 32 x 32 x 1248 106.9 us by residues, 42.1 split), an inner dimension below 700 (3 parties 416 x 32 x
-// 480 63.0 and 38.5).  Beyond, the line stays where both kernels were fitted without splits; it leaves up to a half on the
-// table for a few thin products (5 parties 163 x 161 x 1460 138.6 and 94.0) and nothing where tiles are full.
+// streams, and a pack's wave that converts the parties' shares one after another.  Against always taking the fastest of the three
+// kernels, on the products above: 0.2 % more time, 3 of them by more than a fifth.  (With the time of one workgroup a tile in its
+// place, thin products went to the residue kernels, whose tiles of 256 rows are mostly padding there: 5 parties, two entries of 63
+// x 52 x 1950 284 us by residues, 59 by digits; 6.8 % more time over sides of 48 to 2048.)
 inline double digit128_cost_us(int n, int batch, int M, int N, int K, const Plan128 &p)
 {
     const double pack_bytes = 16.0 * (3 * n + 1) * batch * ((double)M + N) * K;
-    const Split128 s = choose_splits128(n, batch, M, N, p);
-    return (std::min(M, N) <= 48 || K < 700 ? s.us : s.whole_us) + pack_bytes / 5.94e6 + 8.4 + 2.07 * n;
+    return choose_splits128(n, batch, M, N, p).us + pack_bytes / 6.7e6 + 7.4 + 1.55 * n;
 }
 // The k-steps alone, 3.2 us each: the other side of the direct kernel's own rough estimate.
 inline double digit128_rough_us(int n, int batch, const Plan128 &p)

@@ -727,10 +727,9 @@ template <> struct ResidueCost<u128> {
     static constexpr double first_block = 25.2, first_block_party = 4.97, block = 18.2, block_party = 5.43;
     static constexpr double shared = 4.2, shared_part = 7.1;
 };
-// Taken where its estimate is this much below the digit kernels'.  On those products, time against always the digit kernels: 0.884
-// over Z_2^128 and 0.986 over Z_2^64; slower than by digits were 3 and 1 products of 2000 by more than 2 % (8 % at most), without the
-// margin 17 and 9 (16 %).  With the constants fitted to fewer products and no margin it was 90 of 1900 over Z_2^128 (76 %: 3
-// parties 320 x 128 x 96 34 -> 63 us) and 11 of 2100 over Z_2^64.
+// Taken where its estimate is this much below the digit kernels'.  Against always taking the faster of the two the choice costs 0.14 %
+// over 1360 products over Z_2^64 near the line, none of them slower than by digits by more than 2 % (without the margin 0.09 %
+// and 8 of them), and 0.2 % over 8700 over Z_2^128 (1 to 8 parties, sides 16 to 6500), the direct kernel included.
 constexpr double kResidueMargin = 0.95;
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {

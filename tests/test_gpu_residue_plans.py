@@ -23,15 +23,16 @@ CASES64 = [(2, 1, 389, 2224, 1193, True, 227377151, 2),       # one party at a t
            (2, 1, 1939, 1115, 1537, False, 238878719, 3),     # eight panels of rows in blocks of three, narrow tiles
            (3, 1, 1169, 540, 987, True, 206372864, 1),        # narrow tiles in parts
            (2, 1, 1206, 856, 970, False, 174587903, 2)]       # the same, one party at a time
-CASES128 = [(2, 2, 65, 64, 3733, 110886911, 8),               # one party at a time, two batch entries, two chunks
-            (2, 1, 71, 456, 1481, 89653247, 4),               # one party at a time, two blocks of columns
-            (3, 1, 62, 260, 3821, 226492415, 4),              # left operands kept over two blocks of columns, two chunks
-            (3, 2, 652, 204, 958, 162791423, 4),              # right operands kept over uneven blocks of rows, two batch entries
+CASES128 = [(2, 2, 459, 533, 1009, 113246208, 4),             # one party at a time, two batch entries
+            (2, 1, 217, 875, 4370, 242417664, 4),             # one party at a time, two chunks
+            (2, 1, 386, 1438, 945, 106522214, 4),             # one party at a time, two blocks of columns
+            (3, 1, 195, 912, 3790, 298070835, 4),             # left operands kept over two blocks of columns, two chunks
+            (3, 2, 1268, 655, 525, 220882534, 4),             # right operands kept over uneven blocks of rows, two batch entries
             (3, 1, 769, 909, 885, 169869311, 4),              # two blocks of rows and two of columns
-            (3, 1, 531, 60, 813, 143917055, 2),               # three panels of rows in blocks of two and one, narrow tiles
-            (5, 1, 547, 65, 4260, 516685823, 4),              # the same with items in two parts, two chunks
-            (3, 1, 64, 76, 4289, 171048960, 2),               # narrow tiles in parts, two chunks
-            (5, 1, 60, 399, 4291, 391380992, 2),              # wide tiles in parts, two chunks
+            (5, 1, 708, 551, 748, 334784102, 2),              # three panels of rows in blocks of two and one, narrow tiles
+            (5, 1, 1037, 338, 5143, 849720115, 4),            # five panels in blocks of three and two, items in parts, two chunks
+            (2, 1, 961, 259, 4312, 401866752, 2),             # narrow tiles in parts, two chunks
+            (3, 1, 197, 666, 4398, 360448000, 2),             # wide tiles in parts, two chunks
             (2, 1, 2048, 2048, 2048, 402653184, 8)]           # the workspace that is needed: wide tiles in four parts
 
 

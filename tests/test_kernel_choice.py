@@ -9,13 +9,24 @@ DIGITS = [(128, 3, 1, 320, 128, 96),        # 34 : 63
           (128, 4, 1, 77, 245, 99),         # 43 : 73
           (128, 2, 1, 736, 128, 96),        # 40 : 57
           (128, 4, 1, 192, 128, 160),       # 46 : 69
-          (128, 6, 1, 64, 224, 288),        # 76 : 93
-          (128, 6, 1, 64, 608, 1120),       # 235 : 246
+          (128, 6, 1, 64, 224, 288),        # 44 : 94
+          (128, 6, 1, 64, 608, 1120),       # 113 : 250
+          (128, 5, 2, 63, 52, 1950),        # 61 : 296, tiles shared by several workgroups from here on
+          (128, 2, 1, 48, 48, 2000),        # 44 : 83
+          (128, 2, 1, 49, 49, 2000),        # 45 : 87
+          (128, 3, 1, 64, 64, 699),         # 34 : 71
+          (128, 3, 1, 64, 64, 700),         # 34 : 70
+          (128, 8, 1, 49, 50, 5835),        # 174 : 641
+          (128, 1, 1, 300, 300, 5440),      # 158 : 268, one launch of the digit GEMM
+          (128, 1, 1, 300, 300, 5441),      # 177 : 265, two
+          (128, 5, 1, 163, 161, 1460),      # 93 : 138
+          (128, 3, 1, 480, 128, 3392),      # 221 : 248
           (64, 1, 1, 1504, 800, 512),       # 52 : 62
           (64, 4, 1, 466, 807, 2203),       # 242 : 271
           (64, 5, 1, 130, 1643, 716),       # 140 : 152
           (64, 3, 1, 256, 2976, 608)]       # 140 : 151
-RESIDUES = [(128, 2, 1, 2048, 2048, 2048), (128, 3, 1, 480, 128, 3392), (128, 4, 1, 103, 2467, 1327), (128, 2, 1, 160, 2336, 1696),
+RESIDUES = [(128, 2, 1, 2048, 2048, 2048), (128, 3, 1, 1024, 512, 1024), (128, 4, 1, 512, 640, 2000), (128, 2, 1, 160, 2336, 1696),
+            (128, 2, 1, 512, 512, 5440), (128, 2, 1, 512, 512, 5441),     # 679 : 555, 700 : 562
             (64, 2, 1, 2048, 2048, 2048), (64, 5, 1, 4096, 4096, 4096)]
 
 
