@@ -149,8 +149,8 @@ bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, doubl
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K);
 spin_status launch_matmul_limb32(const MatmulArgs32 &a, hipStream_t s);
 // Large products over Z_2^32 by Strassen's recursion (gemm_strassen.hip) where a.workspace_bytes has room for it and it is
-// estimated to be faster; `taken` says whether it ran.  The first tells the workspace the cheapest plan of at most `most`
-// bytes takes (0: none is faster than the digit kernels alone).
+// estimated to be faster; `taken` says whether it ran.  The first tells the workspace it takes (0: more than `most` bytes, or no
+// faster than the digit kernels alone).
 size_t strassen32_workspace_bytes(int n, int batch, int M, int N, int K, size_t most);
 spin_status launch_matmul_strassen32(const MatmulArgs32 &a, hipStream_t s, bool &taken);
 // Its GEMM: batch products of packed operands ([n+1][batch][M / 32][K / 32][4][1024] and the same of N), whole workgroup tiles, no C.

@@ -11,8 +11,9 @@
 //                           call as entries 49 b .. of the GEMM.  Bound by memory: 2n words in, (n + 1) 49/16 out an element (4.4 TB/s).
 //  limb_gemm_kernel<u32>    the products, without C.
 //  strassen_combine_kernel  Z = C + combinations of the products.
-// Measured, whole call, digit kernels alone against this: two parties 8192^3 15.5 -> 13.8 ms (pack 0.68 -> 1.6, GEMM 14.9 -> 11.7,
-// combine 0.55), three parties 5059 x 7112 x 7399 13.2 -> 11.5 ms; 8 to 14 % less over 15 products.  One level alone gains a quarter of it.
+// Measured back to back, whole calls, digit kernels alone against this: two parties 8192^3 16.7 -> 14.8 ms (pack 0.68 -> 1.6, GEMM 15.9 ->
+// 12.6, combine 0.53), 6144^3 6.96 -> 6.49, five parties 8192^3 42.9 -> 37.5, three parties 5059 x 7112 x 7399 13.2 -> 11.8.  One
+// level alone gains a quarter of it.
 #include <algorithm>
 
 #include "limb_common.hpp"
@@ -206,9 +207,12 @@ struct StrassenPlan {
 };
 inline int part_of(int side, int parts, int multiple) { return ceil_div(ceil_div(side, parts), multiple) * multiple; }
 
-// Rates, measured over 30 products of 1 to 8 parties with sides of 2500 to 11700: int8 operations on random bytes (the digit kernels
-// alone, and under the recursion, whose smaller products start and end more often), bytes of the packs and passes, launches.
-constexpr double kPlainOpsPerUs = 2.92e9, kOpsPerUs = 2.68e9, kPlainBytesPerUs = 5.2e6, kBytesPerUs = 4.1e6, kLaunchUs = 25;
+// Rates of both ways: int8 operations on random bytes, bytes of the packs and of the combination, launches.  A fit to 4060 products of 1
+// to 8 parties (1 to 4 batch entries, sides of 1024 to 12000, 0.3 to 25 ms), within 4 and 3 % (rms).  647 of them are faster by the
+// recursion, 397 by more than 3 %; the rule takes 396, of which 11 are slower by more than 1 %, and costs 0.16 % against always the
+// faster way.  (With rates from 30 products it took 8, and cost 0.69 %.)
+constexpr double kOpsPerUs = 2.69e9, kPackBytesPerUs = 5.46e6, kCombineBytesPerUs = 2.99e6, kLaunchUs = 66;
+constexpr double kPlainOpsPerUs = 2.68e9, kPlainBytesPerUs = 7.16e6, kPlainLaunchUs = 18;
 
 StrassenPlan make_plan(int n, int batch, int M, int N, int K)
 {
@@ -220,9 +224,11 @@ StrassenPlan make_plan(int n, int batch, int M, int N, int K)
     p.Ks = part_of(K, kParts, 32);
     const double left = (double)p.Ms * p.Ks, right = (double)p.Ks * p.Ns, out = (double)p.Ms * p.Ns;
     const double us = 20.0 * 2 * n * batch * kProducts * out * p.Ks / kOpsPerUs + kLaunchUs +
-                      4.0 * batch * ((2 * n * kBlocks + (n + 1) * kProducts) * (left + right) + n * out * (kProducts + 2 * kBlocks)) / kBytesPerUs;
+                      4.0 * batch * (2 * n * kBlocks + (n + 1) * kProducts) * (left + right) / kPackBytesPerUs +
+                      4.0 * batch * n * out * (kProducts + 2 * kBlocks) / kCombineBytesPerUs;
     const double m = part_of(M, 1, 128), c = part_of(N, 1, 128), k = part_of(K, 1, 32);
-    const double plain_us = 20.0 * 2 * n * batch * m * c * k / kPlainOpsPerUs + 4.0 * batch * (3 * n + 1) * (m * k + k * c) / kPlainBytesPerUs;
+    const double plain_us = 20.0 * 2 * n * batch * m * c * k / kPlainOpsPerUs + 4.0 * batch * (3 * n + 1) * (m * k + k * c) / kPlainBytesPerUs +
+                            kPlainLaunchUs;
     const double tiles = (double)n * batch * kProducts * (p.Ms / 128) * (p.Ns / 128);
     const bool fits_grids = (double)n * batch <= 60000 && tiles < 1e9 && (left + right) / 1024 < 1e9 && out / 1024 < 1e9;
     p.faster = us < 0.97 * plain_us && fits_grids;

@@ -6,14 +6,19 @@ import torch
 from paper_2402_02320_amd import spin
 
 R = spin.ring32
-# rows of 16 bytes and not, on either side; one party; sides that fill their last block by one element
-SHAPES = [(2, 1, 7159, 5629, 8785), (1, 1, 8192, 8190, 8188), (1, 2, 8189, 8192, 8064), (3, 1, 5059, 7112, 7399)]
+# rows of 16 bytes and not, on either side; one party; one and several batch entries and parties; last blocks that are full and as empty
+# as blocks in multiples of 128 leave them (1025 of 1536 rows, 1537 of 2048)
+SHAPES = [(2, 1, 7159, 5629, 8785), (1, 1, 8192, 8190, 8188), (1, 2, 8189, 8192, 8064), (3, 1, 5059, 7112, 7399), (2, 2, 6144, 6144, 6144),
+          (2, 1, 5633, 6144, 8192), (1, 1, 7681, 8192, 8191)]
+# measured, us by the digit kernels and by the recursion, in the workspace that each needs
+FASTER = [(2, 1, 6592, 10016, 7328), (4, 1, 3488, 5632, 7424), (3, 1, 4032, 7680, 7680)]           # 15907 : 14081, 9582 : 8434, 11791 : 10455
+SLOWER = [(2, 1, 4096, 4096, 2048), (4, 1, 9376, 3776, 4192)]                                      # the second 9518 : 9564
 
 
 def test_only_large_products_prefer_more_workspace():
-    for dims in SHAPES:
+    for dims in SHAPES + FASTER:
         assert R.beaver_matmul_preferred_workspace_bytes(*dims) > 2 * R.beaver_matmul_workspace_bytes(*dims)
-    for dims in ((2, 1, 4096, 4096, 2048), (2, 1, 8192, 64, 8192), (5, 1, 300, 300, 300), (2, 64, 512, 512, 512)):
+    for dims in SLOWER + [(2, 1, 8192, 64, 8192), (5, 1, 300, 300, 300), (2, 64, 512, 512, 512)]:
         assert R.beaver_matmul_preferred_workspace_bytes(*dims) == R.beaver_matmul_workspace_bytes(*dims)
     assert R.beaver_matmul_preferred_workspace_bytes(0, 1, 8192, 8192, 8192) == 0
 
