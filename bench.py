@@ -295,8 +295,7 @@ def bench_matmul_other_ring(args, bits):
         return torch.empty(shape, dtype=torch.int32, device="cuda").random_(-2 ** 31, 2 ** 31)
     X, Y, A, B, C = (rnd((n, 1, M, M)) for _ in range(5))
     Z = torch.empty_like(C)
-    size = R.beaver_matmul_preferred_workspace_bytes if bits == 128 else R.beaver_matmul_workspace_bytes
-    ws = torch.empty(size(n, 1, M, M, M, path), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(R.beaver_matmul_preferred_workspace_bytes(n, 1, M, M, M, path), dtype=torch.uint8, device="cuda")
     for _ in range(args.warmup):
         R.beaver_matmul(X, Y, A, B, C, path=path, out=Z, workspace=ws)
     torch.cuda.synchronize()
@@ -312,8 +311,11 @@ def bench_matmul_other_ring(args, bits):
     key = "gemm_limb" if path == spin.LIMB_MFMA else "gemm_valu"
     if spin.profile_read("gemm_residue")[1] > 0:
         key, pairs = "gemm_residue", 36                       # residues modulo 36 numbers instead of 136 digit pairs
+    elif spin.profile_read("combine")[1] > 0:
+        pairs *= 49 / 64                                      # two levels of Strassen's recursion above the digit GEMM
     tot, cnt = spin.profile_read(key)
     pk, pc = spin.profile_read("pack")
+    cb, cc = spin.profile_read("combine")
     spin.profile_reset()
     gemm_ms = tot / cnt
     roof = None
@@ -331,7 +333,8 @@ def bench_matmul_other_ring(args, bits):
                       if path == spin.LIMB_MFMA else ring,
                       "data": "synthetic",
                       "config": {"workload": "%d parties, M=N=K=%d over Z_2^%d" % (n, M, bits), "gemm_path": args.path},
-                      "roofline": roof, "gemm_avg_ms": gemm_ms, "pack_avg_ms": pk / pc if pc else None}))
+                      "roofline": roof, "gemm_avg_ms": gemm_ms, "pack_avg_ms": pk / pc if pc else None,
+                      "combine_avg_ms": cb / cc if cc else None}))
 
 
 def bench_grouped(args):
