@@ -1103,33 +1103,9 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
         constexpr int NP = decltype(np)::value;
         {
             KernelTimer timer(SPIN_KERNEL_PACK, s);
-            // At eight parties the kernel of all kinds leaves a SIMD one wave, that of right operands alone two: many of those
-            // have their own launch there (three products 64 x 4096 x 1000, 3072 workgroups: 1030 us a call, 1013 to 1050 together).
-            bool apart = false;
-            if constexpr (NP == 8) {
-                std::vector<GroupedPackSide> some[2];
-                std::vector<unsigned> blocks[2];
-                unsigned long right = 0;
-                for (size_t i = 0; i < sides.size(); ++i) {
-                    const int r = sides[i].kind == 4;
-                    some[r].push_back(sides[i]);
-                    blocks[r].push_back(side_blocks[i]);
-                    if (r) right += side_blocks[i];
-                }
-                apart = right > 2ul * compute_units();
-                if (apart) {
-                    launch_in_tables(some[0], blocks[0], [&](const GroupTable<GroupedPackSide> &t, unsigned total) {
-                        pack_grouped_kernel<NP, kLeft><<<total, 256, 0, s>>>(t);
-                    });
-                    launch_in_tables(some[1], blocks[1], [&](const GroupTable<GroupedPackSide> &t, unsigned total) {
-                        pack_grouped_kernel<NP, kRight><<<total, 256, 0, s>>>(t);
-                    });
-                }
-            }
-            if (!apart)
-                launch_in_tables(sides, side_blocks, [&](const GroupTable<GroupedPackSide> &t, unsigned total) {
-                    pack_grouped_kernel<NP, kBoth><<<total, 256, 0, s>>>(t);
-                });
+            launch_in_tables(sides, side_blocks, [&](const GroupTable<GroupedPackSide> &t, unsigned total) {
+                pack_grouped_kernel<NP><<<total, 256, 0, s>>>(t);
+            });
             st = check_launch("spin_beaver_matmul_grouped(pack)");
             if (st != SPIN_OK) return;
         }

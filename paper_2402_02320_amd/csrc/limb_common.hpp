@@ -423,22 +423,20 @@ struct GroupedPackSide {
     PackArgs<u64> a;
     int kind;                                            // 0, 1: left (16-byte rows or not); 2, 3: transposed right; 4: right
 };
-// SIDE: which kinds a table holds, all, rows (0 to 3) or right (4).
-template <int NP, PackSide SIDE>
+template <int NP>
 __global__ __launch_bounds__(256, (pack_waves_per_simd<NP, u64>)) void pack_grouped_kernel(GroupTable<GroupedPackSide> t)
 {
-    __shared__ __attribute__((aligned(16))) char lds[SIDE == kRight ? 16 : 4 * 32 * turn_row_bytes<u64>];
+    __shared__ __attribute__((aligned(16))) char lds[4 * 32 * turn_row_bytes<u64>];
     const int gi = group_of(t, blockIdx.x);
     const PackArgs<u64> a = t.e[gi].a;
-    const int kind = SIDE == kRight ? 4 : t.e[gi].kind;
+    const int kind = t.e[gi].kind;
     const unsigned local = blockIdx.x - t.first[gi];
     const unsigned per_batch = kind == 4 ? pack_right_blocks<4>(a.nblk, a.KT) : pack_left_blocks<4>(a.nblk, a.KT);
     const unsigned block = local % per_batch;
     const int b = (int)(local / per_batch);
-    if constexpr (SIDE == kRight) pack_right_body<NP, u64, 4, false>(a, block, b);
-    else if (kind == 0 || kind == 2) pack_left_body<NP, u64, true, 4, false>(a, block, b, lds, kind == 2);
+    if (kind == 0 || kind == 2) pack_left_body<NP, u64, true, 4, false>(a, block, b, lds, kind == 2);
     else if (kind == 1 || kind == 3) pack_left_body<NP, u64, false, 4, false>(a, block, b, lds, kind == 3);
-    else if constexpr (SIDE == kBoth) pack_right_body<NP, u64, 4, false>(a, block, b);
+    else pack_right_body<NP, u64, 4, false>(a, block, b);
 }
 
 // One direct-to-LDS load: 64 lanes x 16 bytes from src + lane*16 to the LDS address lds_dst + lane*16.

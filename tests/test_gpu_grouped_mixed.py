@@ -32,7 +32,7 @@ def test_rows_and_tiles_together(n, count):
         assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
-# eight parties: beyond two right-hand pack workgroups a CU those packs have a launch of their own; with and without packs by rows
+# eight parties: few and many right-hand pack workgroups (the kernel of all packs has one wave a SIMD); with and without packs by rows
 @pytest.mark.parametrize("shapes", [[(1, 64, 2048, 512, False), (2, 33, 65, 64, True)], [(1, 64, 2112, 512, False), (2, 33, 65, 64, True)],
                                     [(3, 20, 4100, 301, False)] * 3 + [(1, 70, 50, 33, True)], [(1, 64, 4096, 1000, False)]])
 def test_eight_parties_many_right_operands(shapes):

@@ -1,5 +1,5 @@
-"""Registers of the built pack kernels, read from the metadata of libspin.so's own gfx950 code objects: the waves per SIMD that a
-kernel of one side reaches by itself must not be lost to what another side needs (a SIMD has 512 registers per lane)."""
+"""Registers of the built kernels, read from the metadata of libspin.so's own gfx950 code objects: the waves per SIMD that the packs
+reach (a SIMD has 512 registers per lane), the kernels of one side and those of both, and no spilled registers anywhere."""
 import os
 import re
 import struct
@@ -33,25 +33,22 @@ def kernels():
 
 
 # mangled ring types: o = unsigned __int128, m = unsigned long, j = unsigned int
-@pytest.mark.parametrize("np,ring,side,most", [(2, "o", "left", 256),      # two waves; with the right pack in one kernel: one
-                                               (1, "o", "right", 168),     # three; two
-                                               (2, "m", "right", 168),     # three; two
-                                               (7, "j", "right", 256)])    # two; one
-def test_one_sided_packs_keep_their_waves(np, ring, side, most):
+@pytest.mark.parametrize("np,ring,side,most", [(2, "o", "left", 256), (2, "o", "both", 256),         # two waves
+                                               (1, "o", "right", 168), (1, "o", "both", 168),        # three
+                                               (2, "m", "right", 168), (2, "m", "both", 168),        # three
+                                               (6, "m", "left", 256), (6, "m", "both", 256),         # two
+                                               (7, "j", "right", 256), (8, "j", "both", 168)])       # two, three
+def test_packs_keep_their_waves(np, ring, side, most):
     which = {"both": 0, "left": 1, "right": 2}[side]
     found = {n: v for n, (v, _) in kernels().items()
              if re.search(r"pack_kernelILi%dE%sLb[01]ELb0ELb[01]ELNS\w*PackSideE%dE" % (np, ring, which), n)}
-    assert len(found) >= 2 and max(found.values()) <= most, found
+    assert len(found) >= (1 if side == "both" else 2) and max(found.values()) <= most, found
 
 
-def test_packs_of_three_parties_keep_two_waves():
-    found = {n: v for n, (v, _) in kernels().items() if re.search(r"pack_(grouped_)?kernelILi3E(m|LNS)", n)}
-    assert len(found) >= 5 and max(found.values()) <= 256, found
-
-
-def test_grouped_packs_of_right_operands_for_eight_parties():
-    spilled = [s for n, (_, s) in kernels().items() if re.search(r"pack_grouped_kernelILi8ELNS\w*PackSideE2E", n)]
-    assert len(spilled) == 1 and spilled[0] <= 64            # 388 bytes in one kernel with the packs by rows
+@pytest.mark.parametrize("pattern,least,most", [(r"pack_kernelILi3Em", 5, 256), (r"pack_grouped_kernelILi[1-6]E", 6, 256), (r"strassen_pack_kernelILb", 4, 256)])
+def test_packs_keep_two_waves(pattern, least, most):
+    found = {n: v for n, (v, _) in kernels().items() if re.search(pattern, n)}
+    assert len(found) >= least and max(found.values()) <= most, found
 
 
 def test_no_kernel_spills_vector_registers():
