@@ -1,5 +1,7 @@
 """The row kernel's items: row blocks in eight contiguous shares, column tiles fastest.  Block counts around multiples of 8 and of the
-workgroups a launch has, one to three column tiles, one batch entry and several, against the vector-ALU path.  Exact ring words."""
+workgroups a launch has, one to three column tiles, one batch entry and many, against the vector-ALU path.  Exact ring words; that the
+row kernel made them shows in the workspace, whose first part (left fragments, [n+1][batch][M / 32][K / 32] of 8 KB in whole 128-row
+tiles) it leaves as it was."""
 import pytest
 import torch
 
@@ -7,9 +9,31 @@ from paper_2402_02320_amd import spin
 
 pytestmark = pytest.mark.gpu
 
+# row blocks x column tiles behind each; a launch has 256 workgroups
+SHAPES = [(3, 7, 20, 190, 130), (3, 1, 256, 190, 130), (3, 1, 257, 190, 130),       # 7, 8, 9 x 3
+          (3, 3, 129, 129, 66), (3, 1, 512, 128, 66), (3, 17, 20, 128, 66),         # 15 x 3, 16 x 2, 17 x 2
+          (3, 63, 1, 128, 2), (3, 96, 1, 65, 2), (3, 65, 20, 63, 2),                # 63 x 2, 96 x 2, 65 x 1
+          (3, 255, 20, 1, 2), (3, 256, 20, 1, 2), (3, 300, 1, 40, 2),               # 255, 256, 300 x 1
+          (2, 255, 1, 190, 2), (3, 257, 1, 65, 2), (3, 63, 200, 1, 2),              # 255 x 3, 257 x 2, 441 x 1
+          (3, 64, 128, 128, 64), (3, 65, 127, 129, 64), (3, 513, 32, 64, 64), (3, 511, 20, 100, 66)]    # several rounds of items
 
-@pytest.mark.parametrize("n,batch,M,N,K", [(3, 1, 3 * 32, 64, 2048), (3, 1, 8 * 32 + 1, 40, 2048), (2, 9, 33, 64, 1024), (3, 15, 31, 70, 512), (1, 17, 64, 128, 512),
-                                           (3, 64, 128, 128, 64), (3, 65, 127, 129, 64), (2, 1, 257 * 32, 64, 96), (3, 513, 32, 64, 64), (3, 511, 20, 100, 66)])
+
+def by_rows(call, n, batch, M, K, size):
+    left = (n + 1) * batch * ((M + 127) // 128 * 4) * ((K + 31) // 32) * 8192
+    ws = torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda")
+    spin.profile_reset()
+    spin.profile_enable(True)
+    out = call(ws)
+    torch.cuda.synchronize()
+    spin.profile_enable(False)
+    count = {k: spin.profile_read(k)[1] for k in ("gemm_limb", "gemm_direct", "gemm_residue")}
+    spin.profile_reset()
+    assert count == {"gemm_limb": 1, "gemm_direct": 0, "gemm_residue": 0}
+    assert bool((ws[:left] == 0x5A).all()) and not bool((ws[left:] == 0x5A).all()), "not a product of the row kernel any more"
+    return out
+
+
+@pytest.mark.parametrize("n,batch,M,N,K", SHAPES)
 @pytest.mark.parametrize("transposed", [False, True])
 def test_words(n, batch, M, N, K, transposed):
     g = torch.Generator(device="cuda")
@@ -20,6 +44,8 @@ def test_words(n, batch, M, N, K, transposed):
     y = (N, K) if transposed else (K, N)
     X, Y, A, B, C = u(n, batch, M, K), u(n, batch, *y), u(n, batch, M, K), u(n, batch, *y), u(n, batch, M, N)
     want = spin.beaver_matmul(X, Y, A, B, C, path=spin.VALU, y_transposed=transposed)
-    assert torch.equal(spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed), want)
+    size = spin.beaver_matmul_workspace_bytes(n, batch, M, N, K)
+    assert torch.equal(by_rows(lambda ws: spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed, workspace=ws), n, batch, M, K, size), want)
     group = dict(X=X, Y=Y, A=A, B=B, C=C, y_transposed=transposed)
-    assert all(torch.equal(z, want) for z in spin.beaver_matmul_grouped([group, group]))
+    got = by_rows(lambda ws: spin.beaver_matmul_grouped([group, group], workspace=ws), n, batch, M, K, 2 * size)
+    assert all(torch.equal(z, want) for z in got)
