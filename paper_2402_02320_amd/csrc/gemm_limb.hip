@@ -466,7 +466,7 @@ __device__ __forceinline__ void limb_gemm_rows_body(const RowGemmArgs &g, unsign
     // Workgroup ids are dealt round-robin to the 8 XCDs, and an XCD gets a contiguous eighth of the row blocks (counted over all batch
     // entries), column tiles fastest: the column tiles of a row block meet in one L2, where the raw tiles come from memory once,
     // and so do the row blocks of a batch entry, for its right fragments.  (Row blocks dealt one by one: every entry's right fragments
-    // went to up to eight L2s.  64 entries of 3 parties, 128 x 128 x 64: 44.6 us a call, now 40.2; 131072 x 64 x 576: 1240 -> 1217.)
+    // went to up to eight L2s.  64 entries of 3 parties, 128 x 128 x 64: 44.6 us a call, now 40.2; 131072 x 64 x 576, with one right operand: equal.)
     // A workgroup walks the items first_item, first_item + item_stride, ... (the stride is a multiple of 8, so all
     // of them belong to one XCD); rows_grid pads the id space to 8 equal shares, and a workgroup that has none leaves at once.
     const int rblocks = (g.M + 31) / 32;
@@ -864,7 +864,9 @@ inline int choose_splits(long tiles, int steps)
 // one CU (about a microsecond), the unit of choose_splits: the row kernel walks 2 KT steps per block of 32
 // rows and column tile; the other path adds the left pack, an HBM stream of (3n + 1) operand-sized matrices
 // at about 5 MB per step-time.  The 5 steps were its launch, when it had one of its own; below kPackStreamingBytes it rides
-// with the right pack now.  They were left as measured then: the row kernel keeps the products it had.
+// with the right pack now.  They were left as measured then: the row kernel keeps the products it had.  Over 4400 products near the line (1
+// to 3 parties, M 32 to 20000, N 16 to 400, K to 3000) that takes 0.95 % more time than always the faster kernel, 70 of them more than 16 %
+// (3 parties 2019 x 21 x 332 41.3 us by rows, 28.7 by tiles).
 template <class T> inline double rows_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
 {
     const int cus = compute_units();
@@ -904,7 +906,8 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
 }
 
 // The same in detail, for small products: the waves of a pack convert the parties' shares one after another, and the
-// output counts.  A fit to 19 500 products of 5 us to 2 ms near the line between the two kernels, within 8 (9 over Z_2^32) % (rms).
+// output counts.  A fit to 19 500 products of 5 us to 2 ms near the line between the two kernels, within 8 (9 over Z_2^32) % (rms); since the
+// packs got faster it reads 7 (9) % high.  The choice takes 0.5 (0.7) % more time than always the faster kernel over 3600 (2700) products.
 template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
 {
     const int cus = compute_units();

@@ -112,8 +112,8 @@ template <class T> struct PackArgs {
 // A small pack is bound by what one wave has to issue (one or two waves on a SIMD, 5 cycles an instruction), so the addresses are
 // kept off the vector unit: the wave's place is a scalar, every load a scalar row address plus the lane's 32-bit offset, and a
 // tile inside the matrix is not masked.  With all parties' loads behind one another and 64-bit vector addresses and divisions a
-// wave of three parties took 14.5 us (rows) and 8 us (columns), now 5.3 and 6; whole calls of 320 small products: 4 % less time,
-// up to 24 % where eight parties' shares had spilled.
+// wave of three parties took 14.5 us (rows) and 8 us (columns), now 5.3 and 6; whole calls of 420 small products over the three
+// rings: 2.4 to 4.7 % less time, up to 25 % where eight parties' shares had spilled.
 template <int NP, class T, int WAVES, bool NT>
 __device__ __forceinline__ void pack_right_body(const PackArgs<T> &a, unsigned block, int b)
 {
