@@ -24,11 +24,10 @@
 //                streamed global -> LDS with direct-to-LDS loads, 36 MFMAs per
 //                32x32x32 step into 8 diagonal accumulators, recombined once.
 //  limb_gemm_rows_kernel  products with few column tiles (N <= 64; attention shapes), at most three
-//                parties: no left pack at all -- a producer wave streams the raw X_j, A_j tiles into LDS
-//                and opens E, one consumer wave per party converts its A_p in registers and runs the MFMAs.
+//                parties: no left pack at all -- the workgroup opens E from the raw X_j, A_j itself, converts E and the A_p to
+//                fragments in LDS and multiplies all parties' outputs of a row block.
 //  *_grouped_kernel  the same bodies for several products of different shapes in one launch
-//                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments; row and tile
-//                products share a launch in limb_gemm_mixed_grouped_kernel.
+//                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments.
 // Larger products go to the residue GEMM (gemm_residue.hip; over Z_2^32 to gemm_strassen.hip) and the smallest to one launch of vector arithmetic
 // (gemm_direct.hip); digit_cost_us is this file's side of that choice.
 #include <algorithm>
@@ -371,31 +370,38 @@ __global__ __launch_bounds__(256) void limb_gemm_grouped_kernel(GroupTable<GemmA
 // exactly one output tile, so writing the left operands out as fragments and reading them back (the pack
 // pre-pass) costs more HBM traffic than the product itself.  Here the left fragments never exist in
 // memory.  (Products of a few column tiles and a short inner dimension -- the attention shapes -- take the
-// same kernel once per column tile when that is cheaper than the pre-pass: the raw tiles are then read once
+// same kernel once per column tile when that is cheaper than the pre-pass: the raw shares are then read once
 // per column tile, from L2.)  One workgroup owns a block of 32 rows and one column tile of 64 for ALL
-// parties (NP <= 3) and walks the inner dimension once; the raw 32 x 32 tiles of every X_j and A_j go memory -> LDS exactly once (direct-to-LDS loads,
-// no register is held while they fly).
-//   producer wave (the last one, on a SIMD of its own)  issues those loads one k-tile ahead, opens
-//       E = sum_j (X_j - A_j) from the raw tiles, converts E to digits and lays it out as MFMA fragments
-//       in a two-stage LDS ring;
-//   consumer wave p (one per party, each with the whole accumulator file)  computes
-//       Z_p[32 x 64] = C_p + A_p . F + E . B_p': per 32-deep k-tile a half step on (A_p, F) and one on
-//       (E, B_p'), 72 MFMAs each.  It converts its own A_p from the raw tile in registers (the vector ALU is
-//       idle under the MFMAs) and reads the right fragments (packed beforehand: they are small, shared by
-//       all row blocks and stay in L2) straight from memory into registers, because B_p' has no second
-//       reader inside the workgroup.
-// Nothing is masked at ragged edges: loads that would leave the matrix are redirected to the tile's first
-// element, and what they bring only meets zero-padded rows of the right fragments (k >= K) or lands in
-// output rows that are never stored (row >= M).
-// Synchronisation: one workgroup barrier per k-tile.  In iteration g the consumers read E(g) from ring
-// stage g % 2 (first half) and raw A_p(g+1) from raw slot (g+1) % 3 (second half); the producer reads raw
-// slot (g+1) % 3, writes E(g+1) to stage (g+1) % 2, refills raw slot g % 3 with k-tile g + 3 and waits for
-// k-tile g + 2, issued one iteration earlier: every load has two iterations to arrive.
+// parties (NP <= 3) and walks the inner dimension once.
+//
+// What has to be multiplied per k-tile of 32 is 2 NP units of 32 x 32 outputs (party, column half), twice: E . B_p' and A_p . F,
+// 36 MFMAs each.  Eight waves share it, two to a SIMD and 256 registers each, so that one's waits are covered by the other's MFMAs,
+// and so that every SIMD has the same number of MFMAs: a unit is one wave's, with all eight diagonal accumulators, or two waves', 18
+// MFMAs and four diagonals each (0, 1, 6, 7 and 2, 3, 4, 5; no accumulator exists twice, and the two parts are added through LDS at the end).
+//   NP = 3: units 0 .. 3 whole (waves 0 .. 3), units 4 and 5 in parts (waves 4 .. 7): 54 MFMAs a SIMD and half step, where one
+//           wave per party on three SIMDs had 72;   NP = 2: four units in parts;   NP = 1: two units in parts (waves 0 .. 3).
+// Besides,
+//   waves 0 .. 3 ("loaders")     bring the right fragments (packed beforehand: they are small, shared by all row blocks and stay in
+//       L2) into two LDS stages with direct-to-LDS loads, three half steps ahead;
+//   waves 4 .. 7 ("converters")  load the raw shares of X_j and A_j into registers two k-tiles ahead (each byte of the left operands
+//       is read exactly once: 8 rows x 256 bytes per wave), open E = sum_j (X_j - A_j), convert E and every A_p to digits
+//       and write them to LDS as fragments.
+// A half step is one operand pair of one k-tile and ends with the workgroup's barrier.  In the first half of tile t all waves read
+// E(t) and B'(t) and the converters write A(t); in the second they read A(t) and F(t) and the converters open and write
+// E(t + 1): so E and A need one stage each, which with two of B' and F is all 160 KB of a CU at three parties.
+// Nothing is masked at ragged edges: loads that would leave the matrix are redirected inside it, and what they bring
+// only meets zero-padded rows of the right fragments (k >= K) or lands in output rows that are never stored (row >= M).
 // A launch has at most one workgroup per CU (more would only queue: a workgroup takes a whole CU); each walks
-// its share of the (row block, column tile) items, and g above counts the k-tiles of all its items in one
-// sequence: the producer runs ahead across item boundaries, so that the first tiles of the next item arrive
-// and its E(0) is opened while the consumers recombine and store the current one.  Two more barriers per item
-// frame the consumers' conversion of the item's first A_p tile.
+// its share of the (row block, column tile) items, and t above counts the k-tiles of all its items in one
+// sequence (an odd KT padded by a tile without products, so that a tile's parity tells its registers and stage): loads and conversions
+// run ahead across item boundaries, under the recombination and the stores of the item before.
+//
+// Measured against one wave per party, which converted its A_p between its MFMAs and read right fragments from L2 into registers half a step
+// ahead, and a producer wave for E (whole calls, the pack included): 3 parties 12262 x 59 x 125 59.0 -> 41.3 us, 20000 x 50 x 125 77.9 ->
+// 58.3, 64 entries of 128 x 128 x 64 (keys transposed) 38.1 -> 32.1, of 128 x 64 x 128 34.2 -> 30.8; 2 parties 20 entries of 100^3 25.5 ->
+// 20.8, 131072 x 64 x 576 847 -> 792.  3 parties 131072 x 64 x 576 stay at 1120: its 3.6 GB take 770 us with nothing multiplied, its products 700 with
+// nothing loaded, and together they bring the clock down to 1.2 to 1.65 GHz.  With shares one k-tile ahead (40 registers fewer) the first
+// two take 44.8 and 62.1 us.
 // Workgroups of a row-kernel launch: (row blocks over all batch entries, rounded up to a multiple of 8) x column tiles.
 __host__ __device__ inline long rows_grid(int batch, int M, int tilesN)
 {
@@ -411,410 +417,399 @@ struct RowGemmArgs {
     int batch, M, N, K, KT, tilesN;
 };
 
-// Raw tile in LDS: 32 rows of 256 bytes = 16 pieces of 16 bytes (piece 8 h + q = the q-th pair of k of half h);
-// piece p of row r sits at position p ^ (r & 15) of its row, so that the 16 lanes that read the same piece of
-// 16 consecutive rows hit 16 different 16-byte bank groups of the 256 bytes the LDS serves per cycle (with the
-// swizzle over 8 positions only, rows r and r + 8 collided: a two-way conflict on every read).  In group
-// terms: the row's two 128-byte halves are swapped when bit 3 of r is set, and piece q sits at position
-// q ^ (r & 7) of its half.  A direct-to-LDS load fills 1 KiB = 4 rows x 256 bytes with whole lines of memory.
-constexpr int kRawTile = 32 * 32 * 8;
-constexpr int kRawSlot = 3 * 2 * kRawTile;               // X_j then A_j for up to three parties
-constexpr int kRawSlots = 3;                             // raw k-tiles in LDS: one in use, two in flight
-constexpr int kRowLds = kRawSlots * kRawSlot + 2 * 8 * kFrag;    // + two stages of E fragments: all 160 KB of the CU
-
-// 16 direct-to-LDS loads: the 8 chunks of X_j's and A_j's raw tile.  m0 (LDS base of each load) is put
-// back afterwards; the scalar add that sets it clobbers scc.
-__device__ inline void load_raw_pair(const char *xs, const char *as, u32 lds_dst, const u32 (&voff)[8])
-{
-    u32 saved_m0;
-    asm volatile(
-        "s_mov_b32 %0, m0\n\t"
-        "s_add_u32 m0, %3, 0x0000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %1\n\t"
-        "s_add_u32 m0, %3, 0x2000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %2\n\t"
-        "s_add_u32 m0, %3, 0x0400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %1\n\t"
-        "s_add_u32 m0, %3, 0x2400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %2\n\t"
-        "s_add_u32 m0, %3, 0x0800\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %1\n\t"
-        "s_add_u32 m0, %3, 0x2800\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %2\n\t"
-        "s_add_u32 m0, %3, 0x0c00\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, %1\n\t"
-        "s_add_u32 m0, %3, 0x2c00\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, %2\n\t"
-        "s_add_u32 m0, %3, 0x1000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %8, %1\n\t"
-        "s_add_u32 m0, %3, 0x3000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %8, %2\n\t"
-        "s_add_u32 m0, %3, 0x1400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %9, %1\n\t"
-        "s_add_u32 m0, %3, 0x3400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %9, %2\n\t"
-        "s_add_u32 m0, %3, 0x1800\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %10, %1\n\t"
-        "s_add_u32 m0, %3, 0x3800\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %10, %2\n\t"
-        "s_add_u32 m0, %3, 0x1c00\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %11, %1\n\t"
-        "s_add_u32 m0, %3, 0x3c00\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %11, %2\n\t"
-        "s_mov_b32 m0, %0"
-        : "=&s"(saved_m0)
-        : "s"(xs), "s"(as), "s"(lds_dst), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "v"(voff[4]),
-          "v"(voff[5]), "v"(voff[6]), "v"(voff[7])
-        : "memory", "scc");
-}
-static_assert(kRawTile == 0x2000, "load_raw_pair hard-codes the raw tile size");
-
 typedef __attribute__((address_space(3))) char lds_char;
-typedef __attribute__((address_space(3))) const u64x2 lds_u64x2;
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
+typedef __attribute__((address_space(3))) u32 lds_u32;
+typedef __attribute__((address_space(3))) u64 lds_u64;
 
-template <int NP>
-__device__ __forceinline__ void limb_gemm_rows_body(const RowGemmArgs &g, unsigned first_item, unsigned item_stride)
+constexpr int kRowThreads = 512;
+template <int NP> struct RowLds {
+    static constexpr int unit = 8 * kFrag;                           // the eight digits of 32 rows (columns) and 32 k
+    static constexpr int e = 0, a = unit;                            // E; A_p
+    static constexpr int b = a + NP * unit, b_stage = 2 * NP * unit; // B_p', two column blocks each, two stages
+    static constexpr int f = b + 2 * b_stage, f_stage = 2 * unit;    // F
+    static constexpr int halved = NP == 3 ? 2 : 2 * NP;              // units in two parts: 8 KB of partial sums each,
+    static constexpr int sums = NP == 3 ? a : f + 2 * f_stage;       // over A_p where nothing else is left (16 of 24 KB)
+    static constexpr int bytes = NP == 3 ? f + 2 * f_stage : sums + halved * unit;
+};
+static_assert(RowLds<3>::bytes <= 160 * 1024 && RowLds<2>::bytes <= 160 * 1024, "one CU's LDS");
+
+// The balanced digits of four elements, transposed: out[d] = digit d of elements 0 .. 3.
+__device__ inline void digit_quads(const u64 (&v)[4], u32 (&out)[8])
 {
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int lane = threadIdx.x % 64;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    // Workgroup ids are dealt round-robin to the 8 XCDs, and an XCD gets a contiguous eighth of the row blocks (counted over all batch
-    // entries), column tiles fastest: the column tiles of a row block meet in one L2, where the raw tiles come from memory once,
-    // and so do the row blocks of a batch entry, for its right fragments.  (Row blocks dealt one by one: every entry's right fragments
-    // went to up to eight L2s.  64 entries of 3 parties, 128 x 128 x 64: 44.6 us a call, now 40.2; 131072 x 64 x 576, with one right operand: equal.)
-    // A workgroup walks the items first_item, first_item + item_stride, ... (the stride is a multiple of 8, so all
-    // of them belong to one XCD); rows_grid pads the id space to 8 equal shares, and a workgroup that has none leaves at once.
-    const int rblocks = (g.M + 31) / 32;
-    // Item i = column tile (i / 8) % tilesN of row block i / 8 / tilesN of share i % 8 (all counts are below 2^31, which the
-    // host checks).
-    const unsigned rblocks_all = (unsigned)g.batch * (unsigned)rblocks;
-    const unsigned x = first_item % 8;
-    const unsigned share0 = (unsigned)((u64)rblocks_all * x / 8), share1 = (unsigned)((u64)rblocks_all * (x + 1) / 8);
-    auto rblock_of = [&](unsigned item) -> unsigned { return share0 + item / 8 / (unsigned)g.tilesN; };
-    const unsigned limit = (share1 - share0) * 8 * (unsigned)g.tilesN;
-    const int n_items = first_item < limit ? (int)((limit - 1 - first_item) / item_stride) + 1 : 0;
-    if (n_items == 0) return;                            // all four waves together
-    const int KT = g.KT;
-    lds_char *lds3 = (lds_char *)lds;
-    lds_char *e_ring = lds3 + kRawSlots * kRawSlot;
-    // this lane's 16 consecutive k of row lane % 32, half lane / 32, in a raw tile: piece q at raw_lane ^ (16 q)
-    const u32 raw_lane = (2 * (lane % 32) + (lane / 32 ^ ((lane >> 3) & 1))) * 128 + (lane % 8) * 16;
-
-    if (wave == NP) {
-        // ---------------------------------------------------------------- producer
-        // load i, lane p: row 4 i + p / 16; its 128-byte slot (p / 8) % 2 holds the half (p / 8) % 2 ^ bit 3 of
-        // the row, position p % 8 of it the piece (p % 8) ^ (row & 7); the lane fetches that piece of the row's 256 bytes
-        const size_t row_pitch = (size_t)g.K * 8;
-        const bool k_edge = KT * 32 > g.K;               // the last k-tile is ragged
-        u32 off[8];                                      // per-lane byte offsets from the tile's first element
-        u32 k_ok = 0;                                    // bit i: load i of this lane stays inside K in the last k-tile
+    u64 s[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = 4 * i + lane / 16, half = ((lane / 8) % 2) ^ ((row >> 3) & 1), piece = (lane % 8) ^ (row & 7);
-            off[i] = (u32)(row * row_pitch) + half * 128 + piece * 16;            // K <= 16352: far below 2^32
-            if ((KT - 1) * 32 + 16 * half + 2 * piece < g.K) k_ok |= 1u << i;     // K is even
-        }
-        const size_t party_stride = (size_t)g.batch * g.M * row_pitch;
-        const u32 raw0 = (u32)(uintptr_t)lds3;
-        // The k-tiles of all items form one sequence t = 0, 1, ..: tile t lives in raw slot t % 3, E(t) in fragment
-        // stage t % 2, and the producer runs up to three tiles ahead of the consumers across item boundaries, so
-        // the first tiles of the next item arrive, and its E(0) is opened, while the consumers finish this one.
-        const int total = n_items * KT;
-        unsigned is_item = first_item;                   // issue cursor: item, k-tile within it, raw slot
-        int is_k = 0;
-        u32 is_slot = 0;
-        size_t is_tile0 = 0;
-        int is_row0 = 0;
-        auto set_issue_item = [&]() {
-            const unsigned rblock = rblock_of(is_item);
-            is_row0 = (int)(rblock % (unsigned)rblocks) * 32;
-            is_tile0 = ((size_t)(rblock / (unsigned)rblocks) * g.M + (size_t)is_row0) * row_pitch;      // party 0, k-tile 0
-        };
-        set_issue_item();
-        auto issue = [&]() {                             // all parties' tiles of the cursor's k-tile -> its raw slot
-            const u32 dst = raw0 + is_slot * kRawSlot;
-            const bool last = k_edge && is_k + 1 == KT;
-            u32 voff[8];
+    for (int i = 0; i < 4; ++i) s[i] = to_digits<u64>(v[i]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bool ok = is_row0 + 4 * i + lane / 16 < g.M && (!last || ((k_ok >> i) & 1));
-                voff[i] = ok ? off[i] : 0;
-            }
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const size_t o = is_tile0 + j * party_stride + (size_t)is_k * 256;
-                load_raw_pair((const char *)g.X + o, (const char *)g.A + o, dst + j * (2 * kRawTile), voff);
-            }
-            is_slot = is_slot == kRawSlots - 1 ? 0 : is_slot + 1;
-            if (++is_k == KT) {                          // on to the next item (past the last one nothing is issued)
-                is_k = 0;
-                is_item += item_stride;
-                set_issue_item();
-            }
-        };
-        u32 op_slot = 0, op_stage = 0;                   // open cursor
-        auto open_tile = [&]() {                         // E of the cursor's tile from its raw slot -> its fragment stage
-            lds_char *slot = lds3 + op_slot * kRawSlot;
-            u64x2 opened[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) opened[q] = (u64x2)(0);
-#pragma unroll
-            for (int j = 0; j < NP; ++j)
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const u64x2 xv = *(lds_u64x2 *)(slot + j * (2 * kRawTile) + (raw_lane ^ (16 * q)));
-                    const u64x2 av = *(lds_u64x2 *)(slot + j * (2 * kRawTile) + kRawTile + (raw_lane ^ (16 * q)));
-                    opened[q] += xv - av;
-                }
-            u64 w[16];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                w[2 * q] = to_digits<u64>(opened[q].x);
-                w[2 * q + 1] = to_digits<u64>(opened[q].y);
-            }
-            store_digit_rows<u64>(w, lds + kRawSlots * kRawSlot + op_stage * (8 * kFrag) + lane * 16);
-            op_slot = op_slot == kRawSlots - 1 ? 0 : op_slot + 1;
-            op_stage ^= 1;
-        };
-        // Two k-tiles are in flight while one is in use.  Loads return in order, so waiting until at most one
-        // k-tile's loads (16 NP) are outstanding means that everything older has landed; before a k-tile is
-        // issued the count is brought down to 15, which keeps it within the wave's 6-bit counter.
-        auto issue_ahead = [&](int t) {                  // issue tile t (if any); on return every older one has landed
-            if (t < total) {
-                wait_loads<15>();
-                issue();
-                wait_loads<16 * NP>();
-            } else {
-                wait_loads<0>();
-            }
-        };
-        issue();
-        wait_loads<0>();
-        if (total > 1) issue();
-        open_tile();
-        issue_ahead(2);
-        wait_lds();
-        int t = 0;
-        for (int item = 0; item < n_items; ++item) {
-            // before these two: raw tiles t and t + 1 and E(t) are in LDS (from the start-up above or from the
-            // last iteration of the item before); between them the consumers take A_p(t) out of its raw slot
-            workgroup_barrier();
-            workgroup_barrier();
-            for (int kt = 0; kt < KT; ++kt, ++t) {       // the barrier that ends iteration t: raw tile t + 2 and E(t + 1) are in LDS
-                if (t + 1 < total) open_tile();
-                issue_ahead(t + 3);                      // into the slot of tile t, which nobody reads any more
-                wait_lds();
-                workgroup_barrier();
-            }
-        }
-        return;
+    for (int word = 0; word < 2; ++word) {
+        const u32 w0 = (u32)(s[0] >> (32 * word)), w1 = (u32)(s[1] >> (32 * word));
+        const u32 w2 = (u32)(s[2] >> (32 * word)), w3 = (u32)(s[3] >> (32 * word));
+        const u32 t0 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), t1 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
+        const u32 t2 = __builtin_amdgcn_perm(w3, w2, 0x05010400u), t3 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+        out[4 * word + 0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+        out[4 * word + 1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+        out[4 * word + 2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+        out[4 * word + 3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
     }
+}
 
-    // -------------------------------------------------------------------- consumer
-    const int party = wave;
+// Part of a unit that a wave multiplies: all diagonals, or those of one of two waves with 18 of the 36 digit pairs each.
+enum RowPart { kWholeUnit, kDiagonals0167, kDiagonals2345, kNoUnit };
+constexpr bool in_part(RowPart part, int d)
+{
+    const bool inner = d >= 2 && d <= 5;
+    return part == kWholeUnit || (part == kDiagonals2345 && inner) || (part == kDiagonals0167 && !inner);
+}
+
+// One wave of the row kernel.  unit = 2 party + column half; VEC: rows of X and A are 16-byte aligned (even K).
+template <int NP, bool VEC, bool CONVERTS, RowPart PART>
+__device__ __forceinline__ void rows_wave(const RowGemmArgs &g, unsigned first_item, unsigned item_stride, int n_items, unsigned share0,
+                                          int wave, int unit, int sums_slot, lds_char *lds)
+{
+    using L = RowLds<NP>;
+    const int lane = threadIdx.x % 64;
     const u32 lane16 = lane * 16;
-    // Right fragments are read with buffer loads: one descriptor per operand (uniform, on the scalar unit),
-    // the lane's 16 bytes as the only vector offset, the k-tile and column block in a scalar offset, the
-    // digit as the immediate -- so the 32 loads of a k-tile need no per-lane address arithmetic.
-    const u32 cb_stride = (u32)KT * (8 * kFrag);         // from column block 0 to column block 1 (< 2^22)
-    lds_char *a_raw = lds3 + party * (2 * kRawTile) + kRawTile;      // raw A_p in raw slot 0
-
-    v16i acc[2][8];
-    // fragment registers: [0..15] right (column block q / 8, digit q % 8), [16..23] left (digit q - 16);
-    // buffer 0 serves the (E, B_p') half step, buffer 1 the (A_p, F) half step
-    v4i fr[2][24];
-    auto right_fragment = [&](int q, __amdgpu_buffer_rsrc_t rsrc, u32 koff) -> v4i {
-        const u32 soff = koff + (q / 8) * cb_stride + (q % 8 >= 4 ? 4 * kFrag : 0);
-        return (v4i)__builtin_amdgcn_raw_buffer_load_b128(rsrc, lane16 + (q % 4) * kFrag, soff, 0);
+    const int KT = g.KT, KT2 = (KT + 1) & ~1, total = n_items * KT2;
+    const unsigned rblocks = (unsigned)((g.M + 31) / 32);
+    const int party = unit / 2, half = unit % 2;
+    struct Place { int b, rb, tn; };
+    auto place_of = [&](unsigned item) {
+        const unsigned q = item / 8, rblock = share0 + q / (unsigned)g.tilesN;
+        return Place{(int)(rblock / rblocks), (int)(rblock % rblocks), (int)(q % (unsigned)g.tilesN)};
     };
-    // A_p from the raw tile to the eight left fragments of buffer 1, a quarter (elements 4 c .. 4 c + 3 of this
-    // lane's 16 = pieces 2 c, 2 c + 1 -> component c of every fragment) at a time, in steps small enough to
-    // sit between two MFMAs without holding the matrix pipe up:
-    //   step 0  read the two pieces from LDS          step 1, 2  balanced digits of elements 0, 1 / 2, 3
-    //   step 3..6  the 4 x 4 byte transposes of the low / high words: first level, second level
-    u64x2 piece[2];
-    u64 dig[4];
-    u32 half_t[4];
-    auto convert_step = [&](int c, int step, lds_char *tile) {
-        if (step == 0) {
-            piece[0] = *(lds_u64x2 *)(tile + (raw_lane ^ (32 * c)));
-            piece[1] = *(lds_u64x2 *)(tile + (raw_lane ^ (32 * c + 16)));
-        } else if (step == 1) {
-            dig[0] = to_digits<u64>(piece[0].x);
-            dig[1] = to_digits<u64>(piece[0].y);
-        } else if (step == 2) {
-            dig[2] = to_digits<u64>(piece[1].x);
-            dig[3] = to_digits<u64>(piece[1].y);
-        } else {
-            const int word = (step - 3) / 2;
-            if ((step - 3) % 2 == 0) {
-                const u32 a0 = (u32)(dig[0] >> (32 * word)), a1 = (u32)(dig[1] >> (32 * word));
-                const u32 a2 = (u32)(dig[2] >> (32 * word)), a3 = (u32)(dig[3] >> (32 * word));
-                half_t[0] = __builtin_amdgcn_perm(a1, a0, 0x05010400u);
-                half_t[1] = __builtin_amdgcn_perm(a1, a0, 0x07030602u);
-                half_t[2] = __builtin_amdgcn_perm(a3, a2, 0x05010400u);
-                half_t[3] = __builtin_amdgcn_perm(a3, a2, 0x07030602u);
-            } else {
-                fr[1][16 + 4 * word + 0][c] = (int)__builtin_amdgcn_perm(half_t[2], half_t[0], 0x05040100u);
-                fr[1][16 + 4 * word + 1][c] = (int)__builtin_amdgcn_perm(half_t[2], half_t[0], 0x07060302u);
-                fr[1][16 + 4 * word + 2][c] = (int)__builtin_amdgcn_perm(half_t[3], half_t[1], 0x05040100u);
-                fr[1][16 + 4 * word + 3][c] = (int)__builtin_amdgcn_perm(half_t[3], half_t[1], 0x07060302u);
-            }
+    const unsigned last_item = first_item + (unsigned)(n_items - 1) * item_stride;
+
+    // ---- loaders: F runs one k-tile ahead of the products, B' two.  (For the tile that pads an odd KT the one before it is loaded again.)
+    const size_t cb_stride = (size_t)KT * L::unit;                   // from a column block to the next
+    const size_t slot_stride = (size_t)g.batch * g.tilesN * 2 * cb_stride;
+    struct Cursor { unsigned item; int kt; const char *at; u32 stage; };
+    const u32 lds0 = (u32)(uintptr_t)lds + wave * kFrag;
+    auto cursor_base = [&](unsigned item) -> const char * {
+        const Place p = place_of(item);
+        return g.packB + ((size_t)p.b * g.tilesN + p.tn) * 2 * cb_stride + wave * kFrag;
+    };
+    auto advance = [&](Cursor &c) {
+        c.stage ^= 1;
+        ++c.kt;
+        if (c.kt < KT) c.at += L::unit;
+        if (c.kt == KT2) {
+            c.kt = 0;
+            c.item += item_stride;                                   // past the last item nothing is loaded
+            c.at = cursor_base(c.item);
         }
     };
-    // One half step of 72 MFMAs on buffer CUR; between them the other buffer is filled for the half step
-    // that follows.  After the even MFMAs 0, 2, .. 30: its 16 right fragments (memory).  Its left fragments:
-    // E from the fragment ring (8 LDS reads after the even MFMAs 32 .. 46, CUR = 1), or A_p converted from the
-    // raw tile (CUR = 0): conversion step m = 0 .. 25 after the odd MFMA 2 m + 1, quarter c reading at
-    // m = 6 c - 1 (0 for c = 0) and working at m = 6 c + 2 .. 6 c + 7.  sched_barrier pins the interleave.
-    auto half_step = [&](auto cur_c, auto fill_c, __amdgpu_buffer_rsrc_t rsrc, u32 koff, lds_char *left) {
-        constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1;
-        constexpr bool FILL = decltype(fill_c)::value;
-        int slot = 0;
+    auto load_blocks = [&](const char *src, u32 dst) {               // this wave's quarter of two column blocks
 #pragma unroll
-        for (int da = 0; da < 8; ++da)
-#pragma unroll
-            for (int db = 0; db + da < 8; ++db)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    acc[j][da + db] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[cur][16 + da], fr[cur][8 * j + db],
-                                                                            acc[j][da + db], 0, 0, 0);
-                    if (FILL && slot % 2 == 0) {
-                        const int item = slot / 2;
-                        if (item < 16) {
-                            fr[nxt][item] = right_fragment(item, rsrc, koff);
-                            __builtin_amdgcn_sched_barrier(0);
-                        } else if (cur == 1 && item < 24) {
-                            fr[0][item] = *(lds_v4i *)(left + lane16 + (item - 16) * kFrag);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    }
-                    if (FILL && cur == 0 && slot % 2 == 1) {
-                        const int m = slot / 2;
-                        if (m == 0) convert_step(0, 0, left);
-                        if (m >= 5 && m <= 17 && (m + 1) % 6 == 0) convert_step((m + 1) / 6, 0, left);
-                        if (m >= 2 && m <= 25) convert_step((m - 2) / 6, 1 + (m - 2) % 6, left);
-                        if (m <= 25) __builtin_amdgcn_sched_barrier(0);
-                    }
-                    ++slot;
-                }
+        for (int q = 0; q < 4; ++q) load_fragment_to_lds(src + (q / 2) * cb_stride + (q % 2) * (4 * kFrag), dst + (q / 2) * L::unit + (q % 2) * (4 * kFrag), lane16);
     };
-    using Y = std::true_type;
-    using F = std::false_type;
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
+    auto load_f = [&](Cursor &c) {
+        load_blocks(c.at, lds0 + L::f + c.stage * L::f_stage);
+        advance(c);
+    };
+    auto load_b = [&](Cursor &c) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) load_blocks(c.at + (size_t)(1 + p) * slot_stride, lds0 + L::b + c.stage * L::b_stage + p * (2 * L::unit));
+        advance(c);
+    };
+    // After the loads that a half step waits for, at most one load_f and one load_b were issued; loads return in order.
+    constexpr int kInFlight = 4 + 4 * NP;
 
-    u32 par = 0;                                         // t % 2 and t % 3 of the current tile of the workgroup's sequence
-    u32 slot = 0;
+    // ---- converters: lane (row 8 (wave % 4) + lane / 8, k 4 (lane % 8) ..) of the 32 x 32 tile
+    const int c_row = 8 * (wave % 4) + lane / 8, c_k = 4 * (lane % 8);
+    const size_t pitch = (size_t)g.K * 8, party_stride = (size_t)g.batch * g.M * pitch;
+    struct Shares { u64 e[NP][4]; } x[2], a[2];                      // of even and of odd tiles
+    struct Rows { unsigned item; int kt; size_t tile; u32 off; };
+    auto set_rows = [&](Rows &c) {
+        const Place p = place_of(min(c.item, last_item));
+        c.tile = ((size_t)p.b * g.M + (size_t)p.rb * 32) * pitch;    // of party 0, the row block's first row and k = 0
+        c.off = (u32)min(c_row, g.M - 1 - p.rb * 32) * (u32)pitch + c_k * 8;      // K < 2^15: below 2^24
+    };
+    // Nothing is fetched for the tile that pads an odd KT nor past the last item: the loads are issued all the same, of no bytes, so that
+    // the compiler can tell how many are in flight behind the ones that it waits for.
+    auto load_shares = [&](const u64 *matrix, Rows &c, Shares &v) {
+        const u32 size = c.kt < KT && c.item <= last_item ? 0x7fffffffu : 0u;
+        u32 off[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) off[i] = c.kt * 32 + c_k + i < g.K ? c.off + 8 * i : 0;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((char *)matrix + (c.tile + j * party_stride), 0, size, 0x00020000);
+            if constexpr (VEC) {
+#pragma unroll
+                for (int i = 0; i < 4; i += 2) {
+                    const v4i two = (v4i)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], c.kt * 256, 0);
+                    v.e[j][i] = (u64)(u32)two.y << 32 | (u32)two.x;
+                    v.e[j][i + 1] = (u64)(u32)two.w << 32 | (u32)two.z;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const auto one = __builtin_amdgcn_raw_buffer_load_b64(rsrc, off[i], c.kt * 256, 0);
+                    v.e[j][i] = (u64)(u32)one[1] << 32 | (u32)one[0];
+                }
+            }
+        }
+        if (++c.kt == KT2) {
+            c.kt = 0;
+            c.item += item_stride;
+            set_rows(c);
+        }
+    };
+    lds_char *quad = lds + (c_row + 32 * (c_k / 16)) * 16 + c_k % 16;
+    auto write_digits = [&](const u64 (&v)[4], int at) {
+        u32 d[8];
+        digit_quads(v, d);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *(lds_u32 *)(quad + at + i * kFrag) = d[i];
+    };
+    auto open_left = [&](const Shares &xs, const Shares &as) {
+        u64 e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            e[i] = xs.e[0][i] - as.e[0][i];
+#pragma unroll
+            for (int j = 1; j < NP; ++j) e[i] += xs.e[j][i] - as.e[j][i];
+        }
+        write_digits(e, L::e);
+    };
+
+    // ---- products
+    v16i acc[8];
+    auto multiply = [&](int left_at, int right_at) {
+        if constexpr (PART != kNoUnit) {
+            u32 l16 = lane16;                                        // the addresses made anew: kept, they take six registers
+            asm volatile("" : "+v"(l16));
+            lds_char *left = lds + left_at + l16, *right = lds + right_at + l16;
+            constexpr int digits = PART == kDiagonals2345 ? 6 : 8;
+            if constexpr (PART == kWholeUnit) {
+                v4i l[digits], r[digits];
+#pragma unroll
+                for (int m = 0; m < digits; ++m) {
+                    r[m] = *(lds_v4i *)(right + m * kFrag);
+                    l[m] = *(lds_v4i *)(left + m * kFrag);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                // in the order in which the fragments arrive: after 2 m of them m^2 pairs are there
+#pragma unroll
+                for (int m = 0; m < digits; ++m)
+#pragma unroll
+                    for (int o = 0; o < 2 * m + 1; ++o) {
+                        const int da = o <= m ? m : o - m - 1, db = o <= m ? o : m;
+                        if (da + db < 8) acc[da + db] = __builtin_amdgcn_mfma_i32_32x32x32_i8(l[da], r[db], acc[da + db], 0, 0, 0);
+                    }
+            } else {                                                 // the raw shares leave room for the right fragments and two left ones
+                v4i r[digits], l[2];
+                l[0] = *(lds_v4i *)left;
+#pragma unroll
+                for (int m = 0; m < digits; ++m) r[m] = *(lds_v4i *)(right + m * kFrag);
+#pragma unroll
+                for (int da = 0; da < digits; ++da) {
+                    if (da + 1 < digits) l[(da + 1) % 2] = *(lds_v4i *)(left + (da + 1) * kFrag);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int db = 0; db < digits; ++db)
+                        if (da + db < 8 && in_part(PART, da + db))
+                            acc[da + db] = __builtin_amdgcn_mfma_i32_32x32x32_i8(l[da % 2], r[db], acc[da + db], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);                       // products are not moved behind the half step's barrier
+        }
+    };
+    const int e_at = L::e, a_at = L::a + party * L::unit, b_at = L::b + unit * L::unit, f_at = L::f + half * L::unit;
+
+    // ---- start: B'(0), F(0), B'(1); E(0)
+    Cursor cf{first_item, 0, nullptr, 0}, cb{first_item, 0, nullptr, 0};
+    Rows cx{first_item, 0, 0, 0}, ca{first_item, 0, 0, 0};
+    if constexpr (!CONVERTS) {
+        cf.at = cb.at = cursor_base(first_item);
+        load_b(cb);
+        load_f(cf);
+        load_b(cb);
+        wait_loads<kInFlight>();
+    } else {
+        set_rows(cx);
+        set_rows(ca);
+        load_shares(g.X, cx, x[0]);
+        load_shares(g.A, ca, a[0]);
+        load_shares(g.X, cx, x[1]);
+        load_shares(g.A, ca, a[1]);
+        open_left(x[0], a[0]);
+        load_shares(g.X, cx, x[0]);
+    }
+    wait_lds();
+    workgroup_barrier();
+
+    int t = 0;
     unsigned item_id = first_item;
     for (int item = 0; item < n_items; ++item, item_id += item_stride) {
-    const int tn = (int)(item_id / 8 % (unsigned)g.tilesN);
-    const unsigned rblock = rblock_of(item_id);
-    const int rb = (int)(rblock % (unsigned)rblocks), b = (int)(rblock / (unsigned)rblocks);
-    const char *f_base = g.packB + ((size_t)b * g.tilesN + tn) * 2 * cb_stride;                              // F
-    const char *b_base = g.packB + (((size_t)(1 + party) * g.batch + b) * g.tilesN + tn) * 2 * cb_stride;    // B_p'
-    const __amdgpu_buffer_rsrc_t f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)f_base, 0, 2 * cb_stride, 0x00020000);
-    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)b_base, 0, 2 * cb_stride, 0x00020000);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int d = 0; d < 8; ++d) acc[j][d] = (v16i)(0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) fr[1][q] = right_fragment(q, f_rsrc, 0);   // in flight while the producer starts up
-    workgroup_barrier();                                 // raw tiles t and t + 1 and E(t) are in LDS
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int step = 0; step < 7; ++step) convert_step(c, step, a_raw + slot * kRawSlot);
-    wait_lds();
-    workgroup_barrier();                                 // the raw slot of tile t may be refilled
-    u32 koff = 0;                                        // byte offset of the current k-tile in a fragment stream
-    for (int kt = 0; kt + 1 < KT; ++kt) {                // the last k-tile is peeled: no branch around MFMAs
-        half_step(B1(), Y(), b_rsrc, koff, e_ring + par * (8 * kFrag));                // A_p . F; fills (E, B_p') of kt
-        koff += 8 * kFrag;
-        par ^= 1;
-        slot = slot == kRawSlots - 1 ? 0 : slot + 1;
-        half_step(B0(), Y(), f_rsrc, koff, a_raw + slot * kRawSlot);                    // E . B_p'; fills (A_p, F) of kt + 1
-        wait_lds();
-        workgroup_barrier();
-    }
-    koff = (u32)(KT - 1) * (8 * kFrag);                  // restated from the argument, so that it stays scalar
-    half_step(B1(), Y(), b_rsrc, koff, e_ring + par * (8 * kFrag));
-
-    // C_p is fetched under the last half step (the fragment buffer that half step would have filled is free):
-    // the epilogue then starts with its operands at hand.  Rows and columns beyond the matrix are redirected
-    // to its last row / column; what they bring is never stored.  C may be Z itself: every element is read
-    // and written by the same lane of the same workgroup.
-    const size_t zmat = (size_t)g.M * g.N;
-    const u64 *Cm = g.C + ((size_t)party * g.batch + b) * zmat;
-    u64 *Zm = g.Z + ((size_t)party * g.batch + b) * zmat;
-    const bool interior = (rb + 1) * 32 <= g.M && (tn + 1) * 64 <= g.N;
-    const int row0 = rb * 32 + 4 * (lane / 32);
-    auto row_of = [&](int r) { return row0 + 8 * (r / 4) + r % 4; };
-    u64 cv[2][16];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = min(tn * 64 + j * 32 + lane % 32, g.N - 1);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) cv[j][r] = Cm[(size_t)min(row_of(r), g.M - 1) * g.N + col];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    half_step(B0(), F(), f_rsrc, koff, a_raw);
-    workgroup_barrier();
-    par ^= 1;                                            // past the item's last tile
-    slot = slot == kRawSlots - 1 ? 0 : slot + 1;
-
-    // recombine the diagonals, add C_p, store (same structure as the tile kernel's epilogue)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = tn * 64 + j * 32 + lane % 32;
+        const Place p = place_of(item_id);
+        const size_t zmat = (size_t)g.M * g.N;
+        const size_t block0 = ((size_t)party * g.batch + p.b) * zmat + (size_t)p.rb * 32 * g.N;
+        const char *Cm = (const char *)(g.C + block0);               // the item's rows; 32 of them are below 4 GiB (N <= 2^24)
+        char *Zm = (char *)(g.Z + block0);
+        const bool interior = (p.rb + 1) * 32 <= g.M && (p.tn + 1) * 64 <= g.N;
+        const int rows = g.M - p.rb * 32, col0 = p.tn * 64 + half * 32;
+        // Where the lane's outputs are, from a number of columns and a lane number that the compiler cannot tell to be the same twice: kept
+        // between C and Z, and from item to item, the offsets would take 17 registers that are not there.
+        struct Outputs {
+            int row0, col;
+            u32 cols;
+            __device__ int row(int r) const { return row0 + 8 * (r / 4) + r % 4; }
+            __device__ u32 at(int row, int column) const { return ((u32)row * cols + (u32)column) * 8u; }
+        };
+        auto outputs = [&]() {
+            int c = g.N, l;
+            asm volatile("" : "+s"(c));
+            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+            return Outputs{4 * (l / 32), col0 + l % 32, (u32)c};
+        };
         u64 v[16];
-        __builtin_amdgcn_sched_barrier(0);
+        auto load_c = [&]() {
+            const Outputs o = outputs();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = cv[j][r];
+            for (int r = 0; r < 16; ++r) v[r] = *(const u64 *)(Cm + o.at(min(o.row(r), rows - 1), min(o.col, g.N - 1)));
+        };
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            v[r] += recombine_diagonals(acc[j][0][r], acc[j][1][r], acc[j][2][r], acc[j][3][r], acc[j][4][r], acc[j][5][r],
-                                        acc[j][6][r], acc[j][7][r]);
-        if (interior) {
+        for (int d = 0; d < 8; ++d) acc[d] = (v16i)(0);
+        // one k-tile; ODD: its parity in the sequence, and so its LDS stage and its registers
+        auto tile = [&](auto odd_c, int kt) {
+            constexpr int ODD = decltype(odd_c)::value;
+            const bool real = !ODD || kt < KT;
+            // E . B_p'
+            if constexpr (CONVERTS) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) Zm[(size_t)row_of(r) * g.N + col] = v[r];
-        } else {
+                for (int j = 0; j < NP; ++j) write_digits(a[ODD].e[j], L::a + j * L::unit);
+                load_shares(g.A, ca, a[ODD]);                        // of tile t + 2
+            } else {
+                if (t + 1 < total) load_f(cf);
+            }
+            if (real) multiply(e_at, b_at + ODD * L::b_stage);
+            if constexpr (!CONVERTS) {
+                if (t + 2 < total) wait_loads<kInFlight>(); else wait_loads<0>();        // F(t)
+            }
+            wait_lds();
+            workgroup_barrier();
+            // A_p . F
+            if constexpr (CONVERTS) {
+                open_left(x[ODD ^ 1], a[ODD ^ 1]);
+                load_shares(g.X, cx, x[ODD ^ 1]);                    // of tile t + 3
+            } else {
+                if (t + 2 < total) load_b(cb);
+            }
+            // C_p is fetched under the item's last products.  Rows and columns beyond the matrix are redirected to its last row /
+            // column; what they bring is never stored.  C may be Z itself: every element is read and written by the same lane.
+            if constexpr (ODD && PART == kWholeUnit) {
+                if (kt + 1 == KT2) load_c();
+            }
+            if (real) multiply(a_at, f_at + ODD * L::f_stage);
+            if constexpr (!CONVERTS) {
+                if (t + 2 < total) wait_loads<kInFlight>(); else wait_loads<0>();        // B'(t + 1)
+            }
+            wait_lds();
+            workgroup_barrier();
+            ++t;
+        };
+        for (int kt = 0; kt < KT2; kt += 2) {
+            tile(std::integral_constant<int, 0>(), kt);
+            tile(std::integral_constant<int, 1>(), kt + 1);
+        }
+        // the two parts of a halved unit meet in LDS
+        lds_char *sums = lds + L::sums + sums_slot * L::unit + lane * 8;
+        u64 w[16];
+        if constexpr (PART == kDiagonals2345) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (row_of(r) < g.M && col < g.N) Zm[(size_t)row_of(r) * g.N + col] = v[r];
+            for (int r = 0; r < 16; ++r) *(lds_u64 *)(sums + r * 512) = recombine_diagonals(0, 0, acc[2][r], acc[3][r], acc[4][r], acc[5][r], 0, 0);
+            wait_lds();
+        }
+        workgroup_barrier();
+        if constexpr (PART == kDiagonals0167) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[r] = *(lds_u64 *)(sums + r * 512) + recombine_diagonals(acc[0][r], acc[1][r], 0, 0, 0, 0, acc[6][r], acc[7][r]);
+            wait_lds();
+            __builtin_amdgcn_sched_barrier(0);
+            load_c();                                                // into the accumulators' registers: there are no others
+        }
+        if (NP == 3) workgroup_barrier();                            // the sums lie where A_p goes next
+        if constexpr (PART == kWholeUnit || PART == kDiagonals0167) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (PART == kWholeUnit) v[r] += recombine_diagonals(acc[0][r], acc[1][r], acc[2][r], acc[3][r], acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+                else v[r] += w[r];
+            }
+            const Outputs o = outputs();
+            if (interior) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) *(u64 *)(Zm + o.at(o.row(r), o.col)) = v[r];
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (o.row(r) < rows && o.col < g.N) *(u64 *)(Zm + o.at(o.row(r), o.col)) = v[r];
+            }
         }
     }
-    }                                                    // next item
 }
 
-template <int NP>
-__global__ __launch_bounds__(64 * (NP + 1)) void limb_gemm_rows_kernel(RowGemmArgs g)
+template <int NP, bool VEC>
+__device__ __forceinline__ void limb_gemm_rows_body(const RowGemmArgs &g, unsigned first_item, unsigned item_stride)
 {
-    limb_gemm_rows_body<NP>(g, blockIdx.x, gridDim.x);
+    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+    lds_char *lds = (lds_char *)lds_raw;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // Workgroup ids are dealt round-robin to the 8 XCDs, and an XCD gets a contiguous eighth of the row blocks (counted over all batch
+    // entries), column tiles fastest: the column tiles of a row block meet in one L2, where the raw shares come from memory once,
+    // and so do the row blocks of a batch entry, for its right fragments.  (Row blocks dealt one by one: every entry's right fragments
+    // went to up to eight L2s.  64 entries of 3 parties, 128 x 128 x 64: 44.6 us a call instead of 40.2.)
+    // A workgroup walks the items first_item, first_item + item_stride, ... (the stride is a multiple of 8, so all
+    // of them belong to one XCD); rows_grid pads the id space to 8 equal shares, and a workgroup that has none leaves at once.
+    // Item i = column tile (i / 8) % tilesN of row block i / 8 / tilesN of share i % 8 (all counts are below 2^31, which the
+    // host checks).
+    const unsigned rblocks_all = (unsigned)g.batch * (unsigned)((g.M + 31) / 32);
+    const unsigned share = first_item % 8;
+    const unsigned share0 = (unsigned)((u64)rblocks_all * share / 8), share1 = (unsigned)((u64)rblocks_all * (share + 1) / 8);
+    const unsigned limit = (share1 - share0) * 8 * (unsigned)g.tilesN;
+    const int n_items = first_item < limit ? (int)((limit - 1 - first_item) / item_stride) + 1 : 0;
+    if (n_items == 0) return;                            // all waves together
+    auto go = [&](auto converts, auto part, int unit, int sums_slot) {
+        rows_wave<NP, VEC, decltype(converts)::value, decltype(part)::value>(g, first_item, item_stride, n_items, share0, wave, unit, sums_slot, lds);
+    };
+    using Loads = std::false_type;
+    using Converts = std::true_type;
+    using Whole = std::integral_constant<RowPart, kWholeUnit>;
+    using PartA = std::integral_constant<RowPart, kDiagonals0167>;
+    using PartB = std::integral_constant<RowPart, kDiagonals2345>;
+    using None = std::integral_constant<RowPart, kNoUnit>;
+    if constexpr (NP == 3) {
+        const int pair = (wave - 4) / 2;
+        if (wave < 4) go(Loads(), Whole(), wave, 0);
+        else if (wave % 2 == 0) go(Converts(), PartA(), 4 + pair, pair);
+        else go(Converts(), PartB(), 4 + pair, pair);
+    } else {
+        const int pair = wave / 2;
+        if (wave < 4) {
+            if (wave % 2 == 0) go(Loads(), PartA(), pair, pair);
+            else go(Loads(), PartB(), pair, pair);
+        } else if (NP == 1) {
+            go(Converts(), None(), 0, 0);
+        } else if (wave % 2 == 0) {
+            go(Converts(), PartA(), pair, pair);
+        } else {
+            go(Converts(), PartB(), pair, pair);
+        }
+    }
+}
+
+template <int NP, bool VEC>
+__global__ __launch_bounds__(kRowThreads) void limb_gemm_rows_kernel(RowGemmArgs g)
+{
+    limb_gemm_rows_body<NP, VEC>(g, blockIdx.x, gridDim.x);
 }
 
 template <int NP>
-__global__ __launch_bounds__(64 * (NP + 1)) void limb_gemm_rows_grouped_kernel(GroupTable<RowGemmArgs> t)
+__global__ __launch_bounds__(kRowThreads) void limb_gemm_rows_grouped_kernel(GroupTable<RowGemmArgs> t)
 {
     const int gi = group_of(t, blockIdx.x);
-    limb_gemm_rows_body<NP>(t.e[gi], blockIdx.x - t.first[gi], 0x7fffffffu);
-}
-
-// Row and tile products of one grouped call together: both kinds take a whole CU per workgroup and seldom fill the chip alone.
-// Six attention products of 3 parties: a launch of 27 us (rows) and one of 12.5 us (tiles) became one.  Fewer groups a
-// launch, so that both tables fit the 4 KB of kernel arguments.  The waves beyond a row workgroup's NP + 1 leave at once
-// (ended waves do not count at barriers).
-constexpr int kGroupsTogether = 16;
-template <class Args> struct SmallGroupTable {
-    int count;
-    unsigned first[kGroupsTogether + 1];
-    Args e[kGroupsTogether];
-};
-template <class Args> __device__ inline int group_of(const SmallGroupTable<Args> &t, unsigned id)
-{
-    int g = 0;
-    for (int i = 1; i < t.count; ++i) g += id >= t.first[i] ? 1 : 0;
-    return g;
-}
-template <int NP>
-__global__ __launch_bounds__(256) void limb_gemm_mixed_grouped_kernel(SmallGroupTable<RowGemmArgs> rows, SmallGroupTable<GemmArgs<u64>> tiles,
-                                                                      unsigned row_blocks)
-{
-    if (blockIdx.x < row_blocks) {
-        if (threadIdx.x >= 64 * (NP + 1)) return;
-        const int gi = group_of(rows, blockIdx.x);
-        limb_gemm_rows_body<NP>(rows.e[gi], blockIdx.x - rows.first[gi], 0x7fffffffu);
-    } else {
-        const unsigned id = blockIdx.x - row_blocks;
-        const int gi = group_of(tiles, id);
-        limb_gemm_body<u64>(tiles.e[gi], id - tiles.first[gi]);
-    }
+    if (t.e[gi].K % 2 == 0) limb_gemm_rows_body<NP, true>(t.e[gi], blockIdx.x - t.first[gi], 0x7fffffffu);
+    else limb_gemm_rows_body<NP, false>(t.e[gi], blockIdx.x - t.first[gi], 0x7fffffffu);
 }
 
 // ------------------------------------------------------------------ host ---
@@ -858,36 +853,39 @@ inline int choose_splits(long tiles, int steps)
     return best;
 }
 
-// Whether the row-streaming kernel takes a product: 64-bit ring, at most three parties (one consumer wave
-// each), even K (16-byte row alignment), an inner dimension one launch may accumulate, and a lower
-// estimated cost than the tile kernel plus its pre-pass over the left operands.  Costs are in k-steps of
-// one CU (about a microsecond), the unit of choose_splits: the row kernel walks 2 KT steps per block of 32
-// rows and column tile; the other path adds the left pack, an HBM stream of (3n + 1) operand-sized matrices
-// at about 5 MB per step-time.  The 5 steps were its launch, when it had one of its own; below kPackStreamingBytes it rides
-// with the right pack now.  They were left as measured then: the row kernel keeps the products it had.  Over 4400 products near the line (1
-// to 3 parties, M 32 to 20000, N 16 to 400, K to 3000) that takes 0.95 % more time than always the faster kernel, 70 of them more than 16 %
-// (3 parties 2019 x 21 x 332 41.3 us by rows, 28.7 by tiles).
-template <class T> inline double rows_kernel_cost(const MatmulArgsT<T> &a, const Plan &p)
+// Times of the row kernel and of the tile kernel in microseconds, with their packs and launches: a row item is 2 KT half steps and
+// its start and end, a tile (or the part of one that a workgroup takes) likewise; operands and outputs are streams, and parts that are added onto
+// Z cost its words twice.  Fits to 40 000 products of 5 us to 1 ms (1 to 3 parties; 300 to 30 000 rows and 8 to 200 columns, batches of 2 to
+// 64 entries with sides of 16 to 512, inner dimensions to 1500, odd ones among them), within 6 and 7.5 % (rms).
+template <class T> inline double rows_us(const MatmulArgsT<T> &a, const Plan &p)
 {
     const int cus = compute_units();
-    return (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8);
+    const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus), n = a.n;
+    const double right_mb = 8e-6 * (3 * n + 1) * a.batch * (double)a.N * a.K, left_mb = 16e-6 * n * a.batch * (double)a.M * a.K;
+    const double out_mb = 16e-6 * n * a.batch * (double)a.M * a.N;
+    return 5.29 + 1.52 * n + rounds * ((0.199 + 0.346 * n) * 2 * p.KT + 1.66 + 0.505 * n) + 0.174 * right_mb + 0.060 * left_mb + 0.104 * out_mb;
 }
-template <class T> inline double tile_kernel_cost(const MatmulArgsT<T> &a, const Plan &p, int sp)
+template <class T> inline double tiles_us(const MatmulArgsT<T> &a, const Plan &p, int sp)
 {
     const int cus = compute_units();
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const double pack_bytes = 8.0 * (3 * a.n + 1) * a.batch * (double)a.M * a.K;
-    return (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.0e6 + 5;
+    const double rounds = (double)((tiles * sp + cus - 1) / cus), words = (double)sizeof(T) * (3 * a.n + 1) * a.batch;
+    const double packed_mb = 1e-6 * words * ((double)a.M + a.N) * a.K, out_mb = 2e-6 * sizeof(T) * a.n * a.batch * (double)a.M * a.N;
+    if (sizeof(T) == 8) return 5.74 + 1.05 * a.n + rounds * (1.24 * 2 * ceil_div(p.KT, sp) + 4.34) + 0.179 * packed_mb + (sp > 1 ? 0.524 : 0.107) * out_mb;
+    // over Z_2^32, a fit to 8000 products: within 9 %
+    return 3.7 + 1.36 * a.n + rounds * (0.716 * 2 * ceil_div(p.KT, sp) + 5.56) + 0.2 * packed_mb + 0.161 * out_mb;
 }
-// What all estimates of a product need: which kernel it takes and how many workgroups would share a tile.
+// Which kernel a product takes, and how many workgroups would share a tile: what all estimates of it need.  The row kernel takes products over
+// Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may accumulate, where it is estimated
+// to be the faster one: that costs 0.4 % against always the faster one (products as above), where a count of k-steps cost 6.2 %.
 struct DigitRoute { bool rows; int splits; };
 template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {
     DigitRoute r{false, choose_splits((long)p.tilesM * p.tilesN * a.n * a.batch, 2 * p.KT)};
     if (!std::is_same<T, u64>::value) return r;
-    if (a.n > 3 || a.K % 2 != 0 || p.KT > Ring<u64>::max_chunk_tiles) return r;
+    if (a.n > 3 || p.KT > Ring<u64>::max_chunk_tiles) return r;
     if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return r;
-    r.rows = rows_kernel_cost<T>(a, p) <= tile_kernel_cost<T>(a, p, r.splits);
+    r.rows = rows_us<T>(a, p) <= tiles_us<T>(a, p, r.splits);
     return r;
 }
 
@@ -896,8 +894,8 @@ template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const 
 // Small products are what it is for; large ones come out up to 40 % too high (the packs overlap their launch).
 template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
 {
-    if (r.rows) return 1.5 * rows_kernel_cost<T>(a, p) + 10;
     const int cus = compute_units();
+    if (r.rows) return 1.5 * (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8) + 10;
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = r.splits;
     const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
@@ -905,22 +903,10 @@ template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Pl
     return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
 }
 
-// The same in detail, for small products: the waves of a pack convert the parties' shares one after another, and the
-// output counts.  A fit to 19 500 products of 5 us to 2 ms near the line between the two kernels, within 8 (9 over Z_2^32) % (rms); since the
-// packs got faster it reads 7 (9) % high.  The choice takes 0.5 (0.7) % more time than always the faster kernel over 3600 (2700) products.
+// The same in detail, for small products.
 template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
 {
-    const int cus = compute_units();
-    const double words = (double)sizeof(T) * (3 * a.n + 1) * a.batch, out_mb = 2e-6 * sizeof(T) * a.n * a.batch * (double)a.M * a.N;
-    if (r.rows) {
-        const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
-        return rounds * (1.228 * 2 * p.KT + 3.96) + words * a.N * a.K / 4.35e6 + 3.8 + 2.03 * a.n + 0.236 * out_mb;
-    }
-    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = r.splits;
-    const double rounds = (double)((tiles * sp + cus - 1) / cus), packed = words * ((double)a.M + a.N) * a.K;
-    return sizeof(T) == 8 ? rounds * (1.107 * 2 * ceil_div(p.KT, sp) + 4.78) + packed / 4.49e6 + 4.1 + 1.76 * a.n + 0.181 * out_mb
-                          : rounds * (0.716 * 2 * ceil_div(p.KT, sp) + 5.56) + packed / 5.0e6 + 3.7 + 1.36 * a.n + 0.161 * out_mb;
+    return r.rows ? rows_us<T>(a, p) : tiles_us<T>(a, p, r.splits);
 }
 
 // The same for the choice between them and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
@@ -930,10 +916,7 @@ inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p, const Digi
 {
     const int cus = compute_units();
     const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
-    if (r.rows) {
-        const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus);
-        return rounds * 1.214 * 2 * p.KT + words * a.N * a.K / 3.85e6 + 3.15 * a.n + 0.331 * out_mb;
-    }
+    if (r.rows) return rows_us(a, p);
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = r.splits;
     const double filled = (double)tiles * sp / cus, rounds = std::ceil(filled);
@@ -955,13 +938,17 @@ inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, 
     const unsigned grid = items > resident && ((long)items / resident + 1) * p.KT < (1L << 30) ? resident : items;
     for_party_count(a.n, [&](auto np) {
         constexpr int NP = decltype(np)::value <= 3 ? decltype(np)::value : 3;   // n <= 3 is checked by the caller
-        static OncePerDevice lds_allowed;
-        auto kernel = limb_gemm_rows_kernel<NP>;
-        st = allow_dynamic_lds((const void *)kernel, kRowLds, lds_allowed);
-        if (st != SPIN_OK) return;
-        KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-        kernel<<<grid, 64 * (NP + 1), kRowLds, s>>>(g);
-        st = check_launch(where_gemm);
+        auto go = [&](auto vec) {
+            static OncePerDevice lds_allowed;
+            auto kernel = limb_gemm_rows_kernel<NP, decltype(vec)::value>;
+            st = allow_dynamic_lds((const void *)kernel, RowLds<NP>::bytes, lds_allowed);
+            if (st != SPIN_OK) return;
+            KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
+            kernel<<<grid, kRowThreads, RowLds<NP>::bytes, s>>>(g);
+            st = check_launch(where_gemm);
+        };
+        if (a.K % 2 == 0) go(std::true_type());
+        else go(std::false_type());
     });
     return st;
 }
@@ -1031,8 +1018,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
 // Every group gets its own fragment stores inside the workspace (the packs of all groups run before their
 // GEMMs), chooses the row-streaming or the tile kernel as a single product would, and the groups share launches: all
 // packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, then the row and the
-// tile GEMMs, together in one launch when neither has more than kGroupsTogether groups.  Tiles are not shared between workgroups
-// here (the groups together fill the chip), so Z needs no pre-copy.
+// tile GEMMs in one launch each.  Tiles are not shared between workgroups here (the groups together fill the chip), so Z needs no pre-copy.
 template <class Args, class Launch> inline spin_status launch_in_tables(const std::vector<Args> &args,
                                                                         const std::vector<unsigned> &blocks, Launch &&launch)
 {
@@ -1113,39 +1099,14 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             if (st != SPIN_OK) return;
         }
         constexpr int RP = NP <= 3 ? NP : 3;                 // groups reach the row kernel only when n <= 3
-        if (!rows.empty() && !tiles.empty() && rows.size() <= kGroupsTogether && tiles.size() <= kGroupsTogether) {
-            static OncePerDevice lds_allowed;
-            auto kernel = limb_gemm_mixed_grouped_kernel<RP>;
-            constexpr int lds = std::max(kRowLds, GemmShape<u64>::lds_bytes);
-            st = allow_dynamic_lds((const void *)kernel, lds, lds_allowed);
-            if (st != SPIN_OK) return;
-            SmallGroupTable<RowGemmArgs> rt;
-            SmallGroupTable<GemmArgs<u64>> tt;
-            auto fill = [](auto &t, const auto &args, const std::vector<unsigned> &blocks) {
-                unsigned total = 0;
-                t.count = (int)args.size();
-                for (int i = 0; i < t.count; ++i) {
-                    t.first[i] = total;
-                    t.e[i] = args[i];
-                    total += blocks[i];
-                }
-                for (int i = t.count; i <= kGroupsTogether; ++i) t.first[i] = total;
-                return total;
-            };
-            const unsigned row_total = fill(rt, rows, row_blocks), tile_total = fill(tt, tiles, tile_blocks);
-            KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-            kernel<<<row_total + tile_total, 256, lds, s>>>(rt, tt, row_total);
-            st = check_launch("spin_beaver_matmul_grouped(gemm)");
-            return;
-        }
         if (!rows.empty()) {
             static OncePerDevice lds_allowed;
             auto kernel = limb_gemm_rows_grouped_kernel<RP>;
-            st = allow_dynamic_lds((const void *)kernel, kRowLds, lds_allowed);
+            st = allow_dynamic_lds((const void *)kernel, RowLds<RP>::bytes, lds_allowed);
             if (st != SPIN_OK) return;
             KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
             launch_in_tables(rows, row_blocks, [&](const GroupTable<RowGemmArgs> &t, unsigned total) {
-                kernel<<<total, 64 * (RP + 1), kRowLds, s>>>(t);
+                kernel<<<total, kRowThreads, RowLds<RP>::bytes, s>>>(t);
             });
             st = check_launch("spin_beaver_matmul_grouped(row gemm)");
             if (st != SPIN_OK) return;
