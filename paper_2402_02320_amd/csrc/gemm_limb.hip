@@ -1016,7 +1016,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
 
 // ---- grouped call: products of different shapes, a handful of launches for all of them ----------------
 // Every group gets its own fragment stores inside the workspace (the packs of all groups run before their
-// GEMMs), chooses the row-streaming or the tile kernel as a single product would, and the groups share launches: all
+// GEMMs), takes the row-streaming or the tile kernel (grouped_rows), and the groups share launches: all
 // packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, then the row and the
 // tile GEMMs in one launch each.  Tiles are not shared between workgroups here (the groups together fill the chip), so Z needs no pre-copy.
 template <class Args, class Launch> inline spin_status launch_in_tables(const std::vector<Args> &args,
@@ -1039,6 +1039,29 @@ template <class Args, class Launch> inline spin_status launch_in_tables(const st
 
 }  // namespace
 
+// Which groups take the row kernel.  The groups fill the chip together, so what counts is the time that a group's workgroups take of it,
+// not how long it would take alone; and tile products only have a launch of their own (5 us) where all of them together save as much.  Six
+// attention products of three stages: 31 us, 47 with the rule for single products, which gives two of the six to the tile kernel.
+static std::vector<bool> grouped_rows(int n, int groups, const MatmulArgs *a)
+{
+    std::vector<bool> rows(groups, false), by_tiles(groups, false);
+    double saved = 0;
+    for (int g = 0; g < groups; ++g) {
+        const MatmulArgs &m = a[g];
+        const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K);
+        if (n > 3 || rows_grid(m.batch, m.M, p.tilesN) > 0x7fffffffL) continue;
+        const double cus = compute_units(), mk = 1e-6 * m.batch * (double)m.M * m.K;
+        const double by_rows = rows_grid(m.batch, m.M, p.tilesN) / cus * ((0.199 + 0.346 * n) * 2 * p.KT + 1.66 + 0.505 * n) + 0.060 * 16 * n * mk;
+        const double tiles = (double)p.tilesM * p.tilesN * n * m.batch / cus * (1.24 * 2 * p.KT + 4.34) + 0.179 * 8 * (3 * n + 1) * mk;
+        rows[g] = true;
+        by_tiles[g] = tiles < by_rows;
+        if (by_tiles[g]) saved += by_rows - tiles;
+    }
+    const bool two_kinds = n <= 3 && saved > 5;
+    for (int g = 0; g < groups; ++g) rows[g] = rows[g] && !(two_kinds && by_tiles[g]);
+    return rows;
+}
+
 size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a)
 {
     size_t sum = 0;
@@ -1057,6 +1080,7 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
     std::vector<RowGemmArgs> rows;
     std::vector<GemmArgs<u64>> tiles;
     char *ws = (char *)workspace;
+    const std::vector<bool> by_rows = grouped_rows(n, groups, a);
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
         const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K);
@@ -1071,7 +1095,7 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT}, 4});
             side_blocks.push_back(pack_right_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
         }
-        if (digit_route<u64>(m, p).rows) {
+        if (by_rows[g]) {
             rows.push_back(RowGemmArgs{m.X, m.A, packB, m.C, m.Z, m.batch, m.M, m.N, m.K, p.KT, p.tilesN});
             row_blocks.push_back((unsigned)rows_grid(m.batch, m.M, p.tilesN));
         } else {
