@@ -1,5 +1,5 @@
-"""ctypes binding of libspin.so (include/spin.h).  Argument marshalling only:
-every step of the protocol runs in the library's kernels.
+"""Binding of libspin.so (include/spin.h).  Argument marshalling only: every step of the protocol runs in the library's kernels.
+The frequent calls first go through a compiled binding (csrc/binding.cpp); whatever that does not take is done here with ctypes.
 
 Ring tensors are torch.int64 CUDA tensors (the bit pattern of a uint64 ring
 element), party-major ([n, ...]).  Calls are enqueued on torch's current
@@ -7,6 +7,7 @@ stream.  The library must have been built (python -m paper_2402_02320_amd.build)
 there is no fallback: a missing library raises.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
@@ -18,6 +19,10 @@ LIMB_MFMA, VALU = 0, 1
 MAX_PARTIES = 8
 
 _lib = None
+# The compiled binding (csrc/binding.cpp), there once lib() has loaded the library.  Its functions return None for every call that is not
+# well formed, or not theirs; the code below each of them then says what is wrong, or does it.
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
+_fast = None
 
 
 class SpinError(RuntimeError):
@@ -99,7 +104,29 @@ def lib():
         L.spin_status_string.restype = ctypes.c_char_p
         L.spin_last_hip_error.restype = ctypes.c_char_p
         _lib = L
+        _load_binding(L)
     return _lib
+
+
+def _load_binding(L):
+    global _fast
+    if not os.path.exists(BINDING_PATH):
+        raise SpinError("%s not found: build it with `python -m paper_2402_02320_amd.build`" % BINDING_PATH)
+    spec = importlib.util.spec_from_file_location("_binding", BINDING_PATH)
+    binding = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(binding)
+    entries = ("share", "bshare", "open", "bopen", "beaver_mul", "beaver_and", "trunc", "beaver_matmul", "beaver_matmul_nt",
+               "beaver_matmul_preferred_workspace_bytes", "beaver_matmul_grouped", "beaver_matmul_grouped_workspace_bytes",
+               "completed_square_trunc")
+    binding.bind(tuple(ctypes.cast(getattr(L, "spin_" + e), ctypes.c_void_p).value for e in entries), _UNASKED_BYTES)
+    _fast = binding
+
+
+def _done(result):
+    """What the compiled binding answered with: the result, or a status of the library."""
+    if type(result) is int:
+        _check(result)
+    return result
 
 
 def _check(status):
@@ -142,6 +169,10 @@ def random(count, seed, stream_id, party, first_idx=0, device="cuda"):
 
 
 def share(x, n, seed, stream_id, out=None):
+    if _fast is not None:
+        r = _fast.share(x, n, seed, stream_id, out)
+        if r is not None:
+            return _done(r)
     if out is None:
         out = torch.empty((n,) + tuple(x.shape), dtype=torch.int64, device=x.device)
     _check(lib().spin_share(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev(out, "shares"), _stream()))
@@ -149,6 +180,10 @@ def share(x, n, seed, stream_id, out=None):
 
 
 def open(shares, mask=None, out=None):  # noqa: A001 - named after the C entry point
+    if _fast is not None:
+        r = _fast.open(shares, mask, out)
+        if r is not None:
+            return _done(r)
     n = shares.shape[0]
     if out is None:
         out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
@@ -209,6 +244,10 @@ def _matmul_workspace(dims, path, need_of, preferred_of, device):
 def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_transposed=False):
     """X, A: [n,batch,M,K]; Y, B: [n,batch,K,N] (or [n,batch,N,K] with y_transposed, for X . Y^T);
     C: [n,batch,M,N] -> Z [n,batch,M,N]."""
+    if _fast is not None:
+        r = _fast.matmul(X, Y, A, B, C, path, out, workspace, y_transposed)
+        if r is not None and type(r) is not int:         # a refusal is worded below, after the same refusal there
+            return r
     n, batch, M, K = X.shape
     N = Y.shape[2] if y_transposed else Y.shape[3]
     yshape = (n, batch, N, K) if y_transposed else (n, batch, K, N)
@@ -253,6 +292,10 @@ class _MatmulGroup(ctypes.Structure):
 def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
     """groups: list of dicts with X, Y, A, B, C (as for beaver_matmul), optional out and y_transposed; shapes may
     differ between groups, the party count may not.  Returns the list of Z tensors."""
+    if _fast is not None:
+        r = _fast.grouped(groups, path, workspace)
+        if r is not None:
+            return _done(r)
     n = groups[0]["X"].shape[0]
     desc = (_MatmulGroup * len(groups))()
     outs = []
@@ -284,6 +327,10 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
 
 
 def beaver_mul(x, y, a, b, c, out=None):
+    if _fast is not None:
+        r = _fast.beaver_mul(x, y, a, b, c, out)
+        if r is not None:
+            return _done(r)
     n = x.shape[0]
     shape = x.shape
     for t in (y, a, b, c):
@@ -326,6 +373,10 @@ def beaver_mul_bcast(x, y, a, b, c, over_inner, out=None):
 
 
 def trunc(x, r, r_top, r_msb, f, out=None):
+    if _fast is not None:
+        t = _fast.trunc(x, r, r_top, r_msb, f, out)
+        if t is not None:
+            return _done(t)
     n = x.shape[0]
     shape = x.shape
     for t in (r, r_top, r_msb):
@@ -339,6 +390,10 @@ def trunc(x, r, r_top, r_msb, f, out=None):
 
 
 def bshare(x, n, seed, stream_id, out=None):
+    if _fast is not None:
+        r = _fast.bshare(x, n, seed, stream_id, out)
+        if r is not None:
+            return _done(r)
     if out is None:
         out = torch.empty((n,) + tuple(x.shape), dtype=torch.int64, device=x.device)
     _check(lib().spin_bshare(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev(out, "shares"), _stream()))
@@ -346,6 +401,10 @@ def bshare(x, n, seed, stream_id, out=None):
 
 
 def bopen(shares, mask=None, out=None):
+    if _fast is not None:
+        r = _fast.bopen(shares, mask, out)
+        if r is not None:
+            return _done(r)
     n = shares.shape[0]
     if out is None:
         out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
@@ -357,6 +416,10 @@ def bopen(shares, mask=None, out=None):
 
 
 def beaver_and(x, y, a, b, c, out=None):
+    if _fast is not None:
+        r = _fast.beaver_and(x, y, a, b, c, out)
+        if r is not None:
+            return _done(r)
     n = x.shape[0]
     shape = x.shape
     for t in (y, a, b, c):
@@ -393,6 +456,10 @@ def lincomb_trunc(terms, coefs, constant=0, f=0, tuple_=None, out=None):
 def completed_square_trunc(x, t3, t2, lin, t0, triples, tuples, f, out=None):
     """((x + t3)^2 truncated by f[0], + t2)^2 + lin x + t0, truncated by f[1], in one pass.  t3, t2, lin, t0: public ring
     elements; triples, tuples: two (a, b, c) and two (r, r_top, r_msb) of x's shape."""
+    if _fast is not None:
+        r = _fast.completed_square(x, t3, t2, lin, t0, triples, tuples, f, out)
+        if r is not None:
+            return _done(r)
     for t in tuple(triples[0]) + tuple(tuples[0]) + tuple(triples[1]):
         if t.shape != x.shape:
             raise SpinError("inconsistent operand shapes")

@@ -1,0 +1,92 @@
+"""The compiled binding and the ctypes one below it: the same words, the same `out` object, the same refusals, for well-formed calls and for
+those that only the long way takes (subclasses, ints of other types, strided operands, missing memory formats)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2402_02320_amd import poly, spin
+
+pytestmark = pytest.mark.gpu
+
+
+def u(*s):
+    return torch.empty(s, dtype=torch.int64, device="cuda").random_(-2 ** 63, 2 ** 63 - 1)
+
+
+def calls(n=3, count=1001):
+    x, t = u(n, count), [u(n, count) for _ in range(12)]
+    mm = [u(n, 2, 40, 24), u(n, 2, 24, 70), u(n, 2, 40, 24), u(n, 2, 24, 70), u(n, 2, 40, 70)]
+    nt = [mm[0], mm[1].transpose(2, 3).contiguous(), mm[2], mm[3].transpose(2, 3).contiguous(), mm[4]]
+    groups = [dict(zip("XYABC", mm)), dict(zip("XYABC", nt), y_transposed=True), dict(zip("XYABC", mm), out=u(n, 2, 40, 70))]
+    return {"share": lambda: spin.share(x[0], n, 5, 2), "bshare": lambda: spin.bshare(x[0].view(7, 143), n, -1, 1 << 70),
+            "open": lambda: spin.open(x), "masked": lambda: spin.open(x, t[0]), "bopen": lambda: spin.bopen(x, t[0]),
+            "mul": lambda: spin.beaver_mul(x, *t[:4]), "and": lambda: spin.beaver_and(x, *t[:4]), "trunc": lambda: spin.trunc(x, *t[:3], 16),
+            "matmul": lambda: spin.beaver_matmul(*mm), "nt": lambda: spin.beaver_matmul(*nt, y_transposed=True),
+            "valu": lambda: spin.beaver_matmul(*mm, path=spin.VALU),
+            "workspace": lambda: spin.beaver_matmul(*mm, workspace=torch.empty(1 << 22, dtype=torch.uint8, device="cuda")),
+            "grouped": lambda: spin.beaver_matmul_grouped(groups),
+            "square": lambda: poly.evaluate_completed_square(x, -6, 0.96, 6.15, 24.02, 23.85, 14, [tuple(t[:3]), tuple(t[3:6])],
+                                                             [tuple(t[6:9]), tuple(t[9:])])}
+
+
+@pytest.mark.parametrize("name", ["share", "bshare", "open", "masked", "bopen", "mul", "and", "trunc", "matmul", "nt", "valu", "workspace",
+                                  "grouped", "square"])
+def test_same_words_both_ways(name, monkeypatch):
+    spin.lib()
+    call = calls()[name]
+    calls_made, fast = [], spin._fast
+
+    class Watch:
+        def __getattr__(self, entry):
+            def made(*a):
+                calls_made.append(getattr(fast, entry)(*a))
+                return calls_made[-1]
+            return made
+    monkeypatch.setattr(spin, "_fast", Watch())
+    got = call()
+    assert len(calls_made) == 1 and calls_made[0] is got             # the compiled binding took it
+    monkeypatch.setattr(spin, "_fast", None)
+    want = call()
+    got, want = (got, want) if isinstance(got, list) else ([got], [want])
+    assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_out_is_returned():
+    x, o = u(3, 64), u(3, 64)
+    assert spin.share(x[0], 3, 1, 1, out=o) is o and spin.trunc(x, x, x, x, 16, out=o) is o and spin.beaver_mul(x, x, x, x, x, out=o) is o
+    X, Z = u(2, 1, 32, 32), u(2, 1, 32, 32)
+    assert spin.beaver_matmul(X, X, X, X, X, out=Z) is Z
+    assert spin.beaver_matmul_grouped([dict(X=X, Y=X, A=X, B=X, C=X, out=Z)])[0] is Z
+
+
+@pytest.mark.parametrize("bad", [lambda x: spin.trunc(x, x, x, x, 0), lambda x: spin.trunc(x, x, x, x, 62), lambda x: spin.share(x[0], 9, 1, 1),
+                                 lambda x: spin.share(x[0], 0, 1, 1), lambda x: spin.trunc(x, x, x, x[:2], 16),
+                                 lambda x: spin.beaver_mul(x, x, x, x, x.t()), lambda x: spin.beaver_mul(x, x, x.cpu(), x, x),
+                                 lambda x: spin.beaver_mul(x, x, x.int(), x, x), lambda x: spin.open(x, x[:2]),
+                                 lambda x: spin.trunc(x.repeat(3, 1), *[x.repeat(3, 1)] * 3, 16), lambda x: spin.share(x.view(-1)[1:], 3, 1, 1),
+                                 lambda x: spin.beaver_matmul(*[x.view(3, 1, 8, 8)] * 4, x.view(3, 1, 4, 16)),
+                                 lambda x: spin.beaver_matmul(*[x.view(3, 1, 8, 8)] * 5, path=2),
+                                 lambda x: spin.beaver_matmul(*[x.view(3, 1, 8, 8)] * 5, workspace=torch.empty(16, dtype=torch.uint8, device="cuda")),
+                                 lambda x: spin.beaver_matmul_grouped([dict(zip("XYABC", [x.view(3, 1, 8, 8)] * 5)), dict(zip("XYABC", [x[:2].view(2, 1, 8, 8)] * 5))])])
+def test_refusals(bad):
+    with pytest.raises(spin.SpinError):
+        bad(u(3, 64))
+
+
+def test_the_long_way_takes_the_rest():
+    class Sub(torch.Tensor):
+        pass
+    x = u(3, 64)
+    want = spin.beaver_mul(x, x, x, x, x)
+    sub = x.as_subclass(Sub)
+    assert torch.equal(spin.beaver_mul(sub, x, x, x, x).as_subclass(torch.Tensor), want)
+    assert torch.equal(spin.share(x[0], True + 2, 1, 1), spin.share(x[0], 3, 1, 1))
+    with torch.inference_mode():
+        assert torch.equal(spin.beaver_mul(x, x, x, x, x), want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        z = spin.beaver_mul(x, x, x, x, x)
+    side.synchronize()
+    assert torch.equal(z, want)
+    assert np.array_equal(spin.open(x).cpu().numpy(), x.sum(0).cpu().numpy())
