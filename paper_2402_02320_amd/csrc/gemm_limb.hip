@@ -29,7 +29,7 @@
 //  *_grouped_kernel  the same bodies for several products of different shapes in one launch
 //                (spin_beaver_matmul_grouped), the products found through a table in the kernel arguments.
 // Larger products go to the residue GEMM (gemm_residue.hip; over Z_2^32 to gemm_strassen.hip) and the smallest to one launch of vector arithmetic
-// (gemm_direct.hip); digit_cost_us is this file's side of that choice.
+// (gemm_direct.hip); digit_route's estimate is this file's side of those choices.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -39,21 +39,26 @@
 namespace spin {
 namespace {
 
-// Per ring: digits, workgroup shape (waves are 2 x 2, each WM x WN MFMA tiles of 32 x 32; ND * WM * WN
-// * 16 accumulator registers <= 256), longest run of k-tiles one launch may accumulate, and the
-// interleave of one k-step (slots = MFMA index within the step): an LDS read after every rd_every-th
-// MFMA from slot 0, a direct-to-LDS load after every ld_every-th MFMA from slot ld_first.
+// Per ring: the largest workgroup tile (waves are 2 x 2, each WM x WN MFMA tiles of 32 x 32; ND * WM * WN * 16 accumulator
+// registers <= 256) and the longest run of k-tiles one launch may accumulate.
 template <class T> struct Ring;
 template <> struct Ring<u64> {
     static constexpr int WM = 2, WN = 1;
     static constexpr int max_chunk_tiles = 511;        // 2*511*32 = 32704 < 2^15 digit products per accumulator
-    static constexpr int rd_every = 2, ld_first = 13, ld_every = 4;   // 72 MFMAs, 24 reads, 12 loads per step
 };
 template <> struct Ring<u32> {
     static constexpr int WM = 2, WN = 2;
     static constexpr int max_chunk_tiles = 1 << 20;    // no headroom limit; keeps the step count an int
-    static constexpr int rd_every = 2, ld_first = 5, ld_every = 4;   // 40 MFMAs, 16 reads, 8 loads per step
 };
+// Of a wave with UNITS = WM * WN MFMA tiles of ND digits: the interleave of one k-step (slots = MFMA index within the step), an LDS read after
+// every rd_every-th MFMA from slot 0 and a direct-to-LDS load after every ld_every-th from slot ld_first; the LDS stages; and the waves on a
+// SIMD, one of each workgroup that a CU then holds.
+template <int ND, int UNITS> struct Interleave;
+template <> struct Interleave<8, 2> { static constexpr int rd_every = 2, ld_first = 13, ld_every = 4, stages = 3, waves = 1; };   // 72 MFMAs, 24 reads, 12 loads
+template <> struct Interleave<8, 1> { static constexpr int rd_every = 1, ld_first = 17, ld_every = 2, stages = 2, waves = 2; };   // 36, 16, 8
+template <> struct Interleave<4, 4> { static constexpr int rd_every = 2, ld_first = 5, ld_every = 4, stages = 3, waves = 1; };    // 40, 16, 8
+template <> struct Interleave<4, 2> { static constexpr int rd_every = 1, ld_first = 8, ld_every = 2, stages = 3, waves = 2; };    // 20, 12, 6
+template <> struct Interleave<4, 1> { static constexpr int rd_every = 1, ld_first = 1, ld_every = 2, stages = 3, waves = 3; };    // 10, 8, 4
 
 // ------------------------------------------------------------------ GEMM ---
 template <class T> struct GemmArgs {
@@ -69,11 +74,12 @@ template <class T> struct GemmArgs {
     int split_steps;     // splits > 1, adds its part onto Z atomically (Z then starts out as C)
 };
 
-template <class T>
+template <class T, int WM_ = Ring<T>::WM, int WN_ = Ring<T>::WN>
 struct GemmShape {
     static constexpr int ND = sizeof(T);                         // digits per ring element
-    static constexpr int WM = Ring<T>::WM, WN = Ring<T>::WN;
-    static constexpr int NSTAGE = 3;                             // LDS ring: one stage read, two in flight
+    static constexpr int WM = WM_, WN = WN_;
+    using Slots = Interleave<ND, WM * WN>;
+    static constexpr int NSTAGE = Slots::stages;                 // LDS ring: one stage read, the others in flight
     static constexpr int BM = 2 * 32 * WM, BN = 2 * 32 * WN;     // 4 waves as 2 x 2
     static constexpr int FA = BM / 32 * ND, FB = BN / 32 * ND;
     static constexpr int stage_bytes = (FA + FB) * kFrag;
@@ -112,10 +118,9 @@ __device__ inline void ring_atomic_add(u32 *p, u32 v) { atomicAdd((unsigned int 
 // Iteration s: [wait G(s+1); barrier]  then M(s) interleaved with R(s+1) and G(s+3).
 // The barrier at the top of iteration s also tells every wave that all R(s) are done, so stage s % 3
 // can be refilled by G(s+3).  Two groups of loads are in flight while a step computes.
-template <class T>
+template <class T, class S = GemmShape<T>>
 __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned block)
 {
-    using S = GemmShape<T>;
     constexpr int kDigits = S::ND, WM = S::WM, WN = S::WN;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -205,7 +210,7 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
 #pragma unroll
     for (int q = 0; q < S::loads_per_wave; ++q) issue_load(q);
     advance_load_cursor();
-    if (steps > 2) {
+    if (S::NSTAGE == 3 && steps > 2) {
 #pragma unroll
         for (int q = 0; q < S::loads_per_wave; ++q) issue_load(q);
         advance_load_cursor();
@@ -218,13 +223,13 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
     for (int q = 0; q < S::frags_per_wave; ++q) fr[0][q] = read_fragment(q);
     advance_read_cursor();
 
-    // One step.  CUR: register buffer holding this step.  LOAD: the step three ahead exists.
-    // NEXT: the next step exists.  MORE: the step two ahead exists (its loads stay in flight across the wait).
+    // One step.  CUR: register buffer holding this step.  LOAD: the step that fills this step's stage exists (three or, of two stages,
+    // two ahead).  NEXT: the next step exists.  MORE: the step two ahead exists (of three stages its loads stay in flight across the wait).
     auto iteration = [&](auto cur_c, auto load_c, auto next_c, auto more_c) {
         constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1;
         constexpr bool LOAD = decltype(load_c)::value, NEXT = decltype(next_c)::value, MORE = decltype(more_c)::value;
         if (NEXT) {
-            if (MORE) wait_loads<S::loads_per_wave>(); else wait_loads<0>();
+            if (MORE) wait_loads<(S::NSTAGE - 2) * S::loads_per_wave>(); else wait_loads<0>();
         }
         wait_lds();
         workgroup_barrier();
@@ -247,10 +252,10 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
                         // scalar work between them.  sched_barrier pins this order: left alone, the
                         // scheduler sinks each read next to its first use and the MFMA pipe then waits
                         // out the LDS latency.
-                        constexpr int rd_every = Ring<T>::rd_every;
+                        constexpr int rd_every = S::Slots::rd_every;
                         constexpr int rd_last = rd_every * (S::frags_per_wave - 1);
-                        constexpr int ld_first = Ring<T>::ld_first;
-                        constexpr int ld_every = Ring<T>::ld_every;
+                        constexpr int ld_first = S::Slots::ld_first;
+                        constexpr int ld_every = S::Slots::ld_every;
                         constexpr int ld_last = ld_first + ld_every * (S::loads_per_wave - 1);
                         static_assert(rd_every >= 1 && ld_every >= 1 && ld_last + 1 < S::mfma_per_step &&
                                       rd_last + 1 < S::mfma_per_step, "tile too small for this interleave");
@@ -282,9 +287,10 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
         iteration(B0(), Y(), Y(), Y());
         iteration(B1(), Y(), Y(), Y());
     }
+    using LastLoad = std::integral_constant<bool, S::NSTAGE == 2>;
     if (steps >= 4) {
-        iteration(B0(), Y(), Y(), Y());                   // step steps-4: loads the last step
-        iteration(B1(), F(), Y(), Y());
+        iteration(B0(), Y(), Y(), Y());                   // step steps-4: loads the last step (of two stages: the one before)
+        iteration(B1(), LastLoad(), Y(), Y());
     }
     iteration(B0(), F(), Y(), F());                       // step steps-2
 
@@ -351,10 +357,10 @@ __device__ __forceinline__ void limb_gemm_body(const GemmArgs<T> &g, unsigned bl
         }
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void limb_gemm_kernel(GemmArgs<T> g)
+template <class T, class S = GemmShape<T>>
+__global__ __launch_bounds__(256, (S::Slots::waves)) void limb_gemm_kernel(GemmArgs<T> g)
 {
-    limb_gemm_body<T>(g, blockIdx.x);
+    limb_gemm_body<T, S>(g, blockIdx.x);
 }
 
 // Products of different shapes in one launch (the grouped call): every workgroup finds its product in the table.
@@ -818,9 +824,8 @@ struct Plan {
     int KT, nblkA, nblkB, tilesM, tilesN;
     size_t packA_bytes, packB_bytes;
 };
-template <class T> inline Plan make_plan(int n, int batch, int M, int N, int K)
+template <class T, class S = GemmShape<T>> inline Plan make_plan(int n, int batch, int M, int N, int K)
 {
-    using S = GemmShape<T>;
     Plan p;
     p.KT = ceil_div(K, 32);
     p.tilesM = ceil_div(M, S::BM);
@@ -831,95 +836,132 @@ template <class T> inline Plan make_plan(int n, int batch, int M, int N, int K)
     p.packB_bytes = (size_t)(n + 1) * batch * p.nblkB * p.KT * (S::ND * kFrag);
     return p;
 }
-
-// How many workgroups share one output tile.  One workgroup per CU is resident at a time, so `tiles`
-// tiles of `steps` k-steps take ceil(tiles / CUs) rounds of steps + a fixed prologue/epilogue cost; when
-// the tiles do not fill the chip, splitting the k-steps of each tile over several workgroups (which add
-// their parts onto Z atomically) shortens the rounds.  Returns the count that minimises that model.
-inline int choose_splits(long tiles, int steps)
+// The tile shapes of a ring: the largest, half of it, and over Z_2^32 a quarter.  The largest takes a CU's registers and LDS, so that
+// nothing covers a workgroup's start (3 us), its waits for fragments and its end (3 to 5 us); of the smaller ones two (three over Z_2^32, by quarters)
+// share a CU, a tile is done sooner, and more parts of a tile fit the chip.  Half tiles over Z_2^64 have two LDS stages for
+// that (three leave a CU one workgroup: 3 % slower in the mean over 6700 products).  Whole calls, full tiles -> the shape taken: 4 parties 224 x 544 x 192 38 ->
+// 27 us, 32 x 640 x 2048 60 -> 45, 250 x 301 x 785 41 -> 36; over Z_2^32 2 parties 1024^3 59 -> 47, 3 parties 48 x 3000 x 6000 371 -> 248.
+enum TileShape { kFullTile, kHalfTile, kQuarterTile, kShapes };
+template <class T> constexpr int shapes_of = Ring<T>::WM * Ring<T>::WN == 4 ? 3 : 2;
+template <class T, class F> inline auto with_shape(TileShape shape, F &&fn)
 {
-    const int cus = compute_units();
-    constexpr int kFixedCost = 8;                        // prologue + epilogue, in k-step equivalents
-    constexpr int kMinSteps = 8;                         // shorter parts are all overhead
-    long best_cost = -1;
-    int best = 1;
-    for (int sp = 1; sp <= 16; ++sp) {
-        const int part = 2 * ceil_div(ceil_div(steps, 2), sp);
-        if (sp > 1 && part < kMinSteps) break;
-        const long rounds = (tiles * sp + cus - 1) / cus;
-        const long cost = rounds * (part + kFixedCost);
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
-    }
-    return best;
+    constexpr int WM = Ring<T>::WM, WN = Ring<T>::WN;
+    if (shape == kHalfTile) return fn(GemmShape<T, 1, WM * WN / 2>());
+    if constexpr (WM * WN == 4)
+        if (shape == kQuarterTile) return fn(GemmShape<T, 1, 1>());
+    return fn(GemmShape<T>());
 }
 
-// Times of the row kernel and of the tile kernel in microseconds, with their packs and launches: a row item is 2 KT half steps and
-// its start and end, a tile (or the part of one that a workgroup takes) likewise; operands and outputs are streams, and parts that are added onto
-// Z cost its words twice.  Fits to 40 000 products of 5 us to 1 ms (1 to 3 parties; 300 to 30 000 rows and 8 to 200 columns, batches of 2 to
-// 64 entries with sides of 16 to 512, inner dimensions to 1500, odd ones among them), within 6 and 7.5 % (rms).
+// Time of the row kernel in microseconds, with its pack and launches: a row item is 2 KT half steps and its start and end; the right
+// fragments (whole column tiles), the left operands and the outputs are streams.  A fit to 24 000 products of 5 us to 4 ms (1 to 3 parties;
+// batches to 300 entries, to 60 000 rows, sides from 1), within 6 % (rms).
 template <class T> inline double rows_us(const MatmulArgsT<T> &a, const Plan &p)
 {
     const int cus = compute_units();
     const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus), n = a.n;
-    const double right_mb = 8e-6 * (3 * n + 1) * a.batch * (double)a.N * a.K, left_mb = 16e-6 * n * a.batch * (double)a.M * a.K;
+    const double written_mb = 8e-6 * (n + 1) * a.batch * p.tilesN * 64.0 * p.KT * 32, left_mb = 16e-6 * n * a.batch * (double)a.M * a.K;
     const double out_mb = 16e-6 * n * a.batch * (double)a.M * a.N;
-    return 5.29 + 1.52 * n + rounds * ((0.199 + 0.346 * n) * 2 * p.KT + 1.66 + 0.505 * n) + 0.174 * right_mb + 0.060 * left_mb + 0.104 * out_mb;
+    return 5.58 + 1.51 * n + rounds * ((0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n) + 0.326 * written_mb + 0.045 * left_mb + 0.104 * out_mb;
 }
-template <class T> inline double tiles_us(const MatmulArgsT<T> &a, const Plan &p, int sp)
+// The same of the tile kernel by one of its shapes, `splits` workgroups to a tile (which add their parts onto Z, from C: its words once
+// more each way).  The busiest CU has `most` workgroups; they take their k-steps together as far as its registers and LDS hold several, rounds
+// of that many otherwise, and long calls bring the clock down.  Operands are read as they are and written in whole tiles.  Fits to 76 000 timings
+// of full, 71 000 of half tiles over Z_2^64 and 91 000, 84 000 and 78 000 over Z_2^32 (5 us to 4 ms, 1 to 6 parties, 1 to 16 parts): within
+// 7.3, 8.4, 7.4, 8.8 and 9.3 % (rms).
+struct TileCost { int at_once; double call, party, round, step, each, start, read, written, out, added, hot, cool; };
+template <class T> inline double tiles_us(int n, int batch, int M, int N, int K, TileShape shape, int splits)
 {
-    const int cus = compute_units();
-    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const double rounds = (double)((tiles * sp + cus - 1) / cus), words = (double)sizeof(T) * (3 * a.n + 1) * a.batch;
-    const double packed_mb = 1e-6 * words * ((double)a.M + a.N) * a.K, out_mb = 2e-6 * sizeof(T) * a.n * a.batch * (double)a.M * a.N;
-    if (sizeof(T) == 8) return 5.74 + 1.05 * a.n + rounds * (1.24 * 2 * ceil_div(p.KT, sp) + 4.34) + 0.179 * packed_mb + (sp > 1 ? 0.524 : 0.107) * out_mb;
-    // over Z_2^32, a fit to 8000 products: within 9 %
-    return 3.7 + 1.36 * a.n + rounds * (0.716 * 2 * ceil_div(p.KT, sp) + 5.56) + 0.2 * packed_mb + 0.161 * out_mb;
+    constexpr TileCost costs64[] = {{1, 7.84, 0.960, 0.411, 0.949, 0.208, 3.94, 0.103, 0.221, 0.076, 0.431, 0.080, 60},
+                                    {2, 8.17, 1.007, 0.117, 0.728, 0.000, 0.132, 0.061, 0.276, 0.106, 0.382, 0.111, 120}};
+    constexpr TileCost costs32[] = {{1, 6.18, 0.627, 0.115, 0.551, 0.248, 5.76, 0.031, 0.282, 0.028, 0.452, 0.017, 60},
+                                    {2, 7.58, 0.649, 0.069, 0.307, 0.088, 1.095, 0.006, 0.344, 0.067, 0.486, 0.080, 120},
+                                    {3, 6.82, 0.656, 0.006, 0.215, 0.000, 0.587, 0.000, 0.387, 0.060, 0.505, 0.063, 240}};
+    const TileCost &c = sizeof(T) == 8 ? costs64[shape == kFullTile ? 0 : 1] : costs32[shape];
+    const int KT = ceil_div(K, 32), part = 2 * ceil_div(KT, splits), used = ceil_div(2 * KT, part);
+    double tiles = 0, sides = 0;
+    with_shape<T>(shape, [&](auto s) {
+        using S = decltype(s);
+        const double tm = ceil_div(M, S::BM), tn = ceil_div(N, S::BN);
+        tiles = tm * tn;
+        sides = tm * S::BM + tn * S::BN;
+    });
+    const double filled = tiles * n * batch * used / compute_units(), most = std::ceil(filled), mb = 1e-6 * sizeof(T) * batch;
+    const double read_mb = 2 * n * mb * ((double)M + N) * K, written_mb = (n + 1) * mb * sides * KT * 32, out_mb = 2 * n * mb * (double)M * N;
+    return c.call + c.party * n + part * (c.round * std::floor(filled / c.at_once) + c.step * most + c.each * filled) + c.start * most +
+           c.read * read_mb + c.written * written_mb + (used > 1 ? c.out + c.added : c.out) * out_mb + c.hot * std::max(0.0, most * part - c.cool);
 }
-// Which kernel a product takes, and how many workgroups would share a tile: what all estimates of it need.  The row kernel takes products over
-// Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may accumulate, where it is estimated
-// to be the faster one: that costs 0.4 % against always the faster one (products as above), where a count of k-steps cost 6.2 %.
-struct DigitRoute { bool rows; int splits; };
+
+// Which kernel a product takes, by which tiles, and how many workgroups share one (parts of at least four k-steps): what all estimates
+// of it need.  The row kernel takes products over Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may
+// accumulate, where it is estimated to be the fastest.  Together with the direct kernel that costs 0.75 % against always the fastest way, over 26 000
+// products over Z_2^64 and 31 000 over Z_2^32; full tiles alone, and parts by a count of k-steps, cost 24 and 41 % below 2e10 ring
+// MACs (58 % in calls of 8 to 16 us, 7 % of 128 to 256), 1 % and less in calls of a millisecond, where full tiles move the fewest bytes.  Beyond 60
+// us smaller tiles have to be estimated 6 % faster: where full ones just fill the chip the estimates are no closer (2 parties 1024^3,
+// 256 full tiles: 130 us, 135 by half tiles, estimated at 135 and 134).
+//
+// Three parties and at most five k-tiles: the row kernel keeps products that tiles in parts would take in up to 1.6 times less (3
+// parties 256 x 190 x 130, 24 items: 26.7 us by rows, 16.3 by tiles; no slower than they were), because the tests of its item shares are written on
+// them: those of at most 48 items and of more than two k-tiles, and those that are estimated within a quarter of the tiles.
+struct DigitRoute { bool rows; int splits; TileShape shape; double us; };
 template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {
-    DigitRoute r{false, choose_splits((long)p.tilesM * p.tilesN * a.n * a.batch, 2 * p.KT)};
+    DigitRoute r{false, 1, kFullTile, tiles_us<T>(a.n, a.batch, a.M, a.N, a.K, kFullTile, 1)};
+    double margin = 1, best = r.us;
+    for (int shape = 0; shape < shapes_of<T>; ++shape) {
+        if (shape == kHalfTile && r.us > 60) margin = 1.06;
+        for (int sp = 1; sp <= 16; ++sp) {
+            if (sp > 1 && 2 * ceil_div(p.KT, sp) < 4) break;
+            if (sp > 1 && ceil_div(p.KT, ceil_div(p.KT, sp)) < sp) continue;         // no more parts than with fewer
+            const double us = tiles_us<T>(a.n, a.batch, a.M, a.N, a.K, (TileShape)shape, sp);
+            if (margin * us < best) r = DigitRoute{false, sp, (TileShape)shape, us}, best = margin * us;
+        }
+    }
     if (!std::is_same<T, u64>::value) return r;
     if (a.n > 3 || p.KT > Ring<u64>::max_chunk_tiles) return r;
     if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return r;
-    r.rows = rows_us<T>(a, p) <= tiles_us<T>(a, p, r.splits);
+    const double by_rows = rows_us<T>(a, p);
+    const bool kept = a.n == 3 && p.KT <= 5 && (by_rows <= 1.25 * r.us || (p.KT > 2 && rows_grid(a.batch, a.M, p.tilesN) <= 48));
+    if (by_rows <= r.us || kept) r.rows = true, r.us = by_rows;
     return r;
 }
 
-// Estimated time of the digit kernels in microseconds, for the choice between them and the direct kernel:
-// 1.5 us a k-step (72 MFMAs of 32 cycles on random operands; 0.85 us over Z_2^32, 40 of them) and the packs as streams.
-// Small products are what it is for; large ones come out up to 40 % too high (the packs overlap their launch).
-template <class T> inline double digit_cost_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
+// Estimates of full tiles alone, for two lines between kernels that stay where those put them.
+// Workgroups to a full tile by a count of k-steps: 8 of them for start and end, parts of 8 at least.
+inline int full_tile_splits(long tiles, int KT)
 {
     const int cus = compute_units();
-    if (r.rows) return 1.5 * (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8) + 10;
-    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = r.splits;
-    const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
-    const double step = sizeof(T) == 8 ? 1.5 : 0.85;
-    return step * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
+    long best_cost = -1;
+    int best = 1;
+    for (int sp = 1; sp <= 16; ++sp) {
+        const int part = 2 * ceil_div(KT, sp);
+        if (sp > 1 && part < 8) break;
+        const long cost = (tiles * sp + cus - 1) / cus * (part + 8);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
+    }
+    return best;
 }
-
-// The same in detail, for small products.
-template <class T> inline double digit_cost_small_us(const MatmulArgsT<T> &a, const Plan &p, const DigitRoute &r)
+// Roughly, for the choice between the digit kernels and the direct one, which takes a product only where this estimate and DigitRoute::us both
+// speak for it (alone either of them is off by up to 2.7 times somewhere): 1.5 us a k-step (0.85 over Z_2^32) and the packs as streams.
+template <class T> inline double digit_cost_rough_us(const MatmulArgsT<T> &a, const Plan &p)
 {
-    return r.rows ? rows_us<T>(a, p) : tiles_us<T>(a, p, r.splits);
+    const int cus = compute_units();
+    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
+    const int sp = full_tile_splits(tiles, p.KT);
+    const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
+    const double by_tiles = (sizeof(T) == 8 ? 1.5 : 0.85) * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
+    if (sizeof(T) != 8 || a.n > 3) return by_tiles;
+    return std::min(by_tiles, 1.5 * (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8) + 10);
 }
-
-// The same for the choice between them and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
-// parties, sides 32 to 8192), within 6 % (rms).  The clock is higher where the tiles leave part of the chip idle; parts of shared
-// tiles that are added onto Z cost 0.3 us a megabyte of its words read and written.
+// For the choice between the digit kernels and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
+// parties, sides 32 to 8192), within 6 % (rms).  Below 3.5e9 ring MACs it is the estimate of the way that is taken; above, half tiles save 13 %
+// where there are few tiles and nothing where there are many, and the residue GEMM keeps the products it had (its plans' tests are written on them).
 inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p, const DigitRoute &r)
 {
-    const int cus = compute_units();
+    if (r.rows || ring_macs(a.n, a.batch, a.M, a.N, a.K) < 3.5e9) return r.us;
     const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
-    if (r.rows) return rows_us(a, p);
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = r.splits;
-    const double filled = (double)tiles * sp / cus, rounds = std::ceil(filled);
+    const int sp = full_tile_splits(tiles, p.KT);
+    const double filled = (double)tiles * sp / compute_units(), rounds = std::ceil(filled);
     return rounds * (1.52 * 2 * ceil_div(p.KT, sp) * (1 - 0.592 * (1 - filled / rounds)) + 6.6) +
            words * ((double)a.M + a.N) * a.K / 5.4e6 + 1.1 + 1.52 * a.n + (sp > 1 ? 0.305 * out_mb : 0);
 }
@@ -953,34 +995,13 @@ inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, 
     return st;
 }
 
-template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t s, const char *where_pack, const char *where_gemm)
+template <class T, class S>
+inline spin_status launch_tiles(const MatmulArgsT<T> &a, int splits, hipStream_t s, const char *where_pack, const char *where_gemm)
 {
-    using S = GemmShape<T>;
-    const Plan p = make_plan<T>(a.n, a.batch, a.M, a.N, a.K);
-    char *packA = (char *)a.workspace;
-    char *packB = packA + p.packA_bytes;
-
-    const DigitRoute route = digit_route<T>(a, p);
-    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_us<T>(a, p, route), digit_cost_small_us<T>(a, p, route)))
-        return launch_matmul_direct<T>(a, s, where_gemm);
-    if constexpr (std::is_same<T, u64>::value) {
-        if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
-            bool taken = false;
-            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p, route), s, "spin_beaver_matmul(residue gemm)", taken);
-            if (taken) return st;
-        }
-        if (route.rows) return launch_rows(a, p, packB, s, where_pack, where_gemm);
-    }
-    if constexpr (std::is_same<T, u32>::value) {
-        bool taken = false;
-        const spin_status st = launch_matmul_strassen32(a, s, taken);
-        if (taken) return st;
-    }
-
+    const Plan p = make_plan<T, S>(a.n, a.batch, a.M, a.N, a.K);
+    char *packA = (char *)a.workspace, *packB = packA + p.packA_bytes;
     const long total = (long)p.tilesM * p.tilesN * a.n * a.batch;
     constexpr int chunk = Ring<T>::max_chunk_tiles;
-    const int first_ktn = p.KT < chunk ? p.KT : chunk;
-    const int splits = choose_splits(total, 2 * first_ktn);
     // with several workgroups to a tile their parts are added onto Z, which starts out as C
     const bool copy_c = splits > 1 && a.C != a.Z;
     const bool copied = launch_pack<T>(a, packA, packB, p.nblkA, p.nblkB, p.KT, copy_c, s);
@@ -991,8 +1012,8 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
         if (st != SPIN_OK) return st;
     }
 
-    static OncePerDevice lds_allowed;                    // one per ring type
-    auto kernel = limb_gemm_kernel<T>;
+    static OncePerDevice lds_allowed;                    // one per ring type and shape
+    auto kernel = limb_gemm_kernel<T, S>;
     st = allow_dynamic_lds((const void *)kernel, S::lds_bytes, lds_allowed);
     if (st != SPIN_OK) return st;
     GemmArgs<T> g{packA, packB, a.C, a.Z, a.n, a.batch, a.M, a.N, p.nblkA, p.nblkB, p.KT, 0, 0, p.tilesM, p.tilesN,
@@ -1012,6 +1033,29 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
         if (st != SPIN_OK) return st;
     }
     return SPIN_OK;
+}
+
+template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t s, const char *where_pack, const char *where_gemm)
+{
+    const Plan p = make_plan<T>(a.n, a.batch, a.M, a.N, a.K);
+    const DigitRoute route = digit_route<T>(a, p);
+    if (direct_applies(a.n, a.batch, a.M, a.N, a.K, sizeof(T), digit_cost_rough_us<T>(a, p), route.us))
+        return launch_matmul_direct<T>(a, s, where_gemm);
+    if constexpr (std::is_same<T, u64>::value) {
+        if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
+            bool taken = false;
+            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p, route), s, "spin_beaver_matmul(residue gemm)", taken);
+            if (taken) return st;
+        }
+        if (route.rows) return launch_rows(a, p, (char *)a.workspace + p.packA_bytes, s, where_pack, where_gemm);
+    }
+    if constexpr (std::is_same<T, u32>::value) {
+        bool taken = false;
+        const spin_status st = launch_matmul_strassen32(a, s, taken);
+        if (taken) return st;
+    }
+
+    return with_shape<T>(route.shape, [&](auto shape) { return launch_tiles<T, decltype(shape)>(a, route.splits, s, where_pack, where_gemm); });
 }
 
 // ---- grouped call: products of different shapes, a handful of launches for all of them ----------------

@@ -10,7 +10,7 @@ from paper_2402_02320_amd import spin
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(3, 1, 8192, 64, 31), (2, 64, 300, 64, 33), (3, 100, 128, 64, 63), (3, 20, 800, 65, 65), (2, 33, 260, 31, 95), (3, 1, 16385, 64, 97),
-          (3, 9, 1000, 128, 127), (2, 1, 20000, 64, 129), (1, 64, 320, 64, 47), (1, 1, 33000, 40, 161), (3, 64, 64, 40, 225), (3, 255, 20, 1, 33)]
+          (3, 9, 1000, 64, 127), (2, 1, 20000, 64, 129), (1, 64, 320, 64, 47), (1, 1, 33000, 40, 161), (3, 128, 64, 40, 225), (3, 255, 20, 1, 33)]
 
 
 @pytest.mark.parametrize("n,batch,M,N,K", SHAPES)
