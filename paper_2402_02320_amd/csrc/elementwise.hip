@@ -22,8 +22,11 @@ constexpr int kBlock = 256;
 // Streaming accesses.  Tensors far larger than the caches are read and written exactly once, and
 // non-temporal loads and stores (no cache retention) measured 14 % faster on the 25-stream truncation
 // pattern (n = 5, 2^24 elements, same process: 6.4 against 5.6 TB/s).
-// Small tensors keep ordinary accesses so that the next kernel finds them in L2 / Infinity Cache.
-constexpr size_t kStreamingBytes = (size_t)64 << 20;    // per call, all parties together
+// Small tensors keep ordinary accesses so that the next kernel finds them in L2 / Infinity Cache.  The line is where that stops to pay in whole
+// passes, measured with it at 8, 16, 32 and 64 MB: 2 parties x 3 550 058 (57 MB), share, multiply and truncate: 146 us with ordinary
+// accesses, 135 with these; the truncation behind 3 parties 480 x 3168 x 32 (36 MB) 67 and 59.5 the pass; 3 parties x 551 742 binary words (13 MB)
+// 26.3 and 30.1; the passes of 17 other sizes within 1 % or faster with the line at 16.
+constexpr size_t kStreamingBytes = (size_t)16 << 20;    // per call, all parties together
 template <bool NT, class V> __device__ inline V ld(const V *p)
 {
     if constexpr (NT && std::is_same<V, u128>::value) {          // the builtin takes no __int128: same 16 bytes as u64x2
