@@ -364,11 +364,11 @@ __global__ __launch_bounds__(256, (S::Slots::waves)) void limb_gemm_kernel(GemmA
 }
 
 // Products of different shapes in one launch (the grouped call): every workgroup finds its product in the table.
-template <class T>
-__global__ __launch_bounds__(256) void limb_gemm_grouped_kernel(GroupTable<GemmArgs<T>> t)
+template <class T, class S>
+__global__ __launch_bounds__(256, (S::Slots::waves)) void limb_gemm_grouped_kernel(GroupTable<GemmArgs<T>> t)
 {
     const int gi = group_of(t, blockIdx.x);
-    limb_gemm_body<T>(t.e[gi], blockIdx.x - t.first[gi]);
+    limb_gemm_body<T, S>(t.e[gi], blockIdx.x - t.first[gi]);
 }
 
 // ------------------------------------------------- row-streaming GEMM ---
@@ -1106,6 +1106,18 @@ static std::vector<bool> grouped_rows(int n, int groups, const MatmulArgs *a)
     return rows;
 }
 
+// Full or half tiles, for all tile products of a call: what they would take one after another, whole tiles.
+static TileShape grouped_shape(int n, int groups, const MatmulArgs *a, const std::vector<bool> &by_rows)
+{
+    double full = 0, half = 0;
+    for (int g = 0; g < groups; ++g) {
+        if (by_rows[g]) continue;
+        full += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kFullTile, 1);
+        half += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kHalfTile, 1);
+    }
+    return half < full ? kHalfTile : kFullTile;
+}
+
 size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a)
 {
     size_t sum = 0;
@@ -1125,9 +1137,13 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
     std::vector<GemmArgs<u64>> tiles;
     char *ws = (char *)workspace;
     const std::vector<bool> by_rows = grouped_rows(n, groups, a);
+    const TileShape shape = grouped_shape(n, groups, a, by_rows);
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
-        const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K);
+        // the row kernel's column tiles are a full tile's
+        const Plan p = by_rows[g] ? make_plan<u64>(n, m.batch, m.M, m.N, m.K) : with_shape<u64>(shape, [&](auto s) {
+            return make_plan<u64, decltype(s)>(n, m.batch, m.M, m.N, m.K);
+        });
         if (p.KT > Ring<u64>::max_chunk_tiles) return SPIN_ERANGE;
         const int odd = m.K % 2;                         // rows not 16-byte aligned
         char *packA = ws, *packB = ws + p.packA_bytes;
@@ -1180,14 +1196,18 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             if (st != SPIN_OK) return;
         }
         if (!tiles.empty()) {
-            static OncePerDevice lds_allowed;
-            auto kernel = limb_gemm_grouped_kernel<u64>;
-            st = allow_dynamic_lds((const void *)kernel, GemmShape<u64>::lds_bytes, lds_allowed);
-            if (st != SPIN_OK) return;
-            KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-            launch_in_tables(tiles, tile_blocks, [&](const GroupTable<GemmArgs<u64>> &t, unsigned total) {
-                kernel<<<total, 256, GemmShape<u64>::lds_bytes, s>>>(t);
+            with_shape<u64>(shape, [&](auto sh) {
+                using S = decltype(sh);
+                static OncePerDevice lds_allowed;
+                auto kernel = limb_gemm_grouped_kernel<u64, S>;
+                st = allow_dynamic_lds((const void *)kernel, S::lds_bytes, lds_allowed);
+                if (st != SPIN_OK) return;
+                KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
+                launch_in_tables(tiles, tile_blocks, [&](const GroupTable<GemmArgs<u64>> &t, unsigned total) {
+                    kernel<<<total, 256, S::lds_bytes, s>>>(t);
+                });
             });
+            if (st != SPIN_OK) return;
             st = check_launch("spin_beaver_matmul_grouped(tile gemm)");
         }
     });
