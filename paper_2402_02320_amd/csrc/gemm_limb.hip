@@ -1083,26 +1083,31 @@ template <class Args, class Launch> inline spin_status launch_in_tables(const st
 
 }  // namespace
 
-// Which groups take the row kernel.  The groups fill the chip together, so what counts is the time that a group's workgroups take of it,
-// not how long it would take alone; and tile products only have a launch of their own (5 us) where all of them together save as much.  Six
-// attention products of three stages: 31 us, 47 with the rule for single products, which gives two of the six to the tile kernel.
+// Which groups take the row kernel: all that can, or none.  The groups fill the chip together, so a call takes as long as its workgroups' share of
+// it, or as its longest workgroup; half tiles are done sooner, and need their left operands packed.  In us, as in rows_us and tiles_us.  Six
+// attention products of three stages, by rows and by half tiles: 3 parties 33.1 : 28.4, at twice the batch entries 44.0 : 41.4, at five times 84.7 :
+// 87.2; 2 parties, twice 34.4 : 32.6, three times 37.7 : 38.7.  (With the rule for single products two of the six went to another launch:
+// 47.8 us.)  Calls of at most five k-tiles stay with the row kernel, as single products of few items do (digit_route).
 static std::vector<bool> grouped_rows(int n, int groups, const MatmulArgs *a)
 {
-    std::vector<bool> rows(groups, false), by_tiles(groups, false);
-    double saved = 0;
+    std::vector<bool> rows(groups, false);
+    if (n > 3) return rows;
+    double row_work = 0, row_longest = 0, tile_work = 0, tile_longest = 0, packs = 0;
+    int KT = 0;
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
-        const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K);
-        if (n > 3 || rows_grid(m.batch, m.M, p.tilesN) > 0x7fffffffL) continue;
-        const double cus = compute_units(), mk = 1e-6 * m.batch * (double)m.M * m.K;
-        const double by_rows = rows_grid(m.batch, m.M, p.tilesN) / cus * ((0.199 + 0.346 * n) * 2 * p.KT + 1.66 + 0.505 * n) + 0.060 * 16 * n * mk;
-        const double tiles = (double)p.tilesM * p.tilesN * n * m.batch / cus * (1.24 * 2 * p.KT + 4.34) + 0.179 * 8 * (3 * n + 1) * mk;
-        rows[g] = true;
-        by_tiles[g] = tiles < by_rows;
-        if (by_tiles[g]) saved += by_rows - tiles;
+        const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K), h = make_plan<u64, GemmShape<u64, 1, 1>>(n, m.batch, m.M, m.N, m.K);
+        rows[g] = rows_grid(m.batch, m.M, p.tilesN) <= 0x7fffffffL;
+        if (!rows[g]) continue;
+        const double item = (0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n, tile = (0.117 / 2 + 0.728) * 2 * p.KT + 0.132, left = 16e-6 * n * m.batch * (double)m.M * m.K;
+        row_work += rows_grid(m.batch, m.M, p.tilesN) * item / compute_units() + 0.045 * left;
+        row_longest = std::max(row_longest, item);
+        tile_work += (double)h.tilesM * h.tilesN * n * m.batch * tile / compute_units();
+        tile_longest = std::max(tile_longest, tile);
+        packs += 0.061 * left + 0.276e-6 * h.packA_bytes;
+        KT = std::max(KT, p.KT);
     }
-    const bool two_kinds = n <= 3 && saved > 5;
-    for (int g = 0; g < groups; ++g) rows[g] = rows[g] && !(two_kinds && by_tiles[g]);
+    if (KT > 5 && std::max(tile_work, tile_longest) + packs < 0.97 * std::max(row_work, row_longest)) rows.assign(groups, false);
     return rows;
 }
 
