@@ -863,19 +863,19 @@ template <class T> inline double rows_us(const MatmulArgsT<T> &a, const Plan &p)
     const double out_mb = 16e-6 * n * a.batch * (double)a.M * a.N;
     return 5.58 + 1.51 * n + rounds * ((0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n) + 0.326 * written_mb + 0.045 * left_mb + 0.104 * out_mb;
 }
-// The same of the tile kernel by one of its shapes, `splits` workgroups to a tile (which add their parts onto Z, from C: its words once
-// more each way).  The busiest CU has `most` workgroups; they take their k-steps together as far as its registers and LDS hold several, rounds
-// of that many otherwise, and long calls bring the clock down.  Operands are read as they are and written in whole tiles.  Fits to 76 000 timings
+// The same of the tile kernel by one of its shapes, `splits` workgroups to a tile, each of which adds its part onto Z (the words of Z once more a
+// part, and those of C before).  The busiest CU has `most` workgroups; they take their k-steps together as far as its registers and LDS hold several,
+// rounds of that many otherwise, and long calls bring the clock down.  Operands are read as they are and written in whole tiles.  Fits to 76 000 timings
 // of full, 71 000 of half tiles over Z_2^64 and 91 000, 84 000 and 78 000 over Z_2^32 (5 us to 4 ms, 1 to 6 parties, 1 to 16 parts): within
-// 7.3, 8.4, 7.4, 8.8 and 9.3 % (rms).
-struct TileCost { int at_once; double call, party, round, step, each, start, read, written, out, added, hot, cool; };
+// 7.0, 8.2, 7.1, 8.5 and 9.1 % (rms).  (With the parts' additions counted once, 4 parties 192 x 224 x 1504 took 16 parts, not 5: 10 % slower.)
+struct TileCost { int at_once; double call, party, round, step, each, start, read, written, out, copied, hot, cool, added, part; };
 template <class T> inline double tiles_us(int n, int batch, int M, int N, int K, TileShape shape, int splits)
 {
-    constexpr TileCost costs64[] = {{1, 7.84, 0.960, 0.411, 0.949, 0.208, 3.94, 0.103, 0.221, 0.076, 0.431, 0.080, 60},
-                                    {2, 8.17, 1.007, 0.117, 0.728, 0.000, 0.132, 0.061, 0.276, 0.106, 0.382, 0.111, 120}};
-    constexpr TileCost costs32[] = {{1, 6.18, 0.627, 0.115, 0.551, 0.248, 5.76, 0.031, 0.282, 0.028, 0.452, 0.017, 60},
-                                    {2, 7.58, 0.649, 0.069, 0.307, 0.088, 1.095, 0.006, 0.344, 0.067, 0.486, 0.080, 120},
-                                    {3, 6.82, 0.656, 0.006, 0.215, 0.000, 0.587, 0.000, 0.387, 0.060, 0.505, 0.063, 240}};
+    constexpr TileCost costs64[] = {{1, 8.52, 0.990, 0.449, 0.955, 0.130, 2.991, 0.083, 0.246, 0.115, 0.034, 0.108, 60, 0.177, 0.014},
+                                    {2, 8.10, 1.018, 0.082, 0.726, 0.000, 0.000, 0.047, 0.284, 0.125, 0.098, 0.133, 120, 0.120, 0.069}};
+    constexpr TileCost costs32[] = {{1, 6.73, 0.650, 0.135, 0.552, 0.208, 4.969, 0.013, 0.304, 0.060, 0.127, 0.038, 60, 0.139, 0.026},
+                                    {2, 7.76, 0.662, 0.074, 0.309, 0.066, 0.727, 0.000, 0.350, 0.103, 0.110, 0.099, 120, 0.163, 0.031},
+                                    {3, 6.98, 0.662, 0.000, 0.215, 0.000, 0.274, 0.000, 0.381, 0.108, 0.170, 0.065, 240, 0.150, 0.038}};
     const TileCost &c = sizeof(T) == 8 ? costs64[shape == kFullTile ? 0 : 1] : costs32[shape];
     const int KT = ceil_div(K, 32), part = 2 * ceil_div(KT, splits), used = ceil_div(2 * KT, part);
     double tiles = 0, sides = 0;
@@ -888,12 +888,13 @@ template <class T> inline double tiles_us(int n, int batch, int M, int N, int K,
     const double filled = tiles * n * batch * used / compute_units(), most = std::ceil(filled), mb = 1e-6 * sizeof(T) * batch;
     const double read_mb = 2 * n * mb * ((double)M + N) * K, written_mb = (n + 1) * mb * sides * KT * 32, out_mb = 2 * n * mb * (double)M * N;
     return c.call + c.party * n + part * (c.round * std::floor(filled / c.at_once) + c.step * most + c.each * filled) + c.start * most +
-           c.read * read_mb + c.written * written_mb + (used > 1 ? c.out + c.added : c.out) * out_mb + c.hot * std::max(0.0, most * part - c.cool);
+           c.read * read_mb + c.written * written_mb + c.out * out_mb + (used > 1 ? (c.copied + c.added * used) * out_mb + c.part * used : 0) +
+           c.hot * std::max(0.0, most * part - c.cool);
 }
 
 // Which kernel a product takes, by which tiles, and how many workgroups share one (parts of at least four k-steps): what all estimates
 // of it need.  The row kernel takes products over Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may
-// accumulate, where it is estimated to be the fastest.  Together with the direct kernel that costs 0.75 % against always the fastest way, over 26 000
+// accumulate, where it is estimated to be the fastest.  Together with the direct kernel that costs 0.65 % against always the fastest way, over 26 000
 // products over Z_2^64 and 31 000 over Z_2^32; full tiles alone, and parts by a count of k-steps, cost 24 and 41 % below 2e10 ring
 // MACs (58 % in calls of 8 to 16 us, 7 % of 128 to 256), 1 % and less in calls of a millisecond, where full tiles move the fewest bytes.  Beyond 60
 // us smaller tiles have to be estimated 6 % faster: where full ones just fill the chip the estimates are no closer (2 parties 1024^3,
@@ -901,7 +902,7 @@ template <class T> inline double tiles_us(int n, int batch, int M, int N, int K,
 //
 // Three parties and at most five k-tiles: the row kernel keeps products that tiles in parts would take in up to 1.6 times less (3
 // parties 256 x 190 x 130, 24 items: 26.7 us by rows, 16.3 by tiles; no slower than they were), because the tests of its item shares are written on
-// them: those of at most 48 items and of more than two k-tiles, and those that are estimated within a quarter of the tiles.
+// them: those of at most 48 items and of more than two k-tiles, and those that are estimated within a quarter of the tiles (two parties: 5 %).
 struct DigitRoute { bool rows; int splits; TileShape shape; double us; };
 template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {
@@ -920,7 +921,7 @@ template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const 
     if (a.n > 3 || p.KT > Ring<u64>::max_chunk_tiles) return r;
     if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return r;
     const double by_rows = rows_us<T>(a, p);
-    const bool kept = a.n == 3 && p.KT <= 5 && (by_rows <= 1.25 * r.us || (p.KT > 2 && rows_grid(a.batch, a.M, p.tilesN) <= 48));
+    const bool kept = a.n >= 2 && p.KT <= 5 && (by_rows <= (a.n == 3 ? 1.25 : 1.05) * r.us || (a.n == 3 && p.KT > 2 && rows_grid(a.batch, a.M, p.tilesN) <= 48));
     if (by_rows <= r.us || kept) r.rows = true, r.us = by_rows;
     return r;
 }
@@ -957,7 +958,7 @@ template <class T> inline double digit_cost_rough_us(const MatmulArgsT<T> &a, co
 // where there are few tiles and nothing where there are many, and the residue GEMM keeps the products it had (its plans' tests are written on them).
 inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p, const DigitRoute &r)
 {
-    if (r.rows || ring_macs(a.n, a.batch, a.M, a.N, a.K) < 3.5e9) return r.us;
+    if ((r.rows && p.tilesN <= 8) || ring_macs(a.n, a.batch, a.M, a.N, a.K) < 3.5e9) return r.us;
     const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
     const int sp = full_tile_splits(tiles, p.KT);
