@@ -3,7 +3,7 @@
 // arguments and up to 2.5 on allocating in Python, as long as its kernels run on the smallest inputs: a 64^3 layer of three parties
 // (two sharings, a product, a truncation) took 22 us back to back, of which its kernels are 12.
 //
-// Every function returns the result, or None for whatever it does not take (other types, shapes that disagree, subclasses, modes that
+// Every function returns the result, or None for whatever it does not take (other types, shapes that disagree, an `out` that is too short, subclasses, modes that
 // look at calls, workspaces beyond what needs no look at the device's memory, no memory left): spin.py then goes the way that
 // says what is wrong, or does it.  A status of the library other than SPIN_OK comes back as an int.  Nothing is kept between calls but the
 // addresses of the library's functions.
@@ -100,7 +100,7 @@ PyObject *sharing(PyObject *const *a, Py_ssize_t count, decltype(lib.share) fn)
         int n;
         uint64_t seed, stream_id;
         if (!x || !integer(a[1], 1, SPIN_MAX_PARTIES, n) || !word(a[2], seed) || !word(a[3], stream_id)) return none();
-        if (a[4] != Py_None && !(out = ring_tensor(a[4]))) return none();
+        if (a[4] != Py_None && (!(out = ring_tensor(a[4])) || out->numel() < n * x->numel())) return none();
         at::Tensor fresh;
         if (!out) {
             c10::SmallVector<int64_t, 8> shape{n};
@@ -122,7 +122,8 @@ PyObject *opening(PyObject *const *a, Py_ssize_t count, decltype(lib.open) fn)
         const at::Tensor *shares = count == 3 ? ring_tensor(a[0]) : nullptr, *mask = nullptr, *out = nullptr;
         if (!shares || shares->dim() < 1 || !parties(shares->size(0))) return none();
         if (a[1] != Py_None && (!(mask = ring_tensor(a[1])) || mask->sizes() != shares->sizes())) return none();
-        if (a[2] != Py_None && !(out = ring_tensor(a[2]))) return none();
+        // the library reads the number of elements off `out`
+        if (a[2] != Py_None && (!(out = ring_tensor(a[2])) || out->numel() != shares->numel() / shares->size(0))) return none();
         at::Tensor fresh;
         if (!out) {
             fresh = at::empty(shares->sizes().slice(1), shares->options());
@@ -145,7 +146,7 @@ template <int INPUTS, class F> inline PyObject *elementwise(PyObject *const *a, 
         if (!t[i] || t[i]->sizes() != t[0]->sizes()) return none();
     }
     if (t[0]->dim() < 1 || !parties(t[0]->size(0))) return none();
-    if (out_arg != Py_None && !(out = ring_tensor(out_arg))) return none();
+    if (out_arg != Py_None && (!(out = ring_tensor(out_arg)) || out->numel() < t[0]->numel())) return none();
     at::Tensor fresh;
     if (!out) {
         fresh = at::empty(t[0]->sizes(), t[0]->options());
@@ -199,7 +200,7 @@ inline bool product(PyObject *const *a, PyObject *out, bool transposed, Product 
     if (p.Y->sizes() != at::IntArrayRef(y) || p.A->sizes() != p.X->sizes() || p.B->sizes() != p.Y->sizes() || p.C->sizes() != at::IntArrayRef(z))
         return false;
     p.out = nullptr;
-    if (out != Py_None && !(p.out = ring_tensor(out))) return false;
+    if (out != Py_None && (!(p.out = ring_tensor(out)) || p.out->numel() < p.C->numel())) return false;
     if (!p.out) {
         p.fresh = at::empty(p.C->sizes(), p.C->options());
         p.out = &p.fresh;

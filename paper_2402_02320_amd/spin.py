@@ -152,6 +152,19 @@ def _dev(t, name):
     return t.data_ptr()
 
 
+def _enough(out, words, exactly=False):
+    """Raises where the caller's `out` is not the size of the result: the kernels write that many words wherever it points.  A longer
+    one holds the result in front, except where the library reads the number of elements off it."""
+    if out.numel() < words or (exactly and out.numel() != words):
+        raise SpinError("out has %d words, the result %d" % (out.numel(), words))
+
+
+def _dev_out(t, name, words, exactly=False):
+    ptr = _dev(t, name)
+    _enough(t, words, exactly)
+    return ptr
+
+
 # The handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object around it, 2.6 us of the 6 to 9
 # a call takes on the host; the raw query takes 0.3 us.  Every call asks anew: streams are the caller's to change.
 if hasattr(torch._C, "_cuda_getCurrentRawStream"):
@@ -175,7 +188,7 @@ def share(x, n, seed, stream_id, out=None):
             return _done(r)
     if out is None:
         out = torch.empty((n,) + tuple(x.shape), dtype=torch.int64, device=x.device)
-    _check(lib().spin_share(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev(out, "shares"), _stream()))
+    _check(lib().spin_share(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev_out(out, "shares", n * x.numel()), _stream()))
     return out
 
 
@@ -190,7 +203,7 @@ def open(shares, mask=None, out=None):  # noqa: A001 - named after the C entry p
     if mask is not None and mask.shape != shares.shape:
         raise SpinError("mask must have the shape of shares")
     _check(lib().spin_open(_dev(shares, "shares"), None if mask is None else _dev(mask, "mask"),
-                           out.numel(), n, _dev(out, "out"), _stream()))
+                           out.numel(), n, _dev_out(out, "out", shares.numel() // (n or 1), True), _stream()))
     return out
 
 
@@ -262,7 +275,7 @@ def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_tra
         raise SpinError("workspace must be a contiguous CUDA tensor")
     call = lib().spin_beaver_matmul_nt if y_transposed else lib().spin_beaver_matmul
     _check_matmul(call(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"), _dev(C, "C"),
-                       _dev(out, "Z"), path, workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream()),
+                       _dev_out(out, "Z", C.numel()), path, workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream()),
                   beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
     return out
 
@@ -314,6 +327,7 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
         outs.append(out)
         d.batch, d.M, d.N, d.K = batch, M, N, K
         d.X, d.Y, d.A, d.B, d.C, d.Z = (_dev(t, k) for t, k in ((X, "X"), (Y, "Y"), (A, "A"), (B, "B"), (C, "C"), (out, "Z")))
+        _enough(out, C.numel())
         d.y_transposed = 1 if yt else 0
     L = lib()
     need = int(L.spin_beaver_matmul_grouped_workspace_bytes(n, len(groups), desc, path))
@@ -339,7 +353,7 @@ def beaver_mul(x, y, a, b, c, out=None):
     if out is None:
         out = torch.empty_like(x)
     _check(lib().spin_beaver_mul(n, x.numel() // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
-                                 _dev(c, "c"), _dev(out, "z"), _stream()))
+                                 _dev(c, "c"), _dev_out(out, "z", x.numel()), _stream()))
     return out
 
 
@@ -354,7 +368,7 @@ def beaver_mul_trunc(x, y, a, b, c, r, r_top, r_msb, f, out=None):
         out = torch.empty_like(x)
     _check(lib().spin_beaver_mul_trunc(n, x.numel() // (n or 1), f, _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
                                        _dev(c, "c"), _dev(r, "r"), _dev(r_top, "r_top"), _dev(r_msb, "r_msb"),
-                                       _dev(out, "out"), _stream()))
+                                       _dev_out(out, "out", x.numel()), _stream()))
     return out
 
 
@@ -368,7 +382,7 @@ def beaver_mul_bcast(x, y, a, b, c, over_inner, out=None):
     if out is None:
         out = torch.empty_like(y)
     _check(lib().spin_beaver_mul_bcast(n, outer, mid, inner, 1 if over_inner else 0, _dev(x, "x"), _dev(y, "y"),
-                                       _dev(a, "a"), _dev(b, "b"), _dev(c, "c"), _dev(out, "z"), _stream()))
+                                       _dev(a, "a"), _dev(b, "b"), _dev(c, "c"), _dev_out(out, "z", y.numel()), _stream()))
     return out
 
 
@@ -385,7 +399,7 @@ def trunc(x, r, r_top, r_msb, f, out=None):
     if out is None:
         out = torch.empty_like(x)
     _check(lib().spin_trunc(n, x.numel() // (n or 1), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
-                            _dev(r_msb, "r_msb"), _dev(out, "out"), _stream()))
+                            _dev(r_msb, "r_msb"), _dev_out(out, "out", x.numel()), _stream()))
     return out
 
 
@@ -396,7 +410,7 @@ def bshare(x, n, seed, stream_id, out=None):
             return _done(r)
     if out is None:
         out = torch.empty((n,) + tuple(x.shape), dtype=torch.int64, device=x.device)
-    _check(lib().spin_bshare(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev(out, "shares"), _stream()))
+    _check(lib().spin_bshare(_dev(x, "x"), x.numel(), n, seed, stream_id, _dev_out(out, "shares", n * x.numel()), _stream()))
     return out
 
 
@@ -411,7 +425,7 @@ def bopen(shares, mask=None, out=None):
     if mask is not None and mask.shape != shares.shape:
         raise SpinError("mask must have the shape of shares")
     _check(lib().spin_bopen(_dev(shares, "shares"), None if mask is None else _dev(mask, "mask"),
-                            out.numel(), n, _dev(out, "out"), _stream()))
+                            out.numel(), n, _dev_out(out, "out", shares.numel() // (n or 1), True), _stream()))
     return out
 
 
@@ -428,7 +442,7 @@ def beaver_and(x, y, a, b, c, out=None):
     if out is None:
         out = torch.empty_like(x)
     _check(lib().spin_beaver_and(n, x.numel() // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"), _dev(b, "b"),
-                                 _dev(c, "c"), _dev(out, "z"), _stream()))
+                                 _dev(c, "c"), _dev_out(out, "z", x.numel()), _stream()))
     return out
 
 
@@ -449,7 +463,7 @@ def lincomb_trunc(terms, coefs, constant=0, f=0, tuple_=None, out=None):
             if t.numel() != terms[0].numel():
                 raise SpinError("truncation tuple must have the shape of the terms")
     _check(lib().spin_lincomb_trunc(n, terms[0].numel() // (n or 1), len(terms), ptrs, cf, int(constant) % (1 << 64), f,
-                                    r, rt, rm, _dev(out, "out"), _stream()))
+                                    r, rt, rm, _dev_out(out, "out", terms[0].numel()), _stream()))
     return out
 
 
@@ -475,7 +489,7 @@ def completed_square_trunc(x, t3, t2, lin, t0, triples, tuples, f, out=None):
     u_ptr = six(*[_dev(t, "tuple") for t in (r0, rt0, rm0, r1, rt1, rm1)])
     const = [int(v) % (1 << 64) for v in (t3, t2, lin, t0)]
     _check(lib().spin_completed_square_trunc(x.shape[0], x.numel() // (x.shape[0] or 1), _dev(x, "x"), *const, t_ptr, u_ptr,
-                                             (ctypes.c_int * 2)(*f), _dev(out, "out"), _stream()))
+                                             (ctypes.c_int * 2)(*f), _dev_out(out, "out", x.numel()), _stream()))
     return out
 
 
@@ -493,7 +507,7 @@ class ring128:
     def share(x, n, seed, stream_id, out=None):
         if out is None:
             out = torch.empty((n,) + tuple(x.shape), dtype=torch.int64, device=x.device)
-        _check(lib().spin128_share(_dev(x, "x"), ring128._elems(x), n, seed, stream_id, _dev(out, "shares"), _stream()))
+        _check(lib().spin128_share(_dev(x, "x"), ring128._elems(x), n, seed, stream_id, _dev_out(out, "shares", n * x.numel()), _stream()))
         return out
 
     @staticmethod
@@ -502,7 +516,7 @@ class ring128:
         if out is None:
             out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
         _check(lib().spin128_open(_dev(shares, "shares"), None if mask is None else _dev(mask, "mask"),
-                                  ring128._elems(out), n, _dev(out, "out"), _stream()))
+                                  ring128._elems(out), n, _dev_out(out, "out", shares.numel() // (n or 1), True), _stream()))
         return out
 
     @staticmethod
@@ -526,7 +540,7 @@ class ring128:
             workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin128_beaver_matmul_workspace_bytes,
                                           lib().spin128_beaver_matmul_preferred_workspace_bytes, X.device)
         _check_matmul(lib().spin128_beaver_matmul(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"),
-                                                  _dev(C, "C"), _dev(out, "Z"), path, workspace.data_ptr(),
+                                                  _dev(C, "C"), _dev_out(out, "Z", C.numel()), path, workspace.data_ptr(),
                                                   workspace.numel() * workspace.element_size(), _stream()),
                       ring128.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
         return out
@@ -537,7 +551,7 @@ class ring128:
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin128_beaver_mul(n, ring128._elems(x) // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"),
-                                        _dev(b, "b"), _dev(c, "c"), _dev(out, "z"), _stream()))
+                                        _dev(b, "b"), _dev(c, "c"), _dev_out(out, "z", x.numel()), _stream()))
         return out
 
     @staticmethod
@@ -546,8 +560,14 @@ class ring128:
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin128_trunc(n, ring128._elems(x) // (n or 1), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
-                                   _dev(r_msb, "r_msb"), _dev(out, "out"), _stream()))
+                                   _dev(r_msb, "r_msb"), _dev_out(out, "out", x.numel()), _stream()))
         return out
+
+
+def _dev32_out(t, name, words, exactly=False):
+    ptr = _dev32(t, name)
+    _enough(t, words, exactly)
+    return ptr
 
 
 def _dev32(t, name):
@@ -565,14 +585,14 @@ class ring32:
         """Local Fixed64 -> Fixed32 cast: every party keeps the low half of its own share."""
         if out is None:
             out = torch.empty(tuple(shares.shape), dtype=torch.int32, device=shares.device)
-        _check(lib().spin_cast_64_to_32(_dev(shares, "shares"), shares.numel(), _dev32(out, "out"), _stream()))
+        _check(lib().spin_cast_64_to_32(_dev(shares, "shares"), shares.numel(), _dev32_out(out, "out", shares.numel()), _stream()))
         return out
 
     @staticmethod
     def share(x, n, seed, stream_id, out=None):
         if out is None:
             out = torch.empty((n,) + tuple(x.shape), dtype=torch.int32, device=x.device)
-        _check(lib().spin32_share(_dev32(x, "x"), x.numel(), n, seed, stream_id, _dev32(out, "shares"), _stream()))
+        _check(lib().spin32_share(_dev32(x, "x"), x.numel(), n, seed, stream_id, _dev32_out(out, "shares", n * x.numel()), _stream()))
         return out
 
     @staticmethod
@@ -583,7 +603,7 @@ class ring32:
         if mask is not None and mask.shape != shares.shape:
             raise SpinError("mask must have the shape of shares")
         _check(lib().spin32_open(_dev32(shares, "shares"), None if mask is None else _dev32(mask, "mask"),
-                                 out.numel(), n, _dev32(out, "out"), _stream()))
+                                 out.numel(), n, _dev32_out(out, "out", shares.numel() // (n or 1), True), _stream()))
         return out
 
     @staticmethod
@@ -608,7 +628,7 @@ class ring32:
             workspace = _matmul_workspace((n, batch, M, N, K), path, L.spin32_beaver_matmul_workspace_bytes,
                                           L.spin32_beaver_matmul_preferred_workspace_bytes, X.device)
         _check_matmul(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
-                                                 _dev32(B, "B"), _dev32(C, "C"), _dev32(out, "Z"), path,
+                                                 _dev32(B, "B"), _dev32(C, "C"), _dev32_out(out, "Z", C.numel()), path,
                                                  workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                                  _stream()),
                       ring32.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
@@ -620,7 +640,7 @@ class ring32:
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin32_beaver_mul(n, x.numel() // (n or 1), _dev32(x, "x"), _dev32(y, "y"), _dev32(a, "a"),
-                                       _dev32(b, "b"), _dev32(c, "c"), _dev32(out, "z"), _stream()))
+                                       _dev32(b, "b"), _dev32(c, "c"), _dev32_out(out, "z", x.numel()), _stream()))
         return out
 
     @staticmethod
@@ -629,7 +649,7 @@ class ring32:
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin32_trunc(n, x.numel() // (n or 1), f, _dev32(x, "x"), _dev32(r, "r"), _dev32(r_top, "r_top"),
-                                  _dev32(r_msb, "r_msb"), _dev32(out, "out"), _stream()))
+                                  _dev32(r_msb, "r_msb"), _dev32_out(out, "out", x.numel()), _stream()))
         return out
 
 
@@ -644,7 +664,7 @@ def probe_mfma(operands, blocks, iters, sink=None):
         raise SpinError("operands must hold 24 fragments of 128 words")
     if sink is None:
         sink = torch.empty(blocks * 256, dtype=torch.int64, device=operands.device)
-    _check(lib().spin_probe_mfma(_dev(operands, "operands"), blocks, iters, _dev(sink, "sink"), _stream()))
+    _check(lib().spin_probe_mfma(_dev(operands, "operands"), blocks, iters, _dev_out(sink, "sink", blocks * 256), _stream()))
     return sink
 
 

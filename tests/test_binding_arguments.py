@@ -1,0 +1,106 @@
+"""What the Python binding looks at before it hands a pointer to the library.  On the CPU, with a library in whose place every call is
+written down: a call that has to be refused must not reach it."""
+import pytest
+import torch
+
+from paper_2402_02320_amd import spin
+
+
+class Record:
+    """In place of the loaded library: every entry point returns `answers` of its name (0 otherwise) and is written down."""
+
+    def __init__(self, **answers):
+        self.answers, self.launched = answers, []
+
+    def __getattr__(self, name):
+        def entry(*args):
+            if not name.endswith(("_bytes", "_string", "_error")):
+                self.launched.append(name)
+            return self.answers.get(name, 1024 if name.endswith("_bytes") else b"" if name.endswith(("_string", "_error")) else 0)
+        return entry
+
+
+@pytest.fixture
+def record(monkeypatch):
+    r = Record()
+    monkeypatch.setattr(spin, "_lib", r)
+    monkeypatch.setattr(spin, "_fast", None)
+    monkeypatch.setattr(spin, "_dev", lambda t, name: t.data_ptr())
+    monkeypatch.setattr(spin, "_dev32", lambda t, name: t.data_ptr())
+    monkeypatch.setattr(spin, "_stream", lambda: 0)
+    return r
+
+
+class Workspace:
+    """A workspace that says it is on the GPU."""
+    is_cuda = True
+
+    def is_contiguous(self): return True
+    def data_ptr(self): return 256
+    def numel(self): return 1024
+    def element_size(self): return 1
+
+
+def w(*shape, words=1):
+    return torch.zeros(shape + ((2,) if words == 2 else ()), dtype=torch.int64)
+
+
+WS = Workspace()
+MM, MM2 = [w(2, 1, 4, 4)] * 5, [w(2, 1, 4, 4, words=2)] * 5
+# name -> words of the result, call with `out`
+CALLS = {
+    "share": (24, lambda o: spin.share(w(8), 3, 1, 1, out=o)),
+    "bshare": (24, lambda o: spin.bshare(w(8), 3, 1, 1, out=o)),
+    "mul": (24, lambda o: spin.beaver_mul(*[w(3, 8)] * 5, out=o)),
+    "and": (24, lambda o: spin.beaver_and(*[w(3, 8)] * 5, out=o)),
+    "mul_trunc": (24, lambda o: spin.beaver_mul_trunc(*[w(3, 8)] * 8, 16, out=o)),
+    "mul_bcast": (48, lambda o: spin.beaver_mul_bcast(w(3, 2, 4), w(3, 2, 4, 2), w(3, 2, 4), *[w(3, 2, 4, 2)] * 2, True, out=o)),
+    "trunc": (24, lambda o: spin.trunc(*[w(3, 8)] * 4, 16, out=o)),
+    "lincomb": (24, lambda o: spin.lincomb_trunc([w(3, 8)] * 2, [1, 2], out=o)),
+    "square": (24, lambda o: spin.completed_square_trunc(w(3, 8), 1, 2, 3, 4, [(w(3, 8),) * 3] * 2, [(w(3, 8),) * 3] * 2, (14, 15), out=o)),
+    "matmul": (32, lambda o: spin.beaver_matmul(*MM, out=o, workspace=WS)),
+    "grouped": (32, lambda o: spin.beaver_matmul_grouped([dict(zip("XYABC", MM)), dict(zip("XYABC", MM), out=o)], workspace=WS)),
+    "share128": (48, lambda o: spin.ring128.share(w(8, 2), 3, 1, 1, out=o)),
+    "mul128": (48, lambda o: spin.ring128.beaver_mul(*[w(3, 8, 2)] * 5, out=o)),
+    "trunc128": (48, lambda o: spin.ring128.trunc(*[w(3, 8, 2)] * 4, 16, out=o)),
+    "matmul128": (64, lambda o: spin.ring128.beaver_matmul(*MM2, out=o, workspace=WS)),
+    "cast32": (24, lambda o: spin.ring32.cast_from_64(w(3, 8), out=o)),
+    "share32": (24, lambda o: spin.ring32.share(w(8), 3, 1, 1, out=o)),
+    "mul32": (24, lambda o: spin.ring32.beaver_mul(*[w(3, 8)] * 5, out=o)),
+    "trunc32": (24, lambda o: spin.ring32.trunc(*[w(3, 8)] * 4, 16, out=o)),
+    "matmul32": (32, lambda o: spin.ring32.beaver_matmul(*MM, out=o, workspace=WS)),
+    "probe": (512, lambda o: spin.probe_mfma(w(24 * 128), 2, 1, sink=o)),
+}
+OPENS = {
+    "open": (8, lambda o: spin.open(w(3, 8), out=o)), "bopen": (8, lambda o: spin.bopen(w(3, 8), out=o)),
+    "open128": (16, lambda o: spin.ring128.open(w(3, 8, 2), out=o)), "open32": (8, lambda o: spin.ring32.open(w(3, 8), out=o)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CALLS) + sorted(OPENS))
+def test_an_out_that_is_too_short_reaches_no_kernel(name, record):
+    words, call = (CALLS.get(name) or OPENS[name])
+    two = 2 if name.endswith("128") else 1               # words of an element
+    for short in (words - two, two):
+        with pytest.raises(spin.SpinError):
+            call(w(short // two, words=two))
+    assert record.launched == []
+    call(w(words // two, words=two))
+    assert len(record.launched) == 1
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_a_longer_out_holds_the_result_in_front(name, record):
+    words, call = CALLS[name]
+    two = 2 if name.endswith("128") else 1
+    call(w(words // two + 1, words=two))
+    assert len(record.launched) == 1
+
+
+@pytest.mark.parametrize("name", sorted(OPENS))
+def test_a_longer_out_of_an_opening_would_read_past_the_shares(name, record):
+    words, call = OPENS[name]
+    two = 2 if name.endswith("128") else 1
+    with pytest.raises(spin.SpinError):
+        call(w(words // two + 1, words=two))
+    assert record.launched == []

@@ -90,3 +90,33 @@ def test_the_long_way_takes_the_rest():
     side.synchronize()
     assert torch.equal(z, want)
     assert np.array_equal(spin.open(x).cpu().numpy(), x.sum(0).cpu().numpy())
+
+
+OUTS = {"share": (192, lambda x, o: spin.share(x[0], 3, 1, 1, out=o)), "bshare": (192, lambda x, o: spin.bshare(x[0], 3, 1, 1, out=o)),
+        "open": (64, lambda x, o: spin.open(x, out=o)), "bopen": (64, lambda x, o: spin.bopen(x, x, out=o)),
+        "mul": (192, lambda x, o: spin.beaver_mul(x, x, x, x, x, out=o)), "and": (192, lambda x, o: spin.beaver_and(x, x, x, x, x, out=o)),
+        "trunc": (192, lambda x, o: spin.trunc(x, x, x, x, 16, out=o)),
+        "matmul": (192, lambda x, o: spin.beaver_matmul(*[x.view(3, 1, 8, 8)] * 5, out=o)),
+        "grouped": (192, lambda x, o: spin.beaver_matmul_grouped([dict(zip("XYABC", [x.view(3, 1, 8, 8)] * 5), out=o)])[0]),
+        "square": (192, lambda x, o: spin.completed_square_trunc(x, 1, 2, 3, 4, [(x,) * 3] * 2, [(x,) * 3] * 2, (14, 15), out=o))}
+
+
+@pytest.mark.parametrize("fast", [True, False])
+@pytest.mark.parametrize("name", sorted(OUTS))
+def test_out_of_another_size(name, fast, monkeypatch):
+    # refused on the host, before anything is launched, where it is too short (of an opening: of another size); a longer one holds the result in front
+    spin.lib()
+    if not fast:
+        monkeypatch.setattr(spin, "_fast", None)
+    words, call = OUTS[name]
+    x = u(3, 64)
+    with pytest.raises(spin.SpinError):
+        call(x, u(words - 1))
+    if name in ("open", "bopen"):
+        with pytest.raises(spin.SpinError):
+            call(x, u(words + 1))
+        return
+    longer = u(words + 7)
+    tail = longer[words:].clone()
+    assert call(x, longer) is longer
+    assert torch.equal(longer[:words], call(x, None).view(-1)) and torch.equal(longer[words:], tail)
