@@ -165,6 +165,19 @@ def _dev_out(t, name, words, exactly=False):
     return ptr
 
 
+def _workspace_ptr(t):
+    if not (t.is_cuda and t.is_contiguous()):
+        raise SpinError("workspace must be a contiguous CUDA tensor")
+    return t.data_ptr()
+
+
+def _same_words(x, *others):
+    """Raises where an operand of an elementwise call has another number of words than the first: the library takes one count for all."""
+    for t in others:
+        if t is not None and t.numel() != x.numel():
+            raise SpinError("inconsistent operand shapes")
+
+
 # The handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object around it, 2.6 us of the 6 to 9
 # a call takes on the host; the raw query takes 0.3 us.  Every call asks anew: streams are the caller's to change.
 if hasattr(torch._C, "_cuda_getCurrentRawStream"):
@@ -271,11 +284,9 @@ def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_tra
     if workspace is None:
         workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin_beaver_matmul_workspace_bytes,
                                       lib().spin_beaver_matmul_preferred_workspace_bytes, X.device)
-    if not (workspace.is_cuda and workspace.is_contiguous()):
-        raise SpinError("workspace must be a contiguous CUDA tensor")
     call = lib().spin_beaver_matmul_nt if y_transposed else lib().spin_beaver_matmul
     _check_matmul(call(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"), _dev(C, "C"),
-                       _dev_out(out, "Z", C.numel()), path, workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream()),
+                       _dev_out(out, "Z", C.numel()), path, _workspace_ptr(workspace), workspace.numel() * workspace.element_size(), _stream()),
                   beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
     return out
 
@@ -335,7 +346,7 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
         raise SpinError("invalid matmul dimensions")
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=outs[0].device)
-    _check(L.spin_beaver_matmul_grouped(n, len(groups), desc, path, workspace.data_ptr(),
+    _check(L.spin_beaver_matmul_grouped(n, len(groups), desc, path, _workspace_ptr(workspace),
                                         workspace.numel() * workspace.element_size(), _stream()))
     return outs
 
@@ -513,6 +524,7 @@ class ring128:
     @staticmethod
     def open(shares, mask=None, out=None):  # noqa: A003
         n = shares.shape[0]
+        _same_words(shares, mask)
         if out is None:
             out = torch.empty(tuple(shares.shape[1:]), dtype=torch.int64, device=shares.device)
         _check(lib().spin128_open(_dev(shares, "shares"), None if mask is None else _dev(mask, "mask"),
@@ -540,7 +552,7 @@ class ring128:
             workspace = _matmul_workspace((n, batch, M, N, K), path, lib().spin128_beaver_matmul_workspace_bytes,
                                           lib().spin128_beaver_matmul_preferred_workspace_bytes, X.device)
         _check_matmul(lib().spin128_beaver_matmul(n, batch, M, N, K, _dev(X, "X"), _dev(Y, "Y"), _dev(A, "A"), _dev(B, "B"),
-                                                  _dev(C, "C"), _dev_out(out, "Z", C.numel()), path, workspace.data_ptr(),
+                                                  _dev(C, "C"), _dev_out(out, "Z", C.numel()), path, _workspace_ptr(workspace),
                                                   workspace.numel() * workspace.element_size(), _stream()),
                       ring128.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
         return out
@@ -548,6 +560,7 @@ class ring128:
     @staticmethod
     def beaver_mul(x, y, a, b, c, out=None):
         n = x.shape[0]
+        _same_words(x, y, a, b, c)
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin128_beaver_mul(n, ring128._elems(x) // (n or 1), _dev(x, "x"), _dev(y, "y"), _dev(a, "a"),
@@ -557,6 +570,7 @@ class ring128:
     @staticmethod
     def trunc(x, r, r_top, r_msb, f, out=None):
         n = x.shape[0]
+        _same_words(x, r, r_top, r_msb)
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin128_trunc(n, ring128._elems(x) // (n or 1), f, _dev(x, "x"), _dev(r, "r"), _dev(r_top, "r_top"),
@@ -629,7 +643,7 @@ class ring32:
                                           L.spin32_beaver_matmul_preferred_workspace_bytes, X.device)
         _check_matmul(lib().spin32_beaver_matmul(n, batch, M, N, K, _dev32(X, "X"), _dev32(Y, "Y"), _dev32(A, "A"),
                                                  _dev32(B, "B"), _dev32(C, "C"), _dev32_out(out, "Z", C.numel()), path,
-                                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                                                 _workspace_ptr(workspace), workspace.numel() * workspace.element_size(),
                                                  _stream()),
                       ring32.beaver_matmul_workspace_bytes, n, batch, M, N, K, path)
         return out
@@ -637,6 +651,7 @@ class ring32:
     @staticmethod
     def beaver_mul(x, y, a, b, c, out=None):
         n = x.shape[0]
+        _same_words(x, y, a, b, c)
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin32_beaver_mul(n, x.numel() // (n or 1), _dev32(x, "x"), _dev32(y, "y"), _dev32(a, "a"),
@@ -646,6 +661,7 @@ class ring32:
     @staticmethod
     def trunc(x, r, r_top, r_msb, f, out=None):
         n = x.shape[0]
+        _same_words(x, r, r_top, r_msb)
         if out is None:
             out = torch.empty_like(x)
         _check(lib().spin32_trunc(n, x.numel() // (n or 1), f, _dev32(x, "x"), _dev32(r, "r"), _dev32(r_top, "r_top"),

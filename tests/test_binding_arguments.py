@@ -104,3 +104,35 @@ def test_a_longer_out_of_an_opening_would_read_past_the_shares(name, record):
     with pytest.raises(spin.SpinError):
         call(w(words // two + 1, words=two))
     assert record.launched == []
+
+
+def replaced(operands, i, other):
+    return operands[:i] + [other] + operands[i + 1:]
+
+
+@pytest.mark.parametrize("words", [14, 18])
+@pytest.mark.parametrize("ring,call,count", [(ring, call, count) for ring in ("ring128", "ring32") for call, count in (("beaver_mul", 5), ("trunc", 4))]
+                         + [("ring128", "open", 2), ("ring32", "open", 2)])
+def test_operands_of_another_size_reach_no_kernel(ring, call, count, words, record):
+    entry, two = getattr(getattr(spin, ring), call), 2 if ring == "ring128" else 1
+    more = [16] if call == "trunc" else []
+    same = [w(2, 8, words=two)] * count
+    for i in range(1, count):
+        with pytest.raises(spin.SpinError):
+            entry(*replaced(same, i, w(2, words // 2, words=two)), *more)
+    assert record.launched == []
+    entry(*same, *more)
+    assert len(record.launched) == 1
+
+
+@pytest.mark.parametrize("workspace", [torch.zeros(4096, dtype=torch.uint8), "expanded"])
+@pytest.mark.parametrize("call", [lambda ws: spin.beaver_matmul(*MM, workspace=ws),
+                                  lambda ws: spin.beaver_matmul_grouped([dict(zip("XYABC", MM))], workspace=ws),
+                                  lambda ws: spin.ring128.beaver_matmul(*MM2, workspace=ws), lambda ws: spin.ring32.beaver_matmul(*MM, workspace=ws)])
+def test_a_workspace_on_the_host_or_of_repeated_bytes_reaches_no_kernel(call, workspace, record, monkeypatch):
+    if isinstance(workspace, str):
+        workspace = Workspace()
+        monkeypatch.setattr(workspace, "is_contiguous", lambda: False, raising=False)
+    with pytest.raises(spin.SpinError):
+        call(workspace)
+    assert record.launched == []
