@@ -272,7 +272,9 @@ def beaver_matmul(X, Y, A, B, C, path=LIMB_MFMA, out=None, workspace=None, y_tra
     C: [n,batch,M,N] -> Z [n,batch,M,N]."""
     if _fast is not None:
         r = _fast.matmul(X, Y, A, B, C, path, out, workspace, y_transposed)
-        if r is not None and type(r) is not int:         # a refusal is worded below, after the same refusal there
+        if r is not None:
+            if type(r) is int:                           # never called again: a launch that failed may have added a part onto out
+                _check_matmul(r, beaver_matmul_workspace_bytes, *X.shape[:3], C.shape[3], X.shape[3], path)
             return r
     n, batch, M, K = X.shape
     N = Y.shape[2] if y_transposed else Y.shape[3]

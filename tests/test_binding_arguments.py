@@ -136,3 +136,29 @@ def test_a_workspace_on_the_host_or_of_repeated_bytes_reaches_no_kernel(call, wo
     with pytest.raises(spin.SpinError):
         call(workspace)
     assert record.launched == []
+
+
+@pytest.mark.parametrize("status", [1, 2, 3, 4])
+def test_a_call_that_failed_is_not_made_again(status, record, monkeypatch):
+    # a launch may fail with earlier ones of the same call under way, and out may be C: a second call would add their parts twice
+    class Failing:
+        @staticmethod
+        def matmul(*args):
+            return status
+    monkeypatch.setattr(spin, "_fast", Failing)
+    with pytest.raises(spin.SpinError):
+        spin.beaver_matmul(*MM, out=MM[4], workspace=WS)
+    assert record.launched == []
+
+
+def test_the_dimensions_of_a_refused_product_are_named(record, monkeypatch):
+    class Failing:
+        @staticmethod
+        def matmul(*args):
+            return 2
+    asked = []
+    monkeypatch.setattr(spin, "_fast", Failing)
+    monkeypatch.setattr(spin, "beaver_matmul_workspace_bytes", lambda *dims: asked.append(dims) or 0)
+    with pytest.raises(spin.SpinError, match="invalid matmul dimensions"):
+        spin.beaver_matmul(w(2, 3, 4, 5), w(2, 3, 5, 6), w(2, 3, 4, 5), w(2, 3, 5, 6), w(2, 3, 4, 6))
+    assert asked == [(2, 3, 4, 6, 5, spin.LIMB_MFMA)]
