@@ -37,15 +37,15 @@ def _run(cmd, verbose):
         print(out)
 
 
-def build_binding(verbose=False):
+def build_binding(verbose=False, source=os.path.join(CSRC, "binding.cpp"), target=BINDING):
     import sysconfig
     from torch.utils import cpp_extension
     dirs = cpp_extension.include_paths() + ["/opt/rocm/include", sysconfig.get_paths()["include"]]
     libs = cpp_extension.library_paths()
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
-         + [f for d in dirs for f in ("-isystem", d)] + [os.path.join(CSRC, "binding.cpp"), "-o", BINDING]
+         + [f for d in dirs for f in ("-isystem", d)] + [source, "-o", target]
          + [f for d in libs for f in ("-L" + d, "-Wl,-rpath," + d)] + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
-    return BINDING
+    return target
 
 
 def build(verbose=False, extra=(), jobs=None):

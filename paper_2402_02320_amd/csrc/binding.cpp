@@ -15,6 +15,7 @@
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <array>
 #include <vector>
@@ -68,14 +69,22 @@ inline bool parties(int64_t n) { return n >= 1 && n <= SPIN_MAX_PARTIES; }
 
 PyObject *none() { Py_RETURN_NONE; }
 
-// The call on torch's current stream, without the interpreter's lock (so it must not throw: tensors are asked for their pointers
-// before); the result, or the status as an int.
+// The interpreter's lock is given up for a library call, and taken again however that ends: guarded() answers exceptions with it.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+// The call on torch's current stream (which is asked for before: that may throw).
+template <class F> inline spin_status unlocked(F &&call)
+{
+    const spin_stream stream = (spin_stream)c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream();
+    const Unlocked scope;
+    return call(stream);
+}
+// The result, or the status as an int.
 template <class F> inline PyObject *run(const at::Tensor &result, F &&call)
 {
-    spin_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = call((spin_stream)c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream());
-    Py_END_ALLOW_THREADS
+    const spin_status st = unlocked(call);
     return st == SPIN_OK ? THPVariable_Wrap(result) : PyLong_FromLong(st);
 }
 
@@ -284,22 +293,16 @@ PyObject *grouped(PyObject *const *a, Py_ssize_t count)
         }
         void *space = ws->mutable_data_ptr();
         const size_t bytes = (size_t)ws->numel() * ws->element_size();
-        PyObject *list = PyList_New(groups);
+        THPObjectPtr list(PyList_New(groups));
         if (!list) return PyErr_Clear(), none();
         for (Py_ssize_t i = 0; i < groups; ++i) {
             PyObject *out = PyDict_GetItemWithError(PyList_GET_ITEM(a[0], i), keys[5]);
             PyObject *z = p[i].fresh.defined() ? THPVariable_Wrap(p[i].fresh) : Py_NewRef(out);
-            if (!z) return PyErr_Clear(), Py_DECREF(list), none();
-            PyList_SET_ITEM(list, i, z);
+            if (!z) return PyErr_Clear(), none();
+            PyList_SET_ITEM(list.get(), i, z);
         }
-        spin_status st;
-        Py_BEGIN_ALLOW_THREADS
-        st = lib.grouped(p[0].n, (int)groups, desc.data(), path, space, bytes,
-                         (spin_stream)c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream());
-        Py_END_ALLOW_THREADS
-        if (st == SPIN_OK) return list;
-        Py_DECREF(list);
-        return PyLong_FromLong(st);
+        const spin_status st = unlocked([&](spin_stream s) { return lib.grouped(p[0].n, (int)groups, desc.data(), path, space, bytes, s); });
+        return st == SPIN_OK ? list.release() : PyLong_FromLong(st);
     });
 }
 
