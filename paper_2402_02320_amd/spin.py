@@ -103,8 +103,8 @@ def lib():
         L.spin_status_string.argtypes = [i32]
         L.spin_status_string.restype = ctypes.c_char_p
         L.spin_last_hip_error.restype = ctypes.c_char_p
-        _lib = L
         _load_binding(L)
+        _lib = L                                         # last: a binding that does not load raises on every call
     return _lib
 
 
@@ -113,8 +113,11 @@ def _load_binding(L):
     if not os.path.exists(BINDING_PATH):
         raise SpinError("%s not found: build it with `python -m paper_2402_02320_amd.build`" % BINDING_PATH)
     spec = importlib.util.spec_from_file_location("_binding", BINDING_PATH)
-    binding = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(binding)
+    try:
+        binding = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(binding)
+    except ImportError as e:                             # built against another torch, above all
+        raise SpinError("%s does not load (build it anew with `python -m paper_2402_02320_amd.build`): %s" % (BINDING_PATH, e)) from e
     entries = ("share", "bshare", "open", "bopen", "beaver_mul", "beaver_and", "trunc", "beaver_matmul", "beaver_matmul_nt",
                "beaver_matmul_preferred_workspace_bytes", "beaver_matmul_grouped", "beaver_matmul_grouped_workspace_bytes",
                "completed_square_trunc")

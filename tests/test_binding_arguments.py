@@ -162,3 +162,16 @@ def test_the_dimensions_of_a_refused_product_are_named(record, monkeypatch):
     with pytest.raises(spin.SpinError, match="invalid matmul dimensions"):
         spin.beaver_matmul(w(2, 3, 4, 5), w(2, 3, 5, 6), w(2, 3, 4, 5), w(2, 3, 5, 6), w(2, 3, 4, 6))
     assert asked == [(2, 3, 4, 6, 5, spin.LIMB_MFMA)]
+
+
+@pytest.mark.parametrize("content", [None, b"not a shared object"])
+def test_a_binding_that_does_not_load_raises_every_time(content, monkeypatch, tmp_path):
+    if content is not None:
+        (tmp_path / "_binding.so").write_bytes(content)
+    monkeypatch.setattr(spin, "_lib", None)
+    monkeypatch.setattr(spin, "_fast", None)
+    monkeypatch.setattr(spin, "BINDING_PATH", str(tmp_path / "_binding.so"))
+    for _ in range(2):
+        with pytest.raises(spin.SpinError, match="_binding.so"):
+            spin.lib()
+    assert spin._lib is None and spin._fast is None
