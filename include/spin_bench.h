@@ -60,6 +60,36 @@ void spin_profile_reset(void);
 spin_status spin_probe_mfma(const uint64_t *operands, int blocks, int iters, uint64_t *sink,
                             spin_stream stream);
 
+/* The kernel that a matmul on the digit path (SPIN_GEMM_LIMB_MFMA) takes, and a matmul by a kernel that the caller names.  The calls of
+ * spin.h choose by estimated time; these two let a test or a measurement say what it runs, and leave the choice alone.
+ * parts: workgroups that share an output tile, 1 to 16 (tile kernels; 1 for the others). */
+typedef enum {
+    SPIN_WAY_DIRECT = 0,        /* one launch on the vector ALU */
+    SPIN_WAY_ROWS = 1,          /* row kernel: 64-bit words, at most three parties, K <= 16352 */
+    SPIN_WAY_FULL_TILES = 2,    /* tiles of 128 x 64 (64-bit words), 128 x 128 (32-bit) */
+    SPIN_WAY_HALF_TILES = 3,    /* 64 x 64, 64 x 128 */
+    SPIN_WAY_QUARTER_TILES = 4, /* 32-bit words: 64 x 64 */
+    SPIN_WAY_RESIDUES = 5,      /* residue GEMM, by the best plan for the workspace: 64-bit words */
+    SPIN_WAY_SEPARATE = 6       /* of a grouped call: one product after another */
+} spin_way_kernel;
+typedef struct { int kernel; int parts; } spin_matmul_way;
+
+/* What the library would take for a product of 32- or 64-bit words if its digit kernels and the direct one were all there are (the residue
+ * GEMM and the recursion over Z_2^32, where they are estimated to be faster, come before), and for the products of a grouped
+ * call.  Launches nothing and touches no pointer of desc. */
+spin_status spin_matmul_way_of(int word_bits, int n, int batch, int M, int N, int K, spin_matmul_way *way);
+spin_status spin_matmul_grouped_way_of(int n, int groups, const spin_matmul_group *desc, spin_matmul_way *way);
+
+/* spin_beaver_matmul (word_bits 64; spin_beaver_matmul_nt with y_transposed), spin32_beaver_matmul (32) and
+ * spin_beaver_matmul_grouped on the path SPIN_GEMM_LIMB_MFMA, with their arguments and workspaces, by `way` (SPIN_WAY_DIRECT and
+ * SPIN_WAY_SEPARATE are not among them).  SPIN_EINVAL: not a product of that kernel, or not so many parts of whole pairs of k-steps;
+ * SPIN_EWORKSPACE too where no plan of the residue GEMM fits; SPIN_ERANGE: not in one launch. */
+spin_status spin_matmul_by(spin_matmul_way way, int word_bits, int n, int batch, int M, int N, int K, const void *X, const void *Y,
+                           const void *A, const void *B, const void *C, void *Z, int y_transposed, void *workspace,
+                           size_t workspace_bytes, spin_stream stream);
+spin_status spin_matmul_grouped_by(spin_matmul_way way, int n, int groups, const spin_matmul_group *desc, void *workspace,
+                                   size_t workspace_bytes, spin_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -126,9 +126,13 @@ size_t valu_workspace_bytes(int n, int batch, int M, int N, int K, int elem_byte
 template <class T> spin_status launch_matmul_valu(const MatmulArgsT<T> &a, hipStream_t s);
 size_t limb_workspace_bytes(int n, int batch, int M, int N, int K);
 spin_status launch_matmul_limb(const MatmulArgs &a, hipStream_t s);
-// groups of different shapes in shared launches (a[g].workspace is ignored: every group gets its own part of `workspace`)
-size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a);
-spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s);
+// groups of different shapes in shared launches (a[g].workspace is ignored: every group gets its own part of `workspace`), by their own
+// choice or by `way`
+spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s, const spin_matmul_way *way = nullptr);
+// The choice among the digit kernels and the direct one, and a product by a named kernel (spin_bench.h).  T = u32 or u64
+template <class T> spin_matmul_way matmul_way(int n, int batch, int M, int N, int K);
+spin_matmul_way matmul_grouped_way(int n, int groups, const MatmulArgs *a);
+template <class T> spin_status launch_matmul_by(const MatmulArgsT<T> &a, const spin_matmul_way &way, hipStream_t s);
 // Ring multiply-adds below which the residue GEMM is not even estimated: it measured no faster than the digit kernels at
 // 2 x 512^3 (64-bit, 49.6 against 50.9 us) and 2 x 128^3 (128-bit, 52 against 48 us), and the estimate costs host time.
 constexpr double kResidueMinMacs64 = 4e8, kResidueMinMacs128 = 1e7;

@@ -852,6 +852,13 @@ template <class T, class F> inline auto with_shape(TileShape shape, F &&fn)
     return fn(GemmShape<T>());
 }
 
+// The row kernel takes products over Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may accumulate.
+inline bool rows_possible(int n, int batch, int M, const Plan &p)
+{
+    return n <= 3 && p.KT <= Ring<u64>::max_chunk_tiles && rows_grid(batch, M, p.tilesN) <= 0x7fffffffL;
+}
+constexpr int way_of_shape(TileShape shape) { return SPIN_WAY_FULL_TILES + (int)shape; }
+
 // Time of the row kernel in microseconds, with its pack and launches: a row item is 2 KT half steps and its start and end; the right
 // fragments (whole column tiles), the left operands and the outputs are streams.  A fit to 24 000 products of 5 us to 4 ms (1 to 3 parties;
 // batches to 300 entries, to 60 000 rows, sides from 1), within 6 % (rms).
@@ -918,8 +925,7 @@ template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const 
         }
     }
     if (!std::is_same<T, u64>::value) return r;
-    if (a.n > 3 || p.KT > Ring<u64>::max_chunk_tiles) return r;
-    if (rows_grid(a.batch, a.M, p.tilesN) > 0x7fffffffL) return r;
+    if (!rows_possible(a.n, a.batch, a.M, p)) return r;
     const double by_rows = rows_us<T>(a, p);
     const bool kept = a.n >= 2 && p.KT <= 5 && (by_rows <= (a.n == 3 ? 1.25 : 1.05) * r.us || (a.n == 3 && p.KT > 2 && rows_grid(a.batch, a.M, p.tilesN) <= 48));
     if (by_rows <= r.us || kept) r.rows = true, r.us = by_rows;
@@ -1084,22 +1090,19 @@ template <class Args, class Launch> inline spin_status launch_in_tables(const st
 
 }  // namespace
 
-// Which groups take the row kernel: all that can, or none.  The groups fill the chip together, so a call takes as long as its workgroups' share of
+// Rows or tiles, for all products of a call.  The groups fill the chip together, so a call takes as long as its workgroups' share of
 // it, or as its longest workgroup; half tiles are done sooner, and need their left operands packed.  In us, as in rows_us and tiles_us.  Six
 // attention products of three stages, by rows and by half tiles: 3 parties 33.1 : 28.4, at twice the batch entries 44.0 : 41.4, at five times 84.7 :
 // 87.2; 2 parties, twice 34.4 : 32.6, three times 37.7 : 38.7.  (With the rule for single products two of the six went to another launch:
 // 47.8 us.)  Calls of at most five k-tiles stay with the row kernel, as single products of few items do (digit_route).
-static std::vector<bool> grouped_rows(int n, int groups, const MatmulArgs *a)
+static bool grouped_by_rows(int n, int groups, const MatmulArgs *a)
 {
-    std::vector<bool> rows(groups, false);
-    if (n > 3) return rows;
     double row_work = 0, row_longest = 0, tile_work = 0, tile_longest = 0, packs = 0;
     int KT = 0;
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
         const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K), h = make_plan<u64, GemmShape<u64, 1, 1>>(n, m.batch, m.M, m.N, m.K);
-        rows[g] = rows_grid(m.batch, m.M, p.tilesN) <= 0x7fffffffL;
-        if (!rows[g]) continue;
+        if (!rows_possible(n, m.batch, m.M, p)) return false;
         const double item = (0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n, tile = (0.117 / 2 + 0.728) * 2 * p.KT + 0.132, left = 16e-6 * n * m.batch * (double)m.M * m.K;
         row_work += rows_grid(m.batch, m.M, p.tilesN) * item / compute_units() + 0.045 * left;
         row_longest = std::max(row_longest, item);
@@ -1108,76 +1111,102 @@ static std::vector<bool> grouped_rows(int n, int groups, const MatmulArgs *a)
         packs += 0.061 * left + 0.276e-6 * h.packA_bytes;
         KT = std::max(KT, p.KT);
     }
-    if (KT > 5 && std::max(tile_work, tile_longest) + packs < 0.97 * std::max(row_work, row_longest)) rows.assign(groups, false);
-    return rows;
+    return KT <= 5 || std::max(tile_work, tile_longest) + packs >= 0.97 * std::max(row_work, row_longest);
 }
 
-// Full or half tiles, for all tile products of a call: what they would take one after another, whole tiles.
-static TileShape grouped_shape(int n, int groups, const MatmulArgs *a, const std::vector<bool> &by_rows)
+// Full or half tiles, for all products of a call: what they would take one after another, whole tiles.
+static TileShape grouped_shape(int n, int groups, const MatmulArgs *a)
 {
     double full = 0, half = 0;
     for (int g = 0; g < groups; ++g) {
-        if (by_rows[g]) continue;
         full += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kFullTile, 1);
         half += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kHalfTile, 1);
     }
     return half < full ? kHalfTile : kFullTile;
 }
 
-size_t limb_grouped_workspace_bytes(int n, int groups, const MatmulArgs *a)
+struct GroupedWay { bool rows; TileShape shape; };       // rows: with the column tiles of a full tile
+static Plan grouped_plan(int n, const MatmulArgs &m, const GroupedWay &w)
 {
-    size_t sum = 0;
-    for (int g = 0; g < groups; ++g) sum += limb_workspace_bytes(n, a[g].batch, a[g].M, a[g].N, a[g].K);
-    return sum;
+    return with_shape<u64>(w.rows ? kFullTile : w.shape, [&](auto s) { return make_plan<u64, decltype(s)>(n, m.batch, m.M, m.N, m.K); });
+}
+// Workgroups of a group's packs and products.
+static unsigned long right_pack_blocks(const MatmulArgs &m, const Plan &p)
+{
+    return (unsigned long)(m.y_transposed ? pack_left_blocks<4>(p.nblkB, p.KT) : pack_right_blocks<4>(p.nblkB, p.KT)) * m.batch;
+}
+static unsigned long left_pack_blocks(const MatmulArgs &m, const Plan &p) { return (unsigned long)pack_left_blocks<4>(p.nblkA, p.KT) * m.batch; }
+static unsigned long grouped_blocks(int n, const MatmulArgs &m, const Plan &p, const GroupedWay &w)
+{
+    return w.rows ? (unsigned long)rows_grid(m.batch, m.M, p.tilesN) : (unsigned long)p.tilesM * p.tilesN * n * m.batch;
 }
 
-// Returns SPIN_ERANGE, before anything is launched, when a group cannot go into a shared launch (an inner dimension
-// that must be accumulated in several launches, or more workgroups than a grid holds); the caller then enqueues
-// the groups one after another.
-spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s)
+// Whether the groups can share launches: not an inner dimension that must be accumulated in several, nor more workgroups
+// than a grid holds.
+static bool grouped_fits(int n, int groups, const MatmulArgs *a, const GroupedWay &w)
 {
-    constexpr int WAVES = 4;
+    unsigned long packs = 0, gemms = 0;
+    for (int g = 0; g < groups; ++g) {
+        const Plan p = grouped_plan(n, a[g], w);
+        if (p.KT > Ring<u64>::max_chunk_tiles) return false;
+        packs += right_pack_blocks(a[g], p) + (w.rows ? 0 : left_pack_blocks(a[g], p));
+        gemms += grouped_blocks(n, a[g], p, w);
+    }
+    return packs <= 0x7fffffffUL && gemms <= 0x3fffffffUL;
+}
+
+// Rows or tiles as estimated, or as asked for; SPIN_EINVAL where that cannot be, SPIN_ERANGE where the groups cannot share launches.
+static spin_status grouped_way(int n, int groups, const MatmulArgs *a, const spin_matmul_way *asked, GroupedWay &w)
+{
+    if (asked == nullptr) {
+        w = GroupedWay{grouped_by_rows(n, groups, a), grouped_shape(n, groups, a)};
+    } else {
+        if (asked->parts != 1 || (asked->kernel != SPIN_WAY_ROWS && asked->kernel != SPIN_WAY_FULL_TILES && asked->kernel != SPIN_WAY_HALF_TILES)) return SPIN_EINVAL;
+        w = GroupedWay{asked->kernel == SPIN_WAY_ROWS, asked->kernel == SPIN_WAY_HALF_TILES ? kHalfTile : kFullTile};
+        for (int g = 0; g < groups; ++g)
+            if (w.rows && !rows_possible(n, a[g].batch, a[g].M, make_plan<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K))) return SPIN_EINVAL;
+    }
+    return grouped_fits(n, groups, a, w) ? SPIN_OK : SPIN_ERANGE;
+}
+
+spin_matmul_way matmul_grouped_way(int n, int groups, const MatmulArgs *a)
+{
+    GroupedWay w;
+    if (grouped_way(n, groups, a, nullptr, w) != SPIN_OK) return spin_matmul_way{SPIN_WAY_SEPARATE, 1};
+    return spin_matmul_way{w.rows ? (int)SPIN_WAY_ROWS : way_of_shape(w.shape), 1};
+}
+
+// Returns SPIN_ERANGE, before anything is launched, when the groups cannot share launches; the caller then enqueues
+// them one after another.
+spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, void *workspace, hipStream_t s, const spin_matmul_way *asked)
+{
+    GroupedWay way;
+    spin_status st = grouped_way(n, groups, a, asked, way);
+    if (st != SPIN_OK) return st;
     std::vector<GroupedPackSide> sides;
-    std::vector<unsigned> side_blocks, row_blocks, tile_blocks;
+    std::vector<unsigned> side_blocks, gemm_blocks;
     std::vector<RowGemmArgs> rows;
     std::vector<GemmArgs<u64>> tiles;
     char *ws = (char *)workspace;
-    const std::vector<bool> by_rows = grouped_rows(n, groups, a);
-    const TileShape shape = grouped_shape(n, groups, a, by_rows);
     for (int g = 0; g < groups; ++g) {
         const MatmulArgs &m = a[g];
-        // the row kernel's column tiles are a full tile's
-        const Plan p = by_rows[g] ? make_plan<u64>(n, m.batch, m.M, m.N, m.K) : with_shape<u64>(shape, [&](auto s) {
-            return make_plan<u64, decltype(s)>(n, m.batch, m.M, m.N, m.K);
-        });
-        if (p.KT > Ring<u64>::max_chunk_tiles) return SPIN_ERANGE;
+        const Plan p = grouped_plan(n, m, way);
         const int odd = m.K % 2;                         // rows not 16-byte aligned
         char *packA = ws, *packB = ws + p.packA_bytes;
         ws += p.packA_bytes + p.packB_bytes;
-        if (m.y_transposed) {
-            sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.N, m.K, p.nblkB, p.KT}, 2 + odd});
-            side_blocks.push_back(pack_left_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
-        } else {
-            sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT}, 4});
-            side_blocks.push_back(pack_right_blocks<WAVES>(p.nblkB, p.KT) * m.batch);
-        }
-        if (by_rows[g]) {
+        if (m.y_transposed) sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.N, m.K, p.nblkB, p.KT}, 2 + odd});
+        else sides.push_back({PackArgs<u64>{m.Y, m.B, packB, n, m.batch, m.K, m.N, p.nblkB, p.KT}, 4});
+        side_blocks.push_back((unsigned)right_pack_blocks(m, p));
+        if (way.rows) {
             rows.push_back(RowGemmArgs{m.X, m.A, packB, m.C, m.Z, m.batch, m.M, m.N, m.K, p.KT, p.tilesN});
-            row_blocks.push_back((unsigned)rows_grid(m.batch, m.M, p.tilesN));
         } else {
             sides.push_back({PackArgs<u64>{m.X, m.A, packA, n, m.batch, m.M, m.K, p.nblkA, p.KT}, odd});
-            side_blocks.push_back(pack_left_blocks<WAVES>(p.nblkA, p.KT) * m.batch);
+            side_blocks.push_back((unsigned)left_pack_blocks(m, p));
             tiles.push_back(GemmArgs<u64>{packA, packB, m.C, m.Z, n, m.batch, m.M, m.N, p.nblkA, p.nblkB, p.KT, 0, p.KT,
                                           p.tilesM, p.tilesN, 1, 2 * p.KT});
-            tile_blocks.push_back((unsigned)((long)p.tilesM * p.tilesN * n * m.batch));
         }
+        gemm_blocks.push_back((unsigned)grouped_blocks(n, m, p, way));
     }
-    for (const std::vector<unsigned> *v : {&side_blocks, &row_blocks, &tile_blocks}) {
-        unsigned long sum = 0;                           // a launch must fit a grid, the rows and the tiles together too
-        for (unsigned b : *v) sum += b;
-        if (sum > (v == &side_blocks ? 0x7fffffffUL : 0x3fffffffUL)) return SPIN_ERANGE;
-    }
-    spin_status st = SPIN_OK;
     for_party_count(n, [&](auto np) {
         constexpr int NP = decltype(np)::value;
         {
@@ -1189,27 +1218,25 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
             if (st != SPIN_OK) return;
         }
         constexpr int RP = NP <= 3 ? NP : 3;                 // groups reach the row kernel only when n <= 3
-        if (!rows.empty()) {
+        if (way.rows) {
             static OncePerDevice lds_allowed;
             auto kernel = limb_gemm_rows_grouped_kernel<RP>;
             st = allow_dynamic_lds((const void *)kernel, RowLds<RP>::bytes, lds_allowed);
             if (st != SPIN_OK) return;
             KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-            launch_in_tables(rows, row_blocks, [&](const GroupTable<RowGemmArgs> &t, unsigned total) {
+            launch_in_tables(rows, gemm_blocks, [&](const GroupTable<RowGemmArgs> &t, unsigned total) {
                 kernel<<<total, kRowThreads, RowLds<RP>::bytes, s>>>(t);
             });
             st = check_launch("spin_beaver_matmul_grouped(row gemm)");
-            if (st != SPIN_OK) return;
-        }
-        if (!tiles.empty()) {
-            with_shape<u64>(shape, [&](auto sh) {
+        } else {
+            with_shape<u64>(way.shape, [&](auto sh) {
                 using S = decltype(sh);
                 static OncePerDevice lds_allowed;
                 auto kernel = limb_gemm_grouped_kernel<u64, S>;
                 st = allow_dynamic_lds((const void *)kernel, S::lds_bytes, lds_allowed);
                 if (st != SPIN_OK) return;
                 KernelTimer timer(SPIN_KERNEL_GEMM_LIMB, s);
-                launch_in_tables(tiles, tile_blocks, [&](const GroupTable<GemmArgs<u64>> &t, unsigned total) {
+                launch_in_tables(tiles, gemm_blocks, [&](const GroupTable<GemmArgs<u64>> &t, unsigned total) {
                     kernel<<<total, 256, S::lds_bytes, s>>>(t);
                 });
             });
@@ -1220,8 +1247,46 @@ spin_status launch_matmul_limb_grouped(int n, int groups, const MatmulArgs *a, v
     return st;
 }
 
-namespace {
-}  // namespace
+template <class T> spin_matmul_way matmul_way(int n, int batch, int M, int N, int K)
+{
+    MatmulArgsT<T> a{};
+    a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
+    const Plan p = make_plan<T>(n, batch, M, N, K);
+    const DigitRoute r = digit_route<T>(a, p);
+    if (direct_applies(n, batch, M, N, K, sizeof(T), digit_cost_rough_us<T>(a, p), r.us)) return spin_matmul_way{SPIN_WAY_DIRECT, 1};
+    return r.rows ? spin_matmul_way{SPIN_WAY_ROWS, 1} : spin_matmul_way{way_of_shape(r.shape), r.splits};
+}
+template spin_matmul_way matmul_way<u32>(int, int, int, int, int);
+template spin_matmul_way matmul_way<u64>(int, int, int, int, int);
+
+template <class T> spin_status launch_matmul_by(const MatmulArgsT<T> &a, const spin_matmul_way &way, hipStream_t s)
+{
+    constexpr const char *where = "spin_matmul_by";
+    const Plan p = make_plan<T>(a.n, a.batch, a.M, a.N, a.K);
+    if (way.kernel >= SPIN_WAY_FULL_TILES && way.kernel < SPIN_WAY_FULL_TILES + shapes_of<T>) {
+        const int ktn = std::min(p.KT, Ring<T>::max_chunk_tiles);
+        if (way.parts < 1 || way.parts > 16 || way.parts > ktn || ceil_div(ktn, ceil_div(ktn, way.parts)) != way.parts) return SPIN_EINVAL;
+        return with_shape<T>((TileShape)(way.kernel - SPIN_WAY_FULL_TILES), [&](auto shape) {
+            using S = decltype(shape);
+            const Plan sp = make_plan<T, S>(a.n, a.batch, a.M, a.N, a.K);
+            if ((unsigned long)sp.tilesM * sp.tilesN * a.n * a.batch * way.parts > 0xffffffffUL / 256) return SPIN_ERANGE;
+            return launch_tiles<T, S>(a, way.parts, s, where, where);
+        });
+    }
+    if (way.parts != 1) return SPIN_EINVAL;
+    if constexpr (std::is_same<T, u64>::value) {
+        if (way.kernel == SPIN_WAY_ROWS)
+            return rows_possible(a.n, a.batch, a.M, p) ? launch_rows(a, p, (char *)a.workspace + p.packA_bytes, s, where, where) : SPIN_EINVAL;
+        if (way.kernel == SPIN_WAY_RESIDUES) {
+            bool taken = false;
+            const spin_status st = launch_matmul_residue<T>(a, HUGE_VAL, s, where, taken);
+            return taken ? st : SPIN_EWORKSPACE;
+        }
+    }
+    return SPIN_EINVAL;
+}
+template spin_status launch_matmul_by<u32>(const MatmulArgs32 &, const spin_matmul_way &, hipStream_t);
+template spin_status launch_matmul_by<u64>(const MatmulArgs &, const spin_matmul_way &, hipStream_t);
 
 size_t limb_workspace_bytes(int n, int batch, int M, int N, int K)
 {

@@ -214,12 +214,17 @@ size_t spin_beaver_matmul_grouped_workspace_bytes(int n, int groups, const spin_
     return path == SPIN_GEMM_LIMB_MFMA ? sum : largest;
 }
 
-spin_status spin_beaver_matmul_grouped(int n, int groups, const spin_matmul_group *desc, int path,
-                                       void *workspace, size_t workspace_bytes, spin_stream stream)
+static MatmulArgs group_args(int n, const spin_matmul_group &d)
+{
+    return MatmulArgs{n, d.batch, d.M, d.N, d.K, d.X, d.Y, d.A, d.B, d.C, d.Z, nullptr, 0, d.y_transposed != 0};
+}
+
+// Everything is checked before anything is launched.
+static spin_status check_grouped(int n, int groups, const spin_matmul_group *desc, int path, const void *workspace, size_t workspace_bytes)
 {
     if (desc == nullptr || groups < 1 || groups > SPIN_MAX_GROUPS) return SPIN_EINVAL;
     if (path != SPIN_GEMM_LIMB_MFMA && path != SPIN_GEMM_VALU) return SPIN_EINVAL;
-    for (int g = 0; g < groups; ++g) {                   // everything is checked before anything is launched
+    for (int g = 0; g < groups; ++g) {
         const spin_matmul_group &d = desc[g];
         if (bad_ptr(d.X) || bad_ptr(d.Y) || bad_ptr(d.A) || bad_ptr(d.B) || bad_ptr(d.C) || bad_ptr(d.Z)) return SPIN_EINVAL;
         spin_status st = check_matmul_dims(n, d.batch, d.M, d.N, d.K);
@@ -228,12 +233,17 @@ spin_status spin_beaver_matmul_grouped(int n, int groups, const spin_matmul_grou
     const size_t need = spin_beaver_matmul_grouped_workspace_bytes(n, groups, desc, path);
     if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0 || need == 0 || workspace_bytes < need)
         return SPIN_EWORKSPACE;
+    return SPIN_OK;
+}
+
+spin_status spin_beaver_matmul_grouped(int n, int groups, const spin_matmul_group *desc, int path,
+                                       void *workspace, size_t workspace_bytes, spin_stream stream)
+{
+    const spin_status checked = check_grouped(n, groups, desc, path, workspace, workspace_bytes);
+    if (checked != SPIN_OK) return checked;
     if (path == SPIN_GEMM_LIMB_MFMA) {
         MatmulArgs args[SPIN_MAX_GROUPS];
-        for (int g = 0; g < groups; ++g) {
-            const spin_matmul_group &d = desc[g];
-            args[g] = MatmulArgs{n, d.batch, d.M, d.N, d.K, d.X, d.Y, d.A, d.B, d.C, d.Z, nullptr, 0, d.y_transposed != 0};
-        }
+        for (int g = 0; g < groups; ++g) args[g] = group_args(n, desc[g]);
         const spin_status st = launch_matmul_limb_grouped(n, groups, args, workspace, (hipStream_t)stream);
         if (st != SPIN_ERANGE) return st;                // SPIN_ERANGE: a group does not fit a shared launch, nothing was launched
     }
@@ -596,6 +606,56 @@ spin_status spin_probe_mfma(const uint64_t *operands, int blocks, int iters, uin
     if (bad_ptr(operands) || bad_ptr(sink)) return SPIN_EINVAL;
     if (blocks < 1 || blocks > (1 << 20) || iters < 1 || iters > (1 << 20)) return SPIN_EINVAL;
     return launch_mfma_probe(operands, blocks, iters, sink, (hipStream_t)stream);
+}
+
+spin_status spin_matmul_way_of(int word_bits, int n, int batch, int M, int N, int K, spin_matmul_way *way)
+{
+    if (way == nullptr || (word_bits != 32 && word_bits != 64)) return SPIN_EINVAL;
+    const spin_status st = check_matmul_dims(n, batch, M, N, K);
+    if (st != SPIN_OK) return st;
+    *way = word_bits == 64 ? matmul_way<u64>(n, batch, M, N, K) : matmul_way<u32>(n, batch, M, N, K);
+    return SPIN_OK;
+}
+
+spin_status spin_matmul_grouped_way_of(int n, int groups, const spin_matmul_group *desc, spin_matmul_way *way)
+{
+    if (way == nullptr || desc == nullptr || groups < 1 || groups > SPIN_MAX_GROUPS) return SPIN_EINVAL;
+    MatmulArgs args[SPIN_MAX_GROUPS];
+    for (int g = 0; g < groups; ++g) {
+        const spin_status st = check_matmul_dims(n, desc[g].batch, desc[g].M, desc[g].N, desc[g].K);
+        if (st != SPIN_OK) return st;
+        args[g] = group_args(n, desc[g]);
+    }
+    *way = matmul_grouped_way(n, groups, args);
+    return SPIN_OK;
+}
+
+spin_status spin_matmul_by(spin_matmul_way way, int word_bits, int n, int batch, int M, int N, int K, const void *X, const void *Y,
+                           const void *A, const void *B, const void *C, void *Z, int y_transposed, void *workspace,
+                           size_t workspace_bytes, spin_stream stream)
+{
+    if ((word_bits != 32 && word_bits != 64) || (word_bits == 32 && y_transposed)) return SPIN_EINVAL;
+    if (bad_ptr(X) || bad_ptr(Y) || bad_ptr(A) || bad_ptr(B) || bad_ptr(C) || bad_ptr(Z)) return SPIN_EINVAL;
+    const spin_status st = check_matmul_dims(n, batch, M, N, K);
+    if (st != SPIN_OK) return st;
+    const size_t need = word_bits == 64 ? limb_workspace_bytes(n, batch, M, N, K) : limb32_workspace_bytes(n, batch, M, N, K);
+    if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return SPIN_EWORKSPACE;
+    auto go = [&](auto word) {
+        using T = decltype(word);
+        return launch_matmul_by<T>(MatmulArgsT<T>{n, batch, M, N, K, (const T *)X, (const T *)Y, (const T *)A, (const T *)B, (const T *)C, (T *)Z,
+                                                  workspace, workspace_bytes, y_transposed != 0}, way, (hipStream_t)stream);
+    };
+    return word_bits == 64 ? go(u64()) : go(u32());
+}
+
+spin_status spin_matmul_grouped_by(spin_matmul_way way, int n, int groups, const spin_matmul_group *desc, void *workspace,
+                                   size_t workspace_bytes, spin_stream stream)
+{
+    const spin_status st = check_grouped(n, groups, desc, SPIN_GEMM_LIMB_MFMA, workspace, workspace_bytes);
+    if (st != SPIN_OK) return st;
+    MatmulArgs args[SPIN_MAX_GROUPS];
+    for (int g = 0; g < groups; ++g) args[g] = group_args(n, desc[g]);
+    return launch_matmul_limb_grouped(n, groups, args, workspace, (hipStream_t)stream, &way);
 }
 
 const char *spin_status_string(int status)

@@ -98,6 +98,12 @@ def lib():
         for name in ("spin32_share", "spin32_open", "spin32_beaver_matmul", "spin32_beaver_mul", "spin32_trunc",
                      "spin_cast_64_to_32"):
             getattr(L, name).restype = i32
+        L.spin_matmul_way_of.argtypes = [i32] * 6 + [ctypes.POINTER(_MatmulWay)]
+        L.spin_matmul_grouped_way_of.argtypes = [i32, i32, p, ctypes.POINTER(_MatmulWay)]
+        L.spin_matmul_by.argtypes = [_MatmulWay] + [i32] * 6 + [p] * 6 + [i32, p, sz, p]
+        L.spin_matmul_grouped_by.argtypes = [_MatmulWay, i32, i32, p, p, sz, p]
+        for name in ("spin_matmul_way_of", "spin_matmul_grouped_way_of", "spin_matmul_by", "spin_matmul_grouped_by"):
+            getattr(L, name).restype = i32
         L.spin_probe_mfma.argtypes = [p, i32, i32, p, p]
         L.spin_probe_mfma.restype = i32
         L.spin_status_string.argtypes = [i32]
@@ -312,6 +318,10 @@ def beaver_matmul_static(X, Y, A, B, C, out, path=LIMB_MFMA):
     return out
 
 
+class _MatmulWay(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int), ("parts", ctypes.c_int)]
+
+
 class _MatmulGroup(ctypes.Structure):
     _fields_ = [("batch", ctypes.c_int), ("M", ctypes.c_int), ("N", ctypes.c_int), ("K", ctypes.c_int),
                 ("X", ctypes.c_void_p), ("Y", ctypes.c_void_p), ("A", ctypes.c_void_p), ("B", ctypes.c_void_p),
@@ -325,6 +335,20 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
         r = _fast.grouped(groups, path, workspace)
         if r is not None:
             return _done(r)
+    n, desc, outs = _descriptors(groups)
+    L = lib()
+    need = int(L.spin_beaver_matmul_grouped_workspace_bytes(n, len(groups), desc, path))
+    if need == 0:
+        raise SpinError("invalid matmul dimensions")
+    if workspace is None:
+        workspace = torch.empty(need, dtype=torch.uint8, device=outs[0].device)
+    _check(L.spin_beaver_matmul_grouped(n, len(groups), desc, path, _workspace_ptr(workspace),
+                                        workspace.numel() * workspace.element_size(), _stream()))
+    return outs
+
+
+def _descriptors(groups):
+    """The party count, the library's description of the groups and their results."""
     n = groups[0]["X"].shape[0]
     desc = (_MatmulGroup * len(groups))()
     outs = []
@@ -345,15 +369,7 @@ def beaver_matmul_grouped(groups, path=LIMB_MFMA, workspace=None):
         d.X, d.Y, d.A, d.B, d.C, d.Z = (_dev(t, k) for t, k in ((X, "X"), (Y, "Y"), (A, "A"), (B, "B"), (C, "C"), (out, "Z")))
         _enough(out, C.numel())
         d.y_transposed = 1 if yt else 0
-    L = lib()
-    need = int(L.spin_beaver_matmul_grouped_workspace_bytes(n, len(groups), desc, path))
-    if need == 0:
-        raise SpinError("invalid matmul dimensions")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=outs[0].device)
-    _check(L.spin_beaver_matmul_grouped(n, len(groups), desc, path, _workspace_ptr(workspace),
-                                        workspace.numel() * workspace.element_size(), _stream()))
-    return outs
+    return n, desc, outs
 
 
 def beaver_mul(x, y, a, b, c, out=None):
@@ -690,6 +706,59 @@ def probe_mfma(operands, blocks, iters, sink=None):
 
 
 PROBE_OPS_PER_WAVE_ITERATION = 72 * 65536      # 72 MFMAs of 32x32x32 multiply-adds, two operations each
+
+
+# Kernels by name (spin_bench.h): what a matmul would take, and a matmul by the one that is named, for tests and measurements.
+WAYS = {"direct": 0, "rows": 1, "full": 2, "half": 3, "quarter": 4, "residues": 5, "separate": 6}
+_WAY_NAMES = {v: k for k, v in WAYS.items()}
+
+
+def matmul_way(n, batch, M, N, K, bits=64):
+    """(name, parts) of the kernel among the digit kernels and the direct one; needs no GPU."""
+    way = _MatmulWay()
+    _check(lib().spin_matmul_way_of(bits, n, batch, M, N, K, ctypes.byref(way)))
+    return _WAY_NAMES[way.kernel], way.parts
+
+
+def matmul_grouped_way(n, shapes):
+    """The name of the kernel that a grouped call takes; shapes: (batch, M, N, K) or (batch, M, N, K, y_transposed).  Needs no GPU."""
+    desc = (_MatmulGroup * len(shapes))()
+    for d, s in zip(desc, shapes):
+        d.batch, d.M, d.N, d.K = s[:4]
+        d.y_transposed = 1 if len(s) > 4 and s[4] else 0
+    way = _MatmulWay()
+    _check(lib().spin_matmul_grouped_way_of(n, len(shapes), desc, ctypes.byref(way)))
+    return _WAY_NAMES[way.kernel]
+
+
+def beaver_matmul_by(name, parts, X, Y, A, B, C, out=None, workspace=None, y_transposed=False):
+    """beaver_matmul (or, of int32 tensors, ring32.beaver_matmul) by the named kernel."""
+    n, batch, M, K = X.shape
+    N = C.shape[3]
+    if tuple(Y.shape) != ((n, batch, N, K) if y_transposed else (n, batch, K, N)) or A.shape != X.shape or B.shape != Y.shape \
+            or tuple(C.shape) != (n, batch, M, N):
+        raise SpinError("inconsistent operand shapes")
+    bits, dev, dev_out = (64, _dev, _dev_out) if X.dtype == torch.int64 else (32, _dev32, _dev32_out)
+    if out is None:
+        out = torch.empty_like(C)
+    if workspace is None:
+        need = (beaver_matmul_workspace_bytes if bits == 64 else ring32.beaver_matmul_workspace_bytes)(n, batch, M, N, K)
+        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+    _check(lib().spin_matmul_by(_MatmulWay(WAYS[name], parts), bits, n, batch, M, N, K, dev(X, "X"), dev(Y, "Y"), dev(A, "A"), dev(B, "B"),
+                                dev(C, "C"), dev_out(out, "Z", C.numel()), 1 if y_transposed else 0, _workspace_ptr(workspace),
+                                workspace.numel() * workspace.element_size(), _stream()))
+    return out
+
+
+def beaver_matmul_grouped_by(name, groups, workspace=None):
+    """beaver_matmul_grouped with all products by the named kernel: rows, full or half tiles."""
+    n, desc, outs = _descriptors(groups)
+    if workspace is None:
+        need = int(lib().spin_beaver_matmul_grouped_workspace_bytes(n, len(groups), desc, LIMB_MFMA))
+        workspace = torch.empty(need, dtype=torch.uint8, device=outs[0].device)
+    _check(lib().spin_matmul_grouped_by(_MatmulWay(WAYS[name], 1), n, len(groups), desc, _workspace_ptr(workspace),
+                                        workspace.numel() * workspace.element_size(), _stream()))
+    return outs
 
 
 def profile_enable(on=True):

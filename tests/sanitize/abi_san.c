@@ -77,6 +77,22 @@ int main(void)
         desc[5].Z = NULL;
         EXPECT(spin_beaver_matmul_grouped(3, SPIN_MAX_GROUPS, desc, SPIN_GEMM_VALU, ok, 1 << 30, NULL), SPIN_EINVAL);
     }
+    {   /* products by a named kernel */
+        spin_matmul_way rows = {SPIN_WAY_ROWS, 1}, half = {SPIN_WAY_HALF_TILES, 99}, none = {77, 1}, got;
+        spin_matmul_group d = {1, 8, 8, 8, ok, ok, ok, ok, ok, ok, 0};
+        EXPECT(spin_matmul_by(rows, 64, 4, 1, 8, 8, 8, ok, ok, ok, ok, ok, ok, 0, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_by(half, 64, 4, 1, 8, 8, 8, ok, ok, ok, ok, ok, ok, 0, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_by(none, 32, 4, 1, 8, 8, 8, ok, ok, ok, ok, ok, ok, 0, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_by(rows, 64, 2, 1, 8, 8, 8, ok, odd, ok, ok, ok, ok, 0, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_by(rows, 64, 2, 1, 8, 8, 8, ok, ok, ok, ok, ok, ok, 0, ok, 16, NULL), SPIN_EWORKSPACE);
+        EXPECT(spin_matmul_grouped_by(none, 2, 1, &d, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_grouped_by(rows, 2, 0, &d, ok, 1 << 30, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_way_of(64, 2, 1, 8, 0, 8, &got), SPIN_EINVAL);
+        EXPECT(spin_matmul_way_of(64, 2, 1, 8, 8, 8, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_way_of(64, 2, 1, 8, 8, 8, &got), SPIN_OK);
+        EXPECT(spin_matmul_grouped_way_of(2, 1, &d, NULL), SPIN_EINVAL);
+        EXPECT(spin_matmul_grouped_way_of(2, 1, &d, &got), SPIN_OK);
+    }
     {   /* linear combination: host arrays of pointers and coefficients of every length */
         const uint64_t *in[SPIN_MAX_TERMS + 1];
         uint64_t coef[SPIN_MAX_TERMS + 1];

@@ -181,3 +181,44 @@ def test_validation_of_the_grouped_matmul(L):
     desc[1].K = 8
     desc[1].Z = None
     assert f(2, 2, desc, 0, ws, 1 << 30, None) == EINVAL
+
+
+def test_validation_of_products_by_a_named_kernel(L):
+    from paper_2402_02320_amd.spin import _MatmulGroup, _MatmulWay
+    fake, odd, EINVAL, ERANGE, EWORKSPACE = 0x10000, 0x10008, 1, 2, 3
+    ptrs = [fake] * 6
+
+    def by(kernel, parts, bits, dims, p=ptrs, transposed=0, ws=fake, size=1 << 40):
+        return L.spin_matmul_by(_MatmulWay(kernel, parts), bits, *dims, *p, transposed, ws, size, None)
+    dims = (2, 1, 100, 100, 200)                             # seven k-tiles
+    rows, full, half, quarter, residues = 1, 2, 3, 4, 5
+    for kernel in (0, 6, 7, -1):                             # the direct kernel, and what is no kernel
+        assert by(kernel, 1, 64, dims) == EINVAL
+    assert by(quarter, 1, 64, dims) == by(rows, 1, 32, dims) == by(residues, 1, 32, dims) == EINVAL
+    assert by(rows, 2, 64, dims) == by(residues, 2, 64, dims) == EINVAL
+    for parts in (0, -1, 5, 6, 8, 17):                       # five and six parts of seven k-tiles are four
+        assert by(half, parts, 64, dims) == by(full, parts, 32, dims) == EINVAL
+    assert by(rows, 1, 64, (4, 1, 100, 100, 200)) == by(rows, 1, 64, (2, 1, 100, 100, 511 * 32 + 1)) == EINVAL
+    assert by(full, 1, 48, dims) == by(full, 1, 32, dims, transposed=1) == by(full, 1, 64, (9, 1, 1, 1, 1)) == EINVAL
+    for i in range(6):
+        for bad in (None, odd):
+            assert by(full, 1, 64, dims, ptrs[:i] + [bad] + ptrs[i + 1:]) == EINVAL
+    assert by(full, 1, 64, dims, size=16) == by(full, 1, 64, dims, ws=None) == by(full, 1, 64, dims, ws=fake + 16) == EWORKSPACE
+    assert by(residues, 1, 64, dims, size=L.spin_beaver_matmul_workspace_bytes(*dims, 0)) == EWORKSPACE         # no plan of 256-row panels fits
+    assert by(full, 1, 64, (1, 1, 1 << 25, 1, 1)) == ERANGE
+    way = _MatmulWay()
+    for bits, d in ((48, dims), (64, (0,) + dims[1:])):
+        assert L.spin_matmul_way_of(bits, *d, ctypes.byref(way)) == EINVAL
+    desc = (_MatmulGroup * 2)()
+    for d in desc:
+        d.batch, d.M, d.N, d.K = 1, 100, 100, 200
+        d.X = d.Y = d.A = d.B = d.C = d.Z = fake
+    grouped = L.spin_matmul_grouped_by
+    for kernel in (0, quarter, residues, 6):
+        assert grouped(_MatmulWay(kernel, 1), 2, 2, desc, fake, 1 << 40, None) == EINVAL
+    assert grouped(_MatmulWay(half, 2), 2, 2, desc, fake, 1 << 40, None) == grouped(_MatmulWay(rows, 1), 4, 2, desc, fake, 1 << 40, None) == EINVAL
+    assert grouped(_MatmulWay(half, 1), 2, 2, desc, fake, 16, None) == EWORKSPACE
+    assert L.spin_matmul_grouped_way_of(2, 0, desc, ctypes.byref(way)) == L.spin_matmul_grouped_way_of(2, 2, None, ctypes.byref(way)) == EINVAL
+    desc[1].K = 511 * 32 + 1                                 # accumulated in two launches: not in a shared one
+    assert grouped(_MatmulWay(half, 1), 2, 2, desc, fake, 1 << 40, None) == ERANGE
+    assert L.spin_matmul_grouped_way_of(2, 2, desc, ctypes.byref(way)) == 0 and way.kernel == 6
