@@ -1141,8 +1141,8 @@ static unsigned long grouped_blocks(int n, const MatmulArgs &m, const Plan &p, c
     return w.rows ? (unsigned long)rows_grid(m.batch, m.M, p.tilesN) : (unsigned long)p.tilesM * p.tilesN * n * m.batch;
 }
 
-// Whether the groups can share launches: not an inner dimension that must be accumulated in several, nor more workgroups
-// than a grid holds.
+// Whether the groups can share launches: not an inner dimension that must be accumulated in several, nor more threads
+// than a grid holds (2^32 - 1; a row product's M of 2^24 in 16 batch entries is past it).
 static bool grouped_fits(int n, int groups, const MatmulArgs *a, const GroupedWay &w)
 {
     unsigned long packs = 0, gemms = 0;
@@ -1152,7 +1152,8 @@ static bool grouped_fits(int n, int groups, const MatmulArgs *a, const GroupedWa
         packs += right_pack_blocks(a[g], p) + (w.rows ? 0 : left_pack_blocks(a[g], p));
         gemms += grouped_blocks(n, a[g], p, w);
     }
-    return packs <= 0x7fffffffUL && gemms <= 0x3fffffffUL;
+    constexpr unsigned long most = 0xffffffffUL;
+    return packs <= most / 256 && gemms <= most / (w.rows ? kRowThreads : 256);
 }
 
 // Rows or tiles as estimated, or as asked for; SPIN_EINVAL where that cannot be, SPIN_ERANGE where the groups cannot share launches.

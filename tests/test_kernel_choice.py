@@ -44,3 +44,11 @@ def test_no_workspace_of_gigabytes_for_a_hundredth():
     assert spin.beaver_matmul_workspace_bytes(5, 1, 4096, 4096, 4096) < q(5, 1, 4096, 4096, 4096) < 4e9
     assert spin.beaver_matmul_workspace_bytes(3, 1, 4096, 4096, 2048) < q(3, 1, 4096, 4096, 2048) < 1e9
     assert spin.ring128.beaver_matmul_preferred_workspace_bytes(2, 1, 2048, 2048, 2048) > 1e9     # 4 % faster than in 0.75 GB
+
+
+@pytest.mark.parametrize("n,batch,M,together", [(1, 15, 1 << 24, True), (1, 16, 1 << 24, False), (1, 16, (1 << 24) - 32, True), (1, 16, (1 << 24) - 31, False),
+                                                (3, 17, 1 << 24, False)])
+def test_a_grouped_call_of_more_threads_than_a_grid_holds_is_taken_apart(n, batch, M, together):
+    # one workgroup of 512 threads to 32 rows: 2^23 of them are a grid of 2^32 threads, which HIP refuses
+    assert (spin.matmul_grouped_way(n, [(batch, M, 1, 1)]) == "rows") is together
+    assert (spin.matmul_grouped_way(n, [(batch, M, 1, 1), (1, 8, 8, 8)]) == "rows") is together
