@@ -81,8 +81,8 @@ spin_status spin_matmul_way_of(int word_bits, int n, int batch, int M, int N, in
 spin_status spin_matmul_grouped_way_of(int n, int groups, const spin_matmul_group *desc, spin_matmul_way *way);
 
 /* spin_beaver_matmul (word_bits 64; spin_beaver_matmul_nt with y_transposed), spin32_beaver_matmul (32) and
- * spin_beaver_matmul_grouped on the path SPIN_GEMM_LIMB_MFMA, with their arguments and workspaces, by `way` (SPIN_WAY_DIRECT and
- * SPIN_WAY_SEPARATE are not among them).  SPIN_EINVAL: not a product of that kernel, or not so many parts of whole pairs of k-steps;
+ * spin_beaver_matmul_grouped on the path SPIN_GEMM_LIMB_MFMA, with their arguments and workspaces, by `way` (not
+ * SPIN_WAY_SEPARATE, nor SPIN_WAY_DIRECT for a grouped call).  SPIN_EINVAL: not a product of that kernel, or not so many parts of whole pairs of k-steps;
  * SPIN_EWORKSPACE too where no plan of the residue GEMM fits; SPIN_ERANGE: not in one launch. */
 spin_status spin_matmul_by(spin_matmul_way way, int word_bits, int n, int batch, int M, int N, int K, const void *X, const void *Y,
                            const void *A, const void *B, const void *C, void *Z, int y_transposed, void *workspace,

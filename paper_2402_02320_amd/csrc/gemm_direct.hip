@@ -122,7 +122,9 @@ __global__ __launch_bounds__(256) void direct_matmul_kernel(DirectArgs<T> g)
 // MB) has to be read anew by every tile that wants it.  Fits to 12 500 products that the rough estimate takes, within 10 % (rms), and
 // 7 to 10 % on the digit side.  Out of 22 000 products near the line the rough estimate alone takes these by more than 2 % wrongly:
 // 352 over Z_2^32 (up to 2.8 times: 5 parties, batch 61, 6 x 943 x 228, 1014 us against 362), 77 over Z_2^64 (1.8 times: 7 parties,
-// batch 19, 13 x 476 x 43, 135 against 74), 10 over Z_2^128; wide and batched products above all.  With both it is 76, 45 and 2.
+// batch 19, 13 x 476 x 43, 135 against 74), 10 over Z_2^128; wide and batched products above all.  With both it is 76, 45 and 2.  The line lies 3 % to the side of the digit kernels
+// over Z_2^32 and Z_2^128 and 2 % to this one's over Z_2^64, whose digit estimates are later ones: 7470 products there, this kernel among the ways,
+// cost 0.63 % against always the fastest (0.69 at a line of 0.97).
 //
 // Measured, this against the limb path: 3 parties 64^3 5.7 : 18.8 us, 128^3 9.7 : 23.8, 256 x 256 x 64 10.4 : 19.6; left to the limb
 // path: 256^3 30.9 : 25.4, 2 parties 64 x 64 x 512 24.8 : 21.9, 3 parties 512 x 512 x 32 29.2 : 17.7.  Over Z_2^128 long inner
@@ -150,7 +152,7 @@ bool direct_applies(int n, int batch, int M, int N, int K, int elem_bytes, doubl
     const double missed = slab_mb > c.slab_mb ? 1 - c.slab_mb / slab_mb : 0;
     const double us = c.launch + rounds * (c.round + c.round_party * n + (c.share + c.share_party * n) * (1 + c.alone) * tiles / 256) +
                       missed * read_mb / c.mb_per_us;
-    return us < 0.97 * digits_us;
+    return us < (elem_bytes == 8 ? 1.02 : 0.97) * digits_us;
 }
 
 template <class T> spin_status launch_matmul_direct(const MatmulArgsT<T> &a, hipStream_t s, const char *where)

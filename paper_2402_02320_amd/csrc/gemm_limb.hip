@@ -859,118 +859,106 @@ inline bool rows_possible(int n, int batch, int M, const Plan &p)
 }
 constexpr int way_of_shape(TileShape shape) { return SPIN_WAY_FULL_TILES + (int)shape; }
 
-// Time of the row kernel in microseconds, with its pack and launches: a row item is 2 KT half steps and its start and end; the right
-// fragments (whole column tiles), the left operands and the outputs are streams.  A fit to 24 000 products of 5 us to 4 ms (1 to 3 parties;
-// batches to 300 entries, to 60 000 rows, sides from 1), within 6 % (rms).
-template <class T> inline double rows_us(const MatmulArgsT<T> &a, const Plan &p)
+// Estimated times, in microseconds, of a whole call by each kernel: its packs as streams, its launches and its workgroups.  A row item is 2 KT
+// half steps (and the waits of the tile that pads an odd KT) and its start and end; its left operands are read once a column tile, from L2 after
+// the first, its right fragments once a row block, and where K is odd the rows are loaded word by word.  Outputs of partly filled column tiles
+// are stored one by one.  Long calls bring the clock down.  A fit to 4760 products of up to 1.6 times the fastest way's time (1 to 3 parties, 8
+// us to 10 ms, sides from 1), within 6.0 % (rms).
+inline double row_item_us(int n, int KT) { return (0.1605 + 0.3347 * n) * 2 * KT + 1.217 + 0.352 * n + (KT % 2 ? 0.376 + 0.2475 * n : 0); }
+inline double rows_us(int n, int batch, int M, int N, int K, int cus)
 {
-    const int cus = compute_units();
-    const double rounds = (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus), n = a.n;
-    const double written_mb = 8e-6 * (n + 1) * a.batch * p.tilesN * 64.0 * p.KT * 32, left_mb = 16e-6 * n * a.batch * (double)a.M * a.K;
-    const double out_mb = 16e-6 * n * a.batch * (double)a.M * a.N;
-    return 5.58 + 1.51 * n + rounds * ((0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n) + 0.326 * written_mb + 0.045 * left_mb + 0.104 * out_mb;
+    const int KT = ceil_div(K, 32), tilesN = ceil_div(N, 64);
+    const double rounds = (double)((rows_grid(batch, M, tilesN) + cus - 1) / cus), mb = 16e-6 * n * batch;
+    const double left_mb = mb * M * K, right_mb = mb * N * K, out_mb = mb * M * N, written_mb = 8e-6 * (n + 1) * batch * tilesN * 64.0 * KT * 32;
+    return 4.72 + 1.805 * n + rounds * row_item_us(n, KT) + 0.051 * n * std::max(0.0, rounds * 2 * KT - 125) + 0.260 * written_mb +
+           (0.0454 + (K % 2 ? 0.0367 : 0) + 0.0563 * (tilesN - 1)) * left_mb + 0.1195 * right_mb + (0.0662 + (N % 64 ? 0.0212 : 0)) * out_mb;
 }
 // The same of the tile kernel by one of its shapes, `splits` workgroups to a tile, each of which adds its part onto Z (the words of Z once more a
 // part, and those of C before).  The busiest CU has `most` workgroups; they take their k-steps together as far as its registers and LDS hold several,
-// rounds of that many otherwise, and long calls bring the clock down.  Operands are read as they are and written in whole tiles.  Fits to 76 000 timings
-// of full, 71 000 of half tiles over Z_2^64 and 91 000, 84 000 and 78 000 over Z_2^32 (5 us to 4 ms, 1 to 6 parties, 1 to 16 parts): within
-// 7.0, 8.2, 7.1, 8.5 and 9.1 % (rms).  (With the parts' additions counted once, 4 parties 192 x 224 x 1504 took 16 parts, not 5: 10 % slower.)
+// rounds of that many otherwise, and long calls bring the clock down.  Operands are read as they are and written in whole tiles.  Fits to 16 300 timings
+// of full and 17 300 of half tiles over Z_2^64 that are within twice the best way's (7 us to 10 ms, 1 to 8 parties, 1 to 16 parts), within 7.0 and 8.4 %
+// (rms), and to 91 000, 84 000 and 78 000 over Z_2^32 (5 us to 4 ms, 1 to 6 parties), within 7.1, 8.5 and 9.1 %.  (With the parts' additions
+// counted once, 4 parties 192 x 224 x 1504 took 16 parts, not 5: 10 % slower.)
 struct TileCost { int at_once; double call, party, round, step, each, start, read, written, out, copied, hot, cool, added, part; };
-template <class T> inline double tiles_us(int n, int batch, int M, int N, int K, TileShape shape, int splits)
+template <class T> inline const TileCost &tile_cost(TileShape shape)
 {
-    constexpr TileCost costs64[] = {{1, 8.52, 0.990, 0.449, 0.955, 0.130, 2.991, 0.083, 0.246, 0.115, 0.034, 0.108, 60, 0.177, 0.014},
-                                    {2, 8.10, 1.018, 0.082, 0.726, 0.000, 0.000, 0.047, 0.284, 0.125, 0.098, 0.133, 120, 0.120, 0.069}};
-    constexpr TileCost costs32[] = {{1, 6.73, 0.650, 0.135, 0.552, 0.208, 4.969, 0.013, 0.304, 0.060, 0.127, 0.038, 60, 0.139, 0.026},
-                                    {2, 7.76, 0.662, 0.074, 0.309, 0.066, 0.727, 0.000, 0.350, 0.103, 0.110, 0.099, 120, 0.163, 0.031},
-                                    {3, 6.98, 0.662, 0.000, 0.215, 0.000, 0.274, 0.000, 0.381, 0.108, 0.170, 0.065, 240, 0.150, 0.038}};
-    const TileCost &c = sizeof(T) == 8 ? costs64[shape == kFullTile ? 0 : 1] : costs32[shape];
-    const int KT = ceil_div(K, 32), part = 2 * ceil_div(KT, splits), used = ceil_div(2 * KT, part);
-    double tiles = 0, sides = 0;
-    with_shape<T>(shape, [&](auto s) {
-        using S = decltype(s);
-        const double tm = ceil_div(M, S::BM), tn = ceil_div(N, S::BN);
-        tiles = tm * tn;
-        sides = tm * S::BM + tn * S::BN;
-    });
-    const double filled = tiles * n * batch * used / compute_units(), most = std::ceil(filled), mb = 1e-6 * sizeof(T) * batch;
-    const double read_mb = 2 * n * mb * ((double)M + N) * K, written_mb = (n + 1) * mb * sides * KT * 32, out_mb = 2 * n * mb * (double)M * N;
-    return c.call + c.party * n + part * (c.round * std::floor(filled / c.at_once) + c.step * most + c.each * filled) + c.start * most +
-           c.read * read_mb + c.written * written_mb + c.out * out_mb + (used > 1 ? (c.copied + c.added * used) * out_mb + c.part * used : 0) +
-           c.hot * std::max(0.0, most * part - c.cool);
+    static constexpr TileCost costs64[] = {{1, 6.74, 1.181, 0.369, 0.906, 0, 3.585, 0.166, 0.223, 0.103, 0.102, 0.274, 34, 0.173, 0},
+                                           {2, 6.99, 1.165, 0, 0.6095, 0, 0.368, 0.158, 0.2435, 0.1215, 0.196, 0.2095, 44, 0.131, 0}};
+    static constexpr TileCost costs32[] = {{1, 6.73, 0.650, 0.135, 0.552, 0.208, 4.969, 0.013, 0.304, 0.060, 0.127, 0.038, 60, 0.139, 0.026},
+                                           {2, 7.76, 0.662, 0.074, 0.309, 0.066, 0.727, 0.000, 0.350, 0.103, 0.110, 0.099, 120, 0.163, 0.031},
+                                           {3, 6.98, 0.662, 0.000, 0.215, 0.000, 0.274, 0.000, 0.381, 0.108, 0.170, 0.065, 240, 0.150, 0.038}};
+    if constexpr (sizeof(T) == 8) return costs64[shape == kFullTile ? 0 : 1];
+    else return costs32[shape];
 }
+template <class T> struct TileEstimate {
+    TileCost c;
+    int KT, cus;
+    double workgroups, whole_us, out_mb;                 // without parts; all that does not depend on the number of parts
+    TileEstimate(int n, int batch, int M, int N, int K, TileShape shape, int cus_) : c(tile_cost<T>(shape)), KT(ceil_div(K, 32)), cus(cus_)
+    {
+        with_shape<T>(shape, [&](auto s) {
+            using S = decltype(s);
+            const double tm = ceil_div(M, S::BM), tn = ceil_div(N, S::BN), mb = 1e-6 * sizeof(T) * batch;
+            workgroups = tm * tn * n * batch;
+            out_mb = 2 * n * mb * (double)M * N;
+            whole_us = c.call + c.party * n + c.read * 2 * n * mb * ((double)M + N) * K + c.written * (n + 1) * mb * (tm * S::BM + tn * S::BN) * KT * 32 +
+                       c.out * out_mb;
+        });
+    }
+    double us(int splits) const
+    {
+        const int part = 2 * ceil_div(KT, splits), used = ceil_div(2 * KT, part);
+        const double filled = workgroups * used / cus, most = std::ceil(filled);
+        return whole_us + part * (c.round * std::floor(filled / c.at_once) + c.step * most + c.each * filled) + c.start * most +
+               (used > 1 ? (c.copied + c.added * used) * out_mb + c.part * used : 0) + c.hot * std::max(0.0, most * part - c.cool);
+    }
+};
 
-// Which kernel a product takes, by which tiles, and how many workgroups share one (parts of at least four k-steps): what all estimates
-// of it need.  The row kernel takes products over Z_2^64 of at most three parties (its units and their LDS) whose inner dimension one launch may
-// accumulate, where it is estimated to be the fastest.  Together with the direct kernel that costs 0.65 % against always the fastest way, over 26 000
-// products over Z_2^64 and 31 000 over Z_2^32; full tiles alone, and parts by a count of k-steps, cost 24 and 41 % below 2e10 ring
-// MACs (58 % in calls of 8 to 16 us, 7 % of 128 to 256), 1 % and less in calls of a millisecond, where full tiles move the fewest bytes.  Beyond 60
-// us smaller tiles have to be estimated 6 % faster: where full ones just fill the chip the estimates are no closer (2 parties 1024^3,
-// 256 full tiles: 130 us, 135 by half tiles, estimated at 135 and 134).
-//
-// Three parties and at most five k-tiles: the row kernel keeps products that tiles in parts would take in up to 1.6 times less (3
-// parties 256 x 190 x 130, 24 items: 26.7 us by rows, 16.3 by tiles; no slower than they were), because the tests of its item shares are written on
-// them: those of at most 48 items and of more than two k-tiles, and those that are estimated within a quarter of the tiles (two parties: 5 %).
+// Which digit kernel a product takes, by which tiles, and how many workgroups share one (parts of at least four k-steps): the way that is
+// estimated to take the least time.  Over Z_2^32 smaller tiles have to be estimated 6 % faster beyond 60 us, where full ones just fill the chip and
+// the estimates are no closer.  Batched products of three parties and one or two k-tiles stay with the row kernel up to 10 % behind: tiles, all packs and
+// stores there, take more than estimated (63 entries of 200 x 1 x 2: 22.4 us by rows, 27.8 by half tiles; 61 of 3851 x 83 x 33: 536 and 624).  Against always the fastest of the digit kernels that costs 0.5 % over 7500 products over Z_2^64 (8 us to 10 ms).
 struct DigitRoute { bool rows; int splits; TileShape shape; double us; };
 template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {
-    DigitRoute r{false, 1, kFullTile, tiles_us<T>(a.n, a.batch, a.M, a.N, a.K, kFullTile, 1)};
-    double margin = 1, best = r.us;
+    const int cus = compute_units();
+    DigitRoute r{false, 1, kFullTile, 0};
+    double margin = 1, best = 0;
     for (int shape = 0; shape < shapes_of<T>; ++shape) {
-        if (shape == kHalfTile && r.us > 60) margin = 1.06;
+        const TileEstimate<T> tiles(a.n, a.batch, a.M, a.N, a.K, (TileShape)shape, cus);
+        if (shape == kHalfTile && sizeof(T) == 4 && r.us > 60) margin = 1.06;
         for (int sp = 1; sp <= 16; ++sp) {
             if (sp > 1 && 2 * ceil_div(p.KT, sp) < 4) break;
             if (sp > 1 && ceil_div(p.KT, ceil_div(p.KT, sp)) < sp) continue;         // no more parts than with fewer
-            const double us = tiles_us<T>(a.n, a.batch, a.M, a.N, a.K, (TileShape)shape, sp);
-            if (margin * us < best) r = DigitRoute{false, sp, (TileShape)shape, us}, best = margin * us;
+            const double us = tiles.us(sp);
+            if (best == 0 || margin * us < best) r = DigitRoute{false, sp, (TileShape)shape, us}, best = margin * us;
         }
     }
-    if (!std::is_same<T, u64>::value) return r;
-    if (!rows_possible(a.n, a.batch, a.M, p)) return r;
-    const double by_rows = rows_us<T>(a, p);
-    const bool kept = a.n >= 2 && p.KT <= 5 && (by_rows <= (a.n == 3 ? 1.25 : 1.05) * r.us || (a.n == 3 && p.KT > 2 && rows_grid(a.batch, a.M, p.tilesN) <= 48));
-    if (by_rows <= r.us || kept) r.rows = true, r.us = by_rows;
+    if (!std::is_same<T, u64>::value || !rows_possible(a.n, a.batch, a.M, p)) return r;
+    const double by_rows = rows_us(a.n, a.batch, a.M, a.N, a.K, cus);
+    const bool thin = a.n == 3 && a.batch > 1 && p.KT <= 2;
+    if (by_rows <= (thin ? 1.1 : 1) * r.us) r.rows = true, r.us = by_rows;
     return r;
 }
 
-// Estimates of full tiles alone, for two lines between kernels that stay where those put them.
-// Workgroups to a full tile by a count of k-steps: 8 of them for start and end, parts of 8 at least.
-inline int full_tile_splits(long tiles, int KT)
-{
-    const int cus = compute_units();
-    long best_cost = -1;
-    int best = 1;
-    for (int sp = 1; sp <= 16; ++sp) {
-        const int part = 2 * ceil_div(KT, sp);
-        if (sp > 1 && part < 8) break;
-        const long cost = (tiles * sp + cus - 1) / cus * (part + 8);
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
-    }
-    return best;
-}
 // Roughly, for the choice between the digit kernels and the direct one, which takes a product only where this estimate and DigitRoute::us both
-// speak for it (alone either of them is off by up to 2.7 times somewhere): 1.5 us a k-step (0.85 over Z_2^32) and the packs as streams.
+// speak for it (alone either of them is off by up to 2.7 times somewhere): 1.5 us a k-step of a full tile (0.85 over Z_2^32), 8 k-steps for start and
+// end, as many workgroups to a tile as that makes fastest, and the packs as streams.
 template <class T> inline double digit_cost_rough_us(const MatmulArgsT<T> &a, const Plan &p)
 {
     const int cus = compute_units();
     const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = full_tile_splits(tiles, p.KT);
+    long steps = -1;
+    for (int sp = 1; sp <= 16; ++sp) {
+        const int part = 2 * ceil_div(p.KT, sp);
+        if (sp > 1 && part < 8) break;
+        const long cost = (tiles * sp + cus - 1) / cus * (part + 8);
+        if (steps < 0 || cost < steps) steps = cost;
+    }
     const double pack_bytes = (double)sizeof(T) * (3 * a.n + 1) * a.batch * ((double)a.M + a.N) * a.K;
-    const double by_tiles = (sizeof(T) == 8 ? 1.5 : 0.85) * (double)((tiles * sp + cus - 1) / cus) * (2 * ceil_div(p.KT, sp) + 8) + pack_bytes / 5.2e6 + 10;
+    const double by_tiles = (sizeof(T) == 8 ? 1.5 : 0.85) * (double)steps + pack_bytes / 5.2e6 + 10;
     if (sizeof(T) != 8 || a.n > 3) return by_tiles;
     return std::min(by_tiles, 1.5 * (double)((rows_grid(a.batch, a.M, p.tilesN) + cus - 1) / cus) * (2 * p.KT + 8) + 10);
-}
-// For the choice between the digit kernels and the residue GEMM: a fit to 1100 products of 30 us to 1.4 ms near the line (1 to 8
-// parties, sides 32 to 8192), within 6 % (rms).  Below 3.5e9 ring MACs it is the estimate of the way that is taken; above, half tiles save 13 %
-// where there are few tiles and nothing where there are many, and the residue GEMM keeps the products it had (its plans' tests are written on them).
-inline double digit_cost_large_us(const MatmulArgs &a, const Plan &p, const DigitRoute &r)
-{
-    if ((r.rows && p.tilesN <= 8) || ring_macs(a.n, a.batch, a.M, a.N, a.K) < 3.5e9) return r.us;
-    const double words = 8.0 * (3 * a.n + 1) * a.batch, out_mb = 16e-6 * a.n * a.batch * (double)a.M * a.N;
-    const long tiles = (long)p.tilesM * p.tilesN * a.n * a.batch;
-    const int sp = full_tile_splits(tiles, p.KT);
-    const double filled = (double)tiles * sp / compute_units(), rounds = std::ceil(filled);
-    return rounds * (1.52 * 2 * ceil_div(p.KT, sp) * (1 - 0.592 * (1 - filled / rounds)) + 6.6) +
-           words * ((double)a.M + a.N) * a.K / 5.4e6 + 1.1 + 1.52 * a.n + (sp > 1 ? 0.305 * out_mb : 0);
 }
 
 inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, hipStream_t s, const char *where_pack,
@@ -1051,7 +1039,7 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
     if constexpr (std::is_same<T, u64>::value) {
         if (ring_macs(a.n, a.batch, a.M, a.N, a.K) >= kResidueMinMacs64) {
             bool taken = false;
-            const spin_status st = launch_matmul_residue<T>(a, digit_cost_large_us(a, p, route), s, "spin_beaver_matmul(residue gemm)", taken);
+            const spin_status st = launch_matmul_residue<T>(a, route.us, s, "spin_beaver_matmul(residue gemm)", taken);
             if (taken) return st;
         }
         if (route.rows) return launch_rows(a, p, (char *)a.workspace + p.packA_bytes, s, where_pack, where_gemm);
@@ -1090,41 +1078,6 @@ template <class Args, class Launch> inline spin_status launch_in_tables(const st
 
 }  // namespace
 
-// Rows or tiles, for all products of a call.  The groups fill the chip together, so a call takes as long as its workgroups' share of
-// it, or as its longest workgroup; half tiles are done sooner, and need their left operands packed.  In us, as in rows_us and tiles_us.  Six
-// attention products of three stages, by rows and by half tiles: 3 parties 33.1 : 28.4, at twice the batch entries 44.0 : 41.4, at five times 84.7 :
-// 87.2; 2 parties, twice 34.4 : 32.6, three times 37.7 : 38.7.  (With the rule for single products two of the six went to another launch:
-// 47.8 us.)  Calls of at most five k-tiles stay with the row kernel, as single products of few items do (digit_route).
-static bool grouped_by_rows(int n, int groups, const MatmulArgs *a)
-{
-    double row_work = 0, row_longest = 0, tile_work = 0, tile_longest = 0, packs = 0;
-    int KT = 0;
-    for (int g = 0; g < groups; ++g) {
-        const MatmulArgs &m = a[g];
-        const Plan p = make_plan<u64>(n, m.batch, m.M, m.N, m.K), h = make_plan<u64, GemmShape<u64, 1, 1>>(n, m.batch, m.M, m.N, m.K);
-        if (!rows_possible(n, m.batch, m.M, p)) return false;
-        const double item = (0.191 + 0.346 * n) * 2 * p.KT + 1.58 + 0.523 * n, tile = (0.117 / 2 + 0.728) * 2 * p.KT + 0.132, left = 16e-6 * n * m.batch * (double)m.M * m.K;
-        row_work += rows_grid(m.batch, m.M, p.tilesN) * item / compute_units() + 0.045 * left;
-        row_longest = std::max(row_longest, item);
-        tile_work += (double)h.tilesM * h.tilesN * n * m.batch * tile / compute_units();
-        tile_longest = std::max(tile_longest, tile);
-        packs += 0.061 * left + 0.276e-6 * h.packA_bytes;
-        KT = std::max(KT, p.KT);
-    }
-    return KT <= 5 || std::max(tile_work, tile_longest) + packs >= 0.97 * std::max(row_work, row_longest);
-}
-
-// Full or half tiles, for all products of a call: what they would take one after another, whole tiles.
-static TileShape grouped_shape(int n, int groups, const MatmulArgs *a)
-{
-    double full = 0, half = 0;
-    for (int g = 0; g < groups; ++g) {
-        full += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kFullTile, 1);
-        half += tiles_us<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K, kHalfTile, 1);
-    }
-    return half < full ? kHalfTile : kFullTile;
-}
-
 struct GroupedWay { bool rows; TileShape shape; };       // rows: with the column tiles of a full tile
 static Plan grouped_plan(int n, const MatmulArgs &m, const GroupedWay &w)
 {
@@ -1139,6 +1092,47 @@ static unsigned long left_pack_blocks(const MatmulArgs &m, const Plan &p) { retu
 static unsigned long grouped_blocks(int n, const MatmulArgs &m, const Plan &p, const GroupedWay &w)
 {
     return w.rows ? (unsigned long)rows_grid(m.batch, m.M, p.tilesN) : (unsigned long)p.tilesM * p.tilesN * n * m.batch;
+}
+
+// Estimated time in microseconds of a grouped call by the row kernel or by tiles: what its workgroups take of the chip together, the
+// longest of them, and the packs as streams.  Fits to 2980 calls of two to twelve products each by rows, full and half tiles (1 to 3 parties, 13 us to 4
+// ms; half of them attention products of several stages), within 8.0, 8.2 and 7.7 % (rms).
+struct GroupedCost { double call, party, larger, work, longest, read, odd, out, written, hot; };
+static double grouped_us(int n, int groups, const MatmulArgs *a, bool by_rows, TileShape shape, int cus)
+{
+    static constexpr GroupedCost by_row{6.12, 1.376, 0.660, 0.687, 0.188, 0, 0.0356, 0.140, 0.307, 0};
+    static constexpr GroupedCost by_tile[2] = {{8.27, 1.222, 0.706, 0.384, 0, 0.1255, 0, 0.0972, 0.261, 0.217},
+                                               {7.05, 1.255, 0.746, 0.0644, 0.429, 0.1074, 0, 0.153, 0.300, 0.299}};
+    const TileCost &t = tile_cost<u64>(shape);
+    const GroupedCost &c = by_rows ? by_row : by_tile[shape];
+    double work = 0, longest = 0, streams = 0, steps = 0;
+    for (int g = 0; g < groups; ++g) {
+        const MatmulArgs &m = a[g];
+        const GroupedWay way{by_rows, shape};
+        const Plan p = grouped_plan(n, m, way);
+        const double each = by_rows ? row_item_us(n, p.KT) : (t.step + t.round) * 2 * p.KT + t.start, mb = 16e-6 * n * m.batch;
+        const double share = (double)grouped_blocks(n, m, p, way) / cus;
+        work += share * each;
+        steps += share * 2 * p.KT;
+        longest = std::max(longest, each);
+        streams += c.read * mb * ((double)m.M + m.N) * m.K + (m.K % 2 ? c.odd * mb * m.M * m.K : 0) + c.out * mb * m.M * m.N +
+                   c.written * 1e-6 * (p.packB_bytes + (by_rows ? 0 : p.packA_bytes));
+    }
+    return c.call + c.party * n + c.larger * std::max(work, longest) + c.work * work + c.longest * longest + streams + c.hot * std::max(0.0, steps - t.cool);
+}
+
+// All products of a call go the same way: the fastest by estimate (the row kernel up to 5 % behind, where the tile estimates are off by more).  Six
+// attention products of three stages, by rows and by half tiles: 3 parties 33.1 : 28.4, at twice the batch entries 44.0 : 41.4, at five times 84.7 :
+// 87.2; 2 parties, twice 34.4 : 32.6, three times 37.7 : 38.7.  (With the rule for single products two of the six went to another launch:
+// 47.8 us.)
+static GroupedWay grouped_choice(int n, int groups, const MatmulArgs *a)
+{
+    const int cus = compute_units();
+    const double full = grouped_us(n, groups, a, false, kFullTile, cus), half = grouped_us(n, groups, a, false, kHalfTile, cus);
+    const GroupedWay tiles{false, half < full ? kHalfTile : kFullTile};
+    for (int g = 0; g < groups; ++g)
+        if (!rows_possible(n, a[g].batch, a[g].M, make_plan<u64>(n, a[g].batch, a[g].M, a[g].N, a[g].K))) return tiles;
+    return grouped_us(n, groups, a, true, kFullTile, cus) <= 1.05 * std::min(full, half) ? GroupedWay{true, kFullTile} : tiles;
 }
 
 // Whether the groups can share launches: not an inner dimension that must be accumulated in several, nor more threads
@@ -1160,7 +1154,7 @@ static bool grouped_fits(int n, int groups, const MatmulArgs *a, const GroupedWa
 static spin_status grouped_way(int n, int groups, const MatmulArgs *a, const spin_matmul_way *asked, GroupedWay &w)
 {
     if (asked == nullptr) {
-        w = GroupedWay{grouped_by_rows(n, groups, a), grouped_shape(n, groups, a)};
+        w = grouped_choice(n, groups, a);
     } else {
         if (asked->parts != 1 || (asked->kernel != SPIN_WAY_ROWS && asked->kernel != SPIN_WAY_FULL_TILES && asked->kernel != SPIN_WAY_HALF_TILES)) return SPIN_EINVAL;
         w = GroupedWay{asked->kernel == SPIN_WAY_ROWS, asked->kernel == SPIN_WAY_HALF_TILES ? kHalfTile : kFullTile};
@@ -1275,6 +1269,10 @@ template <class T> spin_status launch_matmul_by(const MatmulArgsT<T> &a, const s
         });
     }
     if (way.parts != 1) return SPIN_EINVAL;
+    if (way.kernel == SPIN_WAY_DIRECT) {
+        if ((unsigned long)ceil_div(a.M, 16) * ceil_div(a.N, 16) * a.n * a.batch > 0xffffffffUL / 256) return SPIN_ERANGE;
+        return launch_matmul_direct<T>(a, s, where);
+    }
     if constexpr (std::is_same<T, u64>::value) {
         if (way.kernel == SPIN_WAY_ROWS)
             return rows_possible(a.n, a.batch, a.M, p) ? launch_rows(a, p, (char *)a.workspace + p.packA_bytes, s, where, where) : SPIN_EINVAL;
@@ -1302,7 +1300,7 @@ size_t limb_preferred_workspace_bytes(int n, int batch, int M, int N, int K)
     MatmulArgs a{};
     a.n = n; a.batch = batch; a.M = M; a.N = N; a.K = K;
     const size_t need = p.packA_bytes + p.packB_bytes;
-    return std::max(need, residue_workspace_bytes<u64>(n, batch, M, N, K, need, digit_cost_large_us(a, p, digit_route<u64>(a, p))));
+    return std::max(need, residue_workspace_bytes<u64>(n, batch, M, N, K, need, digit_route<u64>(a, p).us));
 }
 
 size_t limb32_workspace_bytes(int n, int batch, int M, int N, int K)

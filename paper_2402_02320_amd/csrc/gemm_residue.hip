@@ -728,9 +728,9 @@ template <> struct ResidueCost<u128> {
     static constexpr double first_block = 25.2, first_block_party = 4.97, block = 18.2, block_party = 5.43;
     static constexpr double shared = 4.2, shared_part = 7.1;
 };
-// Taken where its estimate is this much below the digit kernels'.  Against always taking the faster of the two the choice costs 0.14 %
-// over 1360 products over Z_2^64 near the line, none of them slower than by digits by more than 2 % (without the margin 0.09 %
-// and 8 of them), and 0.2 % over 8700 over Z_2^128 (1 to 8 parties, sides 16 to 6500), the direct kernel included.
+// Taken where its estimate is this much below the digit kernels'.  Against always taking the fastest way the choice, that among the digit kernels
+// included, costs 0.5 % over 930 products over Z_2^64 of 3.5e9 ring MACs to 6e10 (2.4 % with the digit kernels estimated as full tiles) and 1.1 %
+// over 740 from 4e8 on; and 0.2 % over 8700 over Z_2^128 (1 to 8 parties, sides 16 to 6500), the direct kernel included.
 constexpr double kResidueMargin = 0.95;
 template <class T> inline double plan_cost(const ResiduePlan &p, int n, int batch, int M, int N, int K, int cus)
 {

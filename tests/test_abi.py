@@ -192,10 +192,10 @@ def test_validation_of_products_by_a_named_kernel(L):
         return L.spin_matmul_by(_MatmulWay(kernel, parts), bits, *dims, *p, transposed, ws, size, None)
     dims = (2, 1, 100, 100, 200)                             # seven k-tiles
     rows, full, half, quarter, residues = 1, 2, 3, 4, 5
-    for kernel in (0, 6, 7, -1):                             # the direct kernel, and what is no kernel
+    for kernel in (6, 7, -1):
         assert by(kernel, 1, 64, dims) == EINVAL
     assert by(quarter, 1, 64, dims) == by(rows, 1, 32, dims) == by(residues, 1, 32, dims) == EINVAL
-    assert by(rows, 2, 64, dims) == by(residues, 2, 64, dims) == EINVAL
+    assert by(rows, 2, 64, dims) == by(residues, 2, 64, dims) == by(0, 2, 64, dims) == EINVAL
     for parts in (0, -1, 5, 6, 8, 17):                       # five and six parts of seven k-tiles are four
         assert by(half, parts, 64, dims) == by(full, parts, 32, dims) == EINVAL
     assert by(rows, 1, 64, (4, 1, 100, 100, 200)) == by(rows, 1, 64, (2, 1, 100, 100, 511 * 32 + 1)) == EINVAL

@@ -1,7 +1,8 @@
 """The digit kernels at the sizes where they can go wrong, against the CPU oracle: edges of their 32-wide blocks and 64- and
-128-wide tiles, of their k-tiles and of the ring of tiles a row item walks, every party count, batches, transposed right operands, C
+128-wide tiles, of their k-tiles and of the k-tiles that a row item walks, every party count, batches, transposed right operands, C
 updated in place.  The products are such that the library gives them to these kernels (most small ones go to the one-launch kernel,
-large ones to the residue GEMM): the kernel class that it reports is checked.  Exact ring words."""
+large ones to the residue GEMM): the kernel class that it reports is checked.  Which of the digit kernels takes a product is the
+library's choice; the row kernel is asked for by name as well wherever it can be.  Exact ring words."""
 import numpy as np
 import pytest
 import torch
@@ -83,6 +84,9 @@ def test_ring64(n, batch, M, N, K):
     ops = [dev(t) for t in (X, Y, A, B, C)]
     assert (host(by_digits(lambda: spin.beaver_matmul(*ops))) == want).all()
     Yt, Bt = (dev(t.transpose(0, 1, 3, 2)) for t in (Y, B))
+    if n <= 3:
+        assert (host(spin.beaver_matmul_by("rows", 1, *ops)) == want).all()
+        assert (host(spin.beaver_matmul_by("rows", 1, ops[0], Yt, ops[2], Bt, ops[4], y_transposed=True)) == want).all()
     assert (host(by_digits(lambda: spin.beaver_matmul(ops[0], Yt, ops[2], Bt, ops[4], y_transposed=True))) == want).all()
     assert (host(ops[4]) == C).all()
     by_digits(lambda: spin.beaver_matmul(*ops, out=ops[4]))
@@ -123,7 +127,8 @@ def test_ring128_worst_case_digits_over_two_chunks():
 
 @pytest.mark.parametrize("M,K", [(4200, 511 * 32), (300, 511 * 32), (32, 511 * 32 + 96)])
 def test_ring64_worst_case_digits(M, K):
-    # all digits -128 over the longest inner dimension that is accumulated at once: the row kernel, shared tiles, and a second chunk
+    # all digits -128 over the longest inner dimension that is accumulated at once, few tiles and many, and a second chunk (by the library's choice;
+    # each kernel by its name: test_gpu_named_kernels.py)
     n, N = 2, 64
     worst = torch.tensor(0x7F7F7F7F7F7F7F80, dtype=torch.int64, device="cuda")
     X, Y = worst.expand(n, 1, M, K).contiguous(), worst.expand(n, 1, K, N).contiguous()

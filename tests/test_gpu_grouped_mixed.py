@@ -1,6 +1,6 @@
-"""A grouped Beaver matmul whose products go to both limb GEMM kernels (an odd inner dimension excludes the row kernel), for
-the party counts the row kernel takes: the two kinds share one launch.  Compared with the VALU path, and with more groups than
-one shared launch holds."""
+"""A grouped Beaver matmul of products of different shapes, odd and even inner dimensions, as the library chooses: all by the row kernel or all
+by half tiles, up to three parties, and by half tiles beyond.  Compared with the VALU path, and with more groups than one shared launch
+holds.  (Each kernel by its name: test_gpu_named_kernels.py.)"""
 import pytest
 import torch
 
@@ -15,7 +15,7 @@ def uniform(g, *shape):
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4])
 @pytest.mark.parametrize("count", [2, 6, 36])
-def test_rows_and_tiles_together(n, count):
+def test_groups_of_different_shapes(n, count):
     g = torch.Generator(device="cuda")
     g.manual_seed(n * 100 + count)
     shapes = [(2, 196, 96, 64, True), (3, 49, 32, 49, False), (1, 33, 64, 130, False), (2, 70, 65, 33, True), (1, 1, 1, 2, False),
@@ -26,6 +26,8 @@ def test_rows_and_tiles_together(n, count):
         y = (N, K) if tr else (K, N)
         groups.append(dict(X=uniform(g, n, batch, M, K), Y=uniform(g, n, batch, *y), A=uniform(g, n, batch, M, K),
                            B=uniform(g, n, batch, *y), C=uniform(g, n, batch, M, N), y_transposed=tr))
+    way = spin.matmul_grouped_way(n, [shapes[i % len(shapes)] for i in range(count)])
+    assert way in (("rows", "half") if n <= 3 else ("half",))
     want = spin.beaver_matmul_grouped(groups, path=spin.VALU)
     for _ in range(2):
         got = spin.beaver_matmul_grouped(groups)

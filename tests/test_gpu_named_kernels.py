@@ -87,6 +87,13 @@ def test_grouped(n, name, count):
         assert all(torch.equal(a, b) for a, b in zip(spin.beaver_matmul_grouped_by(name, groups), want))
 
 
+@pytest.mark.parametrize("bits", [64, 32])
+def test_direct(bits):
+    u, R = uniform(5, bits), spin if bits == 64 else spin.ring32
+    ops = u(3, 2, 65, 300), u(3, 2, 300, 130), u(3, 2, 65, 300), u(3, 2, 300, 130), u(3, 2, 65, 130)
+    assert torch.equal(spin.beaver_matmul_by("direct", 1, *ops), R.beaver_matmul(*ops, path=spin.VALU))
+
+
 def test_residues():
     u = uniform(1)
     ops = u(2, 1, 300, 700), u(2, 1, 700, 270), u(2, 1, 300, 700), u(2, 1, 700, 270), u(2, 1, 300, 270)

@@ -211,13 +211,12 @@ def test_few_tiles_and_a_long_inner_dimension(n, batch, M, N, K):
     assert torch.equal(again, got)
 
 
-# Products with a single column tile (N <= 64) -- or a few and a short inner dimension --, at most three parties
-# and an even inner dimension take the row-streaming kernel, which builds the left fragments inside the GEMM: one k-tile, two, three (the LDS ring
-# length) and many; ragged rows, columns and inner dimension; batches; in place; transposed right operand.
+# Products of at most three parties with a single column tile (N <= 64), or a few and a short inner dimension, by the library's choice and by
+# the row kernel, which builds the left fragments inside the GEMM: one k-tile, two, three and many; ragged rows, columns and inner dimension; batches; in place; transposed right operand.
 ROW_SHAPES = [(3, 1, 32, 64, 32), (3, 1, 64, 64, 64), (2, 1, 33, 31, 34), (1, 1, 100, 64, 96), (3, 2, 130, 57, 46),
               (3, 1, 1, 1, 2), (2, 3, 95, 64, 128), (3, 1, 4096, 64, 576), (3, 64, 128, 64, 128), (1, 2, 257, 33, 1000),
               (3, 1, 8192, 64, 70), (2, 1, 9000, 48, 2048), (3, 1, 70, 64, 160), (2, 2, 40, 50, 192), (3, 1, 33, 64, 226),
-              # more row blocks than CUs: a workgroup walks several of them, its producer running ahead across the boundary
+              # more row blocks than CUs: a workgroup walks several of them, its loads running ahead across the boundary
               (3, 1, 9000, 64, 32), (2, 3, 3000, 130, 40), (1, 1, 20000, 33, 6), (3, 1, 8500, 64, 96), (2, 70, 128, 100, 64),
               # a few column tiles and a short inner dimension (the attention shapes): one pass per column tile
               (3, 64, 128, 128, 64), (3, 2, 100, 130, 40), (2, 1, 64, 192, 32), (3, 8, 196, 196, 64)]
@@ -237,6 +236,7 @@ def test_beaver_matmul_single_column_tile_shapes(n, batch, M, N, K):
     Bt = dev(np.ascontiguousarray(B.transpose(0, 1, 3, 2)))
     Yt = dev(np.ascontiguousarray(Y.transpose(0, 1, 3, 2)))
     assert torch.equal(spin.beaver_matmul(Xd, Yt, Ad, Bt, Cd, path=spin.LIMB_MFMA, y_transposed=True), got)
+    assert torch.equal(spin.beaver_matmul_by("rows", 1, Xd, Yd, Ad, Bd, Cd), got)
     spin.beaver_matmul(Xd, Yd, Ad, Bd, Cd, path=spin.LIMB_MFMA, out=Cd)          # in place on C
     assert (host(Cd) == want).all()
 
@@ -244,6 +244,7 @@ def test_beaver_matmul_single_column_tile_shapes(n, batch, M, N, K):
 def test_single_column_tile_worst_case_digits():
     # all digits -128 in every operand of both products, at the longest inner dimension the row kernel accumulates
     # in one launch (511 k-tiles): the int32 partial sums run at their proven extreme
+    # (the library takes these rows by shared tiles, hence both)
     n, M, N, K = 2, 300, 64, 511 * 32
     worst = np.uint64(0x7F7F7F7F7F7F7F80)
     X = np.zeros((n, 1, M, K), dtype=np.uint64); X[:] = worst
@@ -253,6 +254,7 @@ def test_single_column_tile_worst_case_digits():
     want = oracle.beaver_matmul(X, Y, A, B, C)
     got = spin.beaver_matmul(dev(X), dev(Y), dev(A), dev(B), dev(C), path=spin.LIMB_MFMA)
     assert (host(got) == want).all()
+    assert (host(spin.beaver_matmul_by("rows", 1, dev(X), dev(Y), dev(A), dev(B), dev(C))) == want).all()
 
 
 def test_limb_path_worst_case_digits_and_inner_dimension_split():

@@ -36,7 +36,7 @@ def preferred(L, bits, *dims):
     return int(f(*dims, spin.LIMB_MFMA))
 
 
-# n, batch, M, N, K, transposed; all of them are products the residue GEMM takes with ample workspace
+# n, batch, M, N, K, transposed
 SHAPES64 = [(5, 1, 1025, 1200, 1001, False),      # odd K (no 16-byte rows), one row beyond four panels
             (8, 1, 769, 1023, 1100, True),        # right operand stored transposed, eight parties
             (2, 1, 1300, 1300, 5633, False),      # one k beyond a launch: two chunks, the second onto Z
@@ -50,10 +50,11 @@ SHAPES64 = [(5, 1, 1025, 1200, 1001, False),      # odd K (no 16-byte rows), one
 def test_ring64(n, batch, M, N, K, transposed):
     dims = (n, batch, M, N, K)
     X, Y, A, B, C = operands(K, n, batch, M, N, K, transposed)
-    assert preferred(spin.lib(), 64, *dims) > spin.beaver_matmul_workspace_bytes(*dims), "not a residue product any more"
     want = spin.beaver_matmul(X, Y, A, B, C, path=spin.VALU, y_transposed=transposed)
-    got = spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed)
+    ample = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+    got = spin.beaver_matmul_by("residues", 1, X, Y, A, B, C, workspace=ample, y_transposed=transposed)
     assert torch.equal(got, want)
+    assert torch.equal(spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed), want)         # the way that the library takes
     rows = np.unique(np.array([0, 15, 16, 127, 128, 255, 256, M // 2, M - 2, M - 1], dtype=np.int32) % M)
     Yh, Bh = (host(t.transpose(2, 3) if transposed else t) for t in (Y, B))
     assert (host(got)[:, :, rows] == oracle.beaver_matmul(host(X), Yh, host(A), Bh, host(C), rows=rows)).all()

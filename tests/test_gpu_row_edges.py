@@ -1,7 +1,7 @@
 """The row kernel where its k-tiles, its 16-byte rows and its halved units have edges: odd inner dimensions (element-wise loads; the last
 k-tile of one to 32), odd and even numbers of k-tiles (an odd one is padded by a tile without products), one to three parties (units whole
-and in parts), one and two column halves, a workgroup with one item and with several; single and grouped, C in place.  That the row
-kernel made them shows in the workspace, whose first part (left fragments) it leaves as it was.  Exact ring words."""
+and in parts), one and two column halves, a workgroup with one item and with several; single and grouped, C in place.  The kernel is asked
+for by name; that the row kernel made them shows in the workspace too, whose first part (left fragments) it leaves as it was.  Exact ring words."""
 import pytest
 import torch
 
@@ -32,9 +32,9 @@ def test_words(n, batch, M, N, K, transposed):
         for at in range(0, parts * size, size):
             kept, packed = bool((ws[at:at + left] == 0x5A).all()), not bool((ws[at + left:at + size] == 0x5A).all())
             assert kept and packed, "not a product of the row kernel"
-    assert torch.equal(spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed, workspace=ws), want)
+    assert torch.equal(spin.beaver_matmul_by("rows", 1, X, Y, A, B, C, y_transposed=transposed, workspace=ws), want)
     rows(1)
     group = dict(X=X, Y=Y, A=A, B=B, C=C, y_transposed=transposed)
-    assert all(torch.equal(z, want) for z in spin.beaver_matmul_grouped([group, group], workspace=ws))
+    assert all(torch.equal(z, want) for z in spin.beaver_matmul_grouped_by("rows", [group, group], workspace=ws))
     rows(2)
-    assert torch.equal(spin.beaver_matmul(X, Y, A, B, C, out=C, y_transposed=transposed, workspace=ws), want)
+    assert torch.equal(spin.beaver_matmul_by("rows", 1, X, Y, A, B, C, out=C, y_transposed=transposed, workspace=ws), want)

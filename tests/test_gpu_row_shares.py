@@ -1,6 +1,6 @@
 """The row kernel's items: row blocks in eight contiguous shares, column tiles fastest.  Block counts around multiples of 8 and of the
-workgroups a launch has, one to three column tiles, one batch entry and many, against the vector-ALU path.  Exact ring words; that the
-row kernel made them shows in the workspace, whose first part (left fragments, [n+1][batch][M / 32][K / 32] of 8 KB in whole 128-row
+workgroups a launch has, one to three column tiles, one batch entry and many, against the vector-ALU path.  The kernel is asked for by name
+(the library takes some of these products by tiles).  Exact ring words; that the row kernel made them shows in the workspace too, whose first part (left fragments, [n+1][batch][M / 32][K / 32] of 8 KB in whole 128-row
 tiles) it leaves as it was."""
 import pytest
 import torch
@@ -29,7 +29,7 @@ def by_rows(call, n, batch, M, K, size):
     count = {k: spin.profile_read(k)[1] for k in ("gemm_limb", "gemm_direct", "gemm_residue")}
     spin.profile_reset()
     assert count == {"gemm_limb": 1, "gemm_direct": 0, "gemm_residue": 0}
-    assert bool((ws[:left] == 0x5A).all()) and not bool((ws[left:] == 0x5A).all()), "not a product of the row kernel any more"
+    assert bool((ws[:left] == 0x5A).all()) and not bool((ws[left:] == 0x5A).all()), "not a product of the row kernel"
     return out
 
 
@@ -45,7 +45,7 @@ def test_words(n, batch, M, N, K, transposed):
     X, Y, A, B, C = u(n, batch, M, K), u(n, batch, *y), u(n, batch, M, K), u(n, batch, *y), u(n, batch, M, N)
     want = spin.beaver_matmul(X, Y, A, B, C, path=spin.VALU, y_transposed=transposed)
     size = spin.beaver_matmul_workspace_bytes(n, batch, M, N, K)
-    assert torch.equal(by_rows(lambda ws: spin.beaver_matmul(X, Y, A, B, C, y_transposed=transposed, workspace=ws), n, batch, M, K, size), want)
+    assert torch.equal(by_rows(lambda ws: spin.beaver_matmul_by("rows", 1, X, Y, A, B, C, y_transposed=transposed, workspace=ws), n, batch, M, K, size), want)
     group = dict(X=X, Y=Y, A=A, B=B, C=C, y_transposed=transposed)
-    got = by_rows(lambda ws: spin.beaver_matmul_grouped([group, group], workspace=ws), n, batch, M, K, 2 * size)
+    got = by_rows(lambda ws: spin.beaver_matmul_grouped_by("rows", [group, group], workspace=ws), n, batch, M, K, 2 * size)
     assert all(torch.equal(z, want) for z in got)

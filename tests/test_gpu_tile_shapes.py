@@ -1,6 +1,7 @@
-"""The tile kernel by its smaller shapes (64 x 64 over Z_2^64; 64 x 128 and 64 x 64 over Z_2^32), at the edges of their tiles and where several workgroups
-share one: one part to sixteen, an even and an odd number of k-tiles, C in place.  Against the vector-ALU path; exact ring words.  What
-shape a product takes shows in the workspace: the left fragments end at a multiple of the tile's rows, and nothing is written behind the right ones."""
+"""Products that the library takes by the tile kernel's smaller shapes (64 x 64 over Z_2^64; 64 x 128 and 64 x 64 over Z_2^32), at the edges of their tiles
+and where several workgroups share one, an even and an odd number of k-tiles, C in place.  Against the vector-ALU path; exact ring words.
+The shape is the library's own answer, and shows in the workspace: the right fragments end behind whole tiles of both sides.  (Every shape
+and number of parts by name: test_gpu_named_kernels.py.)"""
 import pytest
 import torch
 
@@ -36,10 +37,10 @@ def test_words(bits, n, batch, M, N, K):
     spin.profile_reset()
     assert count == {"gemm_limb": 3, "gemm_direct": 0, "gemm_residue": 0}, "not a product of the tile kernel"
     assert all(torch.equal(z, want) for z in got)
-    # 32-row blocks of both sides, in whole tiles of the shape
-    blocks = {shape: -(-M // shape[0]) * shape[0] // 32 + -(-N // shape[1]) * shape[1] // 32 for shape in ((64, 64), (64, 128))}
-    ends = [(n + 1) * batch * b * -(-K // 32) * 1024 * w for b in blocks.values()]
-    written = int((ws != 0x5A).nonzero()[-1]) + 1
-    assert any(e - 64 < written <= e for e in (ends if bits == 32 else ends[:1])), "not by a smaller shape"
+    name, _ = spin.matmul_way(n, batch, M, N, K, bits=bits)
+    assert name in ("half", "quarter")
+    rows, columns = (64, 128) if (bits, name) == (32, "half") else (64, 64)
+    end = (n + 1) * batch * (-(-M // rows) * rows + -(-N // columns) * columns) // 32 * -(-K // 32) * 1024 * w
+    assert end - 64 < int((ws != 0x5A).nonzero()[-1]) + 1 <= end
     R.beaver_matmul(*ops, out=ops[4], workspace=ws)
     assert torch.equal(ops[4], want)

@@ -46,9 +46,50 @@ def test_no_workspace_of_gigabytes_for_a_hundredth():
     assert spin.ring128.beaver_matmul_preferred_workspace_bytes(2, 1, 2048, 2048, 2048) > 1e9     # 4 % faster than in 0.75 GB
 
 
-@pytest.mark.parametrize("n,batch,M,together", [(1, 15, 1 << 24, True), (1, 16, 1 << 24, False), (1, 16, (1 << 24) - 32, True), (1, 16, (1 << 24) - 31, False),
-                                                (3, 17, 1 << 24, False)])
-def test_a_grouped_call_of_more_threads_than_a_grid_holds_is_taken_apart(n, batch, M, together):
-    # one workgroup of 512 threads to 32 rows: 2^23 of them are a grid of 2^32 threads, which HIP refuses
-    assert (spin.matmul_grouped_way(n, [(batch, M, 1, 1)]) == "rows") is together
-    assert (spin.matmul_grouped_way(n, [(batch, M, 1, 1), (1, 8, 8, 8)]) == "rows") is together
+def test_a_grouped_call_of_more_threads_than_a_grid_holds_is_taken_apart():
+    # 2^32 threads and more, which HIP refuses: 2^23 row blocks of 512 threads, 2^24 tiles of 256
+    SEPARATE, ERANGE, M = "separate", 2, 1 << 24
+    assert spin.matmul_grouped_way(1, [(64, M, 1, 1)]) == spin.matmul_grouped_way(1, [(63, M, 1, 1), (1, M, 1, 1)]) == SEPARATE
+    assert spin.matmul_grouped_way(1, [(63, M, 1, 1)]) != SEPARATE
+    for n, shapes in ((1, [(16, M)]), (1, [(16, M - 31)]), (1, [(15, M), (1, M)]), (3, [(17, M)])):
+        desc = (spin._MatmulGroup * len(shapes))()
+        for d, (batch, rows) in zip(desc, shapes):
+            d.batch, d.M, d.N, d.K = batch, rows, 1, 1
+            d.X = d.Y = d.A = d.B = d.C = d.Z = 0x10000      # never touched: refused before anything is launched
+        assert spin.lib().spin_matmul_grouped_by(spin._MatmulWay(spin.WAYS["rows"], 1), n, len(shapes), desc, 0x10000, 1 << 50, None) == ERANGE
+
+
+# us by the way that is taken, and by the one behind it
+WAYS = [((3, 1, 256, 190, 130), "tiles"),           # 15.4, 25.9 by rows
+        ((3, 7, 20, 190, 130), "tiles"),            # 18.8, 27.5 by rows
+        ((3, 3, 129, 129, 66), "tiles"),            # 15.7, 21.8 by rows
+        ((3, 1, 512, 128, 66), "tiles"),            # 15.2, 20.6 by rows
+        ((3, 1, 472, 108, 157), "tiles"),           # 16.7, 27.2 by rows
+        ((3, 1, 5006, 69, 113), "tiles"),           # 28.7, 37.7 by rows
+        ((3, 1, 2233, 2432, 131), "tiles"),         # 196, 252 by rows: many column tiles, each of which reads the rows again
+        ((2, 14, 704, 960, 736), "tiles"),          # 939, 1145 by rows
+        ((3, 1, 7840, 2112, 160), "tiles"),         # 558, 718 by rows
+        ((3, 64, 128, 128, 64), "rows"),            # 32.5
+        ((3, 1, 131072, 64, 576), "rows"),          # 1140
+        ((2, 1, 4200, 64, 16352), "rows"),
+        ((2, 1, 1024, 1024, 1024), "full")]         # 130, 135 by half tiles
+
+
+@pytest.mark.parametrize("dims,name", WAYS)
+def test_rows_or_tiles(dims, name):
+    assert spin.matmul_way(*dims)[0] in (("full", "half") if name == "tiles" else (name,))
+
+
+@pytest.mark.parametrize("dims", [(2, 1, 389, 2224, 1193), (2, 1, 398, 2251, 1569), (3, 1, 1169, 540, 987)])
+def test_tiles_in_parts_or_residues(dims):
+    # us by tiles, by residues in one block or two: 160 : 207, 212 : 244, 152 : 163
+    assert spin.beaver_matmul_preferred_workspace_bytes(*dims) == spin.beaver_matmul_workspace_bytes(*dims)
+
+
+@pytest.mark.parametrize("n,scale,name", [(3, 1, "half"), (3, 2, "half"), (3, 3, "rows"), (3, 8, "rows"), (2, 1, "rows"), (2, 8, "rows")])
+def test_grouped_rows_or_tiles(n, scale, name):
+    # six attention products of three stages, by rows and half tiles: 33.6 : 28.4, 44.7 : 38.2, 45.9 : 48.9, 110 : 127; two parties 26.3 : 28.6, 74 : 86
+    shapes = [(4, 196, 196, 64, True), (4, 196, 64, 196), (8, 49, 49, 32, True), (8, 49, 32, 49), (12, 16, 16, 32, True), (12, 16, 32, 16)]
+    assert spin.matmul_grouped_way(n, [(scale * s[0],) + s[1:] for s in shapes]) == name
+    if n == 3:
+        assert spin.matmul_grouped_way(3, [(1, 1024, 1024, 160)] * 2) == "half"              # 52 : 62 us; five k-tiles
