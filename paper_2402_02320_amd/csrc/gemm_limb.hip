@@ -406,8 +406,9 @@ __global__ __launch_bounds__(256, (S::Slots::waves)) void limb_gemm_grouped_kern
 // ahead, and a producer wave for E (whole calls, the pack included): 3 parties 12262 x 59 x 125 59.0 -> 41.3 us, 20000 x 50 x 125 77.9 ->
 // 58.3, 64 entries of 128 x 128 x 64 (keys transposed) 38.1 -> 32.1, of 128 x 64 x 128 34.2 -> 30.8; 2 parties 20 entries of 100^3 25.5 ->
 // 20.8, 131072 x 64 x 576 847 -> 792.  3 parties 131072 x 64 x 576 stay at 1120: its 3.6 GB take 770 us with nothing multiplied, its products 700 with
-// nothing loaded, and together they bring the clock down to 1.2 to 1.65 GHz.  With shares one k-tile ahead (40 registers fewer) the first
-// two take 44.8 and 62.1 us.
+// nothing loaded; together L2 is busy 0.96 of the cycles (9.1 GB asked of it, 4.8 of them right fragments that every row block reads again, at 7.7
+// TB/s) and the matrix pipes 0.54, and the clock is down at 1.2 to 1.65 GHz.  With shares one k-tile ahead (40 registers fewer) the first two
+// take 44.8 and 62.1 us.
 // Workgroups of a row-kernel launch: (row blocks over all batch entries, rounded up to a multiple of 8) x column tiles.
 __host__ __device__ inline long rows_grid(int batch, int M, int tilesN)
 {
@@ -969,7 +970,7 @@ inline spin_status launch_rows(const MatmulArgs &a, const Plan &p, char *packB, 
     if (st != SPIN_OK) return st;
     RowGemmArgs g{a.X, a.A, packB, a.C, a.Z, a.batch, a.M, a.N, a.K, p.KT, p.tilesN};
     // One workgroup fits a CU, so more workgroups than CUs only queue: launch one per CU (a multiple of 8, so that
-    // an item keeps its XCD) and let each walk its items, the producer running ahead across item boundaries.
+    // an item keeps its XCD) and let each walk its items, its loads running ahead across item boundaries.
     const unsigned items = (unsigned)rows_grid(a.batch, a.M, p.tilesN);
     const unsigned resident = (unsigned)std::max(8, compute_units() / 8 * 8);
     const unsigned grid = items > resident && ((long)items / resident + 1) * p.KT < (1L << 30) ? resident : items;
@@ -1055,11 +1056,10 @@ template <class T> spin_status launch_limb(const MatmulArgsT<T> &a, hipStream_t 
 
 // ---- grouped call: products of different shapes, a handful of launches for all of them ----------------
 // Every group gets its own fragment stores inside the workspace (the packs of all groups run before their
-// GEMMs), takes the row-streaming or the tile kernel (grouped_rows), and the groups share launches: all
-// packs (right operands, and left ones of tile-kernel groups) in one per kGroupsPerLaunch sides, then the row and the
-// tile GEMMs in one launch each.  Tiles are not shared between workgroups here (the groups together fill the chip), so Z needs no pre-copy.
-template <class Args, class Launch> inline spin_status launch_in_tables(const std::vector<Args> &args,
-                                                                        const std::vector<unsigned> &blocks, Launch &&launch)
+// GEMMs), and the groups share launches: all packs (right operands, and left ones for tiles) in one per kGroupsPerLaunch sides,
+// then all GEMMs, by the row or by the tile kernel (grouped_choice), in one per kGroupsPerLaunch groups.  Tiles are not shared between workgroups
+// here (the groups together fill the chip), so Z needs no pre-copy.
+template <class Args, class Launch> inline void launch_in_tables(const std::vector<Args> &args, const std::vector<unsigned> &blocks, Launch &&launch)
 {
     for (size_t g0 = 0; g0 < args.size(); g0 += kGroupsPerLaunch) {
         GroupTable<Args> t;
@@ -1073,7 +1073,6 @@ template <class Args, class Launch> inline spin_status launch_in_tables(const st
         for (int i = t.count; i <= kGroupsPerLaunch; ++i) t.first[i] = total;
         launch(t, total);
     }
-    return SPIN_OK;
 }
 
 }  // namespace
@@ -1122,9 +1121,9 @@ static double grouped_us(int n, int groups, const MatmulArgs *a, bool by_rows, T
 }
 
 // All products of a call go the same way: the fastest by estimate (the row kernel up to 5 % behind, where the tile estimates are off by more).  Six
-// attention products of three stages, by rows and by half tiles: 3 parties 33.1 : 28.4, at twice the batch entries 44.0 : 41.4, at five times 84.7 :
-// 87.2; 2 parties, twice 34.4 : 32.6, three times 37.7 : 38.7.  (With the rule for single products two of the six went to another launch:
-// 47.8 us.)
+// attention products of three stages, by rows and by half tiles: 3 parties 33.6 : 28.4, at twice the batch entries 44.7 : 38.2, at three times 45.9 :
+// 48.9, at eight times 110 : 127; 2 parties 26.3 : 28.6, twice 35.6 : 33.3 (and by rows all the same), eight times 74 : 86.  (With the rule for single
+// products two of the six went to another launch: 47.8 us.)
 static GroupedWay grouped_choice(int n, int groups, const MatmulArgs *a)
 {
     const int cus = compute_units();
