@@ -918,7 +918,8 @@ template <class T> struct TileEstimate {
 // Which digit kernel a product takes, by which tiles, and how many workgroups share one (parts of at least four k-steps): the way that is
 // estimated to take the least time.  Over Z_2^32 smaller tiles have to be estimated 6 % faster beyond 60 us, where full ones just fill the chip and
 // the estimates are no closer.  Batched products of three parties and one or two k-tiles stay with the row kernel up to 10 % behind: tiles, all packs and
-// stores there, take more than estimated (63 entries of 200 x 1 x 2: 22.4 us by rows, 27.8 by half tiles; 61 of 3851 x 83 x 33: 536 and 624).  Against always the fastest of the digit kernels that costs 0.5 % over 7500 products over Z_2^64 (8 us to 10 ms).
+// stores there, take more than estimated (61 entries of 3851 x 83 x 33: 536 us by rows, 624 by half tiles; 257 of 1 x 65 x 2: 40.6 and 44.9).
+// Against always the fastest of the digit kernels that costs 0.5 % over 7500 products over Z_2^64 (8 us to 10 ms).
 struct DigitRoute { bool rows; int splits; TileShape shape; double us; };
 template <class T> inline DigitRoute digit_route(const MatmulArgsT<T> &a, const Plan &p)
 {

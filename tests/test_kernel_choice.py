@@ -70,7 +70,7 @@ WAYS = [((3, 1, 256, 190, 130), "tiles"),           # 15.4, 25.9 by rows
         ((2, 14, 704, 960, 736), "tiles"),          # 939, 1145 by rows
         ((3, 1, 7840, 2112, 160), "tiles"),         # 558, 718 by rows
         ((3, 64, 128, 128, 64), "rows"),            # 32.5
-        ((3, 63, 200, 1, 2), "rows"),               # 22.4, 27.8 by tiles
+        ((3, 61, 3851, 83, 33), "rows"),            # 536, 624 by half tiles
         ((3, 1, 131072, 64, 576), "rows"),          # 1140
         ((2, 1, 4200, 64, 16352), "rows"),
         ((2, 1, 1024, 1024, 1024), "full")]         # 130, 135 by half tiles
